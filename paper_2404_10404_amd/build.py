@@ -16,10 +16,10 @@ LIB = os.path.join(HERE, "libgkr.so")
 SOURCES = ["gkr_batch_kernel.hip", "gkr_kernels.hip", "gkr_api.hip", "gkr_tuning.cpp", "gkr_verify.cpp",
            "gkr_profile.cpp", "gkr_batch.hip", "gkr_ubench.hip", "gkr_noalloc.hip", "gkr_general.hip", "gkr_gl.hip",
            "gkr_vpd.hip", "gkr_contract.hip"]
-# Test helper: the device field-code checker the GPU tests load.
+# Test helpers: the device checkers (field code, wave-wide routines) the GPU tests load.
 ROOT = os.path.dirname(HERE)
-CHECKER_SRC = os.path.join(ROOT, "tests", "native", "fr_device_check.hip")
-CHECKER_LIB = os.path.join(ROOT, "tests", "native", "libfrcheck.so")
+CHECKERS = [(os.path.join(ROOT, "tests", "native", src), os.path.join(ROOT, "tests", "native", lib))
+            for src, lib in (("fr_device_check.hip", "libfrcheck.so"), ("wave_check.hip", "libwavecheck.so"))]
 ARCH = "gfx950"
 
 # Packed fp32 instructions are switched off for every device compilation.
@@ -66,25 +66,25 @@ def _compile(src: str) -> str:
     return obj
 
 
-def build_checker() -> str:
-    """The device field-code checker of the tests (tests/native/libfrcheck.so)."""
-    tmp = CHECKER_LIB + ".tmp"
-    cmd = [_hipcc(), "-x", "hip", *COMMON, "-shared", "-o", tmp, CHECKER_SRC]
+def build_checker(src: str, lib: str) -> str:
+    """A device checker of the tests (tests/native/)."""
+    tmp = lib + ".tmp"
+    cmd = [_hipcc(), "-x", "hip", *COMMON, "-shared", "-o", tmp, src]
     res = subprocess.run(cmd, capture_output=True, text=True)
     if res.returncode != 0:
         raise RuntimeError("checker build failed: %s\n%s" % (" ".join(cmd), res.stderr[-4000:]))
-    os.replace(tmp, CHECKER_LIB)
-    return CHECKER_LIB
+    os.replace(tmp, lib)
+    return lib
 
 
 def build(verbose: bool = False) -> str:
     os.makedirs(OBJ, exist_ok=True)
     srcs = [s for s in SOURCES if os.path.exists(os.path.join(CSRC, s))]
     with concurrent.futures.ThreadPoolExecutor(max_workers=min(9, len(srcs) + 1)) as ex:
-        checker = ex.submit(build_checker) if os.path.exists(CHECKER_SRC) else None
+        checkers = [ex.submit(build_checker, *c) for c in CHECKERS if os.path.exists(c[0])]
         objs = list(ex.map(_compile, srcs))
-        if checker is not None:
-            checker.result()
+        for c in checkers:
+            c.result()
     tmp = LIB + ".tmp"
     cmd = [_hipcc(), f"--offload-arch={ARCH}", "-shared", "-fPIC", "-o", tmp, *objs, "-lpthread"]
     res = subprocess.run(cmd, capture_output=True, text=True)

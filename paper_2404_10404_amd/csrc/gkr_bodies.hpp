@@ -28,92 +28,24 @@
 
 #include "gkr_device.hpp"
 #include "gkr_kernels.hpp"
+#include "sha256_wave.hpp"
 
 namespace gkr {
 
 
 // ---------------------------------------------------------- transcript
 
-// SHA-256 of a fixed-length word message (big-endian words).
-template <int L>
-__device__ __forceinline__ Sha256State sha256_fixed(const uint32_t* w) {
-  constexpr int B = (L + 3 + 15) / 16;
-  Sha256State st = sha256_iv();
-#pragma unroll
-  for (int b = 0; b < B; ++b) {
-    Sha256Block blk;
-#pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      const int idx = b * 16 + i;
-      uint32_t v;
-      if (idx < L) v = w[idx];
-      else if (idx == L) v = 0x80000000u;
-      else if (idx == B * 16 - 1) v = (uint32_t)(L * 32);
-      else v = 0u;
-      blk.w[i] = v;
-    }
-    st = sha256_compress_v(st, blk);
-  }
-  return st;
-}
+// A challenge is the chaining value's candidate (254 bits, little-endian),
+// accepted when it is below p; until then the state is rehashed with "GKRC".
+// The challenge is v * 2^-256 mod p, so v itself is its Montgomery form: the
+// limbs are used as they are. Each attempt is accepted with probability
+// p / 2^254 > 3/4; the bound on attempts only guarantees termination. The
+// hashing runs in whole waves (sha256_wave.hpp).
 
-__device__ __forceinline__ Sha256State load_state(const DevState* S) {
-  Sha256State s;
-#pragma unroll
-  for (int k = 0; k < 8; ++k) s.h[k] = S->st[k];
-  return s;
-}
-
-__device__ __forceinline__ void save_state(DevState* S, const Sha256State& s) {
-#pragma unroll
-  for (int k = 0; k < 8; ++k) S->st[k] = s.h[k];
-}
-
-// The current state as a challenge: rehash with "GKRC" until the 254-bit
-// little-endian value v is below p. The challenge is v * 2^-256 mod p, so v
-// itself is its Montgomery form: the limbs returned are used as is. Each
-// attempt is accepted with probability p / 2^254 > 3/4; the bound on
-// attempts only guarantees termination.
-__device__ Fr accept(Sha256State& st) {
-  Fr c = sha256_to_candidate(st);
-  for (int attempt = 0; attempt < 4096 && !fr_is_canonical(c); ++attempt) {
-    uint32_t w[9];
-#pragma unroll
-    for (int k = 0; k < 8; ++k) w[k] = st.h[k];
-    w[8] = kTagChallenge;
-    st = sha256_fixed<9>(w);
-    c = sha256_to_candidate(st);
-  }
-  return c;
-}
-
-__device__ Fr squeeze(Sha256State& st) {
-  uint32_t w[9];
-#pragma unroll
-  for (int k = 0; k < 8; ++k) w[k] = st.h[k];
-  w[8] = kTagChallenge;
-  st = sha256_fixed<9>(w);
-  return accept(st);
-}
-
-__device__ void absorb_element(Sha256State& st, uint32_t tag, const Fr& canonical) {
-  uint32_t w[17];
-#pragma unroll
-  for (int k = 0; k < 8; ++k) w[k] = st.h[k];
-  w[8] = tag;
-#pragma unroll
-  for (int k = 0; k < 8; ++k) w[9 + k] = bswap32(canonical.v[k]);
-  st = sha256_fixed<17>(w);
-}
-
-__device__ void absorb_digest(Sha256State& st, const uint32_t* d) {
-  uint32_t w[17];
-#pragma unroll
-  for (int k = 0; k < 8; ++k) w[k] = st.h[k];
-  w[8] = kTagDigest;
-#pragma unroll
-  for (int k = 0; k < 8; ++k) w[9 + k] = d[k];
-  st = sha256_fixed<17>(w);
+// The shared words of a workgroup's hashing wave.
+__device__ __forceinline__ ShaBuf* sha_buf() {
+  __shared__ __attribute__((aligned(16))) ShaBuf buf;
+  return &buf;
 }
 
 __device__ __forceinline__ Fr fr_one_canonical() { return fr_make(1, 0, 0, 0, 0, 0, 0, 0); }
@@ -126,20 +58,39 @@ __device__ __forceinline__ Fr lane_fr(const Fr& a, int src) {
   return r;
 }
 
-// The transcript half of a round, on a transcript state held in registers
-// (the same in every lane of the wave): one SHA-256 compression absorbs the
-// Montgomery forms of the round's sums e0 and e2, and the accepted hash value
-// is the challenge r in Montgomery form. No product precedes the hash, and
-// the running claim is not needed (e1 enters only the message).
-__device__ __forceinline__ Fr round_hash_wave(Sha256State& state, const Fr& e0, const Fr& e2) {
-  Sha256Block blk;
+// Word `lane mod 16` of the block that absorbs a round: the Montgomery forms
+// of the sums e0 and e2 (16 limbs in shared memory) with the round mark.
+__device__ __forceinline__ uint32_t round_word(const Fr* e) {
+  const uint32_t li = sha_lane() & 15;
+  const uint32_t v = reinterpret_cast<const uint32_t*>(e)[li];
+  return bswap32(li == 15 ? v | kRoundMark : v);
+}
+
+// The transcript half of a round, in a whole wave: one SHA-256 compression
+// absorbs the round's sums (e in shared memory), and the accepted hash value
+// is the challenge r in Montgomery form. No product precedes the hash, and the
+// running claim is not needed (e1 enters only the message).
+template <bool Helped>
+__device__ __forceinline__ void round_hash_wave(ShaLanes& state, const Fr* e,
+                                                ShaHelper* help, uint32_t base) {
+  state = sha_compress_wave<Helped>(state, round_word(e), sha_buf(), help, base);
+  sha_accept_wave(state, sha_buf());
+}
+
+// The challenge of an accepted state to one or two places (r_sh in shared memory).
+__device__ __forceinline__ void store_challenge(const ShaLanes& state, Fr* r_sh, Fr* r_out) {
+  const uint32_t lane = sha_lane();
+  if (lane == 0 || lane == 8) {
+    uint32_t v[4];
+    sha_candidate_limbs(state, v);
+    const uint32_t o = lane ? 0 : 4;
+    if (r_sh) {
 #pragma unroll
-  for (int k = 0; k < 8; ++k) {
-    blk.w[k] = bswap32(e0.v[k]);
-    blk.w[8 + k] = bswap32(k == 7 ? (e2.v[k] | kRoundMark) : e2.v[k]);
+      for (int k = 0; k < 4; ++k) r_sh->v[o + k] = v[k];
+    }
+    GlobalU4* q = (GlobalU4*)r_out;
+    q[lane ? 0 : 1] = U32x4{v[0], v[1], v[2], v[3]};
   }
-  state = sha256_compress_v(state, blk);
-  return accept(state);
 }
 
 // The product half: the next claim g(r) = e0 + r (e1 - e0) + r (r - 1)
@@ -169,15 +120,16 @@ __device__ __forceinline__ Fr round_claim_wave(const Fr& r, const Fr& e0, const 
   return fr_add(e0, t);
 }
 
-// A phase's final value (one thread): store it, write it to the proof and absorb it.
-__device__ __forceinline__ void finish_value(DevState* S, const Fr& v, Fr* v_out, uint32_t* proof_out) {
+// A phase's final value (a whole wave; v the same in every lane): store it,
+// write it to the proof and absorb it.
+__device__ __forceinline__ void finish_value_wave(ShaLanes& state, const Fr& v, Fr* v_out,
+                                                  uint32_t* proof_out) {
   const Fr c = fr_from_mont(v);
-  Sha256State st = load_state(S);
-  absorb_element(st, kTagValue, c);
-  save_state(S, st);
-  *v_out = v;
-#pragma unroll
-  for (int k = 0; k < 8; ++k) proof_out[k] = c.v[k];
+  sha_absorb_words_wave(state, sha_buf(), kTagValue, bswap32(lane_limb(c)));
+  if ((threadIdx.x & 63) == 0) {
+    *v_out = v;
+    stf(reinterpret_cast<Fr*>(proof_out), 0, c);
+  }
 }
 
 // ---------------------------------------------------------------- bodies
@@ -273,49 +225,67 @@ __device__ __forceinline__ void body_digest(const Step& st, uint32_t tile, uint3
 // clears the pending round.
 // p0 S, p1 dig_in, p2 dig_out.
 __device__ __forceinline__ void body_transcript_begin(const Step& st, uint32_t, uint32_t) {
-  if (threadIdx.x != 0) return;
+  if (threadIdx.x >= 64) return;
   DevState* S = P<DevState*>(st, 0);
-  Sha256State sh;
+  sha_init(sha_buf());
+  const uint32_t k = threadIdx.x & 7;
+  ShaLanes sh;
 #pragma unroll
-  for (int k = 0; k < 8; ++k) sh.h[k] = st.w[k];
-  absorb_digest(sh, st.w + 8);
-  absorb_digest(sh, P<const uint32_t*>(st, 1));
-  absorb_digest(sh, P<const uint32_t*>(st, 2));
-  save_state(S, sh);
-  S->counter = 0;
-  S->pending = 0;
+  for (int q = 0; q < 4; ++q) sh.x[q] = sha_sel((threadIdx.x & 8) != 0, st.w[q], st.w[4 + q]);
+  Fr circ;
+#pragma unroll
+  for (int q = 0; q < 8; ++q) circ.v[q] = st.w[8 + q];
+  sha_absorb_words_wave(sh, sha_buf(), kTagDigest, lane_limb(circ));
+  sha_absorb_words_wave(sh, sha_buf(), kTagDigest, P<const uint32_t*>(st, 1)[k]);
+  sha_absorb_words_wave(sh, sha_buf(), kTagDigest, P<const uint32_t*>(st, 2)[k]);
+  sha_lanes_store(S->st, sh);
+  if (threadIdx.x == 0) {
+    S->counter = 0;
+    S->pending = 0;
+  }
 }
 
 // ST_SQUEEZE: u0 challenges into p1 (Montgomery form). p0 S.
 __device__ __forceinline__ void body_squeeze(const Step& st, uint32_t, uint32_t) {
-  if (threadIdx.x != 0) return;
+  if (threadIdx.x >= 64) return;
   DevState* S = P<DevState*>(st, 0);
   Fr* out = P<Fr*>(st, 1);
-  Sha256State sh = load_state(S);
-  for (uint32_t k = 0; k < st.u[0]; ++k) stf(out, k, squeeze(sh));
-  save_state(S, sh);
+  sha_init(sha_buf());
+  ShaLanes sh = sha_lanes_load(S->st);
+  for (uint32_t k = 0; k < st.u[0]; ++k) {
+    sha_rehash_wave(sh, sha_buf());
+    sha_accept_wave(sh, sha_buf());
+    store_challenge(sh, nullptr, out + k);
+  }
+  sha_lanes_store(S->st, sh);
 }
 
 // ST_LAYER_BEGIN: draw alpha, beta (layer > 0) and set the claim to
 // alpha * vu + beta * vv; on layer 0 (u0 = 1) alpha = 1, beta = 0 and claim = vu.
 // p0 S, p1 vu, p2 vv.
 __device__ __forceinline__ void body_layer_begin(const Step& st, uint32_t, uint32_t) {
-  if (threadIdx.x != 0) return;
+  if (threadIdx.x >= 64) return;
   DevState* S = P<DevState*>(st, 0);
-  const Fr vu = *P<const Fr*>(st, 1), vv = *P<const Fr*>(st, 2);
+  const Fr vu = opaque(*P<const Fr*>(st, 1)), vv = opaque(*P<const Fr*>(st, 2));
   if (st.u[0]) {
-    S->alpha = fr_one();
-    S->beta = fr_zero();
-    S->claim = vu;
+    if (threadIdx.x == 0) {
+      S->alpha = fr_one();
+      S->beta = fr_zero();
+      S->claim = vu;
+    }
     return;
   }
-  Sha256State sh = load_state(S);
-  const Fr a = squeeze(sh);
-  const Fr b = squeeze(sh);
-  save_state(S, sh);
-  S->alpha = a;
-  S->beta = b;
-  S->claim = fr_mul_add2(a, vu, b, vv);
+  sha_init(sha_buf());
+  ShaLanes sh = sha_lanes_load(S->st);
+  const Fr a = sha_squeeze_wave(sh, sha_buf());
+  const Fr b = sha_squeeze_wave(sh, sha_buf());
+  sha_lanes_store(S->st, sh);
+  const Fr claim = fr_mul_add2(opaque(a), vu, opaque(b), vv);
+  if (threadIdx.x == 0) {
+    S->alpha = a;
+    S->beta = b;
+    S->claim = claim;
+  }
 }
 
 // ST_EQ: up to four tables out_j[b] = scale_j * prod_k (bit_k(b) ? r_k : 1 - r_k),
@@ -490,12 +460,25 @@ __device__ __forceinline__ void body_p1_init_round(const Step& st, uint32_t tile
 // of (e0, e2) gives r, and the round becomes the pending one. Meanwhile wave 1
 // moves the claim through the previous pending round (if any) and writes that
 // round's message, so the products by r stay off the chain of hashes.
+// With Late (the batch kernel, which has no registers to spare) the transcript
+// state and constants are loaded after the sum instead of during it.
+template <bool Late>
 __device__ __forceinline__ void finish_reduced_round(const Fr* partials, uint32_t ntiles, DevState* S, Fr* r_out,
                                      uint32_t* msg) {
   const uint32_t wid = threadIdx.x >> 6;
-  // wave 0 fetches the transcript state while the partials are summed
-  Sha256State st;
-  if (wid == 0) st = load_state(S);
+  __shared__ Fr e_sh[2];
+  __shared__ ShaHelper help;
+  // wave 0 fetches the transcript state while the partials are summed; wave 2
+  // writes the hash's schedule
+  ShaLanes st;
+  auto fetch = [&] {
+    if (wid == 0) {
+      st = sha_lanes_load(S->st);
+      sha_init(sha_buf());
+    }
+  };
+  if constexpr (!Late) fetch();
+  if (threadIdx.x == 0) help.ready = 0;
   Fr tot[2];
   if (ntiles <= 64) {
     // every partial fits in wave 0: a wave sum, no LDS round trip
@@ -525,27 +508,35 @@ __device__ __forceinline__ void finish_reduced_round(const Fr* partials, uint32_
       pmsg = S->pend_msg;
     }
   }
+  if (threadIdx.x == 0) {
+    e_sh[0] = tot[0];
+    e_sh[1] = tot[1];
+  }
+  if constexpr (Late) fetch();
   // wave 1 has read the pending round before wave 0 overwrites it
   __syncthreads();
   if (wid == 0) {
-    const Fr r = round_hash_wave(st, tot[0], tot[1]);
+    round_hash_wave<true>(st, e_sh, &help, 0);
+    sha_lanes_store(S->st, st);
+    store_challenge(st, nullptr, r_out);
+    store_challenge(st, nullptr, &S->pend_r);
     if (threadIdx.x == 0) {
-      save_state(S, st);
-      stf(r_out, 0, r);
-      S->pend_e0 = tot[0];
-      S->pend_e2 = tot[1];
-      S->pend_r = r;
+      S->pend_e0 = e_sh[0];
+      S->pend_e2 = e_sh[1];
       S->pend_msg = msg;
       S->pending = 1;
     }
+  } else if (wid == 2) {
+    sha_help(round_word(e_sh), sha_buf(), &help, 0);
   } else if (wid == 1 && pend) {
     claim = round_claim_wave(pr, pe0, fr_sub(claim, pe0), pe2, pmsg);
     if (threadIdx.x == 64) S->claim = claim;
   }
 }
 
+template <bool Late>
 __device__ __forceinline__ void finish_p1_init_round(const Step& st, uint32_t ntiles) {
-  finish_reduced_round(P<const Fr*>(st, 10), ntiles, P<DevState*>(st, 9), P<Fr*>(st, 11), P<uint32_t*>(st, 12));
+  finish_reduced_round<Late>(P<const Fr*>(st, 10), ntiles, P<DevState*>(st, 9), P<Fr*>(st, 11), P<uint32_t*>(st, 12));
 }
 
 // Entries b and b + half of one table of a round. With Fold the source has
@@ -639,10 +630,10 @@ __device__ __forceinline__ void body_round(const Step& st, uint32_t tile, uint32
   round_range<Form>(src, dst, GTID, GSTRIDE, half, fold, r, acc[0], acc[1]);
   write_partial<2>(acc, P<Fr*>(st, R::kPart), tile);
 }
-template <class Form>
+template <class Form, bool Late>
 __device__ __forceinline__ void finish_round_step(const Step& st, uint32_t ntiles) {
   using R = RoundPtrs<Form::NT>;
-  finish_reduced_round(P<const Fr*>(st, R::kPart), ntiles, P<DevState*>(st, R::kS), P<Fr*>(st, R::kROut),
+  finish_reduced_round<Late>(P<const Fr*>(st, R::kPart), ntiles, P<DevState*>(st, R::kS), P<Fr*>(st, R::kROut),
                        P<uint32_t*>(st, R::kMsg));
 }
 
@@ -704,12 +695,15 @@ __device__ __forceinline__ void body_tail(const Step& st, uint32_t, uint32_t) {
   __shared__ Fr r_sh, e_sh[2];  // the last round's challenge and sums (e0, e2)
   __shared__ Fr red1[2];
   bool fold = rpending != nullptr;
-  Sha256State state;  // wave 0
+  ShaLanes state;  // wave 0
   // wave 1: the claim and the pending round it has not moved through yet
   Fr claim = fr_zero(), pe0 = fr_zero(), pe2 = fr_zero(), pr = fr_zero();
   uint32_t* pmsg = nullptr;
   bool pend = false;
-  if (wid == 0) state = load_state(S);
+  if (wid == 0) {
+    state = sha_lanes_load(S->st);
+    sha_init(sha_buf());
+  }
   if (wid == 1) {
     claim = S->claim;
     pend = S->pending != 0;
@@ -796,13 +790,13 @@ __device__ __forceinline__ void body_tail(const Step& st, uint32_t, uint32_t) {
       block_sum_to_wave0<2>(acc);
     }
     if (wid == 0) {
-      const Fr r = round_hash_wave(state, acc[0], acc[1]);
       if (threadIdx.x == 0) {
-        r_sh = r;
         e_sh[0] = acc[0];
         e_sh[1] = acc[1];
-        stf(r_out, j, r);
       }
+      lds_order();
+      round_hash_wave<false>(state, e_sh, nullptr, 0);
+      store_challenge(state, &r_sh, r_out + j);
     } else if (wid == 1 && pend) {
       claim = round_claim_wave(pr, pe0, fr_sub(claim, pe0), pe2, pmsg);
       pend = false;
@@ -825,11 +819,11 @@ __device__ __forceinline__ void body_tail(const Step& st, uint32_t, uint32_t) {
       S->pending = 0;
     }
   }
-  if (threadIdx.x == 0) {
-    if (rounds > 0) save_state(S, state);
-    const Fr v = ldf(src[0], 0);
-    if (proof_value) finish_value(S, v, final_out, proof_value);
-    else *final_out = v;
+  if (wid == 0) {
+    const Fr v = opaque(ldf(src[0], 0));
+    if (proof_value) finish_value_wave(state, v, final_out, proof_value);
+    else if (threadIdx.x == 0) *final_out = v;
+    sha_lanes_store(S->st, state);
   }
 }
 
@@ -1041,12 +1035,17 @@ __device__ __forceinline__ void body_tail_pipe(const Step& st, uint32_t, uint32_
   __shared__ Fr r_sh[2], e_sh[2][2], claim_sh[2];
   // Values that cross a barrier live in the shared slots (r_sh, e_sh) rather
   // than in registers: every wave holds the registers of every role.
-  Sha256State state;  // wave 0
+  ShaLanes state;     // wave 0
+  __shared__ ShaHelper help;
   Fr claim;           // waves 1 and 7: the claim before the first round (wave 1 moves it)
   bool grid_pend = false;  // waves 1 and 7: a grid round whose claim move is pending
   if (wid == 0) {
-    state = load_state(S);
-    if (lane == 0) r_sh[1] = pending ? ldf(rpending, 0) : fr_zero();  // r_{-1}
+    state = sha_lanes_load(S->st);
+    sha_init(sha_buf());
+    if (lane == 0) {
+      r_sh[1] = pending ? ldf(rpending, 0) : fr_zero();  // r_{-1}
+      help.ready = 0;
+    }
   } else if (wid == 1 || wid == 7) {
     claim = S->claim;
     grid_pend = S->pending != 0;
@@ -1114,12 +1113,10 @@ __device__ __forceinline__ void body_tail_pipe(const Step& st, uint32_t, uint32_
     }
     __syncthreads();
     const uint64_t next = j + 1 < rounds ? m / 4 : 0;  // tasks of round j + 1
+    if (wid == 4) sha_help(round_word(e_sh[j & 1]), sha_buf(), &help, 3 * j);
     if (wid == 0) {
-      const Fr r = round_hash_wave(state, opaque(e_sh[j & 1][0]), opaque(e_sh[j & 1][1]));
-      if (lane == 0) {
-        r_sh[j & 1] = r;
-        stf(r_out, j, r);
-      }
+      round_hash_wave<true>(state, e_sh[j & 1], &help, 3 * j);
+      store_challenge(state, &r_sh[j & 1], r_out + j);
     } else if (next > 32) {
       if (worker)
         tail_coefficients<Form>(cur, next, false, t2, th, nth, wih,
@@ -1143,12 +1140,10 @@ __device__ __forceinline__ void body_tail_pipe(const Step& st, uint32_t, uint32_
       v = fr_add(a0, fr_mul(r_prev, fr_sub(a1, a0)));
       stf(pick<NT>(dst, lane), 0, v);
     }
-    if (lane == 0) {
-      if (rounds > 0) save_state(S, state);
-      if (!any_fold) v = ldf(src[0], 0);
-      if (proof_value) finish_value(S, v, final_out, proof_value);
-      else *final_out = v;
-    }
+    v = any_fold ? lane_fr(v, 0) : ldf(src[0], 0);
+    if (proof_value) finish_value_wave(state, opaque(v), final_out, proof_value);
+    else if (lane == 0) *final_out = v;
+    sha_lanes_store(S->st, state);
   } else if (wid == 1) {
     if (rounds > 0) {
       const uint32_t q = (rounds - 1) & 1;
@@ -1433,15 +1428,15 @@ __device__ __forceinline__ void run_step_tile(const Step& st, uint32_t tile, uin
     case ST_P1_INIT: body_p1_init(st, tile, ntiles); break;
     case ST_P1_INIT_ROUND:
       body_p1_init_round<false>(st, tile, ntiles);
-      if (last_tile(counter, ntiles)) finish_p1_init_round(st, ntiles);
+      if (last_tile(counter, ntiles)) finish_p1_init_round<true>(st, ntiles);
       break;
     case ST_ROUND_A:
       body_round<FormA>(st, tile, ntiles);
-      if (last_tile(counter, ntiles)) finish_round_step<FormA>(st, ntiles);
+      if (last_tile(counter, ntiles)) finish_round_step<FormA, true>(st, ntiles);
       break;
     case ST_ROUND_B:
       body_round<FormB>(st, tile, ntiles);
-      if (last_tile(counter, ntiles)) finish_round_step<FormB>(st, ntiles);
+      if (last_tile(counter, ntiles)) finish_round_step<FormB, true>(st, ntiles);
       break;
     case ST_TAIL_A: body_tail<FormA>(st, tile, ntiles); break;
     case ST_TAIL_B: body_tail<FormB>(st, tile, ntiles); break;

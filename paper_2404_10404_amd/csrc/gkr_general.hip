@@ -180,37 +180,49 @@ __device__ __forceinline__ void body_g_p2(const Step& st, uint32_t tile, uint32_
 // K coefficients are squeezed. p0 S, p1 coef (K elements out), p2.. p(2+K-1)
 // the claimed values. S->claim = sum_k coef_k value_k; no round pending.
 __device__ __forceinline__ void body_g_layer_begin(const Step& st, uint32_t, uint32_t) {
-  if (threadIdx.x != 0) return;
+  if (threadIdx.x >= 64) return;
   DevState* S = P<DevState*>(st, 0);
   Fr* coef = P<Fr*>(st, 1);
   const uint32_t K = st.u[0];
-  Sha256State sh = load_state(S);
-  Fr claim = fr_zero();
+  sha_init(sha_buf());
+  ShaLanes sh = sha_lanes_load(S->st);
+  // the coefficient of claim k stays in lane k (K <= 14): one product per lane, then a wave sum
+  Fr mine = fr_zero();
   for (uint32_t k = 0; k < K; ++k) {
-    const Fr a = st.u[1] ? fr_one() : squeeze(sh);
-    stf(coef, k, a);
-    claim = fr_add(claim, fr_mul(a, opaque(*P<const Fr*>(st, 2 + k))));
+    const Fr a = st.u[1] ? fr_one() : sha_squeeze_wave(sh, sha_buf());
+#pragma unroll
+    for (int q = 0; q < 8; ++q) mine.v[q] = threadIdx.x == k ? a.v[q] : mine.v[q];
   }
-  if (!st.u[1]) save_state(S, sh);
-  S->claim = claim;
-  S->pending = 0;
+  Fr v = fr_zero();
+  for (uint32_t k = 0; k < K; ++k)
+    if (threadIdx.x == k) v = *P<const Fr*>(st, 2 + k);
+  if (threadIdx.x < K) stf(coef, threadIdx.x, mine);
+  const Fr claim = wave_sum_to_lane63(fr_mul(opaque(mine), opaque(v)));
+  if (!st.u[1]) sha_lanes_store(S->st, sh);
+  if (threadIdx.x == 63) {
+    S->claim = claim;
+    S->pending = 0;
+  }
 }
 
 // ST_G_VALUES: the layer's block values (Montgomery, u0 of them at p1) go to
 // the proof (canonical, p2) and into the transcript, one "GKRV" absorb each.
 __device__ __forceinline__ void body_g_values(const Step& st, uint32_t, uint32_t) {
-  if (threadIdx.x != 0) return;
+  if (threadIdx.x >= 64) return;
   DevState* S = P<DevState*>(st, 0);
   const Fr* vals = P<const Fr*>(st, 1);
-  uint32_t* proof = P<uint32_t*>(st, 2);
-  Sha256State sh = load_state(S);
-  for (uint32_t b = 0; b < st.u[0]; ++b) {
-    const Fr c = fr_from_mont(ldf(vals, b));
-    absorb_element(sh, kTagValue, c);
-#pragma unroll
-    for (int k = 0; k < 8; ++k) proof[8 * b + k] = c.v[k];
+  Fr* proof = P<Fr*>(st, 2);
+  sha_init(sha_buf());
+  ShaLanes sh = sha_lanes_load(S->st);
+  const uint32_t nb = st.u[0];  // at most a source per later layer, in rounds of 64
+  for (uint32_t b0 = 0; b0 < nb; b0 += 64) {
+    const uint32_t b = b0 + threadIdx.x;
+    const Fr c = fr_from_mont(b < nb ? ldf(vals, b) : fr_zero());  // lane k: value b0 + k
+    if (b < nb) stf(proof, b, c);
+    for (uint32_t k = 0; k < 64 && b0 + k < nb; ++k)
+      sha_absorb_words_wave(sh, sha_buf(), kTagValue, bswap32(lane_limb(shfl_fr(c, (int)k))));
   }
-  save_state(S, sh);
+  sha_lanes_store(S->st, sh);
 }
 
 #undef GTID

@@ -48,16 +48,32 @@ __device__ __forceinline__ uint64_t shfl_xor_u64(uint64_t v, int mask) {
   return ((uint64_t)hi << 32) | lo;
 }
 
+template <int Ctrl, int RowMask>
+__device__ __forceinline__ uint64_t dpp_u64(uint64_t v) {
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)v, Ctrl, RowMask, 0xF, false);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(v >> 32), Ctrl, RowMask, 0xF, false);
+  return ((uint64_t)hi << 32) | lo;
+}
+
+// Sum over the 64 lanes of a wave (all active) into lane 63, by DPP row operations.
+__device__ __forceinline__ uint64_t gl_wave_sum63(uint64_t v) {
+  v = gl_add(v, dpp_u64<0xB1, 0xF>(v));   // quad_perm [1,0,3,2]
+  v = gl_add(v, dpp_u64<0x4E, 0xF>(v));   // quad_perm [2,3,0,1]
+  v = gl_add(v, dpp_u64<0x141, 0xF>(v));  // row_half_mirror
+  v = gl_add(v, dpp_u64<0x140, 0xF>(v));  // row_mirror
+  v = gl_add(v, dpp_u64<0x142, 0xA>(v));  // row_bcast15 into rows 1 and 3
+  v = gl_add(v, dpp_u64<0x143, 0xC>(v));  // row_bcast31 into rows 2 and 3
+  return v;
+}
+
 // Sum of NV values over the workgroup (blockDim.x a multiple of 64); valid in thread 0.
 template <int NV>
-__device__ void gl_block_sum(uint64_t (&v)[NV]) {
+__device__ __forceinline__ void gl_block_sum(uint64_t (&v)[NV]) {
   __shared__ uint64_t red[NV][16];
 #pragma unroll
-  for (int off = 32; off >= 1; off >>= 1)
-#pragma unroll
-    for (int k = 0; k < NV; ++k) v[k] = gl_add(v[k], shfl_xor_u64(v[k], off));
+  for (int k = 0; k < NV; ++k) v[k] = gl_wave_sum63(v[k]);
   const uint32_t lane = threadIdx.x & 63, wid = threadIdx.x >> 6, nw = blockDim.x >> 6;
-  if (lane == 0)
+  if (lane == 63)
 #pragma unroll
     for (int k = 0; k < NV; ++k) red[k][wid] = v[k];
   __syncthreads();
@@ -73,64 +89,34 @@ __device__ void gl_block_sum(uint64_t (&v)[NV]) {
 
 // ---------------------------------------------------------------- transcript (device)
 
-__device__ __forceinline__ uint64_t gl_candidate(const Sha256State& s) {
-  return (uint64_t)bswap32(s.h[0]) | ((uint64_t)bswap32(s.h[1]) << 32);
+// The transcript runs in whole waves (sha256_wave.hpp): v = LE64 of the first
+// two digest words, which the a-lanes hold.
+__device__ __forceinline__ uint64_t gl_candidate(const ShaLanes& s) {
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)s.x[0], 8);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)s.x[1], 8);
+  return (uint64_t)bswap32(lo) | ((uint64_t)bswap32(hi) << 32);
 }
 
-__device__ uint64_t gl_accept(Sha256State& st) {
+__device__ __forceinline__ uint64_t gl_accept_wave(ShaLanes& st) {
   uint64_t v = gl_candidate(st);
   for (int attempt = 0; attempt < 4096 && v >= kGlP; ++attempt) {
-    uint32_t w[9];
-#pragma unroll
-    for (int k = 0; k < 8; ++k) w[k] = st.h[k];
-    w[8] = kTagChallenge;
-    st = sha256_fixed<9>(w);
+    sha_rehash_wave(st, sha_buf());
     v = gl_candidate(st);
   }
   return v;
 }
 
-__device__ uint64_t gl_squeeze(Sha256State& st) {
-  uint32_t w[9];
-#pragma unroll
-  for (int k = 0; k < 8; ++k) w[k] = st.h[k];
-  w[8] = kTagChallenge;
-  st = sha256_fixed<9>(w);
-  return gl_accept(st);
+__device__ __forceinline__ uint64_t gl_squeeze_wave(ShaLanes& st) {
+  sha_rehash_wave(st, sha_buf());
+  return gl_accept_wave(st);
 }
 
-__device__ void gl_absorb_value(Sha256State& st, uint64_t v) {
-  uint32_t w[11];
-#pragma unroll
-  for (int k = 0; k < 8; ++k) w[k] = st.h[k];
-  w[8] = kTagValue;
-  w[9] = bswap32((uint32_t)v);
-  w[10] = bswap32((uint32_t)(v >> 32));
-  st = sha256_fixed<11>(w);
-}
-
-__device__ uint64_t gl_round_hash(Sha256State& st, uint64_t e0, uint64_t e2) {
-  Sha256Block blk;
-#pragma unroll
-  for (int k = 0; k < 16; ++k) blk.w[k] = 0;
-  blk.w[0] = bswap32((uint32_t)e0);
-  blk.w[1] = bswap32((uint32_t)(e0 >> 32));
-  blk.w[2] = bswap32((uint32_t)e2);
-  blk.w[3] = bswap32((uint32_t)(e2 >> 32));
-  blk.w[15] = 1u;
-  st = sha256_compress_v(st, blk);
-  return gl_accept(st);
-}
-
-__device__ __forceinline__ Sha256State gl_load_state(const GlState* S) {
-  Sha256State s;
-#pragma unroll
-  for (int k = 0; k < 8; ++k) s.h[k] = S->st[k];
-  return s;
-}
-__device__ __forceinline__ void gl_save_state(GlState* S, const Sha256State& s) {
-#pragma unroll
-  for (int k = 0; k < 8; ++k) S->st[k] = s.h[k];
+// Word `lane mod 16` of the block that absorbs a round: e0, e2 and the end mark.
+__device__ __forceinline__ uint32_t gl_round_word(uint64_t e0, uint64_t e2) {
+  const uint32_t li = threadIdx.x & 15;
+  const uint64_t e = li < 2 ? e0 : e2;
+  const uint32_t v = (li & 1) ? (uint32_t)(e >> 32) : (uint32_t)e;
+  return li < 4 ? bswap32(v) : (li == 15 ? 1u : 0u);
 }
 
 // SHA-256 of `len` 32-bit words (byte-swapped when swap: element words are
@@ -211,46 +197,57 @@ __global__ void __launch_bounds__(kBlock) k_gl_digest(Step st) {
 // the two vector digests; the reduction counter starts at zero.
 // p0 S, p1 dig_in, p2 dig_out.
 __global__ void __launch_bounds__(kBlock) k_gl_begin(Step st) {
-  if (threadIdx.x != 0) return;
+  if (threadIdx.x >= 64) return;
   GlState* S = P<GlState*>(st, 0);
-  Sha256State sh;
+  sha_init(sha_buf());
+  const uint32_t k = threadIdx.x & 7;
+  ShaLanes sh;
 #pragma unroll
-  for (int k = 0; k < 8; ++k) sh.h[k] = st.w[k];
-  absorb_digest(sh, st.w + 8);
-  absorb_digest(sh, P<const uint32_t*>(st, 1));
-  absorb_digest(sh, P<const uint32_t*>(st, 2));
-  gl_save_state(S, sh);
-  S->counter = 0;
+  for (int q = 0; q < 4; ++q) sh.x[q] = sha_sel((threadIdx.x & 8) != 0, st.w[q], st.w[4 + q]);
+  Fr circ;
+#pragma unroll
+  for (int q = 0; q < 8; ++q) circ.v[q] = st.w[8 + q];
+  sha_absorb_words_wave(sh, sha_buf(), kTagDigest, lane_limb(circ));
+  sha_absorb_words_wave(sh, sha_buf(), kTagDigest, P<const uint32_t*>(st, 1)[k]);
+  sha_absorb_words_wave(sh, sha_buf(), kTagDigest, P<const uint32_t*>(st, 2)[k]);
+  sha_lanes_store(S->st, sh);
+  if (threadIdx.x == 0) S->counter = 0;
 }
 
 // ST_GL_SQUEEZE: u0 challenges into p1. p0 S.
 __global__ void __launch_bounds__(kBlock) k_gl_squeeze(Step st) {
-  if (threadIdx.x != 0) return;
+  if (threadIdx.x >= 64) return;
   GlState* S = P<GlState*>(st, 0);
   uint64_t* out = P<uint64_t*>(st, 1);
-  Sha256State sh = gl_load_state(S);
-  for (uint32_t k = 0; k < st.u[0]; ++k) out[k] = gl_squeeze(sh);
-  gl_save_state(S, sh);
+  sha_init(sha_buf());
+  ShaLanes sh = sha_lanes_load(S->st);
+  for (uint32_t k = 0; k < st.u[0]; ++k) {
+    const uint64_t v = gl_squeeze_wave(sh);
+    if (threadIdx.x == 0) out[k] = v;
+  }
+  sha_lanes_store(S->st, sh);
 }
 
 // ST_GL_LAYER_BEGIN: alpha, beta squeezed (u0 = 0) and claim = alpha vu + beta vv;
 // on layer 0 (u0 = 1) alpha = 1, beta = 0, claim = vu. p0 S, p1 vu, p2 vv.
 __global__ void __launch_bounds__(kBlock) k_gl_layer_begin(Step st) {
-  if (threadIdx.x != 0) return;
+  if (threadIdx.x >= 64) return;
   GlState* S = P<GlState*>(st, 0);
   const uint64_t vu = *P<const uint64_t*>(st, 1), vv = *P<const uint64_t*>(st, 2);
-  if (st.u[0]) {
-    S->alpha = 1;
-    S->beta = 0;
-    S->claim = vu;
-    return;
+  uint64_t a = 1, b = 0;  // the output layer has one claim
+  if (!st.u[0]) {
+    sha_init(sha_buf());
+    ShaLanes sh = sha_lanes_load(S->st);
+    a = gl_squeeze_wave(sh);
+    b = gl_squeeze_wave(sh);
+    sha_lanes_store(S->st, sh);
   }
-  Sha256State sh = gl_load_state(S);
-  const uint64_t a = gl_squeeze(sh), b = gl_squeeze(sh);
-  gl_save_state(S, sh);
-  S->alpha = a;
-  S->beta = b;
-  S->claim = gl_add(gl_mul(a, vu), gl_mul(b, vv));
+  const uint64_t claim = st.u[0] ? vu : gl_add(gl_mul(a, vu), gl_mul(b, vv));
+  if (threadIdx.x == 0) {
+    S->alpha = a;
+    S->beta = b;
+    S->claim = claim;
+  }
 }
 
 // ST_GL_EQ: up to four tables out_j[b] = scale_j prod_k (bit_k(b) ? r_k : 1 - r_k),
@@ -510,18 +507,41 @@ __global__ void __launch_bounds__(kBlock) k_gl_copy_tables(Step st) {
 
 // ---------------------------------------------------------------- rounds
 
-// The transcript step of a round (one thread): message (e0, e1 = claim - e0,
-// e2) to the proof, the hash gives r, the claim moves to the round polynomial at r.
-__device__ __forceinline__ uint64_t gl_round_step(GlState* S, uint64_t e0, uint64_t e2, uint64_t* msg) {
-  const uint64_t e1 = gl_sub(S->claim, e0);
-  msg[0] = e0;
-  msg[1] = e1;
-  msg[2] = e2;
-  Sha256State sh = gl_load_state(S);
-  const uint64_t r = gl_round_hash(sh, e0, e2);
-  gl_save_state(S, sh);
-  S->claim = gl_interp3(e0, e1, e2, r);
-  return r;
+// The transcript step of a grid round (the whole workgroup; e0, e2 in thread
+// 0): the hash in wave 0 with its schedule from wave 2 gives r; then the
+// message (e0, e1 = claim - e0, e2) and the claim at r.
+__device__ __forceinline__ void gl_round_step(GlState* S, uint64_t e0, uint64_t e2, uint64_t* r_out, uint64_t* msg) {
+  __shared__ uint64_t e_sh[2];
+  __shared__ ShaHelper help;
+  const uint32_t wid = threadIdx.x >> 6;
+  ShaLanes sh;
+  if (wid == 0) {
+    sh = sha_lanes_load(S->st);
+    sha_init(sha_buf());
+  }
+  if (threadIdx.x == 0) {
+    e_sh[0] = e0;
+    e_sh[1] = e2;
+    help.ready = 0;
+  }
+  __syncthreads();
+  const uint64_t f0 = e_sh[0], f2 = e_sh[1];
+  if (wid == 2) {
+    sha_help(gl_round_word(f0, f2), sha_buf(), &help, 0);
+  } else if (wid == 0) {
+    const uint64_t claim = S->claim;
+    sh = sha_compress_wave<true>(sh, gl_round_word(f0, f2), sha_buf(), &help, 0);
+    const uint64_t r = gl_accept_wave(sh);
+    sha_lanes_store(S->st, sh);
+    if (threadIdx.x == 0) {
+      const uint64_t e1 = gl_sub(claim, f0);
+      *r_out = r;
+      msg[0] = f0;
+      msg[1] = e1;
+      msg[2] = f2;
+      S->claim = gl_interp3(f0, e1, f2, r);
+    }
+  }
 }
 
 // The summand of a round over NT tables at one point: T0 T1 + T2 (NT = 3) or
@@ -636,7 +656,7 @@ __global__ void __launch_bounds__(kBlock) k_gl_round(Step st) {
       tot[1] = gl_add(tot[1], partials[2 * b + 1]);
     }
     gl_block_sum<2>(tot);
-    if (threadIdx.x == 0) *P<uint64_t*>(st, B + 3) = gl_round_step(S, tot[0], tot[1], P<uint64_t*>(st, B + 4));
+    gl_round_step(S, tot[0], tot[1], P<uint64_t*>(st, B + 3), P<uint64_t*>(st, B + 4));
   }
 }
 
@@ -660,62 +680,158 @@ __global__ void __launch_bounds__(kBlock) k_gl_tail(Step st) {
   GlState* S = P<GlState*>(st, B + 1);
   uint64_t* r_out = P<uint64_t*>(st, B + 2);
   uint64_t* msg = P<uint64_t*>(st, B + 3);
-  __shared__ uint64_t r_sh;
-  bool fold = rpending != nullptr;
-  if (threadIdx.x == 0) r_sh = fold ? *rpending : 0;
-  __syncthreads();
+  // The folded tables stay in shared memory, packed (a level of m entries
+  // takes NT m words, table k from k m): at most 2^kGlTailMaxLog entries per
+  // table. A pair's entries are folded and evaluated by one thread, so a round
+  // is one pass, one sum and the hash.
+  extern __shared__ uint64_t lvl[];
+  __shared__ uint64_t r_sh[2], e_sh[2][2], red[2][kBlock / 64];
+  __shared__ ShaHelper help;
+  const uint32_t wid = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const uint32_t rounds = st.u[0];
+  const bool pending = rpending != nullptr;
   uint64_t size = st.q[0];
-  for (uint32_t j = 0;; ++j) {
-    const uint64_t r = r_sh;
-    if (fold) {
-      const uint64_t m = size / 2;
-      for (uint64_t t = threadIdx.x; t < NT * m; t += blockDim.x) {
-        const uint32_t k = (uint32_t)(t / m);
-        const uint64_t i = t - k * m;
-        const uint64_t* sp = src[0];
-        uint64_t* dp = dst[0];
-#pragma unroll
-        for (int q = 1; q < NT; ++q)
-          if (k == (uint32_t)q) {
-            sp = src[q];
-            dp = dst[q];
-          }
-        const uint64_t a0 = gld(sp, i), a1 = gld(sp, i + m);
-        gst(dp, i, gl_add(a0, gl_mul(r, gl_sub(a1, a0))));
-      }
-      __syncthreads();
-#pragma unroll
-      for (int k = 0; k < NT; ++k) src[k] = dst[k];
-      size = m;
-    }
-    if (j == st.u[0]) break;
-    const uint64_t half = size / 2;
+  ShaLanes sh;
+  uint64_t claim = 0;
+  if (wid == 0) {
+    sh = sha_lanes_load(S->st);
+    sha_init(sha_buf());
+  }
+  if (wid == 1) claim = S->claim;
+  if (threadIdx.x == 0) {
+    r_sh[1] = pending ? *rpending : 0;
+    help.ready = 0;
+  }
+  __syncthreads();
+  bool in_lds = false;  // whether the current level is in lvl
+  for (uint32_t j = 0; j < rounds; ++j) {
+    const bool fold = pending || j > 0;
+    const uint64_t r = r_sh[(j + 1) & 1];
+    if (fold) size /= 2;
+    const uint32_t half = (uint32_t)(size / 2);
+    const uint32_t old = (uint32_t)(fold ? 2 * size : size);  // entries of the level read
     uint64_t acc[2] = {0, 0};
-    for (uint64_t b = threadIdx.x; b < half; b += blockDim.x) gl_pair<NT>(src, dst, false, 0, b, half, acc[0], acc[1]);
-    gl_block_sum<2>(acc);
-    if (threadIdx.x == 0) {
-      const uint64_t rr = gl_round_step(S, acc[0], acc[1], msg + 3 * j);
-      r_out[j] = rr;
-      r_sh = rr;
+    uint64_t lo[NT], hi[NT];
+    // at most one pair per thread and pass; a level that lives in shared
+    // memory is read whole before any of it is overwritten
+    for (uint32_t b0 = 0; b0 < half; b0 += kBlock) {
+      const uint32_t b = b0 + threadIdx.x;
+      const bool act = b < half;
+      if (act) {
+#pragma unroll
+        for (int k = 0; k < NT; ++k) {
+          auto at = [&](uint32_t i) { return in_lds ? lvl[k * old + i] : gld(src[k], i); };
+          if (fold) {
+            const uint32_t m = 2 * half;
+            const uint64_t a0 = at(b), a1 = at(b + m), c0 = at(b + half), c1 = at(b + half + m);
+            lo[k] = gl_add(a0, gl_mul(r, gl_sub(a1, a0)));
+            hi[k] = gl_add(c0, gl_mul(r, gl_sub(c1, c0)));
+          } else {
+            lo[k] = at(b);
+            hi[k] = at(b + half);
+          }
+        }
+      }
+      if (in_lds) __syncthreads();  // a level in shared memory has at most kBlock pairs: one pass
+      if (act) {
+#pragma unroll
+        for (int k = 0; k < NT; ++k) {
+          lvl[k * (uint32_t)size + b] = lo[k];
+          lvl[k * (uint32_t)size + b + half] = hi[k];
+        }
+        acc[0] = gl_add(acc[0], gl_form<NT>(lo));
+        uint64_t t2[NT];
+#pragma unroll
+        for (int k = 0; k < NT; ++k) t2[k] = gl_sub(gl_double(hi[k]), lo[k]);
+        acc[1] = gl_add(acc[1], gl_form<NT>(t2));
+      }
+    }
+    in_lds = true;
+    const uint32_t nw = half >= kBlock ? kBlock / 64 : (half + 63) / 64;  // waves with pairs
+    if (wid < nw) {
+      acc[0] = gl_wave_sum63(acc[0]);
+      acc[1] = gl_wave_sum63(acc[1]);
+      if (lane == 63) {
+        red[0][wid] = acc[0];
+        red[1][wid] = acc[1];
+      }
     }
     __syncthreads();
-    fold = true;
-  }
-  if (threadIdx.x == 0) {
-    const uint64_t v = gld(src[0], 0);
-    *P<uint64_t*>(st, B + 4) = v;
-    uint64_t* proof_value = P<uint64_t*>(st, B + 5);
-    if (proof_value) {
-      *proof_value = v;
-      Sha256State sh = gl_load_state(S);
-      gl_absorb_value(sh, v);
-      gl_save_state(S, sh);
+    if (wid != 3) {
+      uint64_t e0 = red[0][0], e2 = red[1][0];
+      for (uint32_t w = 1; w < nw; ++w) {
+        e0 = gl_add(e0, red[0][w]);
+        e2 = gl_add(e2, red[1][w]);
+      }
+      if (wid == 0) {
+        sh = sha_compress_wave<true>(sh, gl_round_word(e0, e2), sha_buf(), &help, 3 * j);
+        const uint64_t rr = gl_accept_wave(sh);
+        if (lane == 0) {
+          r_sh[j & 1] = rr;
+          r_out[j] = rr;
+        }
+      } else if (wid == 2) {
+        sha_help(gl_round_word(e0, e2), sha_buf(), &help, 3 * j);
+      } else {
+        // wave 1: the claim through the previous round, then this round's message
+        if (j > 0) {
+          const uint32_t q = (j - 1) & 1;
+          claim = gl_interp3(e_sh[q][0], gl_sub(claim, e_sh[q][0]), e_sh[q][1], r_sh[q]);
+        }
+        if (lane == 0) {
+          e_sh[j & 1][0] = e0;
+          e_sh[j & 1][1] = e2;
+          msg[3 * j] = e0;
+          msg[3 * j + 1] = gl_sub(claim, e0);
+          msg[3 * j + 2] = e2;
+        }
+      }
     }
+    __syncthreads();
+  }
+  // the last fold, every table's final entry to its first place (the copy
+  // tables read them there), and the last claim move
+  if (wid == 0) {
+    const bool fold = pending || rounds > 0;
+    const uint64_t r = r_sh[(rounds + 1) & 1];
+    uint64_t v = 0;
+#pragma unroll
+    for (int k = NT - 1; k >= 0; --k) {
+      if (fold) {
+        const uint64_t a0 = in_lds ? lvl[2 * k] : gld(src[k], 0), a1 = in_lds ? lvl[2 * k + 1] : gld(src[k], 1);
+        v = gl_add(a0, gl_mul(r, gl_sub(a1, a0)));
+        if (lane == 0) gst(dst[k], 0, v);
+      } else {
+        v = gld(src[k], 0);
+      }
+    }
+    uint64_t* proof_value = P<uint64_t*>(st, B + 5);
+    if (lane == 0) *P<uint64_t*>(st, B + 4) = v;
+    if (proof_value) {
+      if (lane == 0) *proof_value = v;
+      sha_lanes_store(sha_buf()->msg, sh);
+      if (lane < 3)
+        sha_buf()->msg[8 + lane] = lane == 0 ? kTagValue : bswap32((uint32_t)(lane == 1 ? v : v >> 32));
+      sh = sha_message_wave<11>(sha_buf());
+    }
+    sha_lanes_store(S->st, sh);
+  } else if (wid == 1 && rounds > 0) {
+    const uint32_t q = (rounds - 1) & 1;
+    claim = gl_interp3(e_sh[q][0], gl_sub(claim, e_sh[q][0]), e_sh[q][1], r_sh[q]);
+    if (lane == 0) S->claim = claim;
   }
 }
 
 #undef GTID
 #undef GSTRIDE
+
+// Largest table (log2 of its entries) a tail evaluates: its levels fit the 64
+// KiB of shared memory a kernel has without asking for more.
+constexpr uint32_t kGlTailMaxLog = 10;
+
+static size_t gl_tail_lds(const Step& st, size_t nt) {
+  return 8 * nt * (st.p[2 * nt] ? st.q[0] / 2 : st.q[0]);  // p[2 NT]: the pending challenge
+}
 
 void launch_gl_step(const Step& st, hipStream_t s) {
   const int tok = prof_begin(s);
@@ -731,9 +847,9 @@ void launch_gl_step(const Step& st, hipStream_t s) {
     case ST_GL_WSUM: k_gl_wsum<<<grid, block, 0, s>>>(st); cls = PC_CLAIM; break;
     case ST_GL_P1: k_gl_p1<<<grid, block, 0, s>>>(st); cls = PC_PHASE1_INIT; break;
     case ST_GL_ROUND: k_gl_round<3><<<grid, block, 0, s>>>(st); cls = PC_ROUND_A; break;
-    case ST_GL_TAIL: k_gl_tail<3><<<grid, block, 0, s>>>(st); cls = PC_TAIL_A; break;
+    case ST_GL_TAIL: k_gl_tail<3><<<grid, block, gl_tail_lds(st, 3), s>>>(st); cls = PC_TAIL_A; break;
     case ST_GL_ROUND5: k_gl_round<5><<<grid, block, 0, s>>>(st); cls = PC_ROUND_B; break;
-    case ST_GL_TAIL5: k_gl_tail<5><<<grid, block, 0, s>>>(st); cls = PC_TAIL_B; break;
+    case ST_GL_TAIL5: k_gl_tail<5><<<grid, block, gl_tail_lds(st, 5), s>>>(st); cls = PC_TAIL_B; break;
     case ST_GL_COPY_WEIGHTS: k_gl_copy_weights<<<grid, block, 0, s>>>(st); cls = PC_SMALL; break;
     case ST_GL_P2T: k_gl_p2t<<<grid, block, 0, s>>>(st); cls = PC_PHASE2_TABLES; break;
     case ST_GL_COPY_CONTRACT: k_gl_copy_contract<<<grid, block, 0, s>>>(st); cls = PC_COPY_CONTRACT; break;
@@ -851,7 +967,7 @@ void gl_phase(std::vector<Step>& steps, const uint64_t* const* src0, uint64_t* c
   uint64_t eval = 1ull << nrounds;
   uint32_t j = 0;
   const uint64_t* pending = nullptr;
-  while (j < nrounds && eval > (1ull << tun.tail_log)) {
+  while (j < nrounds && eval > (1ull << std::min(tun.tail_log, kGlTailMaxLog))) {
     const uint64_t half = eval / 2;
     Step st = gl_mk(NT == 3 ? ST_GL_ROUND : ST_GL_ROUND5, gl_tiles((half + 1) / 2, tun.max_round_blocks));
     for (int k = 0; k < NT; ++k) {

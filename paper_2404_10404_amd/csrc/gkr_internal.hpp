@@ -45,7 +45,7 @@ struct DevState {
   uint32_t pending; // 1: the claim has not yet moved through the last round
   uint32_t pad1;
   uint32_t* pend_msg;  // where that round's message goes
-  uint32_t pad[3];
+  uint32_t pad[2];     // the elements below start at a multiple of 16 bytes
   Fr claim;         // running sumcheck claim (before the pending round, if any)
   Fr pend_e0, pend_e2, pend_r;  // the pending round: its sums at t = 0, 2 and its challenge
   Fr alpha, beta;

@@ -48,11 +48,11 @@ __device__ __forceinline__ void run_step_tile_wsum(const Step& st, uint32_t t, u
 }
 __device__ __forceinline__ void run_step_tile_p1_init_round(const Step& st, uint32_t t, uint32_t n) {
   body_p1_init_round<true>(st, t, n);
-  if (last_tile(&P<DevState*>(st, 9)->counter, n)) finish_p1_init_round(st, n);
+  if (last_tile(&P<DevState*>(st, 9)->counter, n)) finish_p1_init_round<false>(st, n);
 }
 __device__ __forceinline__ void run_step_tile_round_a(const Step& st, uint32_t t, uint32_t n) {
   body_round<FormA>(st, t, n);
-  if (last_tile(&P<DevState*>(st, RoundPtrs<3>::kS)->counter, n)) finish_round_step<FormA>(st, n);
+  if (last_tile(&P<DevState*>(st, RoundPtrs<3>::kS)->counter, n)) finish_round_step<FormA, false>(st, n);
 }
 __device__ __forceinline__ void run_step_tile_local_values(const Step& st, uint32_t t, uint32_t n) {
   body_local_values(st, t, n);
@@ -60,7 +60,7 @@ __device__ __forceinline__ void run_step_tile_local_values(const Step& st, uint3
 }
 __device__ __forceinline__ void run_step_tile_round_b(const Step& st, uint32_t t, uint32_t n) {
   body_round<FormB>(st, t, n);
-  if (last_tile(&P<DevState*>(st, RoundPtrs<5>::kS)->counter, n)) finish_round_step<FormB>(st, n);
+  if (last_tile(&P<DevState*>(st, RoundPtrs<5>::kS)->counter, n)) finish_round_step<FormB, false>(st, n);
 }
 
 GKR_PLAIN_KERNEL(k_to_mont, to_mont)

@@ -212,16 +212,6 @@ __device__ __forceinline__ Sha256State node_hash(const uint32_t (&l)[8], const u
   return sha256_compress_v(sha256_iv(), blk);
 }
 
-__device__ void absorb_tagged_digest(Sha256State& st, uint32_t tag, const uint32_t* d) {
-  uint32_t w[17];
-#pragma unroll
-  for (int k = 0; k < 8; ++k) w[k] = st.h[k];
-  w[8] = tag;
-#pragma unroll
-  for (int k = 0; k < 8; ++k) w[9 + k] = d[k];
-  st = sha256_fixed<17>(w);
-}
-
 // ---------------------------------------------------------------- kernels
 
 // ST_VPD_POWERS: p0[i] = base^i for i < q0; base = w[0..7] (Montgomery).
@@ -454,34 +444,37 @@ __global__ void __launch_bounds__(kBlock) k_vpd_tree_top(Step st) {
   }
 }
 
-// ST_VPD_BEGIN (one thread): lam = squeeze. p0 S, p1 V.
-__global__ void k_vpd_begin(Step st) {
-  if (threadIdx.x != 0) return;
+// ST_VPD_BEGIN (one wave): lam = squeeze. p0 S, p1 V.
+__global__ void __launch_bounds__(kBlock) k_vpd_begin(Step st) {
+  if (threadIdx.x >= 64) return;
   DevState* S = P<DevState*>(st, 0);
   VpdState* V = P<VpdState*>(st, 1);
-  Sha256State sh = load_state(S);
-  V->lam = squeeze(sh);
-  save_state(S, sh);
+  sha_init(sha_buf());
+  ShaLanes sh = sha_lanes_load(S->st);
+  sha_rehash_wave(sh, sha_buf());
+  sha_accept_wave(sh, sha_buf());
+  store_challenge(sh, nullptr, &V->lam);
+  sha_lanes_store(S->st, sh);
 }
 
-// ST_VPD_ABSORB (one thread): absorb("GKRM", root p1) and copy the root to
+// ST_VPD_ABSORB (one wave): absorb("GKRM", root p1) and copy the root to
 // the proof at p2 (big-endian bytes), then squeeze u0 challenges into p3.
 // p0 S.
-__global__ void k_vpd_absorb(Step st) {
-  if (threadIdx.x != 0) return;
+__global__ void __launch_bounds__(kBlock) k_vpd_absorb(Step st) {
+  if (threadIdx.x >= 64) return;
   DevState* S = P<DevState*>(st, 0);
-  const uint32_t* root = P<const uint32_t*>(st, 1);
-  uint32_t* proof = P<uint32_t*>(st, 2);
+  const uint32_t r = P<const uint32_t*>(st, 1)[threadIdx.x & 7];
   Fr* out = P<Fr*>(st, 3);
-  Sha256State sh = load_state(S);
-  uint32_t r[8];
-#pragma unroll
-  for (int k = 0; k < 8; ++k) r[k] = root[k];
-  absorb_tagged_digest(sh, kTagCommit, r);
-#pragma unroll
-  for (int k = 0; k < 8; ++k) proof[k] = bswap32(r[k]);
-  for (uint32_t i = 0; i < st.u[0]; ++i) out[i] = squeeze(sh);
-  save_state(S, sh);
+  sha_init(sha_buf());
+  ShaLanes sh = sha_lanes_load(S->st);
+  sha_absorb_words_wave(sh, sha_buf(), kTagCommit, r);
+  if (threadIdx.x < 8) P<uint32_t*>(st, 2)[threadIdx.x] = bswap32(r);
+  for (uint32_t i = 0; i < st.u[0]; ++i) {
+    sha_rehash_wave(sh, sha_buf());
+    sha_accept_wave(sh, sha_buf());
+    store_challenge(sh, nullptr, out + i);
+  }
+  sha_lanes_store(S->st, sh);
 }
 
 // ST_VPD_ROOT_OUT (one thread): the root p0 as 32 big-endian bytes at p1.
@@ -539,25 +532,33 @@ __global__ void __launch_bounds__(kBlock) k_vpd_fold(Step st) {
   }
 }
 
-// ST_VPD_FINAL (one thread): the constant of the last layer p0 into the proof
+// ST_VPD_FINAL (one wave): the constant of the last layer p0 into the proof
 // (p2, canonical) and the transcript ("GKRV"), then u0 query leaves
 // (challenge mod q0) into V->idx. p1 S, p3 V.
-__global__ void k_vpd_final(Step st) {
-  if (threadIdx.x != 0) return;
+__global__ void __launch_bounds__(kBlock) k_vpd_final(Step st) {
+  if (threadIdx.x >= 64) return;
   const Fr* last = P<const Fr*>(st, 0);
   DevState* S = P<DevState*>(st, 1);
   uint32_t* proof = P<uint32_t*>(st, 2);
   VpdState* V = P<VpdState*>(st, 3);
   const Fr c = fr_from_mont(opaque(last[0]));
-  Sha256State sh = load_state(S);
-  absorb_element(sh, kTagValue, c);
+  sha_init(sha_buf());
+  ShaLanes sh = sha_lanes_load(S->st);
+  sha_absorb_words_wave(sh, sha_buf(), kTagValue, bswap32(lane_limb(c)));
+  if (threadIdx.x < 8) proof[threadIdx.x] = lane_limb(c);
+  // 64 challenges at a time, lane q converting the q-th
+  for (uint32_t q0 = 0; q0 < st.u[0]; q0 += 64) {
+    const uint32_t nq = st.u[0] - q0 < 64 ? st.u[0] - q0 : 64;
+    Fr mine = fr_zero();
+    for (uint32_t q = 0; q < nq; ++q) {
+      const Fr a = sha_squeeze_wave(sh, sha_buf());
 #pragma unroll
-  for (int k = 0; k < 8; ++k) proof[k] = c.v[k];
-  for (uint32_t q = 0; q < st.u[0]; ++q) {
-    const Fr r = fr_from_mont(squeeze(sh));
-    V->idx[q] = r.v[0] & (uint32_t)(st.q[0] - 1);
+      for (int k = 0; k < 8; ++k) mine.v[k] = threadIdx.x == q ? a.v[k] : mine.v[k];
+    }
+    const Fr r = fr_from_mont(opaque(mine));
+    if (threadIdx.x < nq) V->idx[q0 + threadIdx.x] = r.v[0] & (uint32_t)(st.q[0] - 1);
   }
-  save_state(S, sh);
+  sha_lanes_store(S->st, sh);
 }
 
 // ST_VPD_QUERIES: thread (query q, part) writes its part of query q's
