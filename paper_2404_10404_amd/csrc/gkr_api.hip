@@ -13,6 +13,8 @@
 #include "gkr_kernels.hpp"
 #include "gkr_program.hpp"
 #include "gkr_contract.hpp"
+#include "gkr_split.hpp"
+#include "gkr_wide.hpp"
 #include "gkr_tuning.hpp"
 #include "gkr_vpd.hpp"
 
@@ -327,6 +329,10 @@ void Program::round(const Fr* const* src, Fr* const* dst, uint64_t half, const F
   }
   st.p[R::kR] = rprev; st.p[R::kS] = S; st.p[R::kPart] = partials; st.p[R::kROut] = r_out; st.p[R::kMsg] = msg;
   st.q[0] = half;
+  if (plain && half <= (NT == 3 ? kWideMaxHalfA : kWideMaxHalfB)) {
+    st.type = NT == 3 ? ST_W_ROUND_A : ST_W_ROUND_B;
+    st.ntiles = (uint32_t)((half + kWidePairs - 1) / kWidePairs);
+  }
   round_work(NT, NT == 3 ? 1.0 : 1.5, half, rprev != nullptr, st.bytes, st.mulmods);
   steps.push_back(st);
 }
@@ -414,7 +420,9 @@ void Program::state_import(DevState* S, const uint8_t* in) {
 
 void Program::run(hipStream_t s) const {
   for (const Step& st : steps) {
-    if (st.type >= ST_CC_BUILD) launch_cc_step(st, s);
+    if (st.type >= ST_W_ROUND_A) launch_wide_step(st, s);
+    else if (st.type >= ST_S_SMALL) launch_split_step(st, s);
+    else if (st.type >= ST_CC_BUILD) launch_cc_step(st, s);
     else if (st.type >= ST_VPD_POWERS) launch_vpd_step(st, s);
     else if (st.type >= ST_GL_FORWARD) launch_gl_step(st, s);
     else if (st.type >= ST_G_GATHER) launch_general_step(st, s);
@@ -437,7 +445,8 @@ static void emit_phase(Program& pg, const Fr* const* src0, Fr* const* dst, uint3
   uint64_t eval = 1ull << (nrounds - first_round);
   uint32_t j = first_round;
   const Fr* pending = first_round ? r_out + first_round - 1 : nullptr;
-  while (j < nrounds && eval > (1ull << tun.tail_log)) {
+  const uint32_t tail_log = pg.plain ? std::min(tun.tail_log, kTailMaxLog) : tun.tail_log;
+  while (j < nrounds && eval > (1ull << tail_log)) {
     pg.round<NT>(src, dst, eval / 2, pending, S, partials, r_out + j, msg + 24 * j, tun);
     if (pending) {
       for (int k = 0; k < NT; ++k) src[k] = dst[k];
@@ -473,7 +482,11 @@ void emit_layer(Program& pg, const gkr_circuit& c, uint32_t i, const Workspace& 
   const Fr* ta_src[3] = {W, w.G, w.H};
   Fr* ta_dst[3] = {w.Wf, w.G, w.H};
   const uint32_t off_vx = 24 * s1, off_p2 = off_vx + 8, off_vy = off_p2 + 24 * s1;
-  if (s1 > tun.tail_log) {
+  // (the contracted form uses kernels that only the plain launcher has)
+  const bool split = pg.plain && tun.matrix_cores && split_applies(n, sg1);
+  if (split) {
+    emit_phase1_split(pg, w, c.wiring[i], W, n, sg1, 1ull << sg, c.mul_gates[i], rx, proof, tun);
+  } else if (s1 > tun.tail_log) {
     pg.p1_init_round(W, w.G, w.H, c.wiring[i], w.aU, w.bV, w.Cu, w.Cv, n, 1ull << (s1 - 1), 1ull << c.s(i), S,
                      w.partials, rx, proof, tun);
     emit_phase<3>(pg, ta_src, ta_dst, s1, S, w.partials, rx, proof, &S->vx, proof + off_vx, tun, 1);
@@ -483,15 +496,17 @@ void emit_layer(Program& pg, const gkr_circuit& c, uint32_t i, const Workspace& 
   }
   // Phase 2: sub-circuit rounds with the copy factors contracted, then the copy rounds.
   {
-    const uint32_t bits[2] = {sg1, n};
-    const Fr* pts[2] = {rx, rx + sg1};
+    // (EL is there already after the contracted phase 1)
+    const uint32_t bits[2] = {n, sg1};
+    const Fr* pts[2] = {rx + sg1, rx};
     const Fr* scl[2] = {nullptr, nullptr};
-    Fr* outs[2] = {w.EL, w.EC};
-    pg.eq(2, bits, pts, scl, outs);
+    Fr* outs[2] = {w.EC, w.EL};
+    pg.eq(split ? 1 : 2, bits, pts, scl, outs);
   }
   pg.copy_weights(w.Cu, w.Cv, w.EC, w.U, w.V, 1ull << n, S);
-  pg.p2_tables(c.wiring[i], w.aU, w.bV, w.EL, S, w.Fa, w.Fb, w.Ka, w.Kb, w.Ks, 1ull << sg1, 1ull << sg);
-  if (pg.matrix_cores && tun.matrix_cores && w.cc && cc_applies(n, sg1)) emit_copy_contract_mfma(pg, W, w.U, w.V, w.P, w.Q, n, sg1, w.cc);
+  if (split) emit_p2_final(pg, w, 1ull << sg1);
+  else pg.p2_tables(c.wiring[i], w.aU, w.bV, w.EL, S, w.Fa, w.Fb, w.Ka, w.Kb, w.Ks, 1ull << sg1, 1ull << sg);
+  if (pg.plain && tun.matrix_cores && w.cc && cc_applies(n, sg1)) emit_contract_mfma(pg, W, w.U, w.V, w.P, w.Q, n, sg1, false, w.cc);
   else pg.copy_contract(W, w.U, w.V, w.P, w.Q, n, 1ull << sg1);
   Fr* tb[5] = {w.P, w.Fa, w.Q, w.Fb, w.Ks};
   const Fr* tb_src[5] = {w.P, w.Fa, w.Q, w.Fb, w.Ks};
@@ -686,21 +701,26 @@ int32_t gkr_circuit_create(uint32_t depth, uint32_t log_copies, const uint32_t* 
       const uint64_t lim = 1ull << c->sigma[i + 1];
       c->gates[i].assign(gates[i], gates[i] + cnt);
       c->mul_gates.push_back(0);
+      uint64_t muls = 0;
       for (uint64_t z = 0; z < cnt; ++z) {
         const gkr_gate& g = c->gates[i][z];
-        c->mul_gates.back() += g.type == GKR_GATE_MUL;
+        muls += g.type == GKR_GATE_MUL;
         if (g.x >= lim || g.y >= lim || g.type > 1) {
           delete c;
           set_error("layer " + std::to_string(i) + " gate " + std::to_string(z) + " is invalid");
           return GKR_EINVAL;
         }
       }
+      c->mul_gates.back() = muls;
     }
     // circuit digest
     {
-      std::vector<uint8_t> msg;
+      size_t bytes = 4 * ((size_t)depth + 3);
+      for (uint32_t i = 0; i < depth; ++i) bytes += (size_t)9 << c->sigma[i];
+      std::vector<uint8_t> msg(bytes);
+      uint8_t* out_byte = msg.data();
       auto put32 = [&](uint32_t v) {
-        for (int k = 0; k < 4; ++k) msg.push_back((uint8_t)(v >> (8 * k)));
+        for (int k = 0; k < 4; ++k) *out_byte++ = (uint8_t)(v >> (8 * k));
       };
       put32(depth);
       put32(log_copies);
@@ -709,12 +729,12 @@ int32_t gkr_circuit_create(uint32_t depth, uint32_t log_copies, const uint32_t* 
         for (const gkr_gate& g : c->gates[i]) {
           put32(g.x);
           put32(g.y);
-          msg.push_back((uint8_t)g.type);
+          *out_byte++ = (uint8_t)g.type;
         }
       sha256_bytes(msg.data(), msg.size(), c->digest);
     }
     // wiring indexes: gate records, CSR by x and by y, in one device block
-    std::vector<size_t> offs(5 * depth);
+    std::vector<size_t> offs(7 * depth);
     size_t total = 0;
     auto take = [&](size_t bytes) {
       size_t o = total;
@@ -728,6 +748,8 @@ int32_t gkr_circuit_create(uint32_t depth, uint32_t log_copies, const uint32_t* 
       offs[5 * i + 2] = take(8 * cnt);
       offs[5 * i + 3] = take(4 * rows);
       offs[5 * i + 4] = take(8 * cnt);
+      offs[5 * depth + 2 * i] = take(4 * rows);
+      offs[5 * depth + 2 * i + 1] = take(4 * std::max<size_t>(1, (rows - 1) / 16));  // 2^(sigma + 1) bits
     }
     std::vector<uint8_t> host(total, 0);
     for (uint32_t i = 0; i < depth; ++i) {
@@ -748,9 +770,27 @@ int32_t gkr_circuit_create(uint32_t depth, uint32_t log_copies, const uint32_t* 
         xrow[r + 1] += xrow[r];
         yrow[r + 1] += yrow[r];
       }
-      std::vector<uint32_t> fx(xrow, xrow + rows), fy(yrow, yrow + rows);
+      // an x's MUL gates come before its ADD gates
+      uint32_t* xmid = reinterpret_cast<uint32_t*>(host.data() + offs[5 * depth + 2 * i]);
+      uint32_t* act = reinterpret_cast<uint32_t*>(host.data() + offs[5 * depth + 2 * i + 1]);
+      for (size_t r = 0; r < rows; ++r) xmid[r] = xrow[r];
+      for (size_t z = 0; z < cnt; ++z) xmid[gl[z].x] += gl[z].type == GKR_GATE_MUL;
+      // the rows with a MUL gate, then each level's from the next larger one's
+      for (size_t r = 0; r < rows; ++r)
+        if (xmid[r] != xrow[r]) act[(rows + r) >> 5] |= 1u << ((rows + r) & 31);
+      for (size_t m = rows / 2; m >= 1; m /= 2) {
+        if (m >= 32) {  // whole words
+          for (size_t v = 0; v < m / 32; ++v) act[m / 32 + v] = act[m / 16 + v] | act[m / 16 + m / 32 + v];
+          continue;
+        }
+        for (size_t r = 0; r < m; ++r) {
+          const size_t lo = 2 * m + r, hi = lo + m;
+          if (((act[lo >> 5] >> (lo & 31)) | (act[hi >> 5] >> (hi & 31))) & 1u) act[(m + r) >> 5] |= 1u << ((m + r) & 31);
+        }
+      }
+      std::vector<uint32_t> fx(xrow, xrow + rows), fa(xmid, xmid + rows), fy(yrow, yrow + rows);
       for (size_t z = 0; z < cnt; ++z) {
-        const uint32_t kx = fx[gl[z].x]++, ky = fy[gl[z].y]++;
+        const uint32_t kx = gl[z].type == GKR_GATE_MUL ? fx[gl[z].x]++ : fa[gl[z].x]++, ky = fy[gl[z].y]++;
         xent[2 * kx] = (uint32_t)z;
         xent[2 * kx + 1] = gl[z].y | ((uint32_t)gl[z].type << 31);
         yent[2 * ky] = (uint32_t)z;
@@ -788,6 +828,8 @@ int32_t gkr_circuit_create(uint32_t depth, uint32_t log_copies, const uint32_t* 
       c->wiring[i].xent = reinterpret_cast<const uint2*>(base + offs[5 * i + 2]);
       c->wiring[i].yrow = reinterpret_cast<const uint32_t*>(base + offs[5 * i + 3]);
       c->wiring[i].yent = reinterpret_cast<const uint2*>(base + offs[5 * i + 4]);
+      c->wiring[i].xmid = reinterpret_cast<const uint32_t*>(base + offs[5 * depth + 2 * i]);
+      c->wiring[i].act = reinterpret_cast<const uint32_t*>(base + offs[5 * depth + 2 * i + 1]);
     }
     plan_workspace(*c, c->plan);
     *out = c;

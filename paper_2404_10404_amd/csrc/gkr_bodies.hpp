@@ -28,6 +28,7 @@
 
 #include "gkr_device.hpp"
 #include "gkr_kernels.hpp"
+#include "fr_row.hpp"
 #include "sha256_wave.hpp"
 
 namespace gkr {
@@ -479,21 +480,30 @@ __device__ __forceinline__ void finish_reduced_round(const Fr* partials, uint32_
   };
   if constexpr (!Late) fetch();
   if (threadIdx.x == 0) help.ready = 0;
-  Fr tot[2];
-  if (ntiles <= 64) {
-    // every partial fits in wave 0: a wave sum, no LDS round trip
-    tot[0] = fr_zero();
-    tot[1] = fr_zero();
-    if (wid == 0) {
-      if (threadIdx.x < ntiles) {
-        tot[0] = ldf(partials, 2ull * threadIdx.x);
-        tot[1] = ldf(partials, 2ull * threadIdx.x + 1);
-      }
-      tot[0] = lane_fr(wave_sum_to_lane63(tot[0]), 63);
-      tot[1] = lane_fr(wave_sum_to_lane63(tot[1]), 63);
+  if constexpr (Late) {
+    Fr tot[2];
+    sum_partials<2>(partials, ntiles, tot);
+    if (threadIdx.x == 0) {
+      e_sh[0] = tot[0];
+      e_sh[1] = tot[1];
     }
   } else {
-    sum_partials<2>(partials, ntiles, tot);
+    // lanes 0..31 of each wave take the sums at t = 0, lanes 32..63 those at t = 2
+    __shared__ Fr red[16][2];
+    const uint32_t lane = threadIdx.x & 63, pt = lane >> 5, nw = blockDim.x >> 6;
+    const uint32_t busy = (ntiles + 31) / 32 < nw ? (ntiles + 31) / 32 : nw;  // waves with partials
+    if (wid < busy) {
+      Fr v = fr_zero();
+      for (uint32_t i = wid * 32 + (lane & 31); i < ntiles; i += nw * 32) v = fr_add(v, ldf(partials, 2ull * i + pt));
+      v = half_wave_sum(v);
+      if ((lane & 31) == 31) red[wid][pt] = v;
+    }
+    __syncthreads();
+    if (wid == 0) {
+      Fr v = red[0][pt];
+      for (uint32_t w = 1; w < busy; ++w) v = fr_add(v, red[w][pt]);
+      if ((lane & 31) == 0) e_sh[pt] = v;
+    }
   }
   bool pend = false;
   Fr claim, pe0, pe2, pr;
@@ -507,10 +517,6 @@ __device__ __forceinline__ void finish_reduced_round(const Fr* partials, uint32_
       pr = S->pend_r;
       pmsg = S->pend_msg;
     }
-  }
-  if (threadIdx.x == 0) {
-    e_sh[0] = tot[0];
-    e_sh[1] = tot[1];
   }
   if constexpr (Late) fetch();
   // wave 1 has read the pending round before wave 0 overwrites it
@@ -835,140 +841,70 @@ __device__ __forceinline__ void body_tail(const Step& st, uint32_t, uint32_t) {
 // entries): t = 0: L[b] and L[b + 2Q]; t = 2: 2 L[b + Q] - L[b] and
 // 2 L[b + 3Q] - L[b + 2Q]. The term (products of pairs of tables plus the
 // additive table) is then a quadratic q(r) fixed by q(0), q(1) and its leading
-// coefficient (the product of the slopes), three products per task and form
-// product; the sums over tasks give e_t(r) = V0 + r (V1 - V0 - C2) + r^2 C2.
+// coefficient (the product of the slopes); the sums over the pairs give
+// e_t(r) = V0 + r (V1 - V0 - C2) + r^2 C2.
 
-// One task of the coefficient sums: pair b of the next level at t = 0 or 2
-// (t2), from level L (4Q entries); adds q(0), q(1) and the leading coefficient.
+// Levels of a tail: at most 2^kTailMaxLog entries per table once evaluated,
+// twice that before the pending fold, all in shared memory.
 template <class Form>
-__device__ __forceinline__ void tail_task(const Fr* const* L, uint64_t b, uint64_t Q, bool t2, Fr (&acc)[3]) {
-  constexpr int NT = Form::NT;
-  Fr p0[NT], p1[NT];
-#pragma unroll
-  for (int k = 0; k < NT; ++k) {
-    const Fr a = ldf(L[k], b), c = ldf(L[k], b + 2 * Q);
-    if (t2) {
-      const Fr a1 = ldf(L[k], b + Q), c1 = ldf(L[k], b + 3 * Q);
-      p0[k] = fr_sub(fr_double(a1), a);
-      p1[k] = fr_sub(fr_double(c1), c);
-    } else {
-      p0[k] = a;
-      p1[k] = c;
-    }
+struct TailLevel {
+  Fr t[Form::NT][2u << kTailMaxLog];
+};
+
+// One table's value of a coefficient stream: s = 0: p(0), s = 1: p(1), s = 2: the slope.
+__device__ __forceinline__ Fr tail_line(const Fr* L, uint32_t b, uint32_t Q, uint32_t s, bool t2) {
+  Fr x0 = fr_zero(), x1 = fr_zero();
+  if (s != 1) {
+    const Fr a = opaque(L[b]);
+    x0 = t2 ? fr_sub(fr_double(opaque(L[b + Q])), a) : a;
   }
-  Fr v0, v1, c2;
-  if constexpr (NT == 3) {
-    v0 = fr_add(fr_mul(p0[0], p0[1]), p0[2]);
-    v1 = fr_add(fr_mul(p1[0], p1[1]), p1[2]);
-    c2 = fr_mul(fr_sub(p1[0], p0[0]), fr_sub(p1[1], p0[1]));
-  } else {
-    v0 = fr_add(fr_mul_add2(p0[0], p0[1], p0[2], p0[3]), p0[4]);
-    v1 = fr_add(fr_mul_add2(p1[0], p1[1], p1[2], p1[3]), p1[4]);
-    c2 = fr_mul_add2(fr_sub(p1[0], p0[0]), fr_sub(p1[1], p0[1]), fr_sub(p1[2], p0[2]), fr_sub(p1[3], p0[3]));
+  if (s != 0) {
+    const Fr c = opaque(L[b + 2 * Q]);
+    x1 = t2 ? fr_sub(fr_double(opaque(L[b + 3 * Q])), c) : c;
   }
-  acc[0] = fr_add(acc[0], v0);
-  acc[1] = fr_add(acc[1], v1);
-  acc[2] = fr_add(acc[2], c2);
+  return s == 0 ? x0 : (s == 1 ? x1 : fr_sub(x1, x0));
 }
 
-// The same for a round whose level needs no fold (the tail's first round when
-// no challenge is pending): pair b of L (2 half entries) at t; a constant
-// quadratic (q(0) = q(1), no leading coefficient).
-template <class Form>
-__device__ __forceinline__ void tail_task_direct(const Fr* const* L, uint64_t b, uint64_t half, bool t2,
-                                                 Fr (&acc)[3]) {
-  constexpr int NT = Form::NT;
-  Fr x[NT];
-#pragma unroll
-  for (int k = 0; k < NT; ++k) {
-    const Fr lo = ldf(L[k], b);
-    x[k] = t2 ? fr_sub(fr_double(ldf(L[k], b + half)), lo) : lo;
-  }
-  Fr v;
-  if constexpr (NT == 3) v = fr_add(fr_mul(x[0], x[1]), x[2]);
-  else v = fr_add(fr_mul_add2(x[0], x[1], x[2], x[3]), x[4]);
-  acc[0] = fr_add(acc[0], v);
-  acc[1] = fr_add(acc[1], v);
-}
-
-// Worker waves whose tasks are nonempty for `tasks` tasks per half.
-__device__ __forceinline__ uint32_t tail_active_waves(uint64_t tasks, uint32_t hw) {
-  const uint64_t w = (tasks + 63) / 64;
-  return w < hw ? (uint32_t)w : hw;
-}
-
-// The coefficient sums of one point over one half of the worker waves: each
-// thread takes tasks th, th + nth, ..; each wave with tasks sums its lanes and
-// stores (V0, V1, C2) in part[wave of the half].
-template <class Form>
-__device__ __forceinline__ void tail_coefficients(const Fr* const* L, uint64_t tasks, bool direct, bool t2,
-                                                  uint32_t th, uint32_t nth, uint32_t wih, uint32_t nact,
-                                                  Fr (*part)[3]) {
-  if (wih >= nact) return;  // the wave has no task
-  Fr acc[3] = {fr_zero(), fr_zero(), fr_zero()};
-  if (direct) {
-    for (uint64_t b = th; b < tasks; b += nth) tail_task_direct<Form>(L, b, tasks, t2, acc);
-  } else {
-    for (uint64_t b = th; b < tasks; b += nth) tail_task<Form>(L, b, tasks, t2, acc);
-  }
-#pragma unroll
-  for (int k = 0; k < 3; ++k) acc[k] = wave_sum_to_lane63(acc[k]);
-  if ((threadIdx.x & 63) == 63) {
-#pragma unroll
-    for (int k = 0; k < 3; ++k) part[wih][k] = acc[k];
-  }
-}
-
-// Round j + 1's coefficient sums for at most 32 pairs: coefficient s (q(0),
-// q(1) or the leading one) of every task in one wave, lanes 0..31 at t = 0 and
-// lanes 32..63 at t = 2, one pair per lane (one product, or one pair of
-// products for Form B); a segmented sum leaves the totals in lanes 31 and 63.
-template <class Form>
-__device__ __forceinline__ void tail_coefficient_stream(const Fr* const* L, uint64_t Q, uint32_t s,
-                                                        Fr (*part)[8][3]) {
+// Coefficient s (q(0), q(1) or the leading one) summed over Q pairs by one
+// wave, lanes 0..31 at t = 0 and lanes 32..63 at t = 2, to part[t][s]. With
+// Direct the level needs no fold (the tail's first round when no challenge is
+// pending; Q pairs of 2Q entries): q is constant, so s = 0 gives both values.
+template <class Form, bool Direct>
+__device__ __forceinline__ void tail_stream(const TailLevel<Form>& lv, uint32_t Q, uint32_t s, Fr (*part)[3]) {
   constexpr int NT = Form::NT;
   const uint32_t lane = threadIdx.x & 63;
   const bool t2 = lane >= 32;
-  const uint64_t b = lane & 31;
   Fr v = fr_zero();
-  if (b < Q) {
+  for (uint32_t b = lane & 31; b < Q; b += 32) {
     Fr p[NT];
 #pragma unroll
     for (int k = 0; k < NT; ++k) {
-      if (s == 2 && k == NT - 1) {  // the additive table has no slope product
-        p[k] = fr_zero();
-        continue;
-      }
-      Fr x0 = fr_zero(), x1 = fr_zero();
-      if (s != 1) {
-        const Fr a = ldf(L[k], b);
-        x0 = t2 ? fr_sub(fr_double(ldf(L[k], b + Q)), a) : a;
-      }
-      if (s != 0) {
-        const Fr c = ldf(L[k], b + 2 * Q);
-        x1 = t2 ? fr_sub(fr_double(ldf(L[k], b + 3 * Q)), c) : c;
-      }
-      p[k] = s == 0 ? x0 : (s == 1 ? x1 : fr_sub(x1, x0));
+      // the additive table has no slope product
+      if (s == 2 && k == NT - 1) p[k] = fr_zero();
+      else p[k] = tail_line(lv.t[k], b, Q, Direct ? 0 : s, t2);
     }
-    if constexpr (NT == 3) v = fr_add(fr_mul(p[0], p[1]), p[2]);
-    else v = fr_add(fr_mul_add2(p[0], p[1], p[2], p[3]), p[4]);
+    if constexpr (NT == 3) v = fr_add(v, fr_add(fr_mul(p[0], p[1]), p[2]));
+    else v = fr_add(v, fr_add(fr_mul_add2(p[0], p[1], p[2], p[3]), p[4]));
   }
-  v = fr_add(v, dpp_fr<0xB1, 0xF>(v));   // quad_perm [1,0,3,2]
-  v = fr_add(v, dpp_fr<0x4E, 0xF>(v));   // quad_perm [2,3,0,1]
-  v = fr_add(v, dpp_fr<0x141, 0xF>(v));  // row_half_mirror
-  v = fr_add(v, dpp_fr<0x140, 0xF>(v));  // row_mirror
-  v = fr_add(v, dpp_fr<0x142, 0xA>(v));  // row_bcast15 into rows 1 and 3
-  if (lane == 31) part[0][0][s] = v;
-  if (lane == 63) part[1][0][s] = v;
+  if (Q > 1) v = fr_add(v, dpp_fr<0xB1, 0xF>(v));    // quad_perm [1,0,3,2]
+  if (Q > 2) v = fr_add(v, dpp_fr<0x4E, 0xF>(v));    // quad_perm [2,3,0,1]
+  if (Q > 4) v = fr_add(v, dpp_fr<0x141, 0xF>(v));   // row_half_mirror
+  if (Q > 8) v = fr_add(v, dpp_fr<0x140, 0xF>(v));   // row_mirror
+  if (Q > 16) v = fr_add(v, dpp_fr<0x142, 0xA>(v));  // row_bcast15 into rows 1 and 3
+  if ((lane & 31) == (Q > 16 ? 31 : 0)) {
+    part[lane >> 5][s] = v;
+    if (Direct) part[lane >> 5][1] = v;
+  }
 }
 
-// The claim through a round with sums e0, e2 (e1 = claim - e0) and challenge
-// r: g(r) = e0 + r (A + r B) with B = (e2 - 2 e1 + e0) / 2, A = e1 - e0 - B.
-__device__ __forceinline__ Fr tail_claim_next(const Fr& claim, const Fr& e0, const Fr& e2, const Fr& r) {
+// The claim through a round with sums e0, e2 (e1 = claim - e0) and challenge r is
+// g(r) = e0 + r X, X = A + r B, B = (e2 - 2 e1 + e0) / 2, A = e1 - e0 - B: X here,
+// the second product in the tail's next half round.
+__device__ __forceinline__ Fr tail_claim_x(const Fr& claim, const Fr& e0, const Fr& e2, const Fr& r) {
   const Fr e1 = fr_sub(claim, e0);
   const Fr B = fr_half(fr_add(fr_sub(e2, fr_double(e1)), e0));
   const Fr A = fr_sub(fr_sub(e1, e0), B);
-  return fr_add(e0, fr_mul(r, fr_add(A, fr_mul(r, B))));
+  return fr_add(A, fr_mul(r, B));
 }
 
 // A round's message (e0, e1 = claim - e0, e2 in canonical form), lane k
@@ -984,31 +920,29 @@ __device__ __forceinline__ void tail_message(const Fr& claim, const Fr& e0, cons
 }
 
 // ST_TAIL_A / ST_TAIL_B, pipelined: the same rounds, messages, challenges and
-// final values as body_tail, with the table work off the hash chain. Eight
-// waves (two per SIMD, wave w on SIMD w mod 4), by role:
-//  - wave 0 holds the transcript: in round j it sums the workers' coefficient
-//    partials of round j, evaluates them at r_{j-1} (two products) and hashes
-//    (e0, e2) into r_j;
-//  - in the first half of round j, wave 1 moves the claim through round
-//    j - 1 (two products) and wave 7 writes round j - 1's message (e0, e1 =
-//    claim - e0, e2 in canonical form) from the claim before it;
-//  - waves 2-7 fold level j - 1 into level j by r_{j-1} (first half of round
-//    j, before a workgroup barrier); then, while wave 0 hashes, waves 1-7
-//    compute round j + 1's coefficients from level j: for more than 32
-//    pairs, one task (three products) per thread; for at most 32, one product
-//    per lane, waves 2, 3 and 5 taking q(0), q(1) and the leading coefficient.
-// Two workgroup barriers per round; the previous round's values sit in
-// alternating shared slots.
+// final values as body_tail, for levels of at most 2^kTailMaxLog entries, with
+// the table work off the hash chain. Eight waves (two per SIMD, wave w on SIMD
+// w mod 4), two workgroup barriers per round:
+//  first half of round j   wave 0: e0, e2 of round j, the coefficient sums at
+//                          r_{j-1}, one limb per lane (fr_row.hpp);
+//                          wave 1: the claim through round j - 2 (second product);
+//                          waves 2-7: level j - 1 folded into level j by r_{j-1};
+//  second half             wave 0 hashes (e0, e2) into r_j, wave 4 writes the
+//                          hash's schedule; waves 2, 3, 5: round j + 1's
+//                          coefficient sums from level j; wave 1: the claim
+//                          through round j - 1 (first product); wave 7: round
+//                          j - 1's message.
+// Round -1 is the grid round whose claim move is pending, if any. Measured with
+// cycle stamps: a round of at most 32 pairs takes 8,600 cycles (three tables)
+// against 14,300 with the sums evaluated in one lane (5,900 cycles instead of
+// 1,900), the claim moved in one half (6,300) and the levels in device memory.
 template <class Form>
 __device__ __forceinline__ void body_tail_pipe(const Step& st, uint32_t, uint32_t) {
   constexpr int NT = Form::NT;
-  const Fr* src[NT];
-  Fr* dst[NT];
-#pragma unroll
-  for (int k = 0; k < NT; ++k) {
-    src[k] = P<const Fr*>(st, k);
-    dst[k] = P<Fr*>(st, NT + k);
-  }
+  __shared__ TailLevel<Form> lv;
+  __shared__ Fr part[2][3];                        // coefficient sums (t; V0, V1, C2) of the next round
+  __shared__ Fr r_sh[4], e_sh[4][2], claim_sh[4];  // by round mod 4; claim before the round
+  __shared__ ShaHelper help;
   const Fr* rpending = P<const Fr*>(st, 2 * NT);
   DevState* S = P<DevState*>(st, 2 * NT + 1);
   Fr* r_out = P<Fr*>(st, 2 * NT + 2);
@@ -1016,152 +950,143 @@ __device__ __forceinline__ void body_tail_pipe(const Step& st, uint32_t, uint32_
   Fr* final_out = P<Fr*>(st, 2 * NT + 4);
   uint32_t* proof_value = P<uint32_t*>(st, 2 * NT + 5);
   const uint32_t wid = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  // Per-thread coefficient tasks: waves 2, 3, 1 at t = 0 and 5, 6, 7, 4 at
-  // t = 2 (the first waves of each group on different SIMDs, for few tasks).
-  // Folds: waves 2, 3, 5, 6, 4, 7 in that order. Wave 4 shares SIMD 0 with
-  // wave 0 and wave 5 SIMD 1 with wave 1: the older wave of a SIMD issues
-  // first, so the transcript, claim and message chains keep their speed.
-  constexpr uint32_t kHw0 = 3, kHw2 = 4;  // coefficient waves for t = 0 and t = 2
-  const bool worker = wid != 0;
-  const bool t2 = wid >= 4;
-  const uint32_t wih = t2 ? (wid == 4 ? 3 : wid - 5) : (wid == 1 ? 2 : wid - 2);  // index in its group
-  const uint32_t th = wih * 64 + lane, nth = (t2 ? kHw2 : kHw0) * 64;
-  const uint32_t ford = wid == 4 ? 4 : (wid == 7 ? 5 : wid - 2 - (wid > 4));
-  const uint32_t fw = ford * 64 + lane, nfw = 6 * 64;  // index among the folders
-  const uint64_t size = st.q[0];
-  const uint32_t rounds = st.u[0];
+  const uint32_t size = (uint32_t)st.q[0], rounds = st.u[0];
   const bool pending = rpending != nullptr;
-  __shared__ Fr part[2][8][3];    // coefficient partials (half, wave, V0 V1 C2)
-  __shared__ Fr r_sh[2], e_sh[2][2], claim_sh[2];
-  // Values that cross a barrier live in the shared slots (r_sh, e_sh) rather
-  // than in registers: every wave holds the registers of every role.
-  ShaLanes state;     // wave 0
-  __shared__ ShaHelper help;
-  Fr claim;           // waves 1 and 7: the claim before the first round (wave 1 moves it)
-  bool grid_pend = false;  // waves 1 and 7: a grid round whose claim move is pending
+  // the folders in the order 2, 3, 5, 6, 7, 4 (wave 4 shares SIMD 0 with wave 0)
+  const uint32_t ford = wid == 4 ? 5 : wid - 2 - (wid > 4);
+  const uint32_t fw = ford * 64 + lane, nfw = 6 * 64;
+  ShaLanes state;  // wave 0
+  Fr claim;        // wave 1: the claim before round j - 1, X of its move
+  Fr claim_x;
+  const bool grid_pend = S->pending != 0;
   if (wid == 0) {
     state = sha_lanes_load(S->st);
     sha_init(sha_buf());
     if (lane == 0) {
-      r_sh[1] = pending ? ldf(rpending, 0) : fr_zero();  // r_{-1}
       help.ready = 0;
+      r_sh[3] = pending ? ldf(rpending, 0) : (grid_pend ? S->pend_r : fr_zero());
     }
-  } else if (wid == 1 || wid == 7) {
-    claim = S->claim;
-    grid_pend = S->pending != 0;
+  } else if (wid == 1) {
+    claim = opaque(S->claim);
+    if (lane == 0) {
+      claim_sh[3] = claim;
+      e_sh[3][0] = S->pend_e0;
+      e_sh[3][1] = S->pend_e2;
+    }
   }
-  const Fr* cur[NT];  // the current level
 #pragma unroll
-  for (int k = 0; k < NT; ++k) cur[k] = src[k];
+  for (int k = 0; k < NT; ++k)
+    for (uint32_t i = threadIdx.x; i < size; i += blockDim.x) lv.t[k][i] = ldf(P<const Fr*>(st, k), i);
+  __syncthreads();
   // round 0's coefficients: from the unfolded tables (a pending fold) or directly
-  uint64_t tasks = 0;
-  if (rounds > 0) tasks = pending ? size / 4 : size / 2;
-  uint32_t nact0 = tail_active_waves(tasks, kHw0), nact2 = tail_active_waves(tasks, kHw2);
-  if (worker && rounds > 0)
-    tail_coefficients<Form>(cur, tasks, !pending, t2, th, nth, wih, t2 ? nact2 : nact0, part[t2 ? 1 : 0]);
+  if (rounds > 0) {
+    if (pending) {
+      if (wid == 2 || wid == 3 || wid == 5)
+        tail_stream<Form, false>(lv, size / 4, wid == 2 ? 0 : (wid == 3 ? 1 : 2), part);
+    } else if (wid == 2) {
+      tail_stream<Form, true>(lv, size / 2, 0, part);
+    } else if (wid == 3 && lane < 2) {
+      part[lane][2] = fr_zero();
+    }
+  }
   __syncthreads();
   for (uint32_t j = 0; j < rounds; ++j) {
     const bool fold = pending || j > 0;
-    const uint64_t m = 1ull << (rounds - j);  // entries of level j
+    const uint32_t m = 1u << (rounds - j);  // entries of level j
+    const uint32_t q = (j + 3) & 3;         // slot of round j - 1
     if (wid == 0) {
-      // round j's sums at r_{j-1}: lane 0 for t = 0, lane 1 for t = 2
-      const uint32_t h = lane & 1, nact = h ? nact2 : nact0;
-      const Fr r_prev = opaque(r_sh[(j - 1) & 1]);
-      Fr v0 = fr_zero(), v1 = fr_zero(), c2 = fr_zero();
-      for (uint32_t a = 0; a < nact; ++a) {
-        v0 = fr_add(v0, part[h][a][0]);
-        v1 = fr_add(v1, part[h][a][1]);
-        c2 = fr_add(c2, part[h][a][2]);
-      }
-      const Fr c1 = fr_sub(fr_sub(v1, v0), c2);
-      const Fr e = fr_add(v0, fr_mul(r_prev, fr_add(c1, fr_mul(r_prev, c2))));
-      if (lane < 2) e_sh[j & 1][lane] = e;
-    } else if (wid == 1) {
-      // the claim through round j - 1 (or the pending grid round)
-      if (j > 0) {
-        const uint32_t q = (j - 1) & 1;
-        claim = tail_claim_next(claim, opaque(e_sh[q][0]), opaque(e_sh[q][1]), opaque(r_sh[q]));
-      }
-      else if (grid_pend) claim = tail_claim_next(claim, opaque(S->pend_e0), opaque(S->pend_e2), opaque(S->pend_r));
-      if (lane == 0) claim_sh[j & 1] = claim;
-    } else {  // waves 2-7: the folders
-      if (wid == 7) {
-        // round j - 1's message (or the pending grid round's), from the claim before it
-        if (j > 0) {
-          const uint32_t q = (j - 1) & 1;
-          tail_message(opaque(claim_sh[q]), opaque(e_sh[q][0]), opaque(e_sh[q][1]), msg + 24 * (j - 1));
-        } else if (grid_pend) {
-          tail_message(claim, opaque(S->pend_e0), opaque(S->pend_e2), S->pend_msg);
-        }
-      }
-      if (fold) {
-        // level j - 1 into level j by r_{j-1} (in place after the first fold)
-        const Fr rf = opaque(r_sh[(j - 1) & 1]);
-        const uint32_t lg = rounds - j;
-        for (uint64_t t = fw; t < NT * m; t += nfw) {
-          const uint32_t k = (uint32_t)(t >> lg);
-          const uint64_t i = t & (m - 1);
-          const Fr* sp = pick<NT>(cur, k);
-          const Fr a0 = ldf(sp, i), a1 = ldf(sp, i + m);
-          stf(pick<NT>(dst, k), i, fr_add(a0, fr_mul(rf, fr_sub(a1, a0))));
-        }
-      }
-    }
-    if (fold) {
+      // round j's sums at r_{j-1}: rows 0 and 2 for t = 0, rows 1 and 3 for t = 2
+      uint32_t r[8];
 #pragma unroll
-      for (int k = 0; k < NT; ++k) cur[k] = dst[k];
+      for (int k = 0; k < 8; ++k) r[k] = r_sh[q].v[k];
+      const uint32_t t = (lane >> 4) & 1, i = lane & 15;
+      uint32_t v0 = 0, v1 = 0, c2 = 0;
+      if (i < 8) {
+        v0 = part[t][0].v[i];
+        v1 = part[t][1].v[i];
+        c2 = part[t][2].v[i];
+      }
+      const uint32_t e = row_quadratic(r, v0, v1, c2);
+      if (lane < 32 && i < 8) e_sh[j & 3][t].v[i] = e;
+    } else if (wid == 1) {
+      if (j > 0) {
+        // the claim through round j - 2, to the one before round j - 1
+        if (j > 1 || grid_pend) {
+          const uint32_t q2 = (j + 2) & 3;
+          claim = fr_add(opaque(e_sh[q2][0]), fr_mul(opaque(r_sh[q2]), claim_x));
+        }
+        if (lane == 0) claim_sh[q] = claim;
+      }
+    } else if (fold) {
+      // level j - 1 into level j by r_{j-1}, in place
+      const Fr rf = opaque(r_sh[q]);
+      const uint32_t lg = rounds - j;
+      for (uint32_t t = fw; t < NT * m; t += nfw) {
+        Fr* L = lv.t[t >> lg];
+        const uint32_t i = t & (m - 1);
+        const Fr a0 = opaque(L[i]), a1 = opaque(L[i + m]);
+        L[i] = fr_add(a0, fr_mul(rf, fr_sub(a1, a0)));
+      }
     }
     __syncthreads();
-    const uint64_t next = j + 1 < rounds ? m / 4 : 0;  // tasks of round j + 1
-    if (wid == 4) sha_help(round_word(e_sh[j & 1]), sha_buf(), &help, 3 * j);
+    const uint32_t next = j + 1 < rounds ? m / 4 : 0;  // pairs of round j + 1
     if (wid == 0) {
-      round_hash_wave<true>(state, e_sh[j & 1], &help, 3 * j);
-      store_challenge(state, &r_sh[j & 1], r_out + j);
-    } else if (next > 32) {
-      if (worker)
-        tail_coefficients<Form>(cur, next, false, t2, th, nth, wih,
-                                t2 ? tail_active_waves(next, kHw2) : tail_active_waves(next, kHw0), part[t2 ? 1 : 0]);
+      round_hash_wave<true>(state, e_sh[j & 3], &help, 3 * j);
+      store_challenge(state, &r_sh[j & 3], r_out + j);
+    } else if (wid == 4) {
+      sha_help(round_word(e_sh[j & 3]), sha_buf(), &help, 3 * j);
+    } else if (wid == 1) {
+      if (j > 0 || grid_pend) claim_x = tail_claim_x(claim, opaque(e_sh[q][0]), opaque(e_sh[q][1]), opaque(r_sh[q]));
+    } else if (wid == 7) {
+      if (j > 0 || grid_pend)
+        tail_message(opaque(claim_sh[q]), opaque(e_sh[q][0]), opaque(e_sh[q][1]), j > 0 ? msg + 24 * (j - 1) : S->pend_msg);
     } else if (next && (wid == 2 || wid == 3 || wid == 5)) {
-      tail_coefficient_stream<Form>(cur, next, wid == 2 ? 0 : (wid == 3 ? 1 : 2), part);
+      tail_stream<Form, false>(lv, next, wid == 2 ? 0 : (wid == 3 ? 1 : 2), part);
     }
-    nact0 = next > 32 ? tail_active_waves(next, kHw0) : 1;
-    nact2 = next > 32 ? tail_active_waves(next, kHw2) : 1;
     __syncthreads();
   }
-  // the final fold (by r_{rounds-1}, or by the pending challenge when no
-  // round is left) and the last claim move
+  // the final fold (by r_{rounds-1}, or by the pending challenge when no round
+  // is left), and the claim to the one before round rounds - 1
   const bool any_fold = pending || rounds > 0;
+  const uint32_t ql = (rounds + 3) & 3;  // slot of the last round
+  Fr v = fr_zero();                      // wave 0, lane k: the final value of table k
   if (wid == 0) {
-    const Fr r_prev = opaque(r_sh[(rounds - 1) & 1]);  // r_{rounds-1}, or r_{-1}
-    Fr v = fr_zero();  // lane k: the final value of table k
+    if (lane < NT) {
+      const Fr* L = lv.t[lane];
+      v = opaque(L[0]);
+      if (any_fold) v = fr_add(v, fr_mul(opaque(r_sh[ql]), fr_sub(opaque(L[1]), v)));
+    }
+  } else if (wid == 1 && rounds > 0) {
+    if (rounds > 1 || grid_pend) {
+      const uint32_t q2 = (rounds + 2) & 3;
+      claim = fr_add(opaque(e_sh[q2][0]), fr_mul(opaque(r_sh[q2]), claim_x));
+    }
+    if (lane == 0) claim_sh[ql] = claim;
+  }
+  __syncthreads();
+  const bool last = rounds > 0 || grid_pend;  // a last round to move the claim through
+  if (wid == 0) {
     if (any_fold && lane < NT) {
-      const Fr* sp = pick<NT>(cur, lane);
-      const Fr a0 = ldf(sp, 0), a1 = ldf(sp, 1);
-      v = fr_add(a0, fr_mul(r_prev, fr_sub(a1, a0)));
-      stf(pick<NT>(dst, lane), 0, v);
+      Fr* dst = P<Fr*>(st, NT);
+#pragma unroll
+      for (int k = 1; k < NT; ++k)
+        if (lane == (uint32_t)k) dst = P<Fr*>(st, NT + k);
+      stf(dst, 0, v);
     }
-    v = any_fold ? lane_fr(v, 0) : ldf(src[0], 0);
-    if (proof_value) finish_value_wave(state, opaque(v), final_out, proof_value);
-    else if (lane == 0) *final_out = v;
+    const Fr v0 = lane_fr(v, 0);
+    if (proof_value) finish_value_wave(state, opaque(v0), final_out, proof_value);
+    else if (lane == 0) *final_out = v0;
     sha_lanes_store(S->st, state);
-  } else if (wid == 1) {
-    if (rounds > 0) {
-      const uint32_t q = (rounds - 1) & 1;
-      claim = tail_claim_next(claim, opaque(e_sh[q][0]), opaque(e_sh[q][1]), opaque(r_sh[q]));
-    } else if (grid_pend) {
-      claim = tail_claim_next(claim, opaque(S->pend_e0), opaque(S->pend_e2), opaque(S->pend_r));
-    }
+  } else if (wid == 1 && last) {
+    const Fr e0 = opaque(e_sh[ql][0]), r = opaque(r_sh[ql]);
+    claim = fr_add(e0, fr_mul(r, tail_claim_x(claim, e0, opaque(e_sh[ql][1]), r)));
     if (lane == 0) {
       S->claim = claim;
       S->pending = 0;
     }
-  } else if (wid == 7) {
-    if (rounds > 0) {
-      const uint32_t q = (rounds - 1) & 1;
-      tail_message(opaque(claim_sh[q]), opaque(e_sh[q][0]), opaque(e_sh[q][1]), msg + 24 * (rounds - 1));
-    } else if (grid_pend) {
-      tail_message(claim, opaque(S->pend_e0), opaque(S->pend_e2), S->pend_msg);
-    }
+  } else if (wid == 7 && last) {
+    tail_message(opaque(claim_sh[ql]), opaque(e_sh[ql][0]), opaque(e_sh[ql][1]),
+                 rounds > 0 ? msg + 24 * (rounds - 1) : S->pend_msg);
   }
 }
 

@@ -108,8 +108,12 @@ __global__ void __launch_bounds__(kBlock) k_cc_bsum(Step st) {
 // holds 16 bytes of row (l mod 16) and of column (l mod 16) at K offset
 // 16 (l / 16) of each 64-byte step (the instruction sums the four lane groups),
 // and receives rows 4 (l / 16) .. + 3 of column l mod 16.
+// Term i of row y is 32 bytes at y q2 + i q3 of W: q3 = 32 for sums along a
+// table's rows (16 bytes per lane at a stride of one row; a row's lines are used
+// whole over the block's four steps), q2 = 32 for sums down its columns (16
+// rows' terms are 512 consecutive bytes).
 // p0 W (bytes), p1 Bt, p2 part (int32 [chunk][row][128]); u0 n, u1 row_tiles;
-// q0 chunk bytes, q1 rows.
+// q0 chunk bytes, q1 rows, q2 row stride, q3 term stride (bytes).
 __global__ void __launch_bounds__(kCcThreads) k_cc_gemm(Step st) {
   __shared__ __attribute__((aligned(16))) uint8_t Bs[kCcCols * kCcLdsStride];
   const uint8_t* W = P<const uint8_t*>(st, 0);
@@ -126,7 +130,9 @@ __global__ void __launch_bounds__(kCcThreads) k_cc_gemm(Step st) {
   const U32x4* bsrc = (const U32x4*)(Bt + (uint64_t)scol * K + k0 + soff);
   const U32x4* arow[2];
 #pragma unroll
-  for (int h = 0; h < 2; ++h) arow[h] = (const U32x4*)(W + (y0 + (2 * wid + h) * 16 + r) * K + k0 + 16 * g);
+  for (int h = 0; h < 2; ++h)
+    arow[h] = (const U32x4*)(W + (y0 + (2 * wid + h) * 16 + r) * st.q[2] + (k0 / 32 + (g >> 1)) * st.q[3] + 16 * (g & 1));
+  const uint64_t astep = 2 * st.q[3] / 16;  // vectors from one 64-byte step (two terms) to the next
   I32x4 acc[2][8];
 #pragma unroll
   for (int h = 0; h < 2; ++h)
@@ -138,7 +144,7 @@ __global__ void __launch_bounds__(kCcThreads) k_cc_gemm(Step st) {
 #pragma unroll
   for (int h = 0; h < 2; ++h)
 #pragma unroll
-    for (int s = 0; s < 4; ++s) anext[h][s] = arow[h][4 * s];  // 64-byte steps: 4 U32x4 apart
+    for (int s = 0; s < 4; ++s) anext[h][s] = arow[h][s * astep];
   for (uint32_t blk = 0; blk < nblk; ++blk) {
     __syncthreads();  // every wave has finished the previous block's LDS reads
 #pragma unroll
@@ -150,13 +156,13 @@ __global__ void __launch_bounds__(kCcThreads) k_cc_gemm(Step st) {
       for (int s = 0; s < 4; ++s) a[h][s] = anext[h][s];
     __syncthreads();
     if (blk + 1 < nblk) {
-      const uint64_t adv = (uint64_t)(blk + 1) * (kCcBlockK / 16);
+      const uint64_t adv = (uint64_t)(blk + 1) * (kCcBlockK / 16), aadv = 4 * (uint64_t)(blk + 1) * astep;
 #pragma unroll
       for (int e = 0; e < 4; ++e) bst[e] = bsrc[adv + e];
 #pragma unroll
       for (int h = 0; h < 2; ++h)
 #pragma unroll
-        for (int s = 0; s < 4; ++s) anext[h][s] = arow[h][adv + 4 * s];
+        for (int s = 0; s < 4; ++s) anext[h][s] = arow[h][aadv + s * astep];
     }
 #pragma unroll
     for (int s = 0; s < 4; ++s) {
@@ -186,37 +192,58 @@ __global__ void __launch_bounds__(kCcThreads) k_cc_gemm(Step st) {
       }
 }
 
-// ST_CC_EPILOGUE: thread (y, v): the chunk sums of row y's 63 band columns of
-// vector v and of the ones column, the offsets, the integer sum_k 2^(8k) E_k
-// (below 2^520), its top bits folded by 2^508 mod p (w[0..7], plain form),
-// then one Montgomery reduction. p0 part, p1 BS, p2 P out, p3 Q out;
-// u0 chunks; q0 rows.
+// ST_CC_EPILOGUE: a workgroup takes u1 rows, two for tables of few rows (which
+// have many chunks: 2^9 rows, 128 chunks took 142 us with eight) and eight
+// otherwise. All threads first add the chunks'
+// partial columns, two rows of 128 consecutive columns at a time, into shared
+// memory; then one thread per (row, vector) takes the 63 band columns of its
+// vector and the ones column, the offsets, the integer sum_k 2^(8k) E_k (below
+// 2^520), its top bits folded by 2^508 mod p (w[0..7], plain form), and makes one
+// Montgomery reduction. (With the two threads of a row also adding the chunks,
+// 63 loads per chunk at a stride of a row, 2^14 rows took 57 us.)
+// p0 part, p1 BS, p2 P out, p3 Q out; u0 chunks, u1 rows per workgroup; q0 rows.
+constexpr uint32_t kCcEpiRows = 8;
+
 __global__ void __launch_bounds__(kBlock) k_cc_epilogue(Step st) {
+  __shared__ int64_t sums[kCcEpiRows][kCcCols + 1];
+  __shared__ uint64_t ps[2][33];  // prefix sums of the vectors' byte sums
   const int32_t* part = P<const int32_t*>(st, 0);
   const uint32_t* BS = P<const uint32_t*>(st, 1);
   const uint32_t chunks = st.u[0];
-  const uint64_t rows = st.q[0];
-  const uint64_t t = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= 2 * rows) return;
-  const uint64_t y = t >> 1;
-  const uint32_t v = (uint32_t)(t & 1);
-  // prefix sums of the vector's byte sums: sum_K b_u of band k covers bytes max(0, k-31) .. min(k, 31)
-  uint64_t ps[33];
-  ps[0] = 0;
-#pragma unroll
-  for (int i = 0; i < 32; ++i) ps[i + 1] = ps[i] + BS[32 * v + i];
-  int64_t rs = 0;
-  for (uint32_t ch = 0; ch < chunks; ++ch) rs += part[((uint64_t)ch * rows + y) * kCcCols + kCcOnes];
+  const uint32_t per = st.u[1];
+  const uint64_t rows = st.q[0], y0 = (uint64_t)blockIdx.x * per;
+  if (threadIdx.x < 2) {
+    uint64_t s = 0;
+    for (int i = 0; i < 32; ++i) {
+      ps[threadIdx.x][i] = s;
+      s += BS[32 * threadIdx.x + i];
+    }
+    ps[threadIdx.x][32] = s;
+  }
+  const uint32_t col = threadIdx.x & (kCcCols - 1);
+  for (uint32_t q = 0; q < per; q += 2) {
+    const uint32_t row = q + threadIdx.x / kCcCols;
+    int64_t d = 0;
+    if (y0 + row < rows) {
+      const int32_t* src = part + (y0 + row) * kCcCols + col;
+#pragma unroll 8
+      for (uint32_t ch = 0; ch < chunks; ++ch) d += src[(uint64_t)ch * rows * kCcCols];
+    }
+    sums[row][col] = d;
+  }
+  __syncthreads();
+  const uint32_t row = threadIdx.x >> 1, v = threadIdx.x & 1;
+  if (threadIdx.x >= 2 * per || y0 + row >= rows) return;
+  const int64_t rs = sums[row][kCcOnes];
   uint64_t acc[18];
 #pragma unroll
   for (int i = 0; i < 18; ++i) acc[i] = 0;
 #pragma unroll
   for (int k = 0; k < 63; ++k) {
-    int64_t d = 0;
-    for (uint32_t ch = 0; ch < chunks; ++ch) d += part[((uint64_t)ch * rows + y) * kCcCols + 64 * v + k];
-    const uint64_t cs = ps[k < 31 ? k + 1 : 32] - ps[k > 31 ? k - 31 : 0];
-    const uint64_t e = (uint64_t)(d + 128 * rs + 128 * (int64_t)cs);  // E_k, below 2^33
-    const uint64_t sh = e << (8 * (k & 3));                          // below 2^57
+    // sum_K b_u of band k covers bytes max(0, k - 31) .. min(k, 31)
+    const uint64_t cs = ps[v][k < 31 ? k + 1 : 32] - ps[v][k > 31 ? k - 31 : 0];
+    const uint64_t e = (uint64_t)(sums[row][64 * v + k] + 128 * rs + 128 * (int64_t)cs);  // E_k, below 2^35
+    const uint64_t sh = e << (8 * (k & 3));                                              // below 2^59
     acc[k >> 2] += sh & 0xffffffffu;
     acc[(k >> 2) + 1] += sh >> 32;
   }
@@ -240,7 +267,8 @@ __global__ void __launch_bounds__(kBlock) k_cc_epilogue(Step st) {
     c2 = s >> 32;
   }
   const Fr out = frw_reduce<4>(T);
-  stf(P<Fr*>(st, 2 + v), y, out);
+  Fr *ou = P<Fr*>(st, 2), *ov = P<Fr*>(st, 3);
+  stf(v ? ov : ou, y0 + row, out);
 }
 
 void launch_cc_step(const Step& st, hipStream_t s) {
@@ -292,14 +320,15 @@ static void two_pow_508(uint32_t out[8]) {
   for (int k = 0; k < 8; ++k) out[k] = plain.v[k];
 }
 
-void emit_copy_contract_mfma(Program& pg, const Fr* W, const Fr* U, const Fr* V, Fr* Pt, Fr* Qt, uint32_t n,
-                             uint32_t sigma, void* scratch) {
-  const CcPlan cp = cc_plan(n, sigma);
+void emit_contract_mfma(Program& pg, const Fr* W, const Fr* U, const Fr* V, Fr* out_u, Fr* out_v, uint32_t log_terms,
+                        uint32_t log_rows, bool transposed, void* scratch) {
+  const uint32_t n = log_terms;
+  const CcPlan cp = cc_plan(log_terms, log_rows);
   uint8_t* base = static_cast<uint8_t*>(scratch);
   uint8_t* Bt = base;
   int32_t* part = reinterpret_cast<int32_t*>(base + cp.bt_bytes);
   uint32_t* BS = reinterpret_cast<uint32_t*>(base + cp.bt_bytes + cp.part_bytes);
-  const uint64_t rows = 1ull << sigma, ncop = 1ull << n;
+  const uint64_t rows = 1ull << log_rows, ncop = 1ull << log_terms;
   auto mk = [](uint32_t type, uint32_t tiles) {
     Step st;
     memset(&st, 0, sizeof(st));
@@ -324,12 +353,15 @@ void emit_copy_contract_mfma(Program& pg, const Fr* W, const Fr* U, const Fr* V,
     Step st = mk(ST_CC_GEMM, cp.row_tiles * cp.chunks);
     st.p[0] = W; st.p[1] = Bt; st.p[2] = part; st.u[0] = n; st.u[1] = cp.row_tiles;
     st.q[0] = cp.chunk_bytes; st.q[1] = rows;
+    st.q[2] = transposed ? 32 : 32 * ncop; st.q[3] = transposed ? 32 * rows : 32;
     st.bytes = 32.0 * (double)(rows << n) + (double)cp.part_bytes;  // no field products: int8 matrix work
     pg.steps.push_back(st);
   }
   {
-    Step st = mk(ST_CC_EPILOGUE, (uint32_t)((2 * rows + kBlock - 1) / kBlock));
-    st.p[0] = part; st.p[1] = BS; st.p[2] = Pt; st.p[3] = Qt; st.u[0] = cp.chunks; st.q[0] = rows;
+    const uint32_t per = rows >= 4096 ? kCcEpiRows : 2;
+    Step st = mk(ST_CC_EPILOGUE, (uint32_t)((rows + per - 1) / per));
+    st.u[1] = per;
+    st.p[0] = part; st.p[1] = BS; st.p[2] = out_u; st.p[3] = out_v; st.u[0] = cp.chunks; st.q[0] = rows;
     two_pow_508(st.w);
     st.bytes = (double)cp.part_bytes + 64.0 * rows;
     st.mulmods = (double)rows;  // one reduction per row and vector

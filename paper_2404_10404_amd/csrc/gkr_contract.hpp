@@ -11,7 +11,7 @@
 
 namespace gkr {
 
-constexpr uint32_t kCcMinLogCopies = 10;  // rows of at least 32 KiB
+constexpr uint32_t kCcMinLogCopies = 9;   // rows of at least 16 KiB
 constexpr uint32_t kCcMinLogRows = 8;     // at least one 256-row tile
 constexpr uint64_t kCcTargetGroups = 256; // workgroups of the product (row tiles x K chunks), one per CU
 
@@ -27,10 +27,12 @@ CcPlan cc_plan(uint32_t n, uint32_t sigma);
 size_t cc_scratch_bytes(uint32_t n, uint32_t sigma);
 
 struct Program;
-// P[y], Q[y] for y < 2^sigma from W (2^sigma rows of 2^n elements), U, V (2^n
-// each); scratch holds cc_scratch_bytes(n, sigma) bytes, 256-byte aligned.
-void emit_copy_contract_mfma(Program& pg, const Fr* W, const Fr* U, const Fr* V, Fr* Pt, Fr* Qt, uint32_t n,
-                             uint32_t sigma, void* scratch);
+// out_u[r] = sum_i U[i] X(r, i) R^-1 and out_v with V, for r < 2^log_rows over i <
+// 2^log_terms, where X(r, i) is entry r 2^log_terms + i of W, or entry
+// i 2^log_rows + r with `transposed` (sums over a table's rows instead of its
+// columns); scratch holds cc_scratch_bytes(log_terms, log_rows) bytes, 256-byte aligned.
+void emit_contract_mfma(Program& pg, const Fr* W, const Fr* U, const Fr* V, Fr* out_u, Fr* out_v, uint32_t log_terms,
+                        uint32_t log_rows, bool transposed, void* scratch);
 void launch_cc_step(const Step& st, hipStream_t s);
 
 }  // namespace gkr

@@ -64,6 +64,16 @@ __device__ __forceinline__ Fr wave_sum_to_lane63(Fr v) {
   return v;
 }
 
+// Sums over lanes 0..31 into lane 31 and over lanes 32..63 into lane 63 (all lanes active).
+__device__ __forceinline__ Fr half_wave_sum(Fr v) {
+  v = fr_add(v, dpp_fr<0xB1, 0xF>(v));   // quad_perm [1,0,3,2]
+  v = fr_add(v, dpp_fr<0x4E, 0xF>(v));   // quad_perm [2,3,0,1]
+  v = fr_add(v, dpp_fr<0x141, 0xF>(v));  // row_half_mirror
+  v = fr_add(v, dpp_fr<0x140, 0xF>(v));  // row_mirror
+  v = fr_add(v, dpp_fr<0x142, 0xA>(v));  // row_bcast15 into rows 1 and 3
+  return v;
+}
+
 // Waits until every vector memory operation this wave has issued is
 // complete (a store has reached the L2; a cache write-back or invalidation
 // has finished). An asm statement with a memory clobber: the compiler moves no

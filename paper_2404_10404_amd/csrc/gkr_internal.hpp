@@ -17,6 +17,7 @@ namespace gkr {
 constexpr int kBlock = 256;             // threads per workgroup (grid-wide kernels, batch kernel)
 constexpr int kTailBlock = 512;         // threads of the single-workgroup tail kernels
 constexpr uint32_t kMaxRoundBlocks = 4096;  // cap on workgroups of a reduction launch
+constexpr uint32_t kTailMaxLog = 7;       // largest table (log2) a pipelined tail evaluates
 constexpr int kMaxPartialValues = 2;    // reduced values per workgroup
 constexpr uint32_t kChunkWords = 256;   // 1 KiB SHA-256 leaf chunk of a tree digest
 
@@ -33,7 +34,9 @@ constexpr uint32_t kRoundMark = 1u << 30;
 struct LayerWiring {
   const uint2* gates;   // [2^{sigma_i}]      .x = x | type<<31, .y = y
   const uint32_t* xrow; // [2^{sigma_{i+1}}+1] CSR of gates by x
-  const uint2* xent;    // [2^{sigma_i}]      .x = z, .y = y | type<<31
+  const uint2* xent;    // [2^{sigma_i}]      .x = z, .y = y | type<<31; an x's MUL gates first
+  const uint32_t* xmid; // [2^{sigma_{i+1}}]  end of x's MUL gates
+  const uint32_t* act;  // bit 2^k + r: some x congruent to r mod 2^k has a MUL gate (k <= sigma_{i+1})
   const uint32_t* yrow; // [2^{sigma_{i+1}}+1] CSR of gates by y
   const uint2* yent;    // [2^{sigma_i}]      .x = z, .y = x | type<<31
 };
@@ -114,6 +117,13 @@ enum StepType : uint32_t {
   ST_GL_LOCAL_VALUES,
   ST_GL_LOCAL_CONTRACT,
   ST_GL_COPY_TABLES,
+  ST_GL_S_SMALL,
+  ST_GL_S_INIT_ROUND,
+  ST_GL_S_ROUND,
+  ST_GL_S_P2_RAW,
+  ST_GL_S_P2_FINAL,
+  ST_GL_S_LOCAL2,
+  ST_GL_S_HANDOFF,
   ST_GL_END,
   // The commitment to the input layer and its opening: launched by
   // launch_vpd_step, plain path only.
@@ -138,7 +148,19 @@ enum StepType : uint32_t {
   ST_CC_BUILD = 192,
   ST_CC_BSUM,
   ST_CC_GEMM,
-  ST_CC_EPILOGUE
+  ST_CC_EPILOGUE,
+  // Phase 1 with the addition gates contracted over the copies: launched by
+  // launch_split_step, plain path only.
+  ST_S_SMALL = 224,
+  ST_S_INIT_ROUND,
+  ST_S_ROUND,
+  ST_S_P2_RAW,
+  ST_S_P2_FINAL,
+  ST_S_HANDOFF,
+  // Rounds over small tables, one product per thread: launched by
+  // launch_wide_step, plain path only.
+  ST_W_ROUND_A = 240,
+  ST_W_ROUND_B
 };
 
 struct Step {

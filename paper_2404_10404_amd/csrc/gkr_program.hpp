@@ -12,9 +12,10 @@ namespace gkr {
 
 struct Program {
   std::vector<Step> steps;
-  // Steps that only the plain launcher runs (the matrix-core contraction) are
-  // allowed; the batch kernel's programs switch this off.
-  bool matrix_cores = true;
+  // Steps that only the plain launcher runs (the matrix-core contractions, the
+  // contracted phase 1, the wide rounds) are allowed; the batch kernel's
+  // programs switch this off.
+  bool plain = true;
 
   void to_mont(const gkr_fr* in, Fr* out, uint64_t n);
   void from_mont(const Fr* in, gkr_fr* out, uint64_t n);
