@@ -412,7 +412,8 @@ __device__ __forceinline__ uint64_t gl_wave_sum(uint64_t v) {
 }
 
 // ST_GL_COPY_CONTRACT: P[y] = sum_c U[c] W[y 2^n + c], Q[y] likewise with V,
-// one wave per row y < q0. p0 W, p1 U, p2 V, p3 P, p4 Q, u0 n.
+// one wave per row y < q0, two adjacent copies per lane (16-byte loads) from 2^7
+// copies up. p0 W, p1 U, p2 V, p3 P, p4 Q, u0 n.
 __global__ void __launch_bounds__(kBlock) k_gl_copy_contract(Step st) {
   const uint64_t *W = P<const uint64_t*>(st, 0), *U = P<const uint64_t*>(st, 1), *V = P<const uint64_t*>(st, 2);
   const uint32_t n = st.u[0];
@@ -421,10 +422,18 @@ __global__ void __launch_bounds__(kBlock) k_gl_copy_contract(Step st) {
   const uint64_t wave = GTID >> 6, nwaves = GSTRIDE >> 6;
   for (uint64_t y = wave; y < st.q[0]; y += nwaves) {
     uint64_t p = 0, q = 0;
-    for (uint64_t c = lane; c < ncop; c += 64) {
-      const uint64_t w = gld(W, (y << n) | c);
-      p = gl_add(p, gl_mul(gld(U, c), w));
-      q = gl_add(q, gl_mul(gld(V, c), w));
+    if (n >= 7) {
+      for (uint64_t c = 2 * lane; c < ncop; c += 128) {
+        const U64x2 w = gld2(W, (y << n) | c), u = gld2(U, c), v = gld2(V, c);
+        p = gl_add(p, gl_add(gl_mul(u.x, w.x), gl_mul(u.y, w.y)));
+        q = gl_add(q, gl_add(gl_mul(v.x, w.x), gl_mul(v.y, w.y)));
+      }
+    } else {
+      for (uint64_t c = lane; c < ncop; c += 64) {
+        const uint64_t w = gld(W, (y << n) | c);
+        p = gl_add(p, gl_mul(gld(U, c), w));
+        q = gl_add(q, gl_mul(gld(V, c), w));
+      }
     }
     p = gl_wave_sum(p);
     q = gl_wave_sum(q);
@@ -617,6 +626,26 @@ __device__ __forceinline__ void gl_pair2(const uint64_t* const* src, uint64_t* c
   }
 }
 
+// The end of a grid round: the workgroup's sums, and in the last tile the total
+// and the round's transcript step.
+__device__ __forceinline__ void gl_finish_round(uint64_t (&acc)[2], GlState* S, uint64_t* partials, uint64_t* r_out,
+                                                uint64_t* msg) {
+  gl_block_sum<2>(acc);
+  if (threadIdx.x == 0) {
+    partials[2 * blockIdx.x] = acc[0];
+    partials[2 * blockIdx.x + 1] = acc[1];
+  }
+  if (gl_last_tile(&S->counter, gridDim.x)) {
+    uint64_t tot[2] = {0, 0};
+    for (uint32_t b = threadIdx.x; b < gridDim.x; b += blockDim.x) {
+      tot[0] = gl_add(tot[0], partials[2 * b]);
+      tot[1] = gl_add(tot[1], partials[2 * b + 1]);
+    }
+    gl_block_sum<2>(tot);
+    gl_round_step(S, tot[0], tot[1], r_out, msg);
+  }
+}
+
 // ST_GL_ROUND (NT = 3) / ST_GL_ROUND5 (NT = 5): one grid-wide round of the
 // NT-table sum (optional fold by the previous challenge, evaluation at
 // t = 0, 2), then in the last tile the round's transcript step. p0..p(NT-1)
@@ -644,21 +673,278 @@ __global__ void __launch_bounds__(kBlock) k_gl_round(Step st) {
   } else {
     for (uint64_t b = GTID; b < half; b += GSTRIDE) gl_pair<NT>(src, dst, fold, r, b, half, acc[0], acc[1]);
   }
-  gl_block_sum<2>(acc);
-  if (threadIdx.x == 0) {
-    partials[2 * blockIdx.x] = acc[0];
-    partials[2 * blockIdx.x + 1] = acc[1];
-  }
-  if (gl_last_tile(&S->counter, gridDim.x)) {
-    uint64_t tot[2] = {0, 0};
-    for (uint32_t b = threadIdx.x; b < gridDim.x; b += blockDim.x) {
-      tot[0] = gl_add(tot[0], partials[2 * b]);
-      tot[1] = gl_add(tot[1], partials[2 * b + 1]);
+  gl_finish_round(acc, S, partials, P<uint64_t*>(st, B + 3), P<uint64_t*>(st, B + 4));
+}
+
+// ---------------------------------------------------------------- contracted phase 1
+//
+// Phase 1 with the addition gates contracted over the copies, as in the BN254
+// prover (gkr_split.hip states the identities): tables over (x, c) only for W and
+// the MUL gates' Gm, whose rows without a MUL gate are neither read nor
+// written; the ADD gates in five 2^sigma tables; two more passes over W.
+
+__device__ __forceinline__ bool gl_row_active(const uint32_t* act, uint32_t k, uint32_t row) {
+  const uint32_t bit = (1u << k) + row;
+  return (act[bit >> 5] >> (bit & 31)) & 1u;
+}
+
+// ST_GL_S_SMALL: sa, sb, h over the ADD gates of x < q0. p0 xrow, p1 xmid, p2 xent,
+// p3 aU, p4 bV, p5 Pu, p6 Pv, p7 sa, p8 sb, p9 h.
+__global__ void __launch_bounds__(kBlock) k_gl_s_small(Step st) {
+  const uint32_t* __restrict__ xrow = P<const uint32_t*>(st, 0);
+  const uint32_t* __restrict__ xmid = P<const uint32_t*>(st, 1);
+  const uint2* __restrict__ xent = P<const uint2*>(st, 2);
+  const uint64_t *aU = P<const uint64_t*>(st, 3), *bV = P<const uint64_t*>(st, 4);
+  const uint64_t *Pu = P<const uint64_t*>(st, 5), *Pv = P<const uint64_t*>(st, 6);
+  for (uint64_t x = GTID; x < st.q[0]; x += GSTRIDE) {
+    uint64_t sa = 0, sb = 0, h = 0;
+    const uint32_t k1 = xrow[x + 1];
+    for (uint32_t k = xmid[x]; k < k1; ++k) {
+      const uint2 e = xent[k];
+      const uint64_t y = e.y & 0x7fffffffu, a = gld(aU, e.x), b = gld(bV, e.x);
+      sa = gl_add(sa, a);
+      sb = gl_add(sb, b);
+      h = gl_add(h, gl_add(gl_mul(a, gld(Pu, y)), gl_mul(b, gld(Pv, y))));
     }
-    gl_block_sum<2>(tot);
-    gl_round_step(S, tot[0], tot[1], P<uint64_t*>(st, B + 3), P<uint64_t*>(st, B + 4));
+    gst(P<uint64_t*>(st, 7), x, sa);
+    gst(P<uint64_t*>(st, 8), x, sb);
+    gst(P<uint64_t*>(st, 9), x, h);
   }
 }
+
+// Two adjacent entries (x, c), (x, c + 1) of Gm over x's MUL gates (at least one).
+__device__ __forceinline__ U64x2 gl_split_entry(const uint64_t* __restrict__ W, const uint2* __restrict__ xent,
+                                                const uint64_t* __restrict__ aU, const uint64_t* __restrict__ bV,
+                                                U64x2 cu, U64x2 cv, uint32_t k0, uint32_t k1, uint32_t n, uint64_t c) {
+  U64x2 g = {0, 0};
+  for (uint32_t k = k0; k < k1; ++k) {
+    const uint2 e = xent[k];
+    const uint64_t a = gld(aU, e.x), b = gld(bV, e.x);
+    const U64x2 w = gld2(W, ((uint64_t)(e.y & 0x7fffffffu) << n) | c);
+    g.x = gl_add(g.x, gl_mul(gl_add(gl_mul(a, cu.x), gl_mul(b, cv.x)), w.x));
+    g.y = gl_add(g.y, gl_mul(gl_add(gl_mul(a, cu.y), gl_mul(b, cv.y)), w.y));
+  }
+  return g;
+}
+
+__device__ __forceinline__ U64x2 gl_sub2(U64x2 a, U64x2 b) { return U64x2{gl_sub(a.x, b.x), gl_sub(a.y, b.y)}; }
+__device__ __forceinline__ U64x2 gl_fold2(uint64_t r, U64x2 a0, U64x2 a1) {
+  return U64x2{gl_add(a0.x, gl_mul(r, gl_sub(a1.x, a0.x))), gl_add(a0.y, gl_mul(r, gl_sub(a1.y, a0.y)))};
+}
+__device__ __forceinline__ U64x2 gl_at2(U64x2 lo, U64x2 hi) {  // 2 hi - lo
+  return U64x2{gl_sub(gl_double(hi.x), lo.x), gl_sub(gl_double(hi.y), lo.y)};
+}
+__device__ __forceinline__ uint64_t gl_dot2(U64x2 a, U64x2 b) { return gl_add(gl_mul(a.x, b.x), gl_mul(a.y, b.y)); }
+
+// ST_GL_S_INIT_ROUND: Gm and round 1. Tiles below u1 take the pairs b < q0 of the
+// (x, c) table, two adjacent ones per thread; the others the q1 pairs of the
+// small tables. p0 W, p1 G, p2 xrow, p3 xmid, p4 xent, p5 aU, p6 bV, p7 Cu, p8 Cv,
+// p9 S, p10 partials, p11 r_out, p12 msg, p13 the first small table, w0..w4 the
+// entry offsets of all five from it; u0 n.
+__global__ void __launch_bounds__(kBlock) k_gl_s_init_round(Step st) {
+  const uint32_t nb = st.u[1];
+  uint64_t acc[2] = {0, 0};
+  if (blockIdx.x < nb) {
+    const uint64_t* __restrict__ W = P<const uint64_t*>(st, 0);
+    uint64_t* __restrict__ G = P<uint64_t*>(st, 1);
+    const uint32_t* __restrict__ xrow = P<const uint32_t*>(st, 2);
+    const uint32_t* __restrict__ xmid = P<const uint32_t*>(st, 3);
+    const uint2* __restrict__ xent = P<const uint2*>(st, 4);
+    const uint64_t *aU = P<const uint64_t*>(st, 5), *bV = P<const uint64_t*>(st, 6);
+    const uint32_t n = st.u[0];
+    const uint64_t mask = (1ull << n) - 1, half = st.q[0];
+    for (uint64_t b = 2 * GTID; b < half; b += 2ull * nb * kBlock) {
+      // a wave's 128 entries lie in one row: its gates are the same in every lane
+      const uint32_t x0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)(b >> n)), x1 = x0 + (uint32_t)(half >> n);
+      const uint64_t c = b & mask;
+      const uint32_t a0 = xrow[x0], e0 = xmid[x0], a1 = xrow[x1], e1 = xmid[x1];
+      if (a0 == e0 && a1 == e1) continue;
+      const U64x2 cu = gld2(P<const uint64_t*>(st, 7), c), cv = gld2(P<const uint64_t*>(st, 8), c);
+      const U64x2 w0 = gld2(W, b), w1 = gld2(W, b + half);
+      U64x2 g0 = {0, 0}, g1 = {0, 0};
+      if (a0 != e0) {
+        g0 = gl_split_entry(W, xent, aU, bV, cu, cv, a0, e0, n, c);
+        gst2(G, b, g0);
+        acc[0] = gl_add(acc[0], gl_dot2(w0, g0));
+      }
+      if (a1 != e1) {
+        g1 = gl_split_entry(W, xent, aU, bV, cu, cv, a1, e1, n, c);
+        gst2(G, b + half, g1);
+      }
+      acc[1] = gl_add(acc[1], gl_dot2(gl_at2(w0, w1), gl_at2(g0, g1)));
+    }
+  } else {
+    const uint64_t* src[5];
+    uint64_t* dst[5];
+#pragma unroll
+    for (int k = 0; k < 5; ++k) {
+      src[k] = P<const uint64_t*>(st, 13) + st.w[k];
+      dst[k] = nullptr;
+    }
+    for (uint64_t b = (uint64_t)(blockIdx.x - nb) * kBlock + threadIdx.x; b < st.q[1];
+         b += (uint64_t)(gridDim.x - nb) * kBlock)
+      gl_pair<5>(src, dst, false, 0, b, st.q[1], acc[0], acc[1]);
+  }
+  gl_finish_round(acc, P<GlState*>(st, 9), P<uint64_t*>(st, 10), P<uint64_t*>(st, 11), P<uint64_t*>(st, 12));
+}
+
+// ST_GL_S_ROUND: a later round: folds by the pending challenge and evaluates.
+// p0 W src, p1 W dst, p2 G (in place), p3 act, p4..p8 small tables (in place),
+// p9 S, p10 partials, p11 r_out, p12 msg, p13 rprev; u0 n, u1 tiles of the big
+// part, u2 k (2^k rows before this round's pairing); q0 pairs, q1 small pairs.
+__global__ void __launch_bounds__(kBlock) k_gl_s_round(Step st) {
+  const uint32_t nb = st.u[1];
+  const uint64_t r = *P<const uint64_t*>(st, 13);
+  uint64_t acc[2] = {0, 0};
+  if (blockIdx.x < nb) {
+    const uint64_t* __restrict__ Ws = P<const uint64_t*>(st, 0);
+    uint64_t *Wd = P<uint64_t*>(st, 1), *G = P<uint64_t*>(st, 2);
+    const uint32_t* __restrict__ act = P<const uint32_t*>(st, 3);
+    const uint32_t n = st.u[0], k = st.u[2], rh = 1u << (k - 1);
+    const uint64_t half = st.q[0], m = 2 * half;
+    for (uint64_t b = 2 * GTID; b < half; b += 2ull * nb * kBlock) {
+      const uint32_t x = (uint32_t)__builtin_amdgcn_readfirstlane((int)(b >> n));
+      const bool f00 = gl_row_active(act, k + 1, x), f01 = gl_row_active(act, k + 1, x + 2 * rh);
+      const bool f10 = gl_row_active(act, k + 1, x + rh), f11 = gl_row_active(act, k + 1, x + 3 * rh);
+      const U64x2 a0 = gld2(Ws, b), a1 = gld2(Ws, b + m), c0 = gld2(Ws, b + half), c1 = gld2(Ws, b + half + m);
+      U64x2 g00 = {0, 0}, g01 = {0, 0}, g10 = {0, 0}, g11 = {0, 0};
+      if (f00) g00 = gld2(G, b);
+      if (f01) g01 = gld2(G, b + m);
+      if (f10) g10 = gld2(G, b + half);
+      if (f11) g11 = gld2(G, b + half + m);
+      const U64x2 wl = gl_fold2(r, a0, a1), wh = gl_fold2(r, c0, c1);
+      gst2(Wd, b, wl);
+      gst2(Wd, b + half, wh);
+      U64x2 gl = {0, 0}, gh = {0, 0};
+      if (f00 || f01) {
+        gl = gl_fold2(r, g00, g01);
+        gst2(G, b, gl);
+        acc[0] = gl_add(acc[0], gl_dot2(wl, gl));
+      }
+      if (f10 || f11) {
+        gh = gl_fold2(r, g10, g11);
+        gst2(G, b + half, gh);
+      }
+      if (f00 || f01 || f10 || f11) acc[1] = gl_add(acc[1], gl_dot2(gl_at2(wl, wh), gl_at2(gl, gh)));
+    }
+  } else {
+    const uint64_t* src[5];
+    uint64_t* dst[5];
+#pragma unroll
+    for (int k = 0; k < 5; ++k) {
+      src[k] = P<const uint64_t*>(st, 4 + k);
+      dst[k] = P<uint64_t*>(st, 4 + k);
+    }
+    for (uint64_t b = (uint64_t)(blockIdx.x - nb) * kBlock + threadIdx.x; b < st.q[1];
+         b += (uint64_t)(gridDim.x - nb) * kBlock)
+      gl_pair<5>(src, dst, true, r, b, st.q[1], acc[0], acc[1]);
+  }
+  gl_finish_round(acc, P<GlState*>(st, 9), P<uint64_t*>(st, 10), P<uint64_t*>(st, 11), P<uint64_t*>(st, 12));
+}
+
+// ST_GL_S_P2_RAW: Ma, Mb, Aa, Ab for y < q0 (see ST_GL_P2T). p0 yrow, p1 yent,
+// p2 aU, p3 bV, p4 EL, p5 Ma, p6 Mb, p7 Aa, p8 Ab.
+__global__ void __launch_bounds__(kBlock) k_gl_s_p2_raw(Step st) {
+  const uint32_t* __restrict__ yrow = P<const uint32_t*>(st, 0);
+  const uint2* __restrict__ yent = P<const uint2*>(st, 1);
+  const uint64_t *aU = P<const uint64_t*>(st, 2), *bV = P<const uint64_t*>(st, 3), *EL = P<const uint64_t*>(st, 4);
+  for (uint64_t y = GTID; y < st.q[0]; y += GSTRIDE) {
+    uint64_t mu = 0, mv = 0, au = 0, av = 0;
+    const uint32_t k1 = yrow[y + 1];
+    for (uint32_t k = yrow[y]; k < k1; ++k) {
+      const uint2 e = yent[k];
+      const uint64_t l = gld(EL, e.y & 0x7fffffffu), tu = gl_mul(gld(aU, e.x), l), tv = gl_mul(gld(bV, e.x), l);
+      if (e.y >> 31) {
+        mu = gl_add(mu, tu);
+        mv = gl_add(mv, tv);
+      } else {
+        au = gl_add(au, tu);
+        av = gl_add(av, tv);
+      }
+    }
+    gst(P<uint64_t*>(st, 5), y, mu);
+    gst(P<uint64_t*>(st, 6), y, mv);
+    gst(P<uint64_t*>(st, 7), y, au);
+    gst(P<uint64_t*>(st, 8), y, av);
+  }
+}
+
+// ST_GL_S_P2_FINAL: Fa, Fb, Ka (holding Aa), Kb (Ab), Ks for y < q0. p0 Fa, p1 Fb,
+// p2 Ka, p3 Kb, p4 Ks, p5 S, p6 Ma, p7 Mb.
+__global__ void __launch_bounds__(kBlock) k_gl_s_p2_final(Step st) {
+  const GlState* S = P<const GlState*>(st, 5);
+  const uint64_t vx = S->vx, su = S->su, sv = S->sv;
+  for (uint64_t y = GTID; y < st.q[0]; y += GSTRIDE) {
+    const uint64_t au = gld(P<const uint64_t*>(st, 2), y), av = gld(P<const uint64_t*>(st, 3), y);
+    const uint64_t ka = gl_mul(vx, au), kb = gl_mul(vx, av);
+    gst(P<uint64_t*>(st, 0), y, gl_add(gl_mul(vx, gld(P<const uint64_t*>(st, 6), y)), au));
+    gst(P<uint64_t*>(st, 1), y, gl_add(gl_mul(vx, gld(P<const uint64_t*>(st, 7), y)), av));
+    gst(P<uint64_t*>(st, 2), y, ka);
+    gst(P<uint64_t*>(st, 3), y, kb);
+    gst(P<uint64_t*>(st, 4), y, gl_add(gl_mul(su, ka), gl_mul(sv, kb)));
+  }
+}
+
+// ST_GL_S_LOCAL2: as ST_GL_LOCAL_CONTRACT with two weight vectors p1, p3 into
+// p2, p4; two adjacent columns per thread (n >= 1).
+__global__ void __launch_bounds__(kBlock) k_gl_s_local2(Step st) {
+  const uint64_t *W = P<const uint64_t*>(st, 0), *A = P<const uint64_t*>(st, 1), *B = P<const uint64_t*>(st, 3);
+  const uint32_t n = st.u[0], lr = st.u[1];
+  const uint64_t mask = (1ull << n) - 1;
+  for (uint64_t g = 2 * GTID; g < st.q[0]; g += 2 * GSTRIDE) {
+    const uint64_t ch = g >> n, c = g & mask;
+    const uint64_t y0 = ch << lr, y1 = y0 + (1ull << lr);
+    U64x2 a = {0, 0}, b = {0, 0};
+    for (uint64_t y = y0; y < y1; ++y) {
+      const U64x2 w = gld2(W, (y << n) | c);
+      const uint64_t ea = gld(A, y), eb = gld(B, y);
+      a.x = gl_add(a.x, gl_mul(ea, w.x));
+      a.y = gl_add(a.y, gl_mul(ea, w.y));
+      b.x = gl_add(b.x, gl_mul(eb, w.x));
+      b.y = gl_add(b.y, gl_mul(eb, w.y));
+    }
+    gst2(P<uint64_t*>(st, 2), g, a);
+    gst2(P<uint64_t*>(st, 4), g, b);
+  }
+}
+
+// ST_GL_S_HANDOFF: the copy tables of phase 1 for c < q0. p0, p1 the chunk partials
+// of A and B (u0 chunks, chunk ch's columns from ch q0), p2 Cu, p3 Cv, p4 sa, p5 sb
+// (two entries left), p6 W src, p7 G, p8 act, p9 rprev, p10 Wc, p11 Gc, p12 Hc.
+// 16 lanes per column add its chunks.
+__global__ void __launch_bounds__(kBlock) k_gl_s_handoff(Step st) {
+  const uint64_t r = *P<const uint64_t*>(st, 9);
+  const uint64_t *Ws = P<const uint64_t*>(st, 6), *G = P<const uint64_t*>(st, 7);
+  const uint32_t* act = P<const uint32_t*>(st, 8);
+  const uint64_t sa0 = gld(P<const uint64_t*>(st, 4), 0), sa1 = gld(P<const uint64_t*>(st, 4), 1);
+  const uint64_t sb0 = gld(P<const uint64_t*>(st, 5), 0), sb1 = gld(P<const uint64_t*>(st, 5), 1);
+  const uint64_t sa = gl_add(sa0, gl_mul(r, gl_sub(sa1, sa0))), sb = gl_add(sb0, gl_mul(r, gl_sub(sb1, sb0)));
+  const uint64_t ncop = st.q[0];
+  const uint32_t lane = threadIdx.x & 15;
+  for (uint64_t base = (uint64_t)blockIdx.x * (kBlock / 16); base < ncop; base += (uint64_t)gridDim.x * (kBlock / 16)) {
+    const uint64_t c = base + threadIdx.x / 16;
+    uint64_t a = 0, b = 0;
+    if (c < ncop)
+      for (uint32_t ch = lane; ch < st.u[0]; ch += 16) {
+        a = gl_add(a, gld(P<const uint64_t*>(st, 0), ch * ncop + c));
+        b = gl_add(b, gld(P<const uint64_t*>(st, 1), ch * ncop + c));
+      }
+    for (int off = 8; off >= 1; off >>= 1) {
+      a = gl_add(a, shfl_xor_u64(a, off));
+      b = gl_add(b, shfl_xor_u64(b, off));
+    }
+    if (lane == 0 && c < ncop) {
+      const uint64_t cu = gld(P<const uint64_t*>(st, 2), c), cv = gld(P<const uint64_t*>(st, 3), c);
+      const uint64_t w0 = gld(Ws, c), w1 = gld(Ws, c + ncop);
+      const uint64_t g0 = gl_row_active(act, 1, 0) ? gld(G, c) : 0, g1 = gl_row_active(act, 1, 1) ? gld(G, c + ncop) : 0;
+      gst(P<uint64_t*>(st, 10), c, gl_add(w0, gl_mul(r, gl_sub(w1, w0))));
+      gst(P<uint64_t*>(st, 11), c, gl_add(gl_add(gl_mul(cu, sa), gl_mul(cv, sb)), gl_add(g0, gl_mul(r, gl_sub(g1, g0)))));
+      gst(P<uint64_t*>(st, 12), c, gl_add(gl_mul(cu, a), gl_mul(cv, b)));
+    }
+  }
+}
+
+// ---------------------------------------------------------------- tails
 
 // ST_GL_TAIL / ST_GL_TAIL5: the remaining u0 rounds in one workgroup, then
 // the final fold; the final value of table 0 goes to *final_out and, when
@@ -856,6 +1142,13 @@ void launch_gl_step(const Step& st, hipStream_t s) {
     case ST_GL_LOCAL_VALUES: k_gl_local_values<<<grid, block, 0, s>>>(st); cls = PC_SMALL; break;
     case ST_GL_LOCAL_CONTRACT: k_gl_local_contract<<<grid, block, 0, s>>>(st); cls = PC_LOCAL_CONTRACT; break;
     case ST_GL_COPY_TABLES: k_gl_copy_tables<<<grid, block, 0, s>>>(st); cls = PC_SMALL; break;
+    case ST_GL_S_SMALL: k_gl_s_small<<<grid, block, 0, s>>>(st); break;
+    case ST_GL_S_INIT_ROUND: k_gl_s_init_round<<<grid, block, 0, s>>>(st); cls = PC_PHASE1_INIT; break;
+    case ST_GL_S_ROUND: k_gl_s_round<<<grid, block, 0, s>>>(st); cls = PC_ROUND_A; break;
+    case ST_GL_S_P2_RAW: k_gl_s_p2_raw<<<grid, block, 0, s>>>(st); cls = PC_PHASE2_TABLES; break;
+    case ST_GL_S_P2_FINAL: k_gl_s_p2_final<<<grid, block, 0, s>>>(st); cls = PC_PHASE2_TABLES; break;
+    case ST_GL_S_LOCAL2: k_gl_s_local2<<<grid, block, 0, s>>>(st); cls = PC_LOCAL_CONTRACT; break;
+    case ST_GL_S_HANDOFF: k_gl_s_handoff<<<grid, block, 0, s>>>(st); break;
     default: break;
   }
   if (tok >= 0) prof_end(tok, s, cls, st.bytes, st.mulmods);
@@ -1004,6 +1297,100 @@ uint32_t gl_ychunks(uint32_t sigma, uint32_t n) {
   return (uint32_t)std::min<uint64_t>(want, 1ull << sigma);
 }
 
+void gl_copy_contract(std::vector<Step>& steps, const uint64_t* W, const uint64_t* U, const uint64_t* V, uint64_t* Pt,
+                      uint64_t* Qt, uint32_t n, uint64_t rows) {
+  Step st = gl_mk(ST_GL_COPY_CONTRACT, gl_tiles(rows * 64, kGlSweepTiles));
+  st.p[0] = W; st.p[1] = U; st.p[2] = V; st.p[3] = Pt; st.p[4] = Qt; st.u[0] = n;
+  st.q[0] = rows;
+  st.bytes = kGE * (double)(rows << n); st.mulmods = 2.0 * (double)(rows << n);
+  steps.push_back(st);
+}
+
+// Layers whose phase 1 takes the contracted form.
+constexpr uint32_t kGlSplitMinLogCopies = 8, kGlSplitMinLogRows = 8, kGlSplitMinLogWidth = 22;
+
+bool gl_split_applies(uint32_t n, uint32_t sigma) {
+  return n >= kGlSplitMinLogCopies && sigma >= kGlSplitMinLogRows && n + sigma >= kGlSplitMinLogWidth;
+}
+
+// Phase 1 of layer i in the contracted form; leaves EL in w.EL and Ma, Mb, Aa, Ab in
+// w.P, w.Q, w.Ka, w.Kb. H, which this form does not use, holds the chunk
+// partials of A and B.
+void gl_emit_phase1_split(std::vector<Step>& steps, const gkr_circuit& c, uint32_t i, const GlWs& w, uint64_t* rx,
+                          uint64_t* msg, const Tuning& tun) {
+  const uint32_t n = c.n, sigma = c.sigma[i + 1], s1 = sigma + n;
+  const LayerWiring& lw = c.wiring[i];
+  const uint64_t rows = 1ull << sigma, ncop = 1ull << n, full = rows << n;
+  const double gates = (double)(1ull << c.sigma[i]), muls = (double)c.mul_gates[i];
+  const uint64_t* W = w.layer[i + 1];
+  gl_copy_contract(steps, W, w.Cu, w.Cv, w.P, w.Q, n, rows);
+  uint64_t* small[5] = {w.P, w.Fa, w.Q, w.Fb, w.Ks};
+  {
+    Step st = gl_mk(ST_GL_S_SMALL, gl_tiles(rows, kGlSweepTiles));
+    st.p[0] = lw.xrow; st.p[1] = lw.xmid; st.p[2] = lw.xent; st.p[3] = w.aU; st.p[4] = w.bV; st.p[5] = w.P;
+    st.p[6] = w.Q; st.p[7] = w.Fa; st.p[8] = w.Fb; st.p[9] = w.Ks; st.q[0] = rows;
+    st.bytes = kGE * (3.0 * rows + 4.0 * (gates - muls)); st.mulmods = 2.0 * (gates - muls);
+    steps.push_back(st);
+  }
+  const uint64_t* Ws = W;
+  for (uint32_t j = 0; j < sigma; ++j) {
+    const uint64_t half = full >> (j + 1), shalf = rows >> (j + 1);
+    Step st = gl_mk(j == 0 ? ST_GL_S_INIT_ROUND : ST_GL_S_ROUND, gl_tiles((half + 1) / 2, j == 0 ? 2048 : 1024));
+    st.u[0] = n; st.u[1] = st.ntiles; st.u[2] = sigma - j;
+    st.ntiles += (uint32_t)std::min<uint64_t>((shalf + kBlock - 1) / kBlock, 64);
+    st.q[0] = half; st.q[1] = shalf;
+    st.p[9] = w.S; st.p[10] = w.partials; st.p[11] = rx + j; st.p[12] = msg + 3 * j;
+    if (j == 0) {
+      st.p[0] = W; st.p[1] = w.G; st.p[2] = lw.xrow; st.p[3] = lw.xmid; st.p[4] = lw.xent; st.p[5] = w.aU;
+      st.p[6] = w.bV; st.p[7] = w.Cu; st.p[8] = w.Cv; st.p[13] = small[0];
+      for (int k = 0; k < 5; ++k) st.w[k] = (uint32_t)(small[k] - small[0]);
+      st.bytes = kGE * (2.0 * muls * ncop + full); st.mulmods = 3.0 * muls * ncop + 2.0 * half;
+    } else {
+      st.p[0] = Ws; st.p[1] = w.Wf; st.p[2] = w.G; st.p[3] = lw.act; st.p[13] = rx + j - 1;
+      for (int k = 0; k < 5; ++k) st.p[4 + k] = small[k];
+      Ws = w.Wf;
+      st.bytes = kGE * 12.0 * half; st.mulmods = 6.0 * half;
+    }
+    steps.push_back(st);
+  }
+  {
+    const uint32_t bits[1] = {sigma};
+    const uint64_t* pts[1] = {rx};
+    const uint64_t* scl[1] = {nullptr};
+    uint64_t* outs[1] = {w.EL};
+    gl_eq(steps, 1, bits, pts, scl, outs);
+  }
+  {
+    Step st = gl_mk(ST_GL_S_P2_RAW, gl_tiles(rows, kGlSweepTiles));
+    st.p[0] = lw.yrow; st.p[1] = lw.yent; st.p[2] = w.aU; st.p[3] = w.bV; st.p[4] = w.EL; st.p[5] = w.P; st.p[6] = w.Q;
+    st.p[7] = w.Ka; st.p[8] = w.Kb; st.q[0] = rows;
+    st.bytes = kGE * (3.0 * gates + 4.0 * rows); st.mulmods = 2.0 * gates;
+    steps.push_back(st);
+  }
+  const uint32_t R = gl_ychunks(sigma, n);
+  uint64_t *partA = w.H, *partB = w.H + (uint64_t)R * ncop;
+  {
+    uint32_t lr = 0;
+    while ((1ull << (lr + 1)) * R <= rows) ++lr;
+    Step st = gl_mk(ST_GL_S_LOCAL2, gl_tiles((uint64_t)R * ncop / 2, kGlSweepTiles));
+    st.p[0] = W; st.p[1] = w.Ka; st.p[2] = partA; st.p[3] = w.Kb; st.p[4] = partB; st.u[0] = n; st.u[1] = lr;
+    st.q[0] = (uint64_t)R * ncop;
+    st.bytes = kGE * (double)(full + 2 * (uint64_t)R * ncop); st.mulmods = 2.0 * full;
+    steps.push_back(st);
+  }
+  {
+    Step st = gl_mk(ST_GL_S_HANDOFF, gl_tiles(16 * ncop, kGlSweepTiles));
+    st.p[0] = partA; st.p[1] = partB; st.p[2] = w.Cu; st.p[3] = w.Cv; st.p[4] = w.Fa; st.p[5] = w.Fb; st.p[6] = Ws;
+    st.p[7] = w.G; st.p[8] = lw.act; st.p[9] = rx + sigma - 1; st.p[10] = w.Wc; st.p[11] = w.Fc; st.p[12] = w.Kc;
+    st.u[0] = R; st.q[0] = ncop;
+    st.bytes = kGE * (double)((2 * R + 9) * ncop); st.mulmods = 6.0 * ncop;
+    steps.push_back(st);
+  }
+  const uint64_t* src[3] = {w.Wc, w.Fc, w.Kc};
+  uint64_t* dst[3] = {w.Wc, w.Fc, w.Kc};
+  gl_phase<3>(steps, src, dst, n, w.S, w.partials, rx + sigma, msg + 3 * sigma, &w.S->vx, msg + 3 * s1, tun);
+}
+
 uint64_t gl_layer_proof_words(const gkr_circuit& c, uint32_t i) { return 6ull * c.s(i + 1) + 2; }
 
 void gl_emit_proof(std::vector<Step>& steps, const gkr_circuit& c, const GlWs& w, uint64_t seed, uint64_t* proof,
@@ -1070,7 +1457,10 @@ void gl_emit_proof(std::vector<Step>& steps, const gkr_circuit& c, const GlWs& w
       gl_eq(steps, 4, bits, pts, scl, outs);
     }
     const LayerWiring& lw = c.wiring[i];
-    {
+    const uint64_t ncop = 1ull << n, rows = 1ull << sg1;
+    const bool split = gl_split_applies(n, sg1);
+    if (split) gl_emit_phase1_split(steps, c, i, w, rx, pr, tun);
+    if (!split) {
       Step st = gl_mk(ST_GL_P1, gl_tiles(1ull << s1, kGlSweepTiles));
       st.p[0] = w.layer[i + 1]; st.p[1] = w.G; st.p[2] = w.H; st.p[3] = lw.xrow; st.p[4] = lw.xent;
       st.p[5] = w.aU; st.p[6] = w.bV; st.p[7] = w.Cu; st.p[8] = w.Cv; st.u[0] = n; st.q[0] = 1ull << s1;
@@ -1078,40 +1468,40 @@ void gl_emit_proof(std::vector<Step>& steps, const gkr_circuit& c, const GlWs& w
       st.mulmods = 3.0 * (1ull << c.s(i));
       steps.push_back(st);
     }
-    {
+    if (!split) {
       const uint64_t* src[3] = {w.layer[i + 1], w.G, w.H};
       uint64_t* dst[3] = {w.Wf, w.G, w.H};
       gl_phase<3>(steps, src, dst, s1, w.S, w.partials, rx, pr, &w.S->vx, pr + 3 * s1, tun);
     }
     {
-      const uint32_t bits[2] = {sg1, n};
-      const uint64_t* pts[2] = {rx, rx + sg1};
+      // (EL is there already after the contracted phase 1)
+      const uint32_t bits[2] = {n, sg1};
+      const uint64_t* pts[2] = {rx + sg1, rx};
       const uint64_t* scl[2] = {nullptr, nullptr};
-      uint64_t* outs[2] = {w.EL, w.EC};
-      gl_eq(steps, 2, bits, pts, scl, outs);
+      uint64_t* outs[2] = {w.EC, w.EL};
+      gl_eq(steps, split ? 1 : 2, bits, pts, scl, outs);
     }
     // phase 2 with the copy factors contracted
-    const uint64_t ncop = 1ull << n, rows = 1ull << sg1;
     {
       Step st = gl_mk(ST_GL_COPY_WEIGHTS, 1);
       st.p[0] = w.EC; st.p[1] = w.Cu; st.p[2] = w.Cv; st.p[3] = w.U; st.p[4] = w.V; st.p[5] = w.S; st.q[0] = ncop;
       st.bytes = kGE * 5.0 * ncop; st.mulmods = 2.0 * ncop;
       steps.push_back(st);
     }
-    {
+    if (split) {
+      Step st = gl_mk(ST_GL_S_P2_FINAL, gl_tiles(rows, kGlSweepTiles));
+      st.p[0] = w.Fa; st.p[1] = w.Fb; st.p[2] = w.Ka; st.p[3] = w.Kb; st.p[4] = w.Ks; st.p[5] = w.S; st.p[6] = w.P;
+      st.p[7] = w.Q; st.q[0] = rows;
+      st.bytes = kGE * 9.0 * rows; st.mulmods = 6.0 * rows;
+      steps.push_back(st);
+    } else {
       Step st = gl_mk(ST_GL_P2T, gl_tiles(rows, kGlSweepTiles));
       st.p[0] = lw.yrow; st.p[1] = lw.yent; st.p[2] = w.aU; st.p[3] = w.bV; st.p[4] = w.EL; st.p[5] = w.S;
       st.p[6] = w.Fa; st.p[7] = w.Fb; st.p[8] = w.Ka; st.p[9] = w.Kb; st.p[10] = w.Ks; st.q[0] = rows;
       st.bytes = kGE * 5.0 * rows; st.mulmods = 2.0 * (double)(1ull << sg) + 6.0 * rows;
       steps.push_back(st);
     }
-    {
-      Step st = gl_mk(ST_GL_COPY_CONTRACT, gl_tiles(rows * 64, kGlSweepTiles));
-      st.p[0] = w.layer[i + 1]; st.p[1] = w.U; st.p[2] = w.V; st.p[3] = w.P; st.p[4] = w.Q; st.u[0] = n;
-      st.q[0] = rows;
-      st.bytes = kGE * (double)(rows * ncop); st.mulmods = 2.0 * rows * ncop;
-      steps.push_back(st);
-    }
+    gl_copy_contract(steps, w.layer[i + 1], w.U, w.V, w.P, w.Q, n, rows);
     {
       const uint64_t* src[5] = {w.P, w.Fa, w.Q, w.Fb, w.Ks};
       uint64_t* dst[5] = {w.P, w.Fa, w.Q, w.Fb, w.Ks};
