@@ -216,25 +216,69 @@ void Program::forward(const Fr* W, Fr* V, const uint2* gates, uint32_t n, uint64
   st.bytes = 3 * kE * count; st.mulmods = (double)mul_gates;
   steps.push_back(st);
 }
-void Program::digest(const gkr_fr* vec, uint64_t nelem, uint32_t* final_out, const Workspace& w) {
-  const uint32_t* in = reinterpret_cast<const uint32_t*>(vec);
-  uint64_t nwords = nelem * 8;
-  int swap = 1;
-  uint32_t* bufs[2] = {w.dig_a, w.dig_b};
-  int which = 0;
-  for (;;) {
-    const uint64_t nchunks = (nwords + kChunkWords - 1) / kChunkWords;
-    uint32_t* out = (nchunks == 1) ? final_out : bufs[which];
-    Step st = mk(ST_DIGEST, tiles_for(nchunks, kSweepTiles));
-    st.p[0] = in; st.p[1] = out; st.q[0] = nwords; st.q[1] = nchunks; st.u[0] = swap;
-    st.bytes = 4.0 * nwords + 32.0 * nchunks;
+void emit_digests(std::vector<Step>& steps, uint32_t thread_type, const DigestJob* jobs, int count, uint32_t* dig_a,
+                  uint32_t* dig_b, uint32_t* small) {
+  // the state of each tree: its current level
+  struct Cur {
+    const uint32_t* in;
+    uint64_t words;
+    uint32_t swap, area;
+    bool done;
+  } cur[2];
+  auto chunks_of = [](uint64_t words) { return (words + kChunkWords - 1) / kChunkWords; };
+  auto advance = [&](int v, uint32_t* out) {
+    cur[v].done = chunks_of(cur[v].words) == 1;
+    cur[v].in = out;
+    cur[v].words = chunks_of(cur[v].words) * 8;
+    cur[v].swap = 0;
+  };
+  auto small_out = [&](int v) {
+    if (chunks_of(cur[v].words) == 1) return jobs[v].out;
+    cur[v].area ^= 1;
+    return small + (2 * v + cur[v].area) * (kDigestWaveChunks * 8);
+  };
+  auto wave_level = [&](int a, int b) {  // b < 0: one tree
+    Step st = mk(ST_DIGEST_WAVE, 1);
+    const int vs[2] = {a, b};
+    uint64_t tiles = 0;
+    for (int k = 0; k < 2; ++k) {
+      const int v = vs[k];
+      if (v < 0) continue;
+      uint32_t* out = small_out(v);
+      st.p[2 * k] = cur[v].in; st.p[2 * k + 1] = out; st.u[k] = cur[v].swap;
+      st.q[2 * k] = cur[v].words; st.q[2 * k + 1] = chunks_of(cur[v].words);
+      st.bytes += 4.0 * cur[v].words + 32.0 * st.q[2 * k + 1];
+      tiles += st.q[2 * k + 1];
+      advance(v, out);
+    }
+    st.ntiles = (uint32_t)tiles;
     steps.push_back(st);
-    if (nchunks == 1) break;
-    in = out;
-    nwords = nchunks * 8;
-    swap = 0;
-    which ^= 1;
+  };
+  for (int v = 0; v < count; ++v) {
+    cur[v] = {jobs[v].in, jobs[v].words, 1, 0, false};
+    uint32_t* bufs[2] = {dig_a, dig_b};
+    int which = 0;
+    bool big = false;
+    while (chunks_of(cur[v].words) > kDigestWaveChunks) {
+      const uint64_t n = chunks_of(cur[v].words);
+      Step st = mk(thread_type, tiles_for(n, kSweepTiles));
+      st.p[0] = cur[v].in; st.p[1] = bufs[which]; st.q[0] = cur[v].words; st.q[1] = n; st.u[0] = cur[v].swap;
+      st.bytes = 4.0 * cur[v].words + 32.0 * n;
+      steps.push_back(st);
+      advance(v, bufs[which]);
+      which ^= 1;
+      big = true;
+    }
+    if (big) wave_level(v, -1);  // the next tree needs dig_a and dig_b
   }
+  if (count == 1) cur[1].done = true;
+  while (!cur[0].done || !cur[1].done) {
+    if (cur[0].done || cur[1].done) wave_level(cur[0].done ? 1 : 0, -1);
+    else wave_level(0, 1);
+  }
+}
+void Program::digests(const DigestJob* jobs, int count, const Workspace& w) {
+  emit_digests(steps, ST_DIGEST, jobs, count, w.dig_a, w.dig_b, reinterpret_cast<uint32_t*>(w.partials));
 }
 void Program::transcript_begin(DevState* S, const Words8& seed_state, const uint32_t* circ,
                                const uint32_t* din, const uint32_t* dout) {
@@ -306,6 +350,23 @@ void Program::p1_init_round(const Fr* W, Fr* G, Fr* H, const LayerWiring& lw, co
   steps.push_back(st);
 }
 
+void Program::p1_wide(const Fr* W, Fr* G, Fr* H, const LayerWiring& lw, const Fr* aU, const Fr* bV, const Fr* Cu,
+                      const Fr* Cv, Fr* tw, uint32_t n, uint64_t half, uint64_t gates, DevState* S, Fr* partials,
+                      Fr* r_out, uint32_t* msg) {
+  Step st = mk(ST_W_P1_GATES, tiles_for(gates, kSweepTiles));
+  st.p[0] = W; st.p[1] = tw; st.p[2] = lw.xent; st.p[3] = aU; st.p[4] = bV; st.p[5] = Cu; st.p[6] = Cv;
+  st.u[0] = n; st.q[0] = gates;
+  st.bytes = 2 * kE * gates; st.mulmods = 2.5 * gates;
+  steps.push_back(st);
+  Step rd = mk(ST_W_P1_ROUND, (uint32_t)((half + kWidePairs - 1) / kWidePairs));
+  rd.p[0] = W; rd.p[1] = G; rd.p[2] = H; rd.p[3] = lw.xrow; rd.p[4] = lw.xmid; rd.p[5] = lw.xent; rd.p[6] = tw;
+  rd.p[7] = aU; rd.p[8] = bV; rd.p[9] = S; rd.p[10] = partials; rd.p[11] = r_out; rd.p[12] = msg; rd.p[13] = Cu;
+  rd.p[14] = Cv;
+  rd.u[0] = n; rd.q[0] = half;
+  rd.bytes = kE * (gates + 6.0 * half); rd.mulmods = 3.0 * half + 2.0 * half;
+  steps.push_back(rd);
+}
+
 // Algorithmic bytes and products of one round over `half` pairs of NT tables
 // (eval_products products per evaluation point).
 // Work of a step in product equivalents: a full Montgomery product is one, an
@@ -329,7 +390,7 @@ void Program::round(const Fr* const* src, Fr* const* dst, uint64_t half, const F
   }
   st.p[R::kR] = rprev; st.p[R::kS] = S; st.p[R::kPart] = partials; st.p[R::kROut] = r_out; st.p[R::kMsg] = msg;
   st.q[0] = half;
-  if (plain && half <= (NT == 3 ? kWideMaxHalfA : kWideMaxHalfB)) {
+  if (plain && half <= (1ull << kWideMaxLogHalf)) {
     st.type = NT == 3 ? ST_W_ROUND_A : ST_W_ROUND_B;
     st.ntiles = (uint32_t)((half + kWidePairs - 1) / kWidePairs);
   }
@@ -366,17 +427,20 @@ void Program::copy_weights(const Fr* Cu, const Fr* Cv, const Fr* EC, Fr* U, Fr* 
 }
 void Program::p2_tables(const LayerWiring& lw, const Fr* aU, const Fr* bV, const Fr* EL, const DevState* S,
                         Fr* Fa, Fr* Fb, Fr* Ka, Fr* Kb, Fr* Ks, uint64_t count, uint64_t gates) {
-  Step st = mk(ST_P2_TABLES, tiles_for(count, kSweepTiles));
+  Step st = mk(ST_P2_TABLES, tiles_for(2 * count, kSweepTiles));
   st.p[0] = lw.yrow; st.p[1] = lw.yent; st.p[2] = aU; st.p[3] = bV; st.p[4] = EL; st.p[5] = S;
   st.p[6] = Fa; st.p[7] = Fb; st.p[8] = Ka; st.p[9] = Kb; st.p[10] = Ks; st.q[0] = count;
   st.bytes = kE * (3.0 * gates + 5.0 * count); st.mulmods = 2.0 * gates + 8.0 * count;
   steps.push_back(st);
 }
 void Program::copy_contract(const Fr* W, const Fr* U, const Fr* V, Fr* Pt, Fr* Qt, uint32_t n, uint64_t rows) {
-  const uint32_t tpr_log = n < 8 ? n : 8;
+  uint32_t tpr_log = 5;
+  while (tpr_log < 8 && (rows << tpr_log) < (1ull << 17)) ++tpr_log;
+  tpr_log = std::min(tpr_log, n);
   const uint64_t rows_per_tile = kBlock >> tpr_log;
   Step st = mk(ST_COPY_CONTRACT, (uint32_t)std::min<uint64_t>((rows + rows_per_tile - 1) / rows_per_tile, kSweepTiles));
-  st.p[0] = W; st.p[1] = U; st.p[2] = V; st.p[3] = Pt; st.p[4] = Qt; st.u[0] = n; st.q[0] = rows;
+  st.p[0] = W; st.p[1] = U; st.p[2] = V; st.p[3] = Pt; st.p[4] = Qt; st.u[0] = n; st.u[1] = tpr_log;
+  st.q[0] = rows;
   const double elems = (double)(rows << n);
   st.bytes = kE * elems; st.mulmods = elems;  // two unreduced products per entry
   steps.push_back(st);
@@ -486,6 +550,12 @@ void emit_layer(Program& pg, const gkr_circuit& c, uint32_t i, const Workspace& 
   const bool split = pg.plain && tun.matrix_cores && split_applies(n, sg1);
   if (split) {
     emit_phase1_split(pg, w, c.wiring[i], W, n, sg1, 1ull << sg, c.mul_gates[i], rx, proof, tun);
+  } else if (pg.plain && s1 > 1 && s1 - 1 <= kWideMaxLogHalf &&
+             (1ull << c.s(i)) <= (uint64_t)c.plan.ychunks << n) {
+    // a product chain per gate, its result in wpart, then the sums and round 1
+    pg.p1_wide(W, w.G, w.H, c.wiring[i], w.aU, w.bV, w.Cu, w.Cv, w.wpart, n, 1ull << (s1 - 1), 1ull << c.s(i), S,
+               w.partials, rx, proof);
+    emit_phase<3>(pg, ta_src, ta_dst, s1, S, w.partials, rx, proof, &S->vx, proof + off_vx, tun, 1);
   } else if (s1 > tun.tail_log) {
     pg.p1_init_round(W, w.G, w.H, c.wiring[i], w.aU, w.bV, w.Cu, w.Cv, n, 1ull << (s1 - 1), 1ull << c.s(i), S,
                      w.partials, rx, proof, tun);
@@ -551,10 +621,17 @@ static size_t layer_proof_words(const gkr_circuit& c, uint32_t i) {
   return (6ull * c.s(i + 1) + 2) * 8;
 }
 
+// The tree digests of the inputs and the outputs.
+static void emit_statement_digests(Program& pg, const gkr_circuit& c, const Workspace& w, const gkr_fr* d_inputs,
+                                   const gkr_fr* d_outputs) {
+  const DigestJob jobs[2] = {{reinterpret_cast<const uint32_t*>(d_inputs), 8ull << c.s(c.depth), w.dig_in},
+                             {reinterpret_cast<const uint32_t*>(d_outputs), 8ull << c.s(0), w.dig_out}};
+  pg.digests(jobs, 2, w);
+}
+
 void emit_statement_and_output_claim(Program& pg, const gkr_circuit& c, const Workspace& w, const gkr_fr* d_inputs,
                                      const gkr_fr* d_outputs, uint64_t seed, const Tuning& tun) {
-  pg.digest(d_inputs, 1ull << c.s(c.depth), w.dig_in, w);
-  pg.digest(d_outputs, 1ull << c.s(0), w.dig_out, w);
+  emit_statement_digests(pg, c, w, d_inputs, d_outputs);
   pg.transcript_begin(w.state, seed_state(seed), c.digest, w.dig_in, w.dig_out);
   emit_output_claim(pg, c, w, tun);
 }
@@ -565,8 +642,7 @@ void emit_prove_circuit(Program& pg, const gkr_circuit& c, const Workspace& w, c
   pg.to_mont(d_inputs, w.layer[c.depth], 1ull << c.s(c.depth));
   emit_forward(pg, c, w);
   pg.from_mont(w.layer[0], d_outputs, 1ull << c.s(0));
-  pg.digest(d_inputs, 1ull << c.s(c.depth), w.dig_in, w);
-  pg.digest(d_outputs, 1ull << c.s(0), w.dig_out, w);
+  emit_statement_digests(pg, c, w, d_inputs, d_outputs);
   pg.transcript_begin(w.state, seed_state(seed), c.digest, w.dig_in, w.dig_out);
   emit_output_claim(pg, c, w, tun);
   uint32_t* proof = reinterpret_cast<uint32_t*>(d_proof);
@@ -595,7 +671,8 @@ void emit_prove_committed(Program& pg, const gkr_circuit& c, const Workspace& w,
   pg.from_mont(w.layer[0], d_outputs, 1ull << c.s(0));
   emit_vpd_commit(pg, vp, vbase, w.layer[d]);
   emit_vpd_root_out(pg, vp, vbase, d_proof);
-  pg.digest(d_outputs, 1ull << c.s(0), w.dig_out, w);
+  const DigestJob dj = {reinterpret_cast<const uint32_t*>(d_outputs), 8ull << c.s(0), w.dig_out};
+  pg.digests(&dj, 1, w);
   pg.transcript_begin(w.state, seed_state(seed), c.digest, vpd_root_words(vp, vbase), w.dig_out);
   emit_output_claim(pg, c, w, tun);
   uint32_t* proof = reinterpret_cast<uint32_t*>(d_proof + 32);
@@ -895,8 +972,7 @@ int32_t gkr_transcript_init(const gkr_circuit* c, uint64_t seed, const gkr_fr* d
   try {
     Workspace w = bind_workspace(*c, d_ws);
     Program pg;
-    pg.digest(d_inputs, 1ull << c->s(c->depth), w.dig_in, w);
-    pg.digest(d_outputs, 1ull << c->s(0), w.dig_out, w);
+    emit_statement_digests(pg, *c, w, d_inputs, d_outputs);
     pg.transcript_begin(w.state, seed_state(seed), c->digest, w.dig_in, w.dig_out);
     pg.state_export(w.state, d_state);
     pg.run(static_cast<hipStream_t>(stream));

@@ -221,6 +221,55 @@ __device__ __forceinline__ void body_digest(const Step& st, uint32_t tile, uint3
   }
 }
 
+// ST_DIGEST_WAVE: one level of one or two tree digests with few chunks, a
+// workgroup per chunk: p0 in, p1 out, q0 words, q1 chunks, u0 swap; the same of
+// the second vector in p2, p3, q2, q3, u1 (tiles from q1 on). The blocks of a
+// chunk chain, so a thread hashing a chunk alone needs 17 x 5,900 cycles (55 us
+// per level); here the schedules of all blocks are written first, 16 at a time
+// (one per row of 16 lanes), and one wave runs the rounds: 17 x 3,140 cycles.
+__device__ __forceinline__ void body_digest_wave(const Step& st, uint32_t tile, uint32_t) {
+  constexpr uint32_t kMaxBlocks = kChunkWords / 16 + 1;
+  __shared__ __attribute__((aligned(16))) uint32_t wk[kMaxBlocks][64];
+  __shared__ __attribute__((aligned(16))) uint32_t one4[4];
+  const bool second = tile >= st.q[1];
+  const uint32_t* in = second ? P<const uint32_t*>(st, 2) : P<const uint32_t*>(st, 0);
+  uint32_t* out = second ? P<uint32_t*>(st, 3) : P<uint32_t*>(st, 1);
+  const uint64_t nwords = second ? st.q[2] : st.q[0], t = second ? tile - st.q[1] : tile;
+  const uint32_t swap = second ? st.u[1] : st.u[0];
+  const uint64_t begin = t * kChunkWords;
+  const uint32_t len = (uint32_t)(begin + kChunkWords < nwords ? kChunkWords : nwords - begin);
+  const uint32_t nblk = (len + 3 + 15) / 16, li = threadIdx.x & 15;
+  const uint32_t c0 = kSha256K[li], c1 = kSha256K[16 + li], c2 = kSha256K[32 + li], c3 = kSha256K[48 + li];
+  if (threadIdx.x < 4) one4[threadIdx.x] = 1;
+  // (whole waves: the schedule reads its neighbours' lanes)
+  for (uint32_t b0 = 0; b0 < nblk; b0 += kBlock / 16) {
+    const uint32_t b = b0 + threadIdx.x / 16;
+    const uint32_t i = 16 * b + li;
+    uint32_t w = 0;
+    if (i < len) {
+      w = in[begin + i];
+      if (swap) w = bswap32(w);
+    } else if (i == len) {
+      w = 0x80000000u;
+    } else if (i == 16 * nblk - 1) {
+      w = len * 32;
+    }
+    const uint32_t w1 = sha_schedule(w), w2 = sha_schedule(w1), w3 = sha_schedule(w2);
+    if (b < nblk) {
+      wk[b][li] = w + c0;
+      wk[b][16 + li] = w1 + c1;
+      wk[b][32 + li] = w2 + c2;
+      wk[b][48 + li] = w3 + c3;
+    }
+  }
+  __syncthreads();
+  if (threadIdx.x < 64) {
+    ShaLanes sh = sha_lanes_iv();
+    for (uint32_t b = 0; b < nblk; ++b) sh = sha_compress_given(sh, wk[b], one4);
+    sha_lanes_store(out + 8 * t, sh);
+  }
+}
+
 // ST_TRANSCRIPT_BEGIN: st = seed state (w0..7), then absorb the circuit digest
 // (w8..15) and the two vector digests; also zeroes the reduction counter and
 // clears the pending round.
@@ -291,35 +340,63 @@ __device__ __forceinline__ void body_layer_begin(const Step& st, uint32_t, uint3
 
 // ST_EQ: up to four tables out_j[b] = scale_j * prod_k (bit_k(b) ? r_k : 1 - r_k),
 // bit 1 = MSB. u0..3 bits, u4 count; p0..3 points, p4..7 scales (null = 1), p8..11 outs.
+// A workgroup first computes, for every table, the 16 products of each group
+// of four variables (groups from the last variable on; the scale in the first
+// group, which may be short), a thread per product; an entry is then a product
+// of bits / 4 of them. An entry alone in its thread took bits + 3 products one
+// after another: 17 us for 12 bits, now 8.
+constexpr uint32_t kEqGroups = 4 * ((GKR_MAX_LOG_WIDTH + 3) / 4);
+
 __device__ __forceinline__ void body_eq(const Step& st, uint32_t tile, uint32_t ntiles) {
+  __shared__ Fr grp[kEqGroups][16];
   uint64_t total = 0;
-  for (uint32_t j = 0; j < st.u[4]; ++j) total += 1ull << st.u[j];
-  for (uint64_t g = GTID; g < total; g += GSTRIDE) {
-    uint64_t t = g;
-    uint32_t j = 0;
-    while (t >= (1ull << st.u[j])) {
-      t -= 1ull << st.u[j];
+  uint32_t groups = 0;
+  for (uint32_t j = 0; j < st.u[4]; ++j) {
+    total += 1ull << st.u[j];
+    groups += (st.u[j] + 3) / 4;
+  }
+  for (uint32_t t = threadIdx.x; t < 16 * groups; t += kBlock) {
+    const uint32_t c = t & 15;
+    uint32_t g = t >> 4, j = 0;
+    while (g >= (st.u[j] + 3) / 4) {
+      g -= (st.u[j] + 3) / 4;
       ++j;
     }
+    // group g of table j: bits 4 g .. 4 g + 3 of the index (from the low end)
     const Fr* r = P<const Fr*>(st, j);
-    const int k = st.u[j];
     const Fr* scale = P<const Fr*>(st, 4 + j);
-    // the k factors in four independent chains (variable i in chain i mod 4),
-    // multiplied together at the end: a dependent chain of about k/4 + 2 products
-    Fr acc[4] = {scale ? *scale : fr_one(), fr_one(), fr_one(), fr_one()};
-    for (int i0 = 0; i0 < k; i0 += 4) {
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int i = i0 + q;
-        if (i < k) {
-          const Fr ri = ldf(r, i);
-          const bool bit = (t >> (k - 1 - i)) & 1;
-          acc[q] = fr_mul(acc[q], bit ? ri : fr_one_minus(ri));
-        }
-      }
-    }
-    stf(P<Fr*>(st, 8 + j), t, fr_mul(fr_mul(acc[0], acc[1]), fr_mul(acc[2], acc[3])));
+    const uint32_t k = st.u[j], have = k - 4 * g < 4 ? k - 4 * g : 4;
+    auto factor = [&](uint32_t b) {
+      if (b >= have) return fr_one();
+      const Fr ri = opaque(ldf(r, k - 1 - 4 * g - b));
+      return (c >> b) & 1 ? ri : fr_one_minus(ri);
+    };
+    Fr v = fr_mul(factor(0), factor(1));
+    if (have > 2) v = fr_mul(v, fr_mul(factor(2), factor(3)));
+    if (g == 0 && scale) v = fr_mul(v, opaque(*scale));
+    grp[t >> 4][c] = v;
   }
+  __syncthreads();
+  for (uint64_t g = (uint64_t)tile * kBlock + threadIdx.x; g < total; g += (uint64_t)ntiles * kBlock) {
+    uint64_t t = g;
+    uint32_t j = 0, base = 0;
+    while (t >= (1ull << st.u[j])) {
+      t -= 1ull << st.u[j];
+      base += (st.u[j] + 3) / 4;
+      ++j;
+    }
+    const uint32_t k = st.u[j];
+    Fr v;
+    if (k == 0) {
+      const Fr* scale = P<const Fr*>(st, 4 + j);
+      v = scale ? *scale : fr_one();
+    } else {
+      v = grp[base][t & 15];
+      for (uint32_t q = 1; 4 * q < k; ++q) v = fr_mul(v, opaque(grp[base + q][(t >> (4 * q)) & 15]));
+    }
+    stf(P<Fr*>(st, 8 + j), t, v);
+  }
+  __syncthreads();  // the batch kernel may run another tile next
 }
 
 // ST_WSUM: sum_e V[e] A[e >> n] B[e & mask] into *p5.
@@ -1119,52 +1196,54 @@ __device__ __forceinline__ void body_copy_weights(const Step& st, uint32_t, uint
 //   M[y,c] = U[c] Ma[y] + V[c] Mb[y],  A[y,c] = U[c] Aa[y] + V[c] Ab[y]
 //   Ma[y] = sum_{MUL z: y_z=y} aU[z] EL[x_z] (Mb with bV; Aa, Ab over ADD gates)
 //   Fa = vx Ma + Aa, Fb = vx Mb + Ab, Ka = vx Aa, Kb = vx Ab, Ks = SU Ka + SV Kb.
+// Two adjacent threads per wire, one for the a tables and one for the b tables
+// (a product per gate instead of two: 26 us for 2^12 wires with one thread, now 16).
 // p0 yrow, p1 yent, p2 aU, p3 bV, p4 EL, p5 S, p6 Fa, p7 Fb, p8 Ka, p9 Kb, p10 Ks, q0 count.
 __device__ __forceinline__ void body_p2_tables(const Step& st, uint32_t tile, uint32_t ntiles) {
   const uint32_t* __restrict__ yrow = P<const uint32_t*>(st, 0);
   const uint2* __restrict__ yent = P<const uint2*>(st, 1);
-  const Fr* __restrict__ aU = P<const Fr*>(st, 2);
-  const Fr* __restrict__ bV = P<const Fr*>(st, 3);
   const Fr* __restrict__ EL = P<const Fr*>(st, 4);
   const DevState* S = P<const DevState*>(st, 5);
-  const Fr vx = S->vx, su = S->su, sv = S->sv;
-  for (uint64_t y = GTID; y < st.q[0]; y += GSTRIDE) {
-    Fr ma = fr_zero(), mb = fr_zero(), aa = fr_zero(), ab = fr_zero();
+  const bool b = threadIdx.x & 1;
+  const Fr* __restrict__ weight = b ? P<const Fr*>(st, 3) : P<const Fr*>(st, 2);
+  Fr* F = b ? P<Fr*>(st, 7) : P<Fr*>(st, 6);
+  Fr* K = b ? P<Fr*>(st, 9) : P<Fr*>(st, 8);
+  const Fr vx = opaque(S->vx), su = opaque(b ? S->sv : S->su);
+  const uint64_t total = 2 * st.q[0];
+  for (uint64_t t = GTID; t < total; t += GSTRIDE) {
+    const uint64_t y = t >> 1;
+    Fr m = fr_zero(), a = fr_zero();
     const uint32_t k1 = yrow[y + 1];
     for (uint32_t k = yrow[y]; k < k1; ++k) {
       const uint2 ent = yent[k];
-      const uint64_t z = ent.x, x = ent.y & 0x7fffffffu;
-      const Fr el = ldf(EL, x);
-      const Fr a = fr_mul(ldf(aU, z), el), b = fr_mul(ldf(bV, z), el);
-      if (ent.y >> 31) {
-        ma = fr_add(ma, a);
-        mb = fr_add(mb, b);
-      } else {
-        aa = fr_add(aa, a);
-        ab = fr_add(ab, b);
-      }
+      const Fr v = fr_mul(ldf(weight, ent.x), ldf(EL, ent.y & 0x7fffffffu));
+      if (ent.y >> 31) m = fr_add(m, v);
+      else a = fr_add(a, v);
     }
-    const Fr ka = fr_mul(vx, aa), kb = fr_mul(vx, ab);
-    stf(P<Fr*>(st, 6), y, fr_add(fr_mul(vx, ma), aa));
-    stf(P<Fr*>(st, 7), y, fr_add(fr_mul(vx, mb), ab));
-    stf(P<Fr*>(st, 8), y, ka);
-    stf(P<Fr*>(st, 9), y, kb);
-    stf(P<Fr*>(st, 10), y, fr_mul_add2(su, ka, sv, kb));
+    const Fr ka = fr_mul(vx, a);
+    stf(F, y, fr_add(fr_mul(vx, m), a));
+    stf(K, y, ka);
+    const Fr part = fr_mul(su, ka);
+    const Fr ks = fr_add(part, shfl_xor_fr(part, 1));
+    if (!b) stf(P<Fr*>(st, 10), y, ks);
   }
 }
 
 // ST_COPY_CONTRACT: row sums over the copies, P[y] = sum_c U[c] W[y,c],
-// Q[y] = sum_c V[c] W[y,c]. A row of 2^n entries is handled by
-// tpr = min(256, 2^n) threads; tile t covers rows t * (256 / tpr) onwards.
-// p0 W, p1 U, p2 V, p3 P, p4 Q, u0 n, q0 rows.
+// Q[y] = sum_c V[c] W[y,c]. A row of 2^n entries is handled by tpr = 2^u1 <= 256
+// threads: enough of them for about 2^17 in all, but at least 32 (of a row of 32
+// entries or more), since a thread's reduction and the sums over the threads
+// cost as much as three entries (2^12 rows of 2^8 entries: 45 us with 256
+// threads per row, 20 with 32).
+// p0 W, p1 U, p2 V, p3 P, p4 Q, u0 n, u1 log2 of tpr, q0 rows.
 __device__ __forceinline__ void body_copy_contract(const Step& st, uint32_t tile, uint32_t ntiles) {
-  __shared__ Fr sp[kBlock], sq[kBlock];
+  __shared__ Fr sw[2][kBlock / 64];
   const Fr* __restrict__ W = P<const Fr*>(st, 0);
   const Fr* __restrict__ U = P<const Fr*>(st, 1);
   const Fr* __restrict__ V = P<const Fr*>(st, 2);
   const uint32_t n = st.u[0];
   const uint64_t rows = st.q[0];
-  const uint32_t tpr_log = n < 8 ? n : 8;
+  const uint32_t tpr_log = st.u[1];
   const uint32_t tpr = 1u << tpr_log;
   const uint32_t lane = threadIdx.x & (tpr - 1);
   const uint64_t rows_per_tile = kBlock >> tpr_log;
@@ -1186,20 +1265,28 @@ __device__ __forceinline__ void body_copy_contract(const Step& st, uint32_t tile
         q = fr_add(q, frw_reduce<16>(frc_wide(qw)));
       }
     }
-    __syncthreads();
-    sp[threadIdx.x] = p;
-    sq[threadIdx.x] = q;
-    __syncthreads();
-    for (uint32_t s = tpr / 2; s >= 1; s >>= 1) {
-      if (lane < s) {
-        sp[threadIdx.x] = fr_add(sp[threadIdx.x], sp[threadIdx.x + s]);
-        sq[threadIdx.x] = fr_add(sq[threadIdx.x], sq[threadIdx.x + s]);
+    for (uint32_t off = (tpr < 64 ? tpr : 64) / 2; off >= 1; off >>= 1) {
+      p = fr_add(p, shfl_xor_fr(p, (int)off));
+      q = fr_add(q, shfl_xor_fr(q, (int)off));
+    }
+    if (tpr > 64) {
+      // the row's waves
+      const uint32_t wid = threadIdx.x >> 6, nw = tpr / 64;
+      __syncthreads();
+      if ((threadIdx.x & 63) == 0) {
+        sw[0][wid] = p;
+        sw[1][wid] = q;
       }
       __syncthreads();
+      if (lane == 0)
+        for (uint32_t w = 1; w < nw; ++w) {
+          p = fr_add(p, opaque(sw[0][wid + w]));
+          q = fr_add(q, opaque(sw[1][wid + w]));
+        }
     }
     if (lane == 0 && row < rows) {
-      stf(P<Fr*>(st, 3), row, sp[threadIdx.x]);
-      stf(P<Fr*>(st, 4), row, sq[threadIdx.x]);
+      stf(P<Fr*>(st, 3), row, p);
+      stf(P<Fr*>(st, 4), row, q);
     }
   }
 }
@@ -1342,6 +1429,7 @@ __device__ __forceinline__ void run_step_tile(const Step& st, uint32_t tile, uin
     case ST_FROM_MONT: body_from_mont(st, tile, ntiles); break;
     case ST_FORWARD: body_forward(st, tile, ntiles); break;
     case ST_DIGEST: body_digest(st, tile, ntiles); break;
+    case ST_DIGEST_WAVE: body_digest_wave(st, tile, ntiles); break;
     case ST_TRANSCRIPT_BEGIN: body_transcript_begin(st, tile, ntiles); break;
     case ST_SQUEEZE: body_squeeze(st, tile, ntiles); break;
     case ST_LAYER_BEGIN: body_layer_begin(st, tile, ntiles); break;

@@ -1211,27 +1211,6 @@ GlWs gl_bind(const gkr_circuit& c, void* base, const uint64_t* d_inputs, uint64_
   return w;
 }
 
-void gl_digest(std::vector<Step>& steps, const uint64_t* vec, uint64_t nelem, uint32_t* final_out, const GlWs& w) {
-  const uint32_t* in = reinterpret_cast<const uint32_t*>(vec);
-  uint64_t nwords = 2 * nelem;
-  int swap = 1;
-  uint32_t* bufs[2] = {w.dig_a, w.dig_b};
-  int which = 0;
-  for (;;) {
-    const uint64_t nchunks = (nwords + kChunkWords - 1) / kChunkWords;
-    uint32_t* out = (nchunks == 1) ? final_out : bufs[which];
-    Step st = gl_mk(ST_GL_DIGEST, gl_tiles(nchunks, kGlSweepTiles));
-    st.p[0] = in; st.p[1] = out; st.q[0] = nwords; st.q[1] = nchunks; st.u[0] = swap;
-    st.bytes = 4.0 * nwords + 32.0 * nchunks;
-    steps.push_back(st);
-    if (nchunks == 1) break;
-    in = out;
-    nwords = nchunks * 8;
-    swap = 0;
-    which ^= 1;
-  }
-}
-
 void gl_eq(std::vector<Step>& steps, int count, const uint32_t* bits, const uint64_t* const* pts,
            const uint64_t* const* scl, uint64_t* const* outs) {
   Step st = gl_mk(ST_GL_EQ, 1);
@@ -1406,8 +1385,9 @@ void gl_emit_proof(std::vector<Step>& steps, const gkr_circuit& c, const GlWs& w
     steps.push_back(st);
   }
   // statement
-  gl_digest(steps, w.layer[d], 1ull << c.s(d), w.dig_in, w);
-  gl_digest(steps, w.layer[0], 1ull << c.s(0), w.dig_out, w);
+  const DigestJob jobs[2] = {{reinterpret_cast<const uint32_t*>(w.layer[d]), 2ull << c.s(d), w.dig_in},
+                             {reinterpret_cast<const uint32_t*>(w.layer[0]), 2ull << c.s(0), w.dig_out}};
+  emit_digests(steps, ST_GL_DIGEST, jobs, 2, w.dig_a, w.dig_b, reinterpret_cast<uint32_t*>(w.partials));
   {
     Step st = gl_mk(ST_GL_BEGIN, 1);
     st.p[0] = w.S; st.p[1] = w.dig_in; st.p[2] = w.dig_out;

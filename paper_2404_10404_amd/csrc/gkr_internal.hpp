@@ -86,6 +86,7 @@ enum StepType : uint32_t {
   ST_LOCAL_VALUES,
   ST_STATE_EXPORT,
   ST_STATE_IMPORT,
+  ST_DIGEST_WAVE,
   ST_COUNT,
   // General circuits (accumulation gates, right inputs from any later layer):
   // launched by launch_general_step, plain path only.
@@ -160,7 +161,9 @@ enum StepType : uint32_t {
   // Rounds over small tables, one product per thread: launched by
   // launch_wide_step, plain path only.
   ST_W_ROUND_A = 240,
-  ST_W_ROUND_B
+  ST_W_ROUND_B,
+  ST_W_P1_GATES,
+  ST_W_P1_ROUND
 };
 
 struct Step {

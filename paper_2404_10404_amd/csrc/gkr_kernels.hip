@@ -27,6 +27,7 @@ GKR_SIMPLE(to_mont, body_to_mont)
 GKR_SIMPLE(from_mont, body_from_mont)
 GKR_SIMPLE(forward, body_forward)
 GKR_SIMPLE(digest, body_digest)
+GKR_SIMPLE(digest_wave, body_digest_wave)
 GKR_SIMPLE(transcript_begin, body_transcript_begin)
 GKR_SIMPLE(squeeze, body_squeeze)
 GKR_SIMPLE(layer_begin, body_layer_begin)
@@ -67,6 +68,7 @@ GKR_PLAIN_KERNEL(k_to_mont, to_mont)
 GKR_PLAIN_KERNEL(k_from_mont, from_mont)
 GKR_PLAIN_KERNEL(k_forward, forward)
 GKR_PLAIN_KERNEL(k_digest, digest)
+GKR_PLAIN_KERNEL(k_digest_wave, digest_wave)
 GKR_PLAIN_KERNEL(k_transcript_begin, transcript_begin)
 GKR_PLAIN_KERNEL(k_squeeze, squeeze)
 GKR_PLAIN_KERNEL(k_layer_begin, layer_begin)
@@ -100,7 +102,7 @@ static const ProfClass kStepClass[ST_COUNT] = {
     PC_CONVERT,        PC_CONVERT, PC_FORWARD, PC_DIGEST,        PC_TRANSCRIPT,    PC_TRANSCRIPT,
     PC_TRANSCRIPT,     PC_EQ,      PC_CLAIM,   PC_PHASE1_INIT,   PC_PHASE1_INIT,   PC_ROUND_A,
     PC_ROUND_B,        PC_TAIL_A,  PC_TAIL_B,  PC_SMALL,         PC_PHASE2_TABLES, PC_COPY_CONTRACT,
-    PC_LOCAL_CONTRACT, PC_SMALL,   PC_SMALL,   PC_SMALL,         PC_SMALL};
+    PC_LOCAL_CONTRACT, PC_SMALL,   PC_SMALL,   PC_SMALL,         PC_SMALL,  PC_DIGEST};
 
 void launch_step(const Step& st, hipStream_t s) {
   const int tok = prof_begin(s);
@@ -110,6 +112,7 @@ void launch_step(const Step& st, hipStream_t s) {
     case ST_FROM_MONT: k_from_mont<<<grid, block, 0, s>>>(st); break;
     case ST_FORWARD: k_forward<<<grid, block, 0, s>>>(st); break;
     case ST_DIGEST: k_digest<<<grid, block, 0, s>>>(st); break;
+    case ST_DIGEST_WAVE: k_digest_wave<<<grid, block, 0, s>>>(st); break;
     case ST_TRANSCRIPT_BEGIN: k_transcript_begin<<<grid, block, 0, s>>>(st); break;
     case ST_SQUEEZE: k_squeeze<<<grid, block, 0, s>>>(st); break;
     case ST_LAYER_BEGIN: k_layer_begin<<<grid, block, 0, s>>>(st); break;

@@ -10,6 +10,25 @@
 
 namespace gkr {
 
+// One vector whose tree digest is wanted: its 32-bit words (little-endian
+// element limbs, byte-swapped at the first level) and where the digest goes.
+struct DigestJob {
+  const uint32_t* in;
+  uint64_t words;
+  uint32_t* out;
+};
+
+// Levels of more than kDigestWaveChunks chunks take a thread per chunk (the chip
+// is full, or nearly), smaller ones a workgroup per chunk, both trees' levels
+// in one launch.
+constexpr uint64_t kDigestWaveChunks = 512;
+
+// The levels of one or two tree digests. dig_a, dig_b hold the large levels,
+// small (four areas of kDigestWaveChunks digests) the others; thread_type is the
+// step type of a thread-per-chunk level.
+void emit_digests(std::vector<Step>& steps, uint32_t thread_type, const DigestJob* jobs, int count, uint32_t* dig_a,
+                  uint32_t* dig_b, uint32_t* small);
+
 struct Program {
   std::vector<Step> steps;
   // Steps that only the plain launcher runs (the matrix-core contractions, the
@@ -20,7 +39,7 @@ struct Program {
   void to_mont(const gkr_fr* in, Fr* out, uint64_t n);
   void from_mont(const Fr* in, gkr_fr* out, uint64_t n);
   void forward(const Fr* W, Fr* V, const uint2* gates, uint32_t n, uint64_t count, uint64_t mul_gates);
-  void digest(const gkr_fr* vec, uint64_t nelem, uint32_t* final_out, const Workspace& w);
+  void digests(const DigestJob* jobs, int count, const Workspace& w);
   void transcript_begin(DevState* S, const Words8& seed_state, const uint32_t* circ, const uint32_t* din,
                         const uint32_t* dout);
   void squeeze(DevState* S, Fr* out, uint32_t count);
@@ -33,6 +52,9 @@ struct Program {
   void p1_init_round(const Fr* W, Fr* G, Fr* H, const LayerWiring& lw, const Fr* aU, const Fr* bV,
                      const Fr* Cu, const Fr* Cv, uint32_t n, uint64_t half, uint64_t gates, DevState* S,
                      Fr* partials, Fr* r_out, uint32_t* msg, const Tuning& tun);
+  void p1_wide(const Fr* W, Fr* G, Fr* H, const LayerWiring& lw, const Fr* aU, const Fr* bV, const Fr* Cu,
+               const Fr* Cv, Fr* tw, uint32_t n, uint64_t half, uint64_t gates, DevState* S, Fr* partials, Fr* r_out,
+               uint32_t* msg);
   template <int NT>
   void round(const Fr* const* src, Fr* const* dst, uint64_t half, const Fr* rprev, DevState* S, Fr* partials,
              Fr* r_out, uint32_t* msg, const Tuning& tun);

@@ -6,8 +6,8 @@
 
 namespace gkr {
 
-// Largest number of pairs of a round that takes this form (three and five tables).
-constexpr uint64_t kWideMaxHalfA = 1u << 13, kWideMaxHalfB = 1u << 13;
+// Largest number of pairs (log2) of a round that takes this form.
+constexpr uint32_t kWideMaxLogHalf = 13;
 constexpr uint32_t kWidePairs = 32;  // pairs per workgroup
 
 void launch_wide_step(const Step& st, hipStream_t s);

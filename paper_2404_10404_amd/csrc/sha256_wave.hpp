@@ -186,6 +186,43 @@ __device__ __forceinline__ ShaLanes sha_compress_wave(const ShaLanes& st, uint32
   r.x[3] = st.x[3] + (at ? x1 : y3);
   return r;
 }
+// The compression with its whole schedule (plus round constants) given in
+// wk[0, 64), 16-byte aligned shared memory; one[0, 4) are ones.
+__device__ __forceinline__ ShaLanes sha_compress_given(const ShaLanes& st, const uint32_t* wk, const uint32_t* one4) {
+  const bool at = (sha_lane() & 8) != 0;
+  uint32_t q, mk, t1, t2, t3;
+  uint32_t x0 = sha_sel(at, st.x[2], st.x[0]), x1 = sha_sel(at, st.x[3], st.x[1]), x2 = st.x[2], x3 = st.x[3];
+  const uint32_t s1 = at ? 2 : 6, s2 = at ? 13 : 11, s3 = at ? 22 : 25, m = at ? ~0u : 0u;
+  const U32x4* rd = reinterpret_cast<const U32x4*>(at ? one4 : wk);
+  const uint32_t step = at ? 0 : 1;
+  U32x4 k0 = rd[0], k1 = rd[step];
+  for (int g = 0; g < 16; g += 2) {
+    const bool first = g == 0;
+    GKR_SHA_STEP(x0, x1, x2, x3, k0.x);
+    x3 = sha_sel(first && at, st.x[1], x3);
+    GKR_SHA_STEP(x3, x0, x1, x2, k0.y);
+    x2 = sha_sel(first && at, st.x[0], x2);
+    GKR_SHA_STEP(x2, x3, x0, x1, k0.z);
+    GKR_SHA_STEP(x1, x2, x3, x0, k0.w);
+    rd += 2 * step;
+    if (g < 14) k0 = rd[0];
+    GKR_SHA_STEP(x0, x1, x2, x3, k1.x);
+    GKR_SHA_STEP(x3, x0, x1, x2, k1.y);
+    GKR_SHA_STEP(x2, x3, x0, x1, k1.z);
+    GKR_SHA_STEP(x1, x2, x3, x0, k1.w);
+    if (g < 14) k1 = rd[step];
+  }
+  const uint32_t y2 = x2, y3 = x3;
+  const uint32_t one = 1;
+  GKR_SHA_STEP(x0, x1, x2, x3, one);
+  GKR_SHA_STEP(x3, x0, x1, x2, one);
+  ShaLanes r;
+  r.x[0] = st.x[0] + (at ? x2 : x0);
+  r.x[1] = st.x[1] + (at ? x3 : x1);
+  r.x[2] = st.x[2] + (at ? x0 : y2);
+  r.x[3] = st.x[3] + (at ? x1 : y3);
+  return r;
+}
 #undef GKR_SHA_STEP
 
 // The helper's part (another wave of the workgroup): groups 1..3 of the
