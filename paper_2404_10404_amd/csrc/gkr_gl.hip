@@ -952,8 +952,14 @@ __global__ void __launch_bounds__(kBlock) k_gl_s_handoff(Step st) {
 // size before the pending fold (if any). p0..p(NT-1) src, pNT..p(2NT-1) dst,
 // then (from B = 2 NT) pB rpending, pB+1 S, pB+2 r_out, pB+3 msg,
 // pB+4 final_out, pB+5 proof_value.
+constexpr int kGlTailThreads = 1024;
+
+// Levels of at most 2^kGlTailLdsLog(NT) entries live in shared memory (48 and 40 KiB),
+// larger ones stay in their tables.
+__host__ __device__ constexpr uint32_t gl_tail_lds_log(int nt) { return nt == 3 ? 11 : 10; }
+
 template <int NT>
-__global__ void __launch_bounds__(kBlock) k_gl_tail(Step st) {
+__global__ void __launch_bounds__(kGlTailThreads) k_gl_tail(Step st) {
   constexpr int B = 2 * NT;
   const uint64_t* src[NT];
   uint64_t* dst[NT];
@@ -966,12 +972,13 @@ __global__ void __launch_bounds__(kBlock) k_gl_tail(Step st) {
   GlState* S = P<GlState*>(st, B + 1);
   uint64_t* r_out = P<uint64_t*>(st, B + 2);
   uint64_t* msg = P<uint64_t*>(st, B + 3);
-  // The folded tables stay in shared memory, packed (a level of m entries
-  // takes NT m words, table k from k m): at most 2^kGlTailMaxLog entries per
-  // table. A pair's entries are folded and evaluated by one thread, so a round
-  // is one pass, one sum and the hash.
+  // The folded tables stay in shared memory once they fit, packed (a level of m
+  // entries takes NT m words, table k from k m). A pair's entries are folded and
+  // evaluated by one thread, so a round is one pass, one sum and the hash: 5 us
+  // at 2^12 entries, where a grid-wide round costs 12.
   extern __shared__ uint64_t lvl[];
-  __shared__ uint64_t r_sh[2], e_sh[2][2], red[2][kBlock / 64];
+  constexpr uint32_t kLds = 1u << gl_tail_lds_log(NT);
+  __shared__ uint64_t r_sh[2], e_sh[2][2], red[2][kGlTailThreads / 64];
   __shared__ ShaHelper help;
   const uint32_t wid = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const uint32_t rounds = st.u[0];
@@ -998,9 +1005,11 @@ __global__ void __launch_bounds__(kBlock) k_gl_tail(Step st) {
     const uint32_t old = (uint32_t)(fold ? 2 * size : size);  // entries of the level read
     uint64_t acc[2] = {0, 0};
     uint64_t lo[NT], hi[NT];
-    // at most one pair per thread and pass; a level that lives in shared
-    // memory is read whole before any of it is overwritten
-    for (uint32_t b0 = 0; b0 < half; b0 += kBlock) {
+    const bool to_lds = size <= kLds;
+    // a level that lives in shared memory is read whole before any of it is
+    // overwritten (it has at most one pair per thread); a level in its tables
+    // is overwritten entry by entry by the thread that read it
+    for (uint32_t b0 = 0; b0 < half; b0 += kGlTailThreads) {
       const uint32_t b = b0 + threadIdx.x;
       const bool act = b < half;
       if (act) {
@@ -1018,12 +1027,17 @@ __global__ void __launch_bounds__(kBlock) k_gl_tail(Step st) {
           }
         }
       }
-      if (in_lds) __syncthreads();  // a level in shared memory has at most kBlock pairs: one pass
+      if (in_lds) __syncthreads();
       if (act) {
 #pragma unroll
         for (int k = 0; k < NT; ++k) {
-          lvl[k * (uint32_t)size + b] = lo[k];
-          lvl[k * (uint32_t)size + b + half] = hi[k];
+          if (to_lds) {
+            lvl[k * (uint32_t)size + b] = lo[k];
+            lvl[k * (uint32_t)size + b + half] = hi[k];
+          } else if (fold) {
+            gst(dst[k], b, lo[k]);
+            gst(dst[k], b + half, hi[k]);
+          }
         }
         acc[0] = gl_add(acc[0], gl_form<NT>(lo));
         uint64_t t2[NT];
@@ -1032,8 +1046,11 @@ __global__ void __launch_bounds__(kBlock) k_gl_tail(Step st) {
         acc[1] = gl_add(acc[1], gl_form<NT>(t2));
       }
     }
-    in_lds = true;
-    const uint32_t nw = half >= kBlock ? kBlock / 64 : (half + 63) / 64;  // waves with pairs
+    in_lds = to_lds;
+    if (!to_lds && fold)
+#pragma unroll
+      for (int k = 0; k < NT; ++k) src[k] = dst[k];
+    const uint32_t nw = half >= kGlTailThreads ? kGlTailThreads / 64 : (half + 63) / 64;  // waves with pairs
     if (wid < nw) {
       acc[0] = gl_wave_sum63(acc[0]);
       acc[1] = gl_wave_sum63(acc[1]);
@@ -1043,7 +1060,7 @@ __global__ void __launch_bounds__(kBlock) k_gl_tail(Step st) {
       }
     }
     __syncthreads();
-    if (wid != 3) {
+    if (wid < 3) {
       uint64_t e0 = red[0][0], e2 = red[1][0];
       for (uint32_t w = 1; w < nw; ++w) {
         e0 = gl_add(e0, red[0][w]);
@@ -1111,13 +1128,16 @@ __global__ void __launch_bounds__(kBlock) k_gl_tail(Step st) {
 #undef GTID
 #undef GSTRIDE
 
-// Largest table (log2 of its entries) a tail evaluates: its levels fit the 64
-// KiB of shared memory a kernel has without asking for more.
-constexpr uint32_t kGlTailMaxLog = 10;
-
-static size_t gl_tail_lds(const Step& st, size_t nt) {
-  return 8 * nt * (st.p[2 * nt] ? st.q[0] / 2 : st.q[0]);  // p[2 NT]: the pending challenge
+static size_t gl_tail_lds(const Step& st, int nt) {
+  const uint64_t eval = st.p[2 * nt] ? st.q[0] / 2 : st.q[0];  // p[2 NT]: the pending challenge
+  return 8 * nt * std::min<uint64_t>(eval, 1ull << gl_tail_lds_log(nt));
 }
+
+// Largest table (log2 of its entries) a tail evaluates: three steps above the
+// tuned limit of the BN254 tails, whose products cost ten times as much, at most
+// 2^12 (c2 shape: 6595 us per proof at 2^10, 6545 at 2^11, 6510 at 2^12, 6768 at
+// 2^13 for three tables).
+static uint32_t gl_tail_log(const Tuning& tun) { return std::min<uint32_t>(tun.tail_log + 3, 12); }
 
 void launch_gl_step(const Step& st, hipStream_t s) {
   const int tok = prof_begin(s);
@@ -1133,9 +1153,9 @@ void launch_gl_step(const Step& st, hipStream_t s) {
     case ST_GL_WSUM: k_gl_wsum<<<grid, block, 0, s>>>(st); cls = PC_CLAIM; break;
     case ST_GL_P1: k_gl_p1<<<grid, block, 0, s>>>(st); cls = PC_PHASE1_INIT; break;
     case ST_GL_ROUND: k_gl_round<3><<<grid, block, 0, s>>>(st); cls = PC_ROUND_A; break;
-    case ST_GL_TAIL: k_gl_tail<3><<<grid, block, gl_tail_lds(st, 3), s>>>(st); cls = PC_TAIL_A; break;
+    case ST_GL_TAIL: k_gl_tail<3><<<grid, dim3(kGlTailThreads), gl_tail_lds(st, 3), s>>>(st); cls = PC_TAIL_A; break;
     case ST_GL_ROUND5: k_gl_round<5><<<grid, block, 0, s>>>(st); cls = PC_ROUND_B; break;
-    case ST_GL_TAIL5: k_gl_tail<5><<<grid, block, gl_tail_lds(st, 5), s>>>(st); cls = PC_TAIL_B; break;
+    case ST_GL_TAIL5: k_gl_tail<5><<<grid, dim3(kGlTailThreads), gl_tail_lds(st, 5), s>>>(st); cls = PC_TAIL_B; break;
     case ST_GL_COPY_WEIGHTS: k_gl_copy_weights<<<grid, block, 0, s>>>(st); cls = PC_SMALL; break;
     case ST_GL_P2T: k_gl_p2t<<<grid, block, 0, s>>>(st); cls = PC_PHASE2_TABLES; break;
     case ST_GL_COPY_CONTRACT: k_gl_copy_contract<<<grid, block, 0, s>>>(st); cls = PC_COPY_CONTRACT; break;
@@ -1239,7 +1259,7 @@ void gl_phase(std::vector<Step>& steps, const uint64_t* const* src0, uint64_t* c
   uint64_t eval = 1ull << nrounds;
   uint32_t j = 0;
   const uint64_t* pending = nullptr;
-  while (j < nrounds && eval > (1ull << std::min(tun.tail_log, kGlTailMaxLog))) {
+  while (j < nrounds && eval > (1ull << gl_tail_log(tun))) {
     const uint64_t half = eval / 2;
     Step st = gl_mk(NT == 3 ? ST_GL_ROUND : ST_GL_ROUND5, gl_tiles((half + 1) / 2, tun.max_round_blocks));
     for (int k = 0; k < NT; ++k) {
