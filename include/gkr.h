@@ -309,7 +309,7 @@ int32_t gkr_prove_layer(const gkr_circuit* circuit, uint32_t layer, const gkr_fr
                         size_t ws_bytes, void* stream);
 
 /*
- * Batched proving (many proofs at once in one persistent kernel). The paper
+ * Batched proving (many proofs at once). The paper
  * runs one prover per worker; batching many proofs in one launch is this
  * library's own (no passage defines it).
  *
@@ -317,9 +317,10 @@ int32_t gkr_prove_layer(const gkr_circuit* circuit, uint32_t layer, const gkr_fr
  * (the buffers gkr_prove_circuit takes). gkr_plan_create records the job's
  * proof as a step program in device memory (allocates and copies: call it
  * outside any timed or captured region). gkr_run_batch then runs 1..64 plans
- * together: resident workgroups take tiles of whichever plan has work, so the
- * serial Fiat-Shamir steps of one proof overlap the table sweeps of the
- * others. A run allocates nothing and copies nothing between host and device
+ * together: on the whole device without a limit in lockstep, a launch per step of
+ * all plans; otherwise in one persistent launch, whose resident workgroups take
+ * tiles of whichever plan has work. Either way the serial Fiat-Shamir steps of
+ * one proof overlap the table sweeps of the others. A run allocates nothing and copies nothing between host and device
  * (graph-capturable). Each plan's proof bytes are identical to its
  * gkr_prove_circuit bytes. Buffers of different jobs must not overlap.
  */
@@ -342,20 +343,22 @@ void gkr_plan_destroy(gkr_plan* plan);
 /* Queue a reset of the plan's progress so its next run proves from the start. */
 int32_t gkr_plan_reset(gkr_plan* plan, void* stream);
 /*
- * Queue one persistent launch over `n` (1..64) distinct plans. d_ctl: 4 device
- * words owned by this call until the stream reaches its end ([0] plans
- * finished in this launch, [1] stop flag, [2] steps completed). workgroups:
- * resident workgroups (0 = fill the device). step_budget > 0 stops the launch
+ * Queue one run over `n` (1..64) distinct plans. d_ctl: 4 device words owned by
+ * this call until the stream reaches its end ([0] plans finished in this run,
+ * [1] stop flag, [2] steps completed). workgroups: resident workgroups of the
+ * persistent launch (0 = the whole device). step_budget > 0 stops the run
  * after about that many completed steps; stop_on_finish stops it when any plan
- * finishes. A stopped launch leaves every plan resumable: run it again to
- * continue. Plans already finished are skipped.
+ * finishes. A stopped run leaves every plan resumable: run it again to
+ * continue. Plans already finished are skipped. With workgroups,
+ * step_budget and stop_on_finish all 0, plans that have not begun run in
+ * lockstep launches; plans begun before go on in the persistent launch after them.
  */
 int32_t gkr_run_batch(gkr_plan* const* plans, uint32_t n, uint32_t* d_ctl, uint32_t workgroups,
                       uint32_t step_budget, uint32_t stop_on_finish, void* stream);
 /* Steps completed so far and the plan's step count (synchronous device read). */
 int32_t gkr_plan_progress(const gkr_plan* plan, uint32_t* done_steps, uint32_t* total_steps);
 /*
- * Convenience: plans for `n` jobs, persistent runs of up to 64 plans each on
+ * Convenience: plans for `n` jobs, runs of up to 64 plans each on
  * `stream`, then a synchronisation and cleanup. Allocates; synchronous.
  */
 int32_t gkr_prove_batch(const gkr_job* jobs, uint32_t n, void* stream);

@@ -16,7 +16,7 @@ LIB = os.path.join(HERE, "libgkr.so")
 SOURCES = ["gkr_batch_kernel.hip", "gkr_kernels.hip", "gkr_api.hip", "gkr_tuning.cpp", "gkr_verify.cpp",
            "gkr_profile.cpp", "gkr_batch.hip", "gkr_ubench.hip", "gkr_noalloc.hip", "gkr_general.hip", "gkr_gl.hip",
            "gkr_vpd.hip", "gkr_contract.hip", "gkr_split.hip",
-           "gkr_wide.hip"]
+           "gkr_wide.hip", "gkr_lock.hip"]
 # Test helpers: the device checkers (field code, wave-wide routines) the GPU tests load.
 ROOT = os.path.dirname(HERE)
 CHECKERS = [(os.path.join(ROOT, "tests", "native", src), os.path.join(ROOT, "tests", "native", lib))

@@ -390,7 +390,7 @@ void Program::round(const Fr* const* src, Fr* const* dst, uint64_t half, const F
   }
   st.p[R::kR] = rprev; st.p[R::kS] = S; st.p[R::kPart] = partials; st.p[R::kROut] = r_out; st.p[R::kMsg] = msg;
   st.q[0] = half;
-  if (plain && half <= (1ull << kWideMaxLogHalf)) {
+  if (wide() && half <= (1ull << (mode == kPlain ? kWideMaxLogHalf : kLockWideMaxLogHalf))) {
     st.type = NT == 3 ? ST_W_ROUND_A : ST_W_ROUND_B;
     st.ntiles = (uint32_t)((half + kWidePairs - 1) / kWidePairs);
   }
@@ -509,7 +509,9 @@ static void emit_phase(Program& pg, const Fr* const* src0, Fr* const* dst, uint3
   uint64_t eval = 1ull << (nrounds - first_round);
   uint32_t j = first_round;
   const Fr* pending = first_round ? r_out + first_round - 1 : nullptr;
-  const uint32_t tail_log = pg.plain ? std::min(tun.tail_log, kTailMaxLog) : tun.tail_log;
+  const uint32_t tail_log = pg.mode == Program::kPlain      ? std::min(tun.tail_log, kTailMaxLog)
+                            : pg.mode == Program::kLockstep ? std::min(tun.tail_log, kLockTailLog)
+                                                            : tun.tail_log;
   while (j < nrounds && eval > (1ull << tail_log)) {
     pg.round<NT>(src, dst, eval / 2, pending, S, partials, r_out + j, msg + 24 * j, tun);
     if (pending) {
@@ -547,10 +549,10 @@ void emit_layer(Program& pg, const gkr_circuit& c, uint32_t i, const Workspace& 
   Fr* ta_dst[3] = {w.Wf, w.G, w.H};
   const uint32_t off_vx = 24 * s1, off_p2 = off_vx + 8, off_vy = off_p2 + 24 * s1;
   // (the contracted form uses kernels that only the plain launcher has)
-  const bool split = pg.plain && tun.matrix_cores && split_applies(n, sg1);
+  const bool split = pg.plain() && tun.matrix_cores && split_applies(n, sg1);
   if (split) {
     emit_phase1_split(pg, w, c.wiring[i], W, n, sg1, 1ull << sg, c.mul_gates[i], rx, proof, tun);
-  } else if (pg.plain && s1 > 1 && s1 - 1 <= kWideMaxLogHalf &&
+  } else if (pg.wide() && s1 > 1 && s1 - 1 <= kWideMaxLogHalf &&
              (1ull << c.s(i)) <= (uint64_t)c.plan.ychunks << n) {
     // a product chain per gate, its result in wpart, then the sums and round 1
     pg.p1_wide(W, w.G, w.H, c.wiring[i], w.aU, w.bV, w.Cu, w.Cv, w.wpart, n, 1ull << (s1 - 1), 1ull << c.s(i), S,
@@ -576,8 +578,11 @@ void emit_layer(Program& pg, const gkr_circuit& c, uint32_t i, const Workspace& 
   pg.copy_weights(w.Cu, w.Cv, w.EC, w.U, w.V, 1ull << n, S);
   if (split) emit_p2_final(pg, w, 1ull << sg1);
   else pg.p2_tables(c.wiring[i], w.aU, w.bV, w.EL, S, w.Fa, w.Fb, w.Ka, w.Kb, w.Ks, 1ull << sg1, 1ull << sg);
-  if (pg.plain && tun.matrix_cores && w.cc && cc_applies(n, sg1)) emit_contract_mfma(pg, W, w.U, w.V, w.P, w.Q, n, sg1, false, w.cc);
-  else pg.copy_contract(W, w.U, w.V, w.P, w.Q, n, 1ull << sg1);
+  if (pg.plain() && tun.matrix_cores && w.cc && cc_applies(n, sg1)) emit_contract_mfma(pg, W, w.U, w.V, w.P, w.Q, n, sg1, false, w.cc);
+  else {
+    pg.copy_contract(W, w.U, w.V, w.P, w.Q, n, 1ull << sg1);
+    pg.steps.back().join = 1;  // independent of the phase-2 tables
+  }
   Fr* tb[5] = {w.P, w.Fa, w.Q, w.Fb, w.Ks};
   const Fr* tb_src[5] = {w.P, w.Fa, w.Q, w.Fb, w.Ks};
   emit_phase<5>(pg, tb_src, tb, sg1, S, w.partials, ry, proof + off_p2, &S->scratch[1], nullptr, tun);
@@ -590,6 +595,7 @@ void emit_layer(Program& pg, const gkr_circuit& c, uint32_t i, const Workspace& 
   }
   pg.local_values(w.EqR, w.Ka, w.Kb, 1ull << sg1, S, w.partials);
   pg.local_contract(W, w.EqR, w.wpart, n, 1ull << sg1, c.plan.ychunks);
+  pg.steps.back().join = 1;  // independent of the local values
   pg.copy_tables(w.wpart, c.plan.ychunks, w.U, w.V, w.Fa, w.Fb, S, w.Wc, w.Fc, w.Kc, 1ull << n);
   Fr* tc[3] = {w.Wc, w.Fc, w.Kc};
   const Fr* tc_src[3] = {w.Wc, w.Fc, w.Kc};

@@ -1,5 +1,5 @@
-// Batched proving: plans (a proof's step program recorded in device memory)
-// and the persistent kernel that runs many plans at once.
+// Batched proving: plans (a proof's step programs recorded in device memory) and
+// their runs, in lockstep launches or by the persistent kernel.
 //
 // A plan is built once per job (allocating, synchronous). Running plans is
 // asynchronous, allocates nothing and copies nothing between host and device:
@@ -10,6 +10,7 @@
 #include <string.h>
 
 #include <algorithm>
+#include <memory>
 #include <new>
 #include <string>
 #include <vector>
@@ -21,10 +22,15 @@
 struct gkr_plan {
   gkr_job job;
   uint32_t nsteps = 0;
-  void* dev = nullptr;  // steps, then counters
+  void* dev = nullptr;  // steps, lockstep steps, then counters
   gkr::Step* steps = nullptr;
-  uint32_t* ctr = nullptr;
+  uint32_t* ctr = nullptr;  // [0] current step, claimed and done tiles per step, then the lockstep flag
   size_t ctr_words = 0;
+  // The lockstep program: its steps in device memory, and per stage (steps that
+  // run together) the first step; per step the workgroups.
+  gkr::Step* lock_steps = nullptr;
+  std::vector<uint32_t> stage_first, lock_tiles;
+  uint32_t* flag() const { return ctr + ctr_words - 1; }
 };
 
 namespace gkr {
@@ -32,6 +38,35 @@ static bool aligned16b(const void* p) { return (reinterpret_cast<uintptr_t>(p) &
 }  // namespace gkr
 
 using namespace gkr;
+
+// The lockstep run of the plans in a that have not begun: a launch decides which
+// they are, then one launch per stage, then one that marks them finished.
+static void run_lockstep(gkr_plan* const* plans, uint32_t n, const BatchArgs& a, hipStream_t s) {
+  uint32_t* flags[kMaxBatchJobs];
+  size_t stages = 0;
+  for (uint32_t i = 0; i < n; ++i) {
+    flags[i] = plans[i]->flag();
+    stages = std::max(stages, plans[i]->stage_first.size() - 1);
+  }
+  launch_lock_begin(a, flags, s);
+  LockArgs la;
+  for (size_t k = 0; k < stages; ++k) {
+    la.n = 0;
+    uint32_t tiles = 0;
+    for (uint32_t i = 0; i < n; ++i) {
+      const gkr_plan& p = *plans[i];
+      if (k + 1 >= p.stage_first.size()) continue;
+      for (uint32_t t = p.stage_first[k]; t < p.stage_first[k + 1]; ++t) {
+        tiles += p.lock_tiles[t];
+        la.end[la.n] = tiles;
+        la.step[la.n] = p.lock_steps + t;
+        la.flag[la.n++] = flags[i];
+      }
+    }
+    launch_lock_stage(la, tiles, s);
+  }
+  launch_lock_end(a, flags, s);
+}
 
 extern "C" {
 
@@ -60,32 +95,41 @@ int32_t gkr_plan_create(const gkr_job* job, gkr_plan** out) {
   try {
     Workspace w = bind_workspace(*c, job->d_ws);
     Program pg;
-    pg.plain = false;
+    pg.mode = Program::kPersistent;
     emit_prove_circuit(pg, *c, w, job->d_inputs, job->seed, job->d_outputs, job->d_proof, current_tuning());
-    gkr_plan* p = new gkr_plan();
+    std::unique_ptr<gkr_plan> p(new gkr_plan());
     p->job = *job;
     p->nsteps = (uint32_t)pg.steps.size();
-    p->ctr_words = 1 + 2ull * p->nsteps;
+    p->ctr_words = 2 + 2ull * p->nsteps;
+    Program lk;
+    lk.mode = Program::kLockstep;
+    emit_prove_circuit(lk, *c, w, job->d_inputs, job->seed, job->d_outputs, job->d_proof, current_tuning());
+    for (size_t k = 0; k < lk.steps.size(); ++k) {
+      if (!lk.steps[k].join) p->stage_first.push_back((uint32_t)k);
+      p->lock_tiles.push_back(lk.steps[k].ntiles);
+    }
+    p->stage_first.push_back((uint32_t)lk.steps.size());
+    const size_t lock_bytes = sizeof(Step) * lk.steps.size();
     const size_t step_bytes = sizeof(Step) * pg.steps.size();
-    const size_t total = step_bytes + 4 * p->ctr_words;
+    const size_t total = step_bytes + lock_bytes + 4 * p->ctr_words;
     if (hipMalloc(&p->dev, total) != hipSuccess) {
       (void)hipGetLastError();
-      delete p;
       set_error("device allocation of the plan failed");
       return GKR_ENOMEM;
     }
     p->steps = static_cast<Step*>(p->dev);
-    p->ctr = reinterpret_cast<uint32_t*>(static_cast<char*>(p->dev) + step_bytes);
+    p->lock_steps = reinterpret_cast<Step*>(static_cast<char*>(p->dev) + step_bytes);
+    p->ctr = reinterpret_cast<uint32_t*>(static_cast<char*>(p->dev) + step_bytes + lock_bytes);
     std::vector<uint32_t> zeros(p->ctr_words, 0);
-    if (hipMemcpy(p->steps, pg.steps.data(), step_bytes, hipMemcpyHostToDevice) != hipSuccess ||
+    pg.steps.insert(pg.steps.end(), lk.steps.begin(), lk.steps.end());
+    if (hipMemcpy(p->steps, pg.steps.data(), step_bytes + lock_bytes, hipMemcpyHostToDevice) != hipSuccess ||
         hipMemcpy(p->ctr, zeros.data(), 4 * p->ctr_words, hipMemcpyHostToDevice) != hipSuccess) {
       (void)hipGetLastError();
       hipFree(p->dev);
-      delete p;
       set_error("upload of the plan failed");
       return GKR_EDEVICE;
     }
-    *out = p;
+    *out = p.release();
     return GKR_OK;
   } catch (const std::bad_alloc&) {
     set_error("host allocation failed");
@@ -139,6 +183,12 @@ int32_t gkr_run_batch(gkr_plan* const* plans, uint32_t n, uint32_t* d_ctl, uint3
   a.step_budget = step_budget;
   a.stop_on_finish = stop_on_finish ? 1 : 0;
   a.ctl = d_ctl;
+  // A run to the end on the whole device takes the plans that have not begun in
+  // lockstep: stage k of every one of them in launch k. The persistent kernel then
+  // finds those finished, and carries on those that an earlier run with a limit
+  // began. A count of workgroups is a limit on the share of the device, which the
+  // lockstep launches do not keep: with one the persistent kernel runs alone.
+  const bool lockstep = workgroups == 0 && step_budget == 0 && !stop_on_finish;
   if (workgroups == 0) {
     int dev = 0, cus = 0;
     hipGetDevice(&dev);
@@ -147,9 +197,13 @@ int32_t gkr_run_batch(gkr_plan* const* plans, uint32_t n, uint32_t* d_ctl, uint3
       cus = 256;
     }
     workgroups = (uint32_t)cus * batch_kernel_max_workgroups_per_cu();
+    // plans begun before: three workgroups per four CUs do best (64 uneven proofs 165
+    // ms, against 212 ms with two per CU, which contend for the step counters)
+    if (lockstep) workgroups = std::max(1u, (uint32_t)cus * 3 / 4);
   }
   hipStream_t s = static_cast<hipStream_t>(stream);
   launch_fill_u32(d_ctl, 4, 0u, s);
+  if (lockstep) run_lockstep(plans, n, a, s);
   launch_batch(a, workgroups, s);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) {

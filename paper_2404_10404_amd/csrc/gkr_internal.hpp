@@ -17,6 +17,12 @@ namespace gkr {
 constexpr int kBlock = 256;             // threads per workgroup (grid-wide kernels, batch kernel)
 constexpr int kTailBlock = 512;         // threads of the single-workgroup tail kernels
 constexpr uint32_t kMaxRoundBlocks = 4096;  // cap on workgroups of a reduction launch
+// Lockstep batches. A stage takes as long as its longest step, so tails are short:
+// 64 uneven proofs took 78.1 ms with tails of at most 2^2 entries, 79.4 with 2^3,
+// 80.4 with 2^5. The other proofs fill the chip, so a round is wide (a product per
+// thread) only while its table is small: at most 2^9 pairs 79.4 ms, 2^13 85.2, 2^5 79.2.
+constexpr uint32_t kLockTailLog = 2;         // largest table (log2) of a tail
+constexpr uint32_t kLockWideMaxLogHalf = 9;  // most pairs (log2) of a wide round
 constexpr uint32_t kTailMaxLog = 7;       // largest table (log2) a pipelined tail evaluates
 constexpr int kMaxPartialValues = 2;    // reduced values per workgroup
 constexpr uint32_t kChunkWords = 256;   // 1 KiB SHA-256 leaf chunk of a tree digest
@@ -167,8 +173,9 @@ enum StepType : uint32_t {
 };
 
 struct Step {
-  uint32_t type;
-  uint32_t ntiles;   // workgroups
+  uint32_t type : 16;
+  uint32_t join : 16;  // 1: independent of the step before it (a lockstep batch runs both together)
+  uint32_t ntiles;     // workgroups
   uint32_t u[6];     // small integers
   uint64_t q[4];     // sizes
   const void* p[16]; // device pointers

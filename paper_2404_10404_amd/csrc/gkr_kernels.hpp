@@ -53,6 +53,19 @@ struct BatchArgs {
   uint32_t* ctl;            // [0] jobs finished, [1] stop, [2] steps completed, [3] spare
 };
 
+// One launch of a lockstep batch: up to two steps per job, workgroup b running
+// tile b - end[i - 1] of the first step i with b < end[i], for jobs whose flag is set.
+constexpr uint32_t kMaxLockSteps = 2 * kMaxBatchJobs;
+struct LockArgs {
+  uint32_t end[kMaxLockSteps];
+  const Step* step[kMaxLockSteps];
+  const uint32_t* flag[kMaxLockSteps];
+  uint32_t n;
+};
+
+void launch_lock_begin(const BatchArgs& a, uint32_t* const* flags, hipStream_t s);
+void launch_lock_stage(const LockArgs& a, uint32_t tiles, hipStream_t s);
+void launch_lock_end(const BatchArgs& a, uint32_t* const* flags, hipStream_t s);
 void launch_batch(const BatchArgs& a, uint32_t workgroups, hipStream_t s);
 void launch_fill_u32(uint32_t* p, uint64_t n, uint32_t v, hipStream_t s);
 uint32_t batch_kernel_max_workgroups_per_cu();

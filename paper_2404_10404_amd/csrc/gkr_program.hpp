@@ -31,10 +31,14 @@ void emit_digests(std::vector<Step>& steps, uint32_t thread_type, const DigestJo
 
 struct Program {
   std::vector<Step> steps;
-  // Steps that only the plain launcher runs (the matrix-core contractions, the
-  // contracted phase 1, the wide rounds) are allowed; the batch kernel's
-  // programs switch this off.
-  bool plain = true;
+  // Who runs the program: the plain launcher (a kernel per step, every step
+  // type), the lockstep kernel of a batch (256-thread workgroups; no matrix-core
+  // contraction, contracted phase 1 or pipelined tail) or the persistent batch
+  // kernel (no wide rounds either).
+  enum Mode { kPlain, kLockstep, kPersistent };
+  Mode mode = kPlain;
+  bool plain() const { return mode == kPlain; }
+  bool wide() const { return mode != kPersistent; }
 
   void to_mont(const gkr_fr* in, Fr* out, uint64_t n);
   void from_mont(const Fr* in, gkr_fr* out, uint64_t n);

@@ -536,9 +536,10 @@ class Plan:
 
 def run_batch(plans: Sequence[Plan], d_ctl, workgroups: int = -1, step_budget: int = 0,
               stop_on_finish: bool = False, stream=None):
-    """gkr_run_batch; workgroups=-1 uses the autotuned count (0 = fill the device)."""
+    """gkr_run_batch; workgroups=-1: the whole device (0) for a run to the end,
+    the autotuned count of the persistent kernel for one with a limit."""
     if workgroups < 0:
-        workgroups = tuned_batch_workgroups()
+        workgroups = tuned_batch_workgroups() if step_budget or stop_on_finish else 0
     arr = (_vp * len(plans))(*[p.handle.value for p in plans])
     _check(_batch_lib().gkr_run_batch(arr, len(plans), _ptr(d_ctl), workgroups, step_budget,
                                       1 if stop_on_finish else 0, _stream(stream)))
