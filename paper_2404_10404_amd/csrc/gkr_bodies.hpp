@@ -16,10 +16,9 @@
 // steps to resident workgroups.
 //
 // Reductions over a whole table (the round polynomials of the sumcheck) end in
-// the last tile to finish: each tile writes its partial sums and publishes
-// them with a device-scope release increment of an atomic counter; the tile
-// that brings the counter to ntiles acquires, adds the partials and runs the
-// round's Fiat-Shamir step: its first wave hashes the sums and takes the
+// the last tile to finish: each tile stores its partial sums past its L2 and
+// counts itself on an atomic counter; the tile that brings the counter to
+// ntiles adds the partials and runs the round's Fiat-Shamir step: its first wave hashes the sums and takes the
 // challenge, its second wave moves the claim through the previous round
 // (the products by r stay off the chain of hashes).
 // Challenges and claims never leave device memory, so a proof is a plain
@@ -571,7 +570,7 @@ __device__ __forceinline__ void finish_reduced_round(const Fr* partials, uint32_
     const uint32_t busy = (ntiles + 31) / 32 < nw ? (ntiles + 31) / 32 : nw;  // waves with partials
     if (wid < busy) {
       Fr v = fr_zero();
-      for (uint32_t i = wid * 32 + (lane & 31); i < ntiles; i += nw * 32) v = fr_add(v, ldf(partials, 2ull * i + pt));
+      for (uint32_t i = wid * 32 + (lane & 31); i < ntiles; i += nw * 32) v = fr_add(v, get_partial(partials, 2ull * i + pt));
       v = half_wave_sum(v);
       if ((lane & 31) == 31) red[wid][pt] = v;
     }

@@ -275,8 +275,6 @@ __global__ void __launch_bounds__(kBlock) k_gl_eq(Step st) {
   }
 }
 
-// Publishes this tile's partials and counts it; true in every thread of the last tile.
-__device__ __forceinline__ bool gl_last_tile(uint32_t* counter, uint32_t ntiles) { return last_tile(counter, ntiles); }
 
 // ST_GL_WSUM: sum_e V[e] A[e >> n] B[e & mask] into *p5.
 // p0 V, p1 A, p2 B, p3 partials, p4 S, p5 dst, u0 n, q0 count.
@@ -292,10 +290,10 @@ __global__ void __launch_bounds__(kBlock) k_gl_wsum(Step st) {
   for (uint64_t e = GTID; e < st.q[0]; e += GSTRIDE)
     acc[0] = gl_add(acc[0], gl_mul(gl_mul(gld(V, e), gld(A, e >> n)), gld(B, e & mask)));
   gl_block_sum<1>(acc);
-  if (threadIdx.x == 0) partials[blockIdx.x] = acc[0];
-  if (gl_last_tile(&S->counter, gridDim.x)) {
+  if (threadIdx.x == 0) put_word(partials + blockIdx.x, acc[0]);
+  if (last_tile(&S->counter, gridDim.x)) {
     uint64_t tot[1] = {0};
-    for (uint32_t b = threadIdx.x; b < gridDim.x; b += blockDim.x) tot[0] = gl_add(tot[0], partials[b]);
+    for (uint32_t b = threadIdx.x; b < gridDim.x; b += blockDim.x) tot[0] = gl_add(tot[0], get_word(partials + b));
     gl_block_sum<1>(tot);
     if (threadIdx.x == 0) *P<uint64_t*>(st, 5) = tot[0];
   }
@@ -632,14 +630,14 @@ __device__ __forceinline__ void gl_finish_round(uint64_t (&acc)[2], GlState* S, 
                                                 uint64_t* msg) {
   gl_block_sum<2>(acc);
   if (threadIdx.x == 0) {
-    partials[2 * blockIdx.x] = acc[0];
-    partials[2 * blockIdx.x + 1] = acc[1];
+    put_word(partials + 2 * blockIdx.x, acc[0]);
+    put_word(partials + 2 * blockIdx.x + 1, acc[1]);
   }
-  if (gl_last_tile(&S->counter, gridDim.x)) {
+  if (last_tile(&S->counter, gridDim.x)) {
     uint64_t tot[2] = {0, 0};
     for (uint32_t b = threadIdx.x; b < gridDim.x; b += blockDim.x) {
-      tot[0] = gl_add(tot[0], partials[2 * b]);
-      tot[1] = gl_add(tot[1], partials[2 * b + 1]);
+      tot[0] = gl_add(tot[0], get_word(partials + 2 * b));
+      tot[1] = gl_add(tot[1], get_word(partials + 2 * b + 1));
     }
     gl_block_sum<2>(tot);
     gl_round_step(S, tot[0], tot[1], r_out, msg);

@@ -29,7 +29,7 @@ __device__ __forceinline__ void wide_finish(const Fr (*ent)[2 * kWidePairs], Fr*
     Fr t = fr_mul(x, y);
     if (NT == 3 || wid == 1) t = fr_add(t, at(NT - 1));
     t = half_wave_sum(t);
-    if (p == 31) stf(partials, ((uint64_t)tile * kEval + wid) * 2 + (lane >> 5), t);
+    if (p == 31) put_partial(partials, ((uint64_t)tile * kEval + wid) * 2 + (lane >> 5), t);
     wait_vmem();
   }
   if (last_tile(&S->counter, ntiles)) finish_reduced_round<false>(partials, ntiles * kEval, S, r_out, msg);
