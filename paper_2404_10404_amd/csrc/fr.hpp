@@ -165,8 +165,10 @@ __device__ __forceinline__ void fr_mac_vs(uint64_t& acc, uint32_t& ov, uint32_t 
 
 // Montgomery product on the device: finely integrated product scanning (FIPS,
 // Koc-Acar-Kaliski 1996). Column k of a*b and of m*p is summed into a 96-bit
-// accumulator; m_k is chosen so the low word of column k vanishes.
-__device__ __forceinline__ Fr fr_mul_device(const Fr& a, const Fr& b) {
+// accumulator; m_k is chosen so the low word of column k vanishes. The result is
+// congruent to a*b/R and, since a*b/R + p bounds it, below 2p for a < 4p and
+// b < p (4p < 2^256 and 4p/R < 0.76).
+__device__ __forceinline__ Fr fr_mul_2p(const Fr& a, const Fr& b) {
   uint32_t m[8];
   Fr r;
   uint64_t acc = 0;
@@ -196,8 +198,10 @@ __device__ __forceinline__ Fr fr_mul_device(const Fr& a, const Fr& b) {
     ov = 0;
   }
   r.v[7] = (uint32_t)acc;
-  return fr_reduce_once(r);
+  return r;
 }
+__device__ __forceinline__ Fr fr_mul_device(const Fr& a, const Fr& b) { return fr_reduce_once(fr_mul_2p(a, b)); }
+
 #else
 // Host form of the column multiply-accumulate: (ov:acc) += x * y.
 GKR_HD void fr_mac_vv(uint64_t& acc, uint32_t& ov, uint32_t x, uint32_t y) {
@@ -407,6 +411,54 @@ GKR_HD Fr fr_mul(const Fr& a, const Fr& b) {
   return fr_reduce_once(r);
 #endif
 }
+
+// Sums and differences of values below 2p (butterflies that reduce fully only at
+// the end of a transform).
+GKR_HD uint32_t p2_limb(int k) { return p_limb(k) << 1 | (k ? p_limb(k - 1) >> 31 : 0u); }
+// a below 4p to below 2p.
+GKR_HD Fr fr_reduce_2p(const Fr& a) {
+  Fr t, r;
+  uint32_t br = 0;
+#pragma unroll
+  for (int k = 0; k < 8; ++k) t.v[k] = sbb32(a.v[k], p2_limb(k), br, br);
+#pragma unroll
+  for (int k = 0; k < 8; ++k) r.v[k] = br ? a.v[k] : t.v[k];
+  return r;
+}
+// a + b mod 2p, for a, b at most 2p and not both 2p.
+GKR_HD Fr fr_add_2p(const Fr& a, const Fr& b) {
+  Fr s;
+  uint32_t c = 0;
+#pragma unroll
+  for (int k = 0; k < 8; ++k) s.v[k] = adc32(a.v[k], b.v[k], c, c);
+  return fr_reduce_2p(s);
+}
+// a - b mod 2p.
+GKR_HD Fr fr_sub_2p(const Fr& a, const Fr& b) {
+  Fr d;
+  uint32_t br = 0;
+#pragma unroll
+  for (int k = 0; k < 8; ++k) d.v[k] = sbb32(a.v[k], b.v[k], br, br);
+  const uint32_t mask = 0u - br;
+  uint32_t c = 0;
+#pragma unroll
+  for (int k = 0; k < 8; ++k) d.v[k] = adc32(d.v[k], p2_limb(k) & mask, c, c);
+  return d;
+}
+// a - b + 2p, below 4p: a factor of fr_mul_2p.
+GKR_HD Fr fr_sub_4p(const Fr& a, const Fr& b) {
+  Fr d;
+  uint32_t c = 0;
+#pragma unroll
+  for (int k = 0; k < 8; ++k) d.v[k] = adc32(a.v[k], p2_limb(k), c, c);
+  uint32_t br = 0;
+#pragma unroll
+  for (int k = 0; k < 8; ++k) d.v[k] = sbb32(d.v[k], b.v[k], br, br);
+  return d;
+}
+#if !defined(__HIP_DEVICE_COMPILE__)
+GKR_HD Fr fr_mul_2p(const Fr& a, const Fr& b) { return fr_mul(fr_reduce_2p(a), b); }
+#endif
 
 GKR_HD Fr fr_sqr(const Fr& a) { return fr_mul(a, a); }
 GKR_HD Fr fr_to_mont(const Fr& a) { return fr_mul(a, fr_r2()); }

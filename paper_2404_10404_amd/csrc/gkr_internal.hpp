@@ -136,9 +136,7 @@ enum StepType : uint32_t {
   // launch_vpd_step, plain path only.
   ST_VPD_POWERS = 128,
   ST_VPD_TWIDDLES,
-  ST_VPD_SCALE,
   ST_VPD_NTT,
-  ST_VPD_MUL,
   ST_VPD_LEAVES,
   ST_VPD_NODES,
   ST_VPD_TREE_TOP,

@@ -235,68 +235,94 @@ __global__ void __launch_bounds__(kBlock) k_vpd_twiddles(Step st) {
   for (uint64_t t = GTID; t < st.q[0]; t += GSTRIDE) stf(T, t, pow2lvl(lo, hi, t));
 }
 
-// ST_VPD_SCALE: the coefficient vector of an NTT input, zero padded to q0 entries:
-//   u0 = 0: src[j]                          (j < N)
-//   u0 = 1: src[j + N]                      (j < N; h from p)
-//   u0 = 2: src[j + 1] + src[j + 1 + N]     (j < N - 1; g' from p)
-//   u0 = 3: w[(N - j) mod N], w[b] = EA[b >> n] EC[b & mask] + EB[b >> n] ED[b & mask]  (q)
-// times 5^j when u1 != 0. p0 src, p1 dst, p2 glo, p3 ghi, p4..p7 EA, EB, EC, ED, u2 n, q0 size, q1 N.
-__global__ void __launch_bounds__(kBlock) k_vpd_scale(Step st) {
-  const Fr* src = P<const Fr*>(st, 0);
-  Fr* dst = P<Fr*>(st, 1);
-  const Fr *glo = P<const Fr*>(st, 2), *ghi = P<const Fr*>(st, 3);
-  const uint32_t mode = st.u[0], n = st.u[2];
-  const uint64_t N = st.q[1], mask = (1ull << n) - 1;
-  for (uint64_t j = GTID; j < st.q[0]; j += GSTRIDE) {
-    Fr v = fr_zero();
-    if (j < N) {
-      if (mode == 0) {
-        v = ldf(src, j);
-      } else if (mode == 1) {
-        v = ldf(src, j + N);
-      } else if (mode == 2) {
-        if (j + 1 < N) v = fr_add(ldf(src, j + 1), ldf(src, j + 1 + N));
-      } else {
-        const uint64_t b = (N - j) & (N - 1);
-        v = fr_mul_add2(ldf(P<const Fr*>(st, 4), b >> n), ldf(P<const Fr*>(st, 6), b & mask),
-                        ldf(P<const Fr*>(st, 5), b >> n), ldf(P<const Fr*>(st, 7), b & mask));
-      }
-      if (st.u[1]) v = fr_mul(v, pow2lvl(glo, ghi, j));
-    }
-    stf(dst, j, v);
-  }
-}
-
 // ST_VPD_NTT: W radix-2 stages j0 .. j0+W-1 of an in-place transform of size
 // 2^L over p0, in one pass through LDS. A workgroup takes a tile of 2^W rows
 // (the index bits L-j0-W .. L-j0-1) by 2^c columns (consecutive low bits),
-// W + c <= 11. Forward (u5 = 0): decimation in frequency, natural order in,
+// W + c <= 10. Forward (u5 = 0): decimation in frequency, natural order in,
 // bit-reversed out; stage j maps (a, b) at distance 2^(L-1-j) to
 // (a + b, (a - b) w^k). Inverse (u5 = 1): the stages undone in reverse order,
-// (a, b) -> (a + b w^-k, a - b w^-k), then a scale by w[0..7] when u4 has
-// bit 8 set. Twiddles w^k = T[k << (j + tshift)] with T[t] = w_{2^(L+tshift)}^t;
-// w^-t = -T[n_T/2 - t]. Stages go two at a time: a thread holds the four
-// elements that two consecutive stages combine (rows r, r + h/2, r + h,
-// r + 3h/2), so a pair of stages costs one LDS round trip and one barrier;
-// an odd last stage is a plain radix-2 step.
-// p0 x, p1 T, u0 L, u1 j0, u2 W, u3 c, u4 tshift (| 256: scale), u5 inverse, q0 n_T / 2.
-constexpr int kNttTile = 2048;
-constexpr int kNttThreads = 512;
+// (a, b) -> (a + b w^-k, a - b w^-k), then a scale by w[0..7]. Twiddles
+// w^k = T[k << (j + tshift)] with T[t] = w_{2^(L+tshift)}^t; w^-t = -T[n_T/2 - t].
+// Stages go two at a time: a thread holds the four elements that two
+// consecutive stages combine (rows r, r + h/2, r + h, r + 3h/2), so a pair of
+// stages costs one LDS round trip and one barrier; an odd last stage is a plain
+// radix-2 step. Values stay below 2p between the stages and the passes of a
+// transform; its last pass (u4 bit 8) reduces them.
+// The first pass makes its own input (u4 bits 12..14, the form F):
+//   F = 1: src[j]                          (j < N)
+//   F = 2: src[j + N]                      (j < N; h from p)
+//   F = 3: src[j + 1] + src[j + 1 + N]     (j < N - 1; g' from p)
+//   F = 4: w[(N - j) mod N], w[b] = EA[b >> n] EC[b & mask] + EB[b >> n] ED[b & mask]  (q)
+// times 5^j with u4 bit 16, zero from N on; F = 5: x[j] src[j] (inverse).
+// p0 x, p1 T, p2 src, p3 glo, p4 ghi, p5..p8 EA, EB, EC, ED, u0 L, u1 j0, u2 W, u3 c,
+// u4 tshift | flags, u5 inverse, q0 n_T / 2, q1 N, q2 n.
+//
+// Bound by the products (half of one per element and stage, 134 G/s) and, where
+// they do not overlap, the tile's loads and stores. The tile is two planes of
+// 16-byte half elements with permuted slots, so 16 lanes of a stage at any
+// distance meet 16 different bank groups; whole 32-byte elements met 4 of 8 in the
+// stages of the smallest distances.
+constexpr uint32_t kNttLog = 10;
+constexpr uint32_t kNttTile = 1u << kNttLog;
+constexpr uint32_t kNttThreads = 256;
+constexpr uint32_t kNttLast = 256u, kNttFormShift = 12, kNttCoset = 1u << 16;
+enum NttForm : uint32_t { NF_NONE = 0, NF_COEFF, NF_UPPER, NF_SHIFTED, NF_EQ, NF_PRODUCT };
 
-// v w^(+-1) for twiddle index t (no product when t = 0).
-__device__ __forceinline__ Fr tw_mul(const Fr& v, const Fr* T, uint64_t t, uint64_t halfT, bool inverse) {
-  if (t == 0) return v;
-  return inverse ? fr_neg(fr_mul(v, ldf(T, halfT - t))) : fr_mul(v, ldf(T, t));
+// The slot of element i: of the index bits that vary over 16 consecutive lanes of a
+// stage (0..3, or 0..k with bits from k + 3 up to 5, or 2..5) the low four slot
+// bits are a bijective image.
+__device__ __forceinline__ uint32_t ntt_slot(uint32_t i) { return i ^ (((i >> 4) & 3u) * 5u); }
+
+struct NttLds {
+  U32x4 lo[kNttTile], hi[kNttTile];
+  __device__ __forceinline__ Fr get(uint32_t i) const {
+    const uint32_t k = ntt_slot(i);
+    const U32x4 a = lo[k], b = hi[k];
+    return fr_make(a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w);
+  }
+  __device__ __forceinline__ void put(uint32_t i, const Fr& x) {
+    const uint32_t k = ntt_slot(i);
+    lo[k] = U32x4{x.v[0], x.v[1], x.v[2], x.v[3]};
+    hi[k] = U32x4{x.v[4], x.v[5], x.v[6], x.v[7]};
+  }
+};
+
+// Entry j < N of a first pass's input.
+__device__ __forceinline__ Fr ntt_input(const Step& st, uint32_t form, uint64_t j) {
+  const Fr* src = P<const Fr*>(st, 2);
+  const uint64_t N = st.q[1];
+  const uint32_t n = (uint32_t)st.q[2];
+  Fr v = fr_zero();
+  if (form == NF_COEFF) {
+    v = ldf(src, j);
+  } else if (form == NF_UPPER) {
+    v = ldf(src, j + N);
+  } else if (form == NF_SHIFTED) {
+    if (j + 1 < N) v = fr_add(ldf(src, j + 1), ldf(src, j + 1 + N));
+  } else {
+    const uint64_t b = (N - j) & (N - 1), mask = (1ull << n) - 1;
+    v = fr_mul_add2(ldf(P<const Fr*>(st, 5), b >> n), ldf(P<const Fr*>(st, 7), b & mask),
+                    ldf(P<const Fr*>(st, 6), b >> n), ldf(P<const Fr*>(st, 8), b & mask));
+  }
+  if (st.u[4] & kNttCoset) v = fr_mul(v, pow2lvl(P<const Fr*>(st, 3), P<const Fr*>(st, 4), j));
+  return v;
 }
 
-__global__ void __launch_bounds__(kNttThreads) k_vpd_ntt(Step st) {
-  __shared__ Fr tile[kNttTile];
+// The table's factor for twiddle index t: w^t, or in an inverse -w^-t.
+template <bool Inverse>
+__device__ __forceinline__ Fr ntt_factor(const Fr* T, uint64_t t, uint64_t halfT) {
+  if (!Inverse) return ldf(T, t);
+  const Fr f = ldf(T, t ? halfT - t : 0);
+  return t ? f : fr_sub(fr_zero(), f);
+}
+
+template <bool Inverse>
+__global__ void __launch_bounds__(kNttThreads, 4) k_vpd_ntt(Step st) {
+  __shared__ NttLds tile;
   Fr* x = P<Fr*>(st, 0);
   const Fr* T = P<const Fr*>(st, 1);
   const uint32_t L = st.u[0], j0 = st.u[1], W = st.u[2], c = st.u[3];
-  const uint32_t tshift = st.u[4] & 255u;
-  const bool do_scale = (st.u[4] >> 8) & 1u;
-  const bool inverse = st.u[5] != 0;
+  const uint32_t tshift = st.u[4] & 255u, form = (st.u[4] >> kNttFormShift) & 7u;
   const uint64_t halfT = st.q[0];
   const uint32_t lo = L - j0 - W;
   const uint32_t C = 1u << c;
@@ -304,14 +330,25 @@ __global__ void __launch_bounds__(kNttThreads) k_vpd_ntt(Step st) {
   const uint64_t colgroup = blockIdx.x & ((1ull << (lo - c)) - 1);
   const uint64_t blk = blockIdx.x >> (lo - c);
   const uint64_t base = (blk << (L - j0)) + (colgroup << c);
-  for (uint32_t e = threadIdx.x; e < nelem; e += kNttThreads) {
-    const uint32_t r = e >> c, col = e & (C - 1);
-    tile[e] = ldf(x, base + ((uint64_t)r << lo) + col);
+  auto at = [&](uint32_t e) { return base + ((uint64_t)(e >> c) << lo) + (e & (C - 1)); };
+  // an input padded to four times its length: only the first of a pair of first
+  // stages' four rows is not zero
+  const bool pad4 = !Inverse && form && W >= 2 && st.q[1] << 2 == 1ull << L;
+  if (form == NF_NONE) {
+    for (uint32_t e = threadIdx.x; e < nelem; e += kNttThreads) tile.put(e, ldf(x, at(e)));
+  } else if (Inverse) {
+    const Fr* y = P<const Fr*>(st, 2);
+    for (uint32_t e = threadIdx.x; e < nelem; e += kNttThreads) tile.put(e, fr_mul(ldf(x, at(e)), ldf(y, at(e))));
+  } else {
+    for (uint32_t e = threadIdx.x; e < (pad4 ? nelem / 4 : nelem); e += kNttThreads) {
+      const uint64_t j = at(e);
+      tile.put(e, j < st.q[1] ? ntt_input(st, form, j) : fr_zero());
+    }
   }
   __syncthreads();
   const uint32_t npairs = W / 2, nops = npairs + (W & 1);
   for (uint32_t op = 0; op < nops; ++op) {
-    const uint32_t fo = inverse ? (nops - 1 - op) : op;  // position in the forward order
+    const uint32_t fo = Inverse ? (nops - 1 - op) : op;  // position in the forward order
     if (fo == npairs) {
       // the odd last stage (jj = W - 1, distance one row)
       const uint32_t j = j0 + W - 1;
@@ -319,14 +356,15 @@ __global__ void __launch_bounds__(kNttThreads) k_vpd_ntt(Step st) {
         const uint32_t col = bi & (C - 1), ra = (bi >> c) * 2;
         const uint64_t t = ((colgroup << c) + col) << (j + tshift);
         const uint32_t ia = (ra << c) + col, ib = ia + C;
-        const Fr a = tile[ia], b = tile[ib];
-        if (!inverse) {
-          tile[ia] = fr_add(a, b);
-          tile[ib] = tw_mul(fr_sub(a, b), T, t, halfT, false);
+        const Fr f = ntt_factor<Inverse>(T, t, halfT);
+        const Fr a = tile.get(ia), b = tile.get(ib);
+        if (!Inverse) {
+          tile.put(ia, fr_add_2p(a, b));
+          tile.put(ib, fr_mul_2p(fr_sub_4p(a, b), f));
         } else {
-          const Fr bw = tw_mul(b, T, t, halfT, true);
-          tile[ia] = fr_add(a, bw);
-          tile[ib] = fr_sub(a, bw);
+          const Fr bw = fr_mul_2p(b, f);
+          tile.put(ia, fr_sub_2p(a, bw));
+          tile.put(ib, fr_add_2p(a, bw));
         }
       }
     } else {
@@ -340,41 +378,66 @@ __global__ void __launch_bounds__(kNttThreads) k_vpd_ntt(Step st) {
         const uint32_t i2 = ((r0 + hr) << c) + col, i3 = ((r0 + hr + h2) << c) + col;
         const uint64_t ka = ((uint64_t)(gr & (h2 - 1)) << lo) + (colgroup << c) + col;
         const uint64_t kb = ka + ((uint64_t)h2 << lo);
-        const uint64_t ta = ka << (j + tshift), tb = kb << (j + tshift), tc = ka << (j + 1 + tshift);
-        const Fr x0 = tile[i0], x1 = tile[i1], x2 = tile[i2], x3 = tile[i3];
-        if (!inverse) {
-          const Fr a0 = fr_add(x0, x2), a2 = tw_mul(fr_sub(x0, x2), T, ta, halfT, false);
-          const Fr a1 = fr_add(x1, x3), a3 = tw_mul(fr_sub(x1, x3), T, tb, halfT, false);
-          tile[i0] = fr_add(a0, a1);
-          tile[i1] = tw_mul(fr_sub(a0, a1), T, tc, halfT, false);
-          tile[i2] = fr_add(a2, a3);
-          tile[i3] = tw_mul(fr_sub(a2, a3), T, tc, halfT, false);
+        // (k = 0 in a whole wave: the factors are 1, and only the quarter turn is left)
+        const bool turns = __ballot(ka != 0) != 0;
+        const Fr fa = ntt_factor<Inverse>(T, ka << (j + tshift), halfT);
+        const Fr fb = ntt_factor<Inverse>(T, kb << (j + tshift), halfT);
+        const Fr fc = ntt_factor<Inverse>(T, ka << (j + 1 + tshift), halfT);
+        const Fr x0 = tile.get(i0);
+        if (!Inverse) {
+          if (pad4 && fo == 0) {
+            tile.put(i0, x0);
+            tile.put(i1, fr_mul_2p(x0, fc));
+            const Fr a2 = fr_mul_2p(x0, fa);
+            tile.put(i2, a2);
+            tile.put(i3, fr_mul_2p(a2, fc));
+            continue;
+          }
+          const Fr x1 = tile.get(i1), x2 = tile.get(i2), x3 = tile.get(i3);
+          const Fr a0 = fr_add_2p(x0, x2), a1 = fr_add_2p(x1, x3);
+          tile.put(i0, fr_add_2p(a0, a1));
+          const Fr a3 = fr_mul_2p(fr_sub_4p(x1, x3), fb);
+          if (turns) {
+            tile.put(i1, fr_mul_2p(fr_sub_4p(a0, a1), fc));
+            const Fr a2 = fr_mul_2p(fr_sub_4p(x0, x2), fa);
+            tile.put(i2, fr_add_2p(a2, a3));
+            tile.put(i3, fr_mul_2p(fr_sub_4p(a2, a3), fc));
+          } else {
+            tile.put(i1, fr_sub_2p(a0, a1));
+            const Fr a2 = fr_sub_2p(x0, x2);
+            tile.put(i2, fr_add_2p(a2, a3));
+            tile.put(i3, fr_sub_2p(a2, a3));
+          }
         } else {
-          const Fr t1 = tw_mul(x1, T, tc, halfT, true), t3 = tw_mul(x3, T, tc, halfT, true);
-          const Fr b0 = fr_add(x0, t1), b1 = fr_sub(x0, t1), b2 = fr_add(x2, t3), b3 = fr_sub(x2, t3);
-          const Fr u2 = tw_mul(b2, T, ta, halfT, true), u3 = tw_mul(b3, T, tb, halfT, true);
-          tile[i0] = fr_add(b0, u2);
-          tile[i1] = fr_add(b1, u3);
-          tile[i2] = fr_sub(b0, u2);
-          tile[i3] = fr_sub(b1, u3);
+          // t = -(x w^-k), added and subtracted the other way round
+          const Fr x1 = tile.get(i1), x2 = tile.get(i2), x3 = tile.get(i3);
+          Fr b0, b1, b2, b3, u2;
+          if (turns) {
+            const Fr t1 = fr_mul_2p(x1, fc), t3 = fr_mul_2p(x3, fc);
+            b0 = fr_sub_2p(x0, t1), b1 = fr_add_2p(x0, t1), b2 = fr_sub_2p(x2, t3), b3 = fr_add_2p(x2, t3);
+            u2 = fr_mul_2p(b2, fa);
+            tile.put(i0, fr_sub_2p(b0, u2));
+            tile.put(i2, fr_add_2p(b0, u2));
+          } else {
+            b0 = fr_add_2p(x0, x1), b1 = fr_sub_2p(x0, x1), b2 = fr_add_2p(x2, x3), b3 = fr_sub_2p(x2, x3);
+            tile.put(i0, fr_add_2p(b0, b2));
+            tile.put(i2, fr_sub_2p(b0, b2));
+          }
+          const Fr u3 = fr_mul_2p(b3, fb);
+          tile.put(i1, fr_sub_2p(b1, u3));
+          tile.put(i3, fr_add_2p(b1, u3));
         }
       }
     }
     __syncthreads();
   }
+  const bool last = (st.u[4] & kNttLast) != 0;
   const Fr sc = words_fr(st.w);
   for (uint32_t e = threadIdx.x; e < nelem; e += kNttThreads) {
-    const uint32_t r = e >> c, col = e & (C - 1);
-    const Fr v = do_scale ? fr_mul(opaque(tile[e]), sc) : tile[e];
-    stf(x, base + ((uint64_t)r << lo) + col, v);
+    Fr v = tile.get(e);
+    if (last) v = Inverse ? fr_mul(v, sc) : fr_reduce_once(v);
+    stf(x, at(e), v);
   }
-}
-
-// ST_VPD_MUL: p0[i] *= p1[i] for i < q0.
-__global__ void __launch_bounds__(kBlock) k_vpd_mul(Step st) {
-  Fr* x = P<Fr*>(st, 0);
-  const Fr* y = P<const Fr*>(st, 1);
-  for (uint64_t i = GTID; i < st.q[0]; i += GSTRIDE) stf(x, i, fr_mul(ldf(x, i), ldf(y, i)));
 }
 
 // ST_VPD_LEAVES: leaf u (u < q0) digests positions 2u, 2u + 1 of p0 (one
@@ -627,9 +690,11 @@ void launch_vpd_step(const Step& st, hipStream_t s) {
   switch (st.type) {
     case ST_VPD_POWERS: k_vpd_powers<<<grid, block, 0, s>>>(st); break;
     case ST_VPD_TWIDDLES: k_vpd_twiddles<<<grid, block, 0, s>>>(st); break;
-    case ST_VPD_SCALE: k_vpd_scale<<<grid, block, 0, s>>>(st); break;
-    case ST_VPD_NTT: k_vpd_ntt<<<grid, dim3(kNttThreads), 0, s>>>(st); cls = PC_VPD_NTT; break;
-    case ST_VPD_MUL: k_vpd_mul<<<grid, block, 0, s>>>(st); break;
+    case ST_VPD_NTT:
+      if (st.u[5]) k_vpd_ntt<true><<<grid, dim3(kNttThreads), 0, s>>>(st);
+      else k_vpd_ntt<false><<<grid, dim3(kNttThreads), 0, s>>>(st);
+      cls = PC_VPD_NTT;
+      break;
     case ST_VPD_LEAVES: k_vpd_leaves<<<grid, block, 0, s>>>(st); cls = PC_VPD_MERKLE; break;
     case ST_VPD_NODES: k_vpd_nodes<<<grid, block, 0, s>>>(st); cls = PC_VPD_MERKLE; break;
     case ST_VPD_TREE_TOP: k_vpd_tree_top<<<grid, block, 0, s>>>(st); cls = PC_VPD_MERKLE; break;
@@ -677,61 +742,66 @@ void powers(Program& pg, Fr* out, const Fr& base, uint64_t count) {
   pg.steps.push_back(st);
 }
 
-void scale(Program& pg, const VpdBufs& b, uint32_t mode, bool coset, const Fr* src, Fr* dst, uint64_t size,
-           uint64_t N, uint32_t n) {
-  Step st = vmk(ST_VPD_SCALE, vtiles(size));
-  st.p[0] = src; st.p[1] = dst; st.p[2] = b.glo; st.p[3] = b.ghi;
-  st.p[4] = b.EA; st.p[5] = b.EB; st.p[6] = b.EC; st.p[7] = b.ED;
-  st.u[0] = mode; st.u[1] = coset ? 1 : 0; st.u[2] = n;
-  st.q[0] = size; st.q[1] = N;
-  st.bytes = kVE * (size + (mode == 2 ? 2 : 1) * N);
-  st.mulmods = (coset ? 2.0 : 0.0) * N + (mode == 3 ? 2.0 * N : 0.0);
-  pg.steps.push_back(st);
-}
-
 // Pass plan of a transform of size 2^L: strided passes of W <= 9 stages over
-// the top L - 11 bits (as many columns as fit in a 2^11-element tile), then
-// one contiguous pass over the last 11 stages.
+// the top L - 10 bits (as many columns as fit in a 2^10-element tile), then
+// one contiguous pass over the last 10 stages.
 struct NttPass {
   uint32_t j0, W, c;
 };
 
 std::vector<NttPass> ntt_plan(uint32_t L) {
   std::vector<NttPass> out;
-  if (L <= 11) {
+  if (L <= kNttLog) {
     out.push_back({0, L, 0});
     return out;
   }
-  const uint32_t top = L - 11, k = (top + 8) / 9;
+  const uint32_t top = L - kNttLog, k = (top + 8) / 9;
   uint32_t j0 = 0;
   for (uint32_t i = 0; i < k; ++i) {
     const uint32_t W = top / k + (i < top % k ? 1 : 0);
     const uint32_t lo = L - j0 - W;
-    out.push_back({j0, W, std::min(11 - W, lo)});
+    out.push_back({j0, W, std::min(kNttLog - W, lo)});
     j0 += W;
   }
-  out.push_back({j0, 11, 0});
+  out.push_back({j0, kNttLog, 0});
   return out;
 }
 
+// The input that the first pass of a transform makes (see k_vpd_ntt).
+struct NttInput {
+  NttForm form;
+  bool coset;      // times 5^j
+  const Fr* src;
+  uint64_t N;      // entries before the zeros
+  uint32_t n;      // copy bits of the eq tables
+};
+
 // Forward (natural -> bit-reversed) or inverse (bit-reversed -> natural,
-// scaled by 1/2^L) transform of x (2^L entries); T holds w_{2^LT}^t, t < 2^(LT-1).
-void ntt(Program& pg, Fr* x, uint32_t L, const Fr* T, uint32_t LT, bool inverse) {
+// scaled by 1/2^L) transform into x (2^L entries); T holds w_{2^LT}^t, t < 2^(LT-1).
+void ntt(Program& pg, const VpdBufs& b, const NttInput& in, Fr* x, uint32_t L, uint32_t LT, bool inverse) {
   std::vector<NttPass> plan = ntt_plan(L);
   if (inverse) std::reverse(plan.begin(), plan.end());
   for (size_t i = 0; i < plan.size(); ++i) {
     const NttPass& ps = plan[i];
     Step st = vmk(ST_VPD_NTT, (uint32_t)(1ull << (L - ps.W - ps.c)));
-    st.p[0] = x; st.p[1] = T;
+    st.p[0] = x; st.p[1] = b.T;
     st.u[0] = L; st.u[1] = ps.j0; st.u[2] = ps.W; st.u[3] = ps.c; st.u[4] = LT - L; st.u[5] = inverse ? 1 : 0;
     st.q[0] = 1ull << (LT - 1);
-    if (inverse && i + 1 == plan.size()) {
-      st.u[4] |= 256u;
-      put_fr(st.w, fr_inverse(fr_to_mont(fr_make(1u << L, 0, 0, 0, 0, 0, 0, 0))));  // L <= 28
-    }
     const double n = (double)(1ull << L);
     st.bytes = 2 * kVE * n;
     st.mulmods = n / 2 * ps.W;
+    if (i == 0) {
+      st.u[4] |= (uint32_t)in.form << kNttFormShift | (in.coset ? kNttCoset : 0u);
+      st.p[2] = in.src; st.p[3] = b.glo; st.p[4] = b.ghi;
+      st.p[5] = b.EA; st.p[6] = b.EB; st.p[7] = b.EC; st.p[8] = b.ED;
+      st.q[1] = in.N; st.q[2] = in.n;
+      st.bytes = kVE * (n + (in.form == NF_PRODUCT ? 2 * n : (double)in.N * (in.form == NF_SHIFTED ? 2 : 1)));
+      st.mulmods += in.form == NF_PRODUCT ? n : (in.coset ? 2.0 : 0.0) * in.N + (in.form == NF_EQ ? 2.0 * in.N : 0.0);
+    }
+    if (i + 1 == plan.size()) {
+      st.u[4] |= kNttLast;
+      if (inverse) put_fr(st.w, fr_inverse(fr_to_mont(fr_make(1u << L, 0, 0, 0, 0, 0, 0, 0))));  // L <= 28
+    }
     pg.steps.push_back(st);
   }
 }
@@ -782,8 +852,7 @@ void emit_vpd_commit(Program& pg, const VpdPlan& vp, void* base, const Fr* d_val
     st.bytes = kVE * (vp.M / 2); st.mulmods = (double)(vp.M / 2);
     pg.steps.push_back(st);
   }
-  scale(pg, b, 0, true, d_vals, b.fL, vp.M, vp.N, 0);
-  ntt(pg, b.fL, logM, b.T, logM, false);
+  ntt(pg, b, {NF_COEFF, true, d_vals, vp.N, 0}, b.fL, logM, logM, false);
   tree(pg, b.fL, nullptr, b.treeF, vp.M / 2);
 }
 
@@ -814,22 +883,12 @@ void emit_vpd_open(Program& pg, const VpdPlan& vp, void* base, const Fr* d_vals,
   // p = f q through transforms of size 2N (the fri region is free until the first fold)
   Fr* buf1 = b.fri;
   Fr* buf2 = b.fri + 2 * N;
-  scale(pg, b, 0, false, d_vals, buf1, 2 * N, N, 0);
-  scale(pg, b, 3, false, nullptr, buf2, 2 * N, N, n);
-  ntt(pg, buf1, s + 1, b.T, logM, false);
-  ntt(pg, buf2, s + 1, b.T, logM, false);
-  {
-    Step st = vmk(ST_VPD_MUL, vtiles(2 * N));
-    st.p[0] = buf1; st.p[1] = buf2; st.q[0] = 2 * N;
-    st.bytes = 3 * kVE * 2 * N; st.mulmods = 2.0 * N;
-    pg.steps.push_back(st);
-  }
-  ntt(pg, buf1, s + 1, b.T, logM, true);
+  ntt(pg, b, {NF_COEFF, false, d_vals, N, 0}, buf1, s + 1, logM, false);
+  ntt(pg, b, {NF_EQ, false, nullptr, N, n}, buf2, s + 1, logM, false);
+  ntt(pg, b, {NF_PRODUCT, false, buf2, 2 * N, 0}, buf1, s + 1, logM, true);
   // h and g' on L
-  scale(pg, b, 1, true, buf1, b.hL, M, N, 0);
-  scale(pg, b, 2, true, buf1, b.gL, M, N, 0);
-  ntt(pg, b.hL, logM, b.T, logM, false);
-  ntt(pg, b.gL, logM, b.T, logM, false);
+  ntt(pg, b, {NF_UPPER, true, buf1, N, 0}, b.hL, logM, logM, false);
+  ntt(pg, b, {NF_SHIFTED, true, buf1, N, 0}, b.gL, logM, logM, false);
   tree(pg, b.hL, b.gL, b.treeHG, M / 2);
   auto absorb = [&](const uint32_t* root, uint32_t* pdst, Fr* out, uint32_t count) {
     Step st = vmk(ST_VPD_ABSORB, 1);
