@@ -138,6 +138,7 @@ enum StepType : uint32_t {
   ST_VPD_TWIDDLES,
   ST_VPD_NTT,
   ST_VPD_LEAVES,
+  ST_VPD_QUOTIENT,
   ST_VPD_NODES,
   ST_VPD_TREE_TOP,
   ST_VPD_BEGIN,
@@ -177,7 +178,7 @@ struct Step {
   uint32_t u[6];     // small integers
   uint64_t q[4];     // sizes
   const void* p[16]; // device pointers
-  uint32_t w[16];    // host words (seed state, circuit digest)
+  uint32_t w[24];    // host words (seed state, circuit digest, field constants)
   double bytes;      // algorithmic HBM bytes (timing reports only)
   double mulmods;    // field products (timing reports only)
 };

@@ -250,11 +250,9 @@ __global__ void __launch_bounds__(kBlock) k_vpd_twiddles(Step st) {
 // transform; its last pass (u4 bit 8) reduces them.
 // The first pass makes its own input (u4 bits 12..14, the form F):
 //   F = 1: src[j]                          (j < N)
-//   F = 2: src[j + N]                      (j < N; h from p)
-//   F = 3: src[j + 1] + src[j + 1 + N]     (j < N - 1; g' from p)
-//   F = 4: w[(N - j) mod N], w[b] = EA[b >> n] EC[b & mask] + EB[b >> n] ED[b & mask]  (q)
-// times 5^j with u4 bit 16, zero from N on; F = 5: x[j] src[j] (inverse).
-// p0 x, p1 T, p2 src, p3 glo, p4 ghi, p5..p8 EA, EB, EC, ED, u0 L, u1 j0, u2 W, u3 c,
+//   F = 2: w[(N - j) mod N], w[b] = EA[b >> n] EC[b & mask] + EB[b >> n] ED[b & mask]  (q)
+// times 5^j with u4 bit 16, zero from N on; F = 3: src[j] p3[j] (inverse).
+// p0 x, p1 T, p2 src, p3 glo (or the second factor), p4 ghi, p5..p8 EA, EB, EC, ED, u0 L, u1 j0, u2 W, u3 c,
 // u4 tshift | flags, u5 inverse, q0 n_T / 2, q1 N, q2 n.
 //
 // Bound by the products (half of one per element and stage, 134 G/s) and, where
@@ -266,7 +264,7 @@ constexpr uint32_t kNttLog = 10;
 constexpr uint32_t kNttTile = 1u << kNttLog;
 constexpr uint32_t kNttThreads = 256;
 constexpr uint32_t kNttLast = 256u, kNttFormShift = 12, kNttCoset = 1u << 16;
-enum NttForm : uint32_t { NF_NONE = 0, NF_COEFF, NF_UPPER, NF_SHIFTED, NF_EQ, NF_PRODUCT };
+enum NttForm : uint32_t { NF_NONE = 0, NF_COEFF, NF_EQ, NF_PRODUCT };
 
 // The slot of element i: of the index bits that vary over 16 consecutive lanes of a
 // stage (0..3, or 0..k with bits from k + 3 up to 5, or 2..5) the low four slot
@@ -289,16 +287,11 @@ struct NttLds {
 
 // Entry j < N of a first pass's input.
 __device__ __forceinline__ Fr ntt_input(const Step& st, uint32_t form, uint64_t j) {
-  const Fr* src = P<const Fr*>(st, 2);
   const uint64_t N = st.q[1];
   const uint32_t n = (uint32_t)st.q[2];
-  Fr v = fr_zero();
+  Fr v;
   if (form == NF_COEFF) {
-    v = ldf(src, j);
-  } else if (form == NF_UPPER) {
-    v = ldf(src, j + N);
-  } else if (form == NF_SHIFTED) {
-    if (j + 1 < N) v = fr_add(ldf(src, j + 1), ldf(src, j + 1 + N));
+    v = ldf(P<const Fr*>(st, 2), j);
   } else {
     const uint64_t b = (N - j) & (N - 1), mask = (1ull << n) - 1;
     v = fr_mul_add2(ldf(P<const Fr*>(st, 5), b >> n), ldf(P<const Fr*>(st, 7), b & mask),
@@ -337,8 +330,8 @@ __global__ void __launch_bounds__(kNttThreads, 4) k_vpd_ntt(Step st) {
   if (form == NF_NONE) {
     for (uint32_t e = threadIdx.x; e < nelem; e += kNttThreads) tile.put(e, ldf(x, at(e)));
   } else if (Inverse) {
-    const Fr* y = P<const Fr*>(st, 2);
-    for (uint32_t e = threadIdx.x; e < nelem; e += kNttThreads) tile.put(e, fr_mul(ldf(x, at(e)), ldf(y, at(e))));
+    const Fr *f = P<const Fr*>(st, 2), *q = P<const Fr*>(st, 3);
+    for (uint32_t e = threadIdx.x; e < nelem; e += kNttThreads) tile.put(e, fr_mul(ldf(f, at(e)), ldf(q, at(e))));
   } else {
     for (uint32_t e = threadIdx.x; e < (pad4 ? nelem / 4 : nelem); e += kNttThreads) {
       const uint64_t j = at(e);
@@ -440,17 +433,49 @@ __global__ void __launch_bounds__(kNttThreads, 4) k_vpd_ntt(Step st) {
   }
 }
 
-// ST_VPD_LEAVES: leaf u (u < q0) digests positions 2u, 2u + 1 of p0 (one
-// block), then of p1 if not null (a second block): the compression function
-// chained from the initial value. p2 digests.
+// ST_VPD_LEAVES: leaf u (u < q0) digests positions 2u, 2u + 1 of p0 (one block).
+// p2 digests.
 __global__ void __launch_bounds__(kBlock) k_vpd_leaves(Step st) {
   const Fr* A = P<const Fr*>(st, 0);
-  const Fr* B = P<const Fr*>(st, 1);
   uint32_t* out = P<uint32_t*>(st, 2);
+  for (uint64_t u = GTID; u < st.q[0]; u += GSTRIDE)
+    store_digest(out, u, sha256_compress_v(sha256_iv(), pair_block(ldf(A, 2 * u), ldf(A, 2 * u + 1))));
+}
+
+// ST_VPD_QUOTIENT: g' on L, and the leaves of the tree of (h, g'). With p = f q =
+// r + h (x^N - 1), deg r < N, and g' = (r - r_0) / x, position by position
+//   g'(x) = (f(x) q(x) - h(x) (x^N - 1) - r_0) / x,
+// three products and a half of one, where a transform of g' takes half of log2 M.
+// Positions 2u, 2u + 1 are x = 5 w^k, k = bitrev(u), and -x; x^N is 5^N times a
+// fourth root of unity given by k mod 4. p6 holds p_j 5^(j - N), so r_0 = p_0 + p_N
+// is p6[0] 5^N + p6[N].
+// p0 f, p1 q in, g' out, p2 h, p3 digests, p4 wilo, p5 wihi, p6 p, u0 log2 M,
+// q0 M / 2, q1 N, w 5^N, 5^N w^N, 1/5.
+__global__ void __launch_bounds__(kBlock) k_vpd_quotient(Step st) {
+  const Fr *F = P<const Fr*>(st, 0), *H = P<const Fr*>(st, 2);
+  Fr* G = P<Fr*>(st, 1);
+  uint32_t* out = P<uint32_t*>(st, 3);
+  const Fr *wilo = P<const Fr*>(st, 4), *wihi = P<const Fr*>(st, 5), *coef = P<const Fr*>(st, 6);
+  const uint32_t logM = st.u[0];
+  const Fr a = words_fr(st.w), b = words_fr(st.w + 8), inv5 = words_fr(st.w + 16);
+  const Fr r0 = fr_add(fr_mul(ldf(coef, 0), a), ldf(coef, st.q[1]));
   for (uint64_t u = GTID; u < st.q[0]; u += GSTRIDE) {
-    Sha256State h = sha256_compress_v(sha256_iv(), pair_block(ldf(A, 2 * u), ldf(A, 2 * u + 1)));
-    if (B) h = sha256_compress_v(h, pair_block(ldf(B, 2 * u), ldf(B, 2 * u + 1)));
-    store_digest(out, u, h);
+    const uint32_t k = bitrev_bits((uint32_t)u, logM - 1);
+    const Fr xinv = fr_mul(pow2lvl(wilo, wihi, k), inv5);
+    Fr h[2], g[2];
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+      const uint32_t kk = k + (e ? 1u << (logM - 1) : 0u);
+      const Fr z = kk & 1 ? b : a;  // x^N up to its sign
+      const Fr nz = kk & 2 ? fr_add(fr_one(), z) : fr_sub(fr_one(), z);
+      h[e] = ldf(H, 2 * u + e);
+      const Fr t = fr_mul_add2(ldf(F, 2 * u + e), ldf(G, 2 * u + e), h[e], nz);
+      g[e] = fr_mul(e ? fr_sub(r0, t) : fr_sub(t, r0), xinv);
+    }
+    stf(G, 2 * u, g[0]);
+    stf(G, 2 * u + 1, g[1]);
+    const Sha256State d = sha256_compress_v(sha256_iv(), pair_block(h[0], h[1]));
+    store_digest(out, u, sha256_compress_v(d, pair_block(g[0], g[1])));
   }
 }
 
@@ -695,6 +720,7 @@ void launch_vpd_step(const Step& st, hipStream_t s) {
       else k_vpd_ntt<false><<<grid, dim3(kNttThreads), 0, s>>>(st);
       cls = PC_VPD_NTT;
       break;
+    case ST_VPD_QUOTIENT: k_vpd_quotient<<<grid, block, 0, s>>>(st); cls = PC_VPD_MERKLE; break;
     case ST_VPD_LEAVES: k_vpd_leaves<<<grid, block, 0, s>>>(st); cls = PC_VPD_MERKLE; break;
     case ST_VPD_NODES: k_vpd_nodes<<<grid, block, 0, s>>>(st); cls = PC_VPD_MERKLE; break;
     case ST_VPD_TREE_TOP: k_vpd_tree_top<<<grid, block, 0, s>>>(st); cls = PC_VPD_MERKLE; break;
@@ -715,6 +741,7 @@ void launch_vpd_step(const Step& st, hipStream_t s) {
 namespace {
 
 constexpr uint32_t kVpdSweepTiles = 65535u * 8;
+constexpr uint32_t kQuotientTiles = 8192;  // a thread's constants serve several pairs of positions
 constexpr double kVE = 32.0;
 
 uint32_t vtiles(uint64_t n) {
@@ -772,13 +799,15 @@ struct NttInput {
   NttForm form;
   bool coset;      // times 5^j
   const Fr* src;
+  const Fr* src2;  // the second factor of NF_PRODUCT
   uint64_t N;      // entries before the zeros
   uint32_t n;      // copy bits of the eq tables
 };
 
 // Forward (natural -> bit-reversed) or inverse (bit-reversed -> natural,
-// scaled by 1/2^L) transform into x (2^L entries); T holds w_{2^LT}^t, t < 2^(LT-1).
-void ntt(Program& pg, const VpdBufs& b, const NttInput& in, Fr* x, uint32_t L, uint32_t LT, bool inverse) {
+// scaled by `factor` / 2^L) transform into x (2^L entries); T holds w_{2^LT}^t, t < 2^(LT-1).
+void ntt(Program& pg, const VpdBufs& b, const NttInput& in, Fr* x, uint32_t L, uint32_t LT, const Fr* factor = nullptr) {
+  const bool inverse = factor != nullptr;
   std::vector<NttPass> plan = ntt_plan(L);
   if (inverse) std::reverse(plan.begin(), plan.end());
   for (size_t i = 0; i < plan.size(); ++i) {
@@ -792,26 +821,30 @@ void ntt(Program& pg, const VpdBufs& b, const NttInput& in, Fr* x, uint32_t L, u
     st.mulmods = n / 2 * ps.W;
     if (i == 0) {
       st.u[4] |= (uint32_t)in.form << kNttFormShift | (in.coset ? kNttCoset : 0u);
-      st.p[2] = in.src; st.p[3] = b.glo; st.p[4] = b.ghi;
+      st.p[2] = in.src; st.p[3] = in.src2 ? in.src2 : b.glo; st.p[4] = b.ghi;
       st.p[5] = b.EA; st.p[6] = b.EB; st.p[7] = b.EC; st.p[8] = b.ED;
       st.q[1] = in.N; st.q[2] = in.n;
-      st.bytes = kVE * (n + (in.form == NF_PRODUCT ? 2 * n : (double)in.N * (in.form == NF_SHIFTED ? 2 : 1)));
+      st.bytes = kVE * (n + (in.form == NF_PRODUCT ? 2 * n : in.form == NF_COEFF ? (double)in.N : 0.0));
       st.mulmods += in.form == NF_PRODUCT ? n : (in.coset ? 2.0 : 0.0) * in.N + (in.form == NF_EQ ? 2.0 * in.N : 0.0);
     }
     if (i + 1 == plan.size()) {
       st.u[4] |= kNttLast;
-      if (inverse) put_fr(st.w, fr_inverse(fr_to_mont(fr_make(1u << L, 0, 0, 0, 0, 0, 0, 0))));  // L <= 28
+      if (inverse) put_fr(st.w, fr_mul(*factor, fr_inverse(fr_to_mont(fr_make(1u << L, 0, 0, 0, 0, 0, 0, 0)))));  // L <= 28
     }
     pg.steps.push_back(st);
   }
 }
 
-// Merkle tree over nl leaves of (A, B) pairs; digests at tree (levels in order).
-void tree(Program& pg, const Fr* A, const Fr* B, uint32_t* tree, uint64_t nl) {
+// The leaf digests of A (2 nl entries).
+void leaves(Program& pg, const Fr* A, uint32_t* tree, uint64_t nl) {
   Step st = vmk(ST_VPD_LEAVES, vtiles(nl));
-  st.p[0] = A; st.p[1] = B; st.p[2] = tree; st.q[0] = nl;
-  st.bytes = kVE * 2 * nl * (B ? 2 : 1) + 32.0 * nl;
+  st.p[0] = A; st.p[2] = tree; st.q[0] = nl;
+  st.bytes = kVE * 2 * nl + 32.0 * nl;
   pg.steps.push_back(st);
+}
+
+// Merkle tree over nl leaf digests (levels in order after them).
+void tree(Program& pg, uint32_t* tree, uint64_t nl) {
   uint64_t cnt = nl;
   uint32_t* lv = tree;
   while (cnt > kTopMax) {
@@ -852,8 +885,9 @@ void emit_vpd_commit(Program& pg, const VpdPlan& vp, void* base, const Fr* d_val
     st.bytes = kVE * (vp.M / 2); st.mulmods = (double)(vp.M / 2);
     pg.steps.push_back(st);
   }
-  ntt(pg, b, {NF_COEFF, true, d_vals, vp.N, 0}, b.fL, logM, logM, false);
-  tree(pg, b.fL, nullptr, b.treeF, vp.M / 2);
+  ntt(pg, b, {NF_COEFF, true, d_vals, nullptr, vp.N, 0}, b.fL, logM, logM);
+  leaves(pg, b.fL, b.treeF, vp.M / 2);
+  tree(pg, b.treeF, vp.M / 2);
 }
 
 void emit_vpd_root_out(Program& pg, const VpdPlan& vp, void* base, uint8_t* proof_out) {
@@ -880,16 +914,28 @@ void emit_vpd_open(Program& pg, const VpdPlan& vp, void* base, const Fr* d_vals,
     Fr* outs[4] = {b.EA, b.EB, b.EC, b.ED};
     pg.eq(4, bits, pts, scl, outs);
   }
-  // p = f q through transforms of size 2N (the fri region is free until the first fold)
-  Fr* buf1 = b.fri;
-  Fr* buf2 = b.fri + 2 * N;
-  ntt(pg, b, {NF_COEFF, false, d_vals, N, 0}, buf1, s + 1, logM, false);
-  ntt(pg, b, {NF_EQ, false, nullptr, N, n}, buf2, s + 1, logM, false);
-  ntt(pg, b, {NF_PRODUCT, false, buf2, 2 * N, 0}, buf1, s + 1, logM, true);
-  // h and g' on L
-  ntt(pg, b, {NF_UPPER, true, buf1, N, 0}, b.hL, logM, logM, false);
-  ntt(pg, b, {NF_SHIFTED, true, buf1, N, 0}, b.gL, logM, logM, false);
-  tree(pg, b.hL, b.gL, b.treeHG, M / 2);
+  // q on L, in the place of g'. The first half of the positions is the coset of the
+  // even powers: p = f q there gives p (2N coefficients), left times 5^(j - N),
+  // whose upper half is then h with the coset's powers. (The fri region is free
+  // until the first fold.) Against transforms of f and q on 2N points and of h and
+  // g' on L this is one transform of size M less in four and a half.
+  Fr* coef = b.fri;
+  const Fr g5 = vpd_shift(), a = fr_pow_u64(g5, N), ainv = fr_inverse(a);
+  ntt(pg, b, {NF_EQ, true, nullptr, nullptr, N, n}, b.gL, logM, logM);
+  ntt(pg, b, {NF_PRODUCT, false, b.fL, b.gL, 2 * N, 0}, coef, s + 1, logM, &ainv);
+  ntt(pg, b, {NF_COEFF, false, coef + N, nullptr, N, 0}, b.hL, logM, logM);
+  {
+    Step st = vmk(ST_VPD_QUOTIENT, std::min(vtiles(M / 2), kQuotientTiles));
+    st.p[0] = b.fL; st.p[1] = b.gL; st.p[2] = b.hL; st.p[3] = b.treeHG; st.p[4] = b.wilo; st.p[5] = b.wihi;
+    st.p[6] = coef;
+    st.u[0] = logM; st.q[0] = M / 2; st.q[1] = N;
+    put_fr(st.w, a);
+    put_fr(st.w + 8, fr_mul(a, fr_pow_u64(vpd_root_of_unity(logM), N)));
+    put_fr(st.w + 16, fr_inverse(g5));
+    st.bytes = kVE * 4 * M + 32.0 * (M / 2); st.mulmods = 4.0 * M;
+    pg.steps.push_back(st);
+  }
+  tree(pg, b.treeHG, M / 2);
   auto absorb = [&](const uint32_t* root, uint32_t* pdst, Fr* out, uint32_t count) {
     Step st = vmk(ST_VPD_ABSORB, 1);
     st.p[0] = S; st.p[1] = root; st.p[2] = pdst; st.p[3] = out; st.u[0] = count;
@@ -912,7 +958,8 @@ void emit_vpd_open(Program& pg, const VpdPlan& vp, void* base, const Fr* d_vals,
     const uint64_t m = M >> i;  // entries of layer i
     Fr* layer = b.fri + fri_offset(M, i);
     uint32_t* t = b.treeFri + 8 * fri_offset(M, i);
-    tree(pg, layer, nullptr, t, m / 2);
+    leaves(pg, layer, t, m / 2);
+    tree(pg, t, m / 2);
     absorb(t + 8 * (m - 2), proof + 8 * i, &b.V->beta[i], 1);
     Step st = vmk(ST_VPD_FOLD, vtiles(m / 2));
     st.p[0] = layer; st.p[1] = b.fri + fri_offset(M, i + 1); st.p[2] = b.V; st.p[3] = b.wilo; st.p[4] = b.wihi;
