@@ -594,9 +594,12 @@ void emit_layer(Program& pg, const gkr_circuit& c, uint32_t i, const Workspace& 
     pg.eq(1, bits, pts, scl, outs);
   }
   pg.local_values(w.EqR, w.Ka, w.Kb, 1ull << sg1, S, w.partials);
-  pg.local_contract(W, w.EqR, w.wpart, n, 1ull << sg1, c.plan.ychunks);
+  // with few columns four rows or more per thread, and at most 512 chunks
+  const uint64_t few = std::min<uint64_t>(c.plan.ychunks, std::min<uint64_t>(512, std::max<uint64_t>(1, (1ull << s1) >> 10)));
+  const uint32_t chunks = n < 8 ? (uint32_t)few : c.plan.ychunks;
+  pg.local_contract(W, w.EqR, w.wpart, n, 1ull << sg1, chunks);
   pg.steps.back().join = 1;  // independent of the local values
-  pg.copy_tables(w.wpart, c.plan.ychunks, w.U, w.V, w.Fa, w.Fb, S, w.Wc, w.Fc, w.Kc, 1ull << n);
+  pg.copy_tables(w.wpart, chunks, w.U, w.V, w.Fa, w.Fb, S, w.Wc, w.Fc, w.Kc, 1ull << n);
   Fr* tc[3] = {w.Wc, w.Fc, w.Kc};
   const Fr* tc_src[3] = {w.Wc, w.Fc, w.Kc};
   emit_phase<3>(pg, tc_src, tc, n, S, w.partials, ry + sg1, proof + off_p2 + 24 * sg1, &S->vy, proof + off_vy, tun);
