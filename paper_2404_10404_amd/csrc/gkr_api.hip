@@ -526,8 +526,9 @@ static void emit_phase(Program& pg, const Fr* const* src0, Fr* const* dst, uint3
 }
 
 void emit_phase_a(Program& pg, const Fr* const* src0, Fr* const* dst, uint32_t nrounds, DevState* S, Fr* partials,
-                  Fr* r_out, uint32_t* msg, Fr* final_out, uint32_t* proof_value, const Tuning& tun) {
-  emit_phase<3>(pg, src0, dst, nrounds, S, partials, r_out, msg, final_out, proof_value, tun);
+                  Fr* r_out, uint32_t* msg, Fr* final_out, uint32_t* proof_value, const Tuning& tun,
+                  uint32_t first_round) {
+  emit_phase<3>(pg, src0, dst, nrounds, S, partials, r_out, msg, final_out, proof_value, tun, first_round);
 }
 
 // One gate layer (A3-A7). W = V_{i+1} in Montgomery form; u, v points of

@@ -29,6 +29,7 @@
 #include "gkr_profile.hpp"
 #include "gkr_program.hpp"
 #include "gkr_tuning.hpp"
+#include "gkr_wide.hpp"
 
 namespace gkr {
 
@@ -146,32 +147,123 @@ __device__ __forceinline__ void body_g_p1(const Step& st, uint32_t tile, uint32_
 //   F = vx M + A, K = vx A.
 // p0 T, p1 EL, p2 EC, p3 vx (one element), p4 F, p5 K, p6 yrow, p7 yent
 // (z, x | type << 31), u0 n, q0 count = 2^{rho_i}.
-__device__ __forceinline__ void body_g_p2(const Step& st, uint32_t tile, uint32_t ntiles) {
+// Bound by the products: one per nested gate and, with vx EC[c] kept by the thread
+// (a grid stride keeps its column), at most three per entry; most entries have
+// gates of one type only and take one or two, the same for all copies of a wave.
+struct GP2Column {
+  uint64_t c = ~0ull;
+  Fr ec, vec;
+};
+__device__ __forceinline__ void g_p2_entry(const Step& st, uint64_t e, GP2Column& col, Fr& f, Fr& kk) {
   const Fr* __restrict__ T = P<const Fr*>(st, 0);
   const Fr* __restrict__ EL = P<const Fr*>(st, 1);
-  const Fr* __restrict__ EC = P<const Fr*>(st, 2);
-  const Fr vx = *P<const Fr*>(st, 3);
-  Fr* __restrict__ F = P<Fr*>(st, 4);
-  Fr* __restrict__ K = P<Fr*>(st, 5);
   const uint32_t* __restrict__ yrow = P<const uint32_t*>(st, 6);
   const uint2* __restrict__ yent = P<const uint2*>(st, 7);
   const uint32_t n = st.u[0];
-  const uint64_t mask = (1ull << n) - 1;
-  for (uint64_t e = GTID; e < st.q[0]; e += GSTRIDE) {
-    const uint64_t y = e >> n, c = e & mask;
-    Fr m = fr_zero(), a = fr_zero();
-    const uint32_t k1 = yrow[y + 1];
-    for (uint32_t k = yrow[y]; k < k1; ++k) {
-      const uint2 r = yent[k];
-      const Fr te = fr_mul(ldf(T, ((uint64_t)r.x << n) | c), ldf(EL, r.y & 0x7fffffffu));
-      if (r.y >> 31) m = fr_add(m, te);
-      else a = fr_add(a, te);
+  const uint64_t y = e >> n, c = e & ((1ull << n) - 1);
+  if (c != col.c) {
+    col.c = c;
+    col.ec = ldf(P<const Fr*>(st, 2), c);
+    col.vec = fr_mul(ldf(P<const Fr*>(st, 3), 0), col.ec);
+  }
+  Fr m = fr_zero(), a = fr_zero();
+  bool has_m = false, has_a = false;
+  const uint32_t k1 = yrow[y + 1];
+  for (uint32_t k = yrow[y]; k < k1; ++k) {
+    const uint2 r = yent[k];
+    const Fr te = fr_mul(ldf(T, ((uint64_t)r.x << n) | c), ldf(EL, r.y & 0x7fffffffu));
+    if (r.y >> 31) {
+      m = has_m ? fr_add(m, te) : te;
+      has_m = true;
+    } else {
+      a = has_a ? fr_add(a, te) : te;
+      has_a = true;
     }
-    const Fr ec = ldf(EC, c);
-    m = fr_mul(m, ec);
-    a = fr_mul(a, ec);
-    stf(F, e, fr_add(fr_mul(vx, m), a));
-    stf(K, e, fr_mul(vx, a));
+  }
+  f = fr_zero();
+  kk = fr_zero();
+  if (has_a) {
+    f = fr_mul(a, col.ec);
+    kk = fr_mul(a, col.vec);
+  }
+  if (has_m) f = fr_add(f, fr_mul(m, col.vec));
+}
+__device__ __forceinline__ void body_g_p2(const Step& st, uint32_t tile, uint32_t ntiles) {
+  GP2Column col;
+  for (uint64_t e = GTID; e < st.q[0]; e += GSTRIDE) {
+    Fr f, k;
+    g_p2_entry(st, e, col, f, k);
+    stf(P<Fr*>(st, 4), e, f);
+    stf(P<Fr*>(st, 5), e, k);
+  }
+}
+
+// The terms of round 1 over tables (V, F, K) from the entries of pair b, added to acc.
+__device__ __forceinline__ void g_first_round(const Fr* V, uint64_t b, uint64_t half, const Fr& f0, const Fr& k0,
+                                              const Fr& f1, const Fr& k1, Fr (&acc)[2]) {
+  const Fr v0 = ldf(V, b), v1 = ldf(V, b + half);
+  acc[0] = fr_add(acc[0], fr_add(fr_mul(v0, f0), k0));
+  const Fr v2 = fr_sub(fr_double(v1), v0), f2 = fr_sub(fr_double(f1), f0), k2 = fr_sub(fr_double(k1), k0);
+  acc[1] = fr_add(acc[1], fr_add(fr_mul(v2, f2), k2));
+}
+
+// ST_G_P2_ROUND: the tables and round 1 of phase 2 in one pass. Pointers as in
+// ST_G_P2, p8 R, p9 S, p10 partials, p11 r_out, p12 msg, q0 half (a multiple of 2^n).
+__device__ __forceinline__ void body_g_p2_round(const Step& st, uint32_t tile, uint32_t ntiles) {
+  const uint64_t half = st.q[0];
+  Fr acc[2] = {fr_zero(), fr_zero()};
+  GP2Column col;
+  for (uint64_t b = GTID; b < half; b += GSTRIDE) {
+    Fr f0, k0, f1, k1;
+    g_p2_entry(st, b, col, f0, k0);
+    stf(P<Fr*>(st, 4), b, f0);
+    stf(P<Fr*>(st, 5), b, k0);
+    g_p2_entry(st, b + half, col, f1, k1);
+    stf(P<Fr*>(st, 4), b + half, f1);
+    stf(P<Fr*>(st, 5), b + half, k1);
+    g_first_round(P<const Fr*>(st, 8), b, half, f0, k0, f1, k1, acc);
+  }
+  write_partial<2>(acc, P<Fr*>(st, 10), tile);
+  if (last_tile(&P<DevState*>(st, 9)->counter, ntiles))
+    finish_reduced_round<false>(P<const Fr*>(st, 10), ntiles, P<DevState*>(st, 9), P<Fr*>(st, 11), P<uint32_t*>(st, 12));
+}
+
+// ST_G_BLOCKS: the values of u1 source blocks, sum over (y, c) of
+// R[(b, y, c)] EL[y] EC[c] into p5[b]; one launch for all blocks, one unreduced
+// product per entry (four blocks of 2^20 entries: 40 us, against 4 x 37 with two
+// products per entry and a launch per block). Tile b u2 + k takes units k, k + u2, ... of
+// block b: a unit is 256 columns (with fewer than 256, all of them and several
+// rows at a time) by one of u3 chunks of rows. A thread keeps its column, so a
+// product is an unreduced multiply-accumulate and EC enters once per unit.
+// p0 R, p1 EL, p2 EC, p3 partials, p4 S, u0 n, q0 rows of a block.
+__device__ __forceinline__ void body_g_blocks(const Step& st, uint32_t tile, uint32_t ntiles) {
+  const Fr* __restrict__ EL = P<const Fr*>(st, 1);
+  const uint32_t n = st.u[0], nb = st.u[1], tpb = st.u[2], chunks = st.u[3];
+  const uint64_t rows = st.q[0], per = (rows + chunks - 1) / chunks;
+  const uint32_t b = tile / tpb;
+  const Fr* __restrict__ R = P<const Fr*>(st, 0) + ((uint64_t)b * rows << n);
+  const uint32_t xb = n > 8 ? 1u << (n - 8) : 1u, step = n < 8 ? kBlock >> n : 1u;
+  Fr tot[1] = {fr_zero()};
+  for (uint32_t u = tile % tpb; u < xb * chunks; u += tpb) {
+    const uint64_t c = n < 8 ? threadIdx.x & ((1u << n) - 1) : (uint64_t)(u % xb) * kBlock + threadIdx.x;
+    const uint64_t y0 = (u / xb) * per, y1 = y0 + per < rows ? y0 + per : rows;
+    Fr acc = fr_zero();
+    for (uint64_t ya = y0 + (n < 8 ? threadIdx.x >> n : 0u); ya < y1; ya += 16ull * step) {
+      FrCols aw = frc_zero();
+      for (uint64_t y = ya; y < y1 && y < ya + 16ull * step; y += step) frc_mac(aw, ldf(EL, y), ldf(R, y << n | c));
+      acc = fr_add(acc, frw_reduce<16>(frc_wide(aw)));
+    }
+    tot[0] = fr_add(tot[0], fr_mul(acc, ldf(P<const Fr*>(st, 2), c)));
+  }
+  write_partial<1>(tot, P<Fr*>(st, 3), tile);
+  if (last_tile(&P<DevState*>(st, 4)->counter, ntiles)) {
+    const uint32_t lane = threadIdx.x & 63;
+    for (uint32_t k = threadIdx.x >> 6; k < nb; k += kBlock / 64) {
+      Fr v = fr_zero();
+      for (uint32_t i = lane; i < tpb; i += 64) v = fr_add(v, get_partial(P<const Fr*>(st, 3), (uint64_t)k * tpb + i));
+      for (uint32_t off = 32; off; off >>= 1) v = fr_add(v, shfl_xor_fr(v, off));
+      if (lane == 0) stf(P<Fr*>(st, 5), k, v);
+    }
   }
 }
 
@@ -236,6 +328,8 @@ GKR_G_KERNEL(k_g_scatter, body_g_scatter)
 GKR_G_KERNEL(k_g_ttable, body_g_ttable)
 GKR_G_KERNEL(k_g_p1, body_g_p1)
 GKR_G_KERNEL(k_g_p2, body_g_p2)
+GKR_G_KERNEL(k_g_p2_round, body_g_p2_round)
+GKR_G_KERNEL(k_g_blocks, body_g_blocks)
 GKR_G_KERNEL(k_g_layer_begin, body_g_layer_begin)
 GKR_G_KERNEL(k_g_values, body_g_values)
 #undef GKR_G_KERNEL
@@ -251,6 +345,8 @@ void launch_general_step(const Step& st, hipStream_t s) {
     case ST_G_TTABLE: k_g_ttable<<<grid, block, 0, s>>>(st); cls = PC_G_CLAIMS; break;
     case ST_G_P1: k_g_p1<<<grid, block, 0, s>>>(st); cls = PC_G_PHASE1_INIT; break;
     case ST_G_P2: k_g_p2<<<grid, block, 0, s>>>(st); cls = PC_G_PHASE2_TABLES; break;
+    case ST_G_P2_ROUND: k_g_p2_round<<<grid, block, 0, s>>>(st); cls = PC_G_PHASE2_TABLES; break;
+    case ST_G_BLOCKS: k_g_blocks<<<grid, block, 0, s>>>(st); cls = PC_G_CLAIMS; break;
     case ST_G_LAYER_BEGIN: k_g_layer_begin<<<grid, block, 0, s>>>(st); cls = PC_TRANSCRIPT; break;
     case ST_G_VALUES: k_g_values<<<grid, block, 0, s>>>(st); cls = PC_TRANSCRIPT; break;
     default: break;
@@ -264,6 +360,16 @@ namespace {
 
 constexpr uint32_t kGSweepTiles = 65535u * 8;
 constexpr double kE = 32.0;
+
+// Phase-2 tables above 2^14 entries get their first round in the pass that makes
+// them (2^22 entries: 175 + 112 us -> 150); below, the rounds with a product per
+// thread are faster than two entries in one thread. The phase-1 tables do not:
+// their gate walks wait for gathers, and two of them in a thread cost more (97 us
+// for 2^20 entries) than the pass saved (47 + 36).
+constexpr uint32_t kGFuseMinLog = kWideMaxLogHalf + 1;
+constexpr uint32_t kGP2Tiles = 4096;       // a thread's column products serve several entries
+constexpr uint32_t kGP2RoundTiles = 2048;  // (512: 2 % of a proof of 2^20 gates x 8 layers slower)
+constexpr uint32_t kGBlocksPerStep = 64;  // source blocks of one ST_G_BLOCKS
 
 uint32_t g_tiles(uint64_t n) {
   uint64_t g = (n + kBlock - 1) / kBlock;
@@ -530,8 +636,9 @@ static void emit_general_layer(Program& pg, const gkr_circuit& c, uint32_t i, co
     Fr* outs[2] = {gw.EL, gw.EC};
     g_eq(pg, 2, bits, pts, scl, outs);
   }
+  const bool fuse = rho > kGFuseMinLog && rho > n;
   {
-    Step st = g_mk(ST_G_P2, g_tiles(1ull << rho));
+    Step st = g_mk(ST_G_P2, std::min(g_tiles(1ull << rho), kGP2Tiles));
     st.p[0] = gw.T;
     st.p[1] = gw.EL;
     st.p[2] = gw.EC;
@@ -543,13 +650,22 @@ static void emit_general_layer(Program& pg, const gkr_circuit& c, uint32_t i, co
     st.u[0] = n;
     st.q[0] = 1ull << rho;
     st.bytes = kE * ((double)(L.recs.size() << n) + 2.0 * (1ull << rho));
-    st.mulmods = (double)(L.recs.size() << n) + 4.0 * (1ull << rho);
+    st.mulmods = (double)(L.recs.size() << n) + 3.0 * (1ull << rho);
+    if (fuse) {
+      st.type = ST_G_P2_ROUND;
+      st.q[0] = 1ull << (rho - 1);
+      st.ntiles = std::min(g_tiles(st.q[0]), kGP2RoundTiles);
+      st.p[8] = gw.R[i]; st.p[9] = S; st.p[10] = gw.w.partials; st.p[11] = ry; st.p[12] = proof + off_p2;
+      st.bytes += kE * (double)(1ull << rho);
+      st.mulmods += (double)(1ull << rho);
+    }
     pg.steps.push_back(st);
   }
   {
     const Fr* src[3] = {gw.R[i], gw.w.G, gw.w.H};
     Fr* dst[3] = {gw.w.Wf, gw.w.G, gw.w.H};
-    emit_phase_a(pg, src, dst, rho, S, gw.w.partials, ry, proof + off_p2, &S->scratch[1], proof + off_vy, tun);
+    emit_phase_a(pg, src, dst, rho, S, gw.w.partials, ry, proof + off_p2, &S->scratch[1], proof + off_vy, tun,
+                 fuse ? 1 : 0);
   }
   // the source blocks' values at the local part of r_y
   {
@@ -560,8 +676,20 @@ static void emit_general_layer(Program& pg, const gkr_circuit& c, uint32_t i, co
     g_eq(pg, 2, bits, pts, scl, outs);
   }
   const uint64_t bsize = 1ull << (L.tau + n);
-  for (size_t b = 0; b < L.sources.size(); ++b)
-    pg.wsum(gw.R[i] + b * bsize, gw.EqL, gw.EqC, n, bsize, gw.w.partials, S, vals + 1 + b, tun);
+  for (size_t b = 0; b < L.sources.size(); b += kGBlocksPerStep) {
+    const uint32_t nb = (uint32_t)std::min<size_t>(kGBlocksPerStep, L.sources.size() - b);
+    // four entries or more per thread, at most 512 workgroups (of at least one per block)
+    const uint64_t units = std::max<uint64_t>(1, bsize >> 10), most = std::max<uint64_t>(1, 512 / nb);
+    const uint32_t tpb = (uint32_t)std::min(units, most), xb = n > 8 ? 1u << (n - 8) : 1u;
+    Step st = g_mk(ST_G_BLOCKS, nb * tpb);
+    st.p[0] = gw.R[i] + b * bsize; st.p[1] = gw.EqL; st.p[2] = gw.EqC; st.p[3] = gw.w.partials; st.p[4] = S;
+    st.p[5] = vals + 1 + b;
+    st.u[0] = n; st.u[1] = nb; st.u[2] = tpb;
+    st.u[3] = (uint32_t)std::min<uint64_t>(1ull << L.tau, std::max<uint32_t>(1, tpb / xb));
+    st.q[0] = 1ull << L.tau;
+    st.bytes = kE * nb * bsize; st.mulmods = 0.5 * nb * bsize;
+    pg.steps.push_back(st);
+  }
   {
     Step st = g_mk(ST_G_VALUES, 1);
     st.p[0] = S;

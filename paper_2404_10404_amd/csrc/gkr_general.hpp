@@ -60,7 +60,8 @@ struct Tuning;
 // Shared emission (gkr_api.hip): one FormA phase (rounds, then the tail), and
 // the statement binding followed by the output point and claim.
 void emit_phase_a(Program& pg, const Fr* const* src0, Fr* const* dst, uint32_t nrounds, DevState* S, Fr* partials,
-                  Fr* r_out, uint32_t* msg, Fr* final_out, uint32_t* proof_value, const Tuning& tun);
+                  Fr* r_out, uint32_t* msg, Fr* final_out, uint32_t* proof_value, const Tuning& tun,
+                  uint32_t first_round = 0);
 void emit_statement_and_output_claim(Program& pg, const gkr_circuit& c, const Workspace& w, const gkr_fr* d_inputs,
                                      const gkr_fr* d_outputs, uint64_t seed, const Tuning& tun);
 

@@ -23,6 +23,10 @@ constexpr uint32_t kMaxRoundBlocks = 4096;  // cap on workgroups of a reduction 
 // thread) only while its table is small: at most 2^9 pairs 79.4 ms, 2^13 85.2, 2^5 79.2.
 constexpr uint32_t kLockTailLog = 2;         // largest table (log2) of a tail
 constexpr uint32_t kLockWideMaxLogHalf = 9;  // most pairs (log2) of a wide round
+// Phase-1 tables with a product chain per gate (ST_W_P1_GATES) go further than in a
+// plain proof: the chain of all gates of an entry in one thread held up every
+// other proof (up to 2^16 pairs 59.8 ms, 2^13 65.5, 2^18 63.1).
+constexpr uint32_t kLockP1MaxLogHalf = 16;
 constexpr uint32_t kTailMaxLog = 7;       // largest table (log2) a pipelined tail evaluates
 constexpr int kMaxPartialValues = 2;    // reduced values per workgroup
 constexpr uint32_t kChunkWords = 256;   // 1 KiB SHA-256 leaf chunk of a tree digest
@@ -104,6 +108,8 @@ enum StepType : uint32_t {
   ST_G_P2,
   ST_G_LAYER_BEGIN,
   ST_G_VALUES,
+  ST_G_P2_ROUND,
+  ST_G_BLOCKS,
   ST_G_END,
   // The Goldilocks-field prover: launched by launch_gl_step, plain path only.
   ST_GL_FORWARD = 96,
