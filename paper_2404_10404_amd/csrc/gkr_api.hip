@@ -553,7 +553,7 @@ void emit_layer(Program& pg, const gkr_circuit& c, uint32_t i, const Workspace& 
   const bool split = pg.plain() && tun.matrix_cores && split_applies(n, sg1);
   if (split) {
     emit_phase1_split(pg, w, c.wiring[i], W, n, sg1, 1ull << sg, c.mul_gates[i], rx, proof, tun);
-  } else if (pg.wide() && s1 > 1 && s1 - 1 <= kWideMaxLogHalf &&
+  } else if (pg.wide() && s1 > 1 && s1 - 1 <= (pg.plain() ? kWideMaxLogHalf : kLockP1MaxLogHalf) &&
              (1ull << c.s(i)) <= (uint64_t)c.plan.ychunks << n) {
     // a product chain per gate, its result in wpart, then the sums and round 1
     pg.p1_wide(W, w.G, w.H, c.wiring[i], w.aU, w.bV, w.Cu, w.Cv, w.wpart, n, 1ull << (s1 - 1), 1ull << c.s(i), S,
