@@ -446,7 +446,7 @@ void Program::copy_contract(const Fr* W, const Fr* U, const Fr* V, Fr* Pt, Fr* Q
   steps.push_back(st);
 }
 void Program::local_contract(const Fr* W, const Fr* EqR, Fr* part, uint32_t n, uint64_t rows, uint32_t R) {
-  const uint64_t xb = ((1ull << n) + kBlock - 1) / kBlock;
+  const uint64_t xb = n > 6 ? 1ull << (n - 6) : 1;
   Step st = mk(ST_LOCAL_CONTRACT, (uint32_t)std::min<uint64_t>(xb * R, kSweepTiles));
   st.p[0] = W; st.p[1] = EqR; st.p[2] = part; st.u[0] = n; st.u[1] = R; st.q[0] = rows;
   const double elems = (double)(rows << n);
@@ -483,7 +483,12 @@ void Program::state_import(DevState* S, const uint8_t* in) {
 }
 
 void Program::run(hipStream_t s) const {
-  for (const Step& st : steps) {
+  for (size_t k = 0; k < steps.size(); ++k) {
+    const Step& st = steps[k];
+    if (k + 1 < steps.size() && steps[k + 1].join && launch_pair(st, steps[k + 1], s)) {
+      ++k;
+      continue;
+    }
     if (st.type >= ST_W_ROUND_A) launch_wide_step(st, s);
     else if (st.type >= ST_S_SMALL) launch_split_step(st, s);
     else if (st.type >= ST_CC_BUILD) launch_cc_step(st, s);
@@ -595,11 +600,15 @@ void emit_layer(Program& pg, const gkr_circuit& c, uint32_t i, const Workspace& 
     pg.eq(1, bits, pts, scl, outs);
   }
   pg.local_values(w.EqR, w.Ka, w.Kb, 1ull << sg1, S, w.partials);
-  // with few columns four rows or more per thread, and at most 512 chunks
-  const uint64_t few = std::min<uint64_t>(c.plan.ychunks, std::min<uint64_t>(512, std::max<uint64_t>(1, (1ull << s1) >> 10)));
-  const uint32_t chunks = n < 8 ? (uint32_t)few : c.plan.ychunks;
+  // a workgroup takes 2^min(n, 6) columns of a chunk: about 2^10 workgroups, with four
+  // entries or more per thread
+  const uint64_t entries = 1ull << s1, col_blocks = n > 6 ? 1ull << (n - 6) : 1;
+  const uint32_t chunks = (uint32_t)std::min<uint64_t>(
+      c.plan.ychunks, std::max<uint64_t>(1, std::min<uint64_t>(n < 6 ? 512 : 1024, entries >> 10) / col_blocks));
   pg.local_contract(W, w.EqR, w.wpart, n, 1ull << sg1, chunks);
-  pg.steps.back().join = 1;  // independent of the local values
+  // Independent of the local values; in one kernel the contraction holds 148 registers
+  // instead of 97, which costs a big one more than a launch (2^26 entries x 24 layers: 2.7 ms).
+  pg.steps.back().join = entries <= 1ull << 22;
   pg.copy_tables(w.wpart, chunks, w.U, w.V, w.Fa, w.Fb, S, w.Wc, w.Fc, w.Kc, 1ull << n);
   Fr* tc[3] = {w.Wc, w.Fc, w.Kc};
   const Fr* tc_src[3] = {w.Wc, w.Fc, w.Kc};

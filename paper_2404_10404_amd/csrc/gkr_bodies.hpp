@@ -1291,58 +1291,38 @@ __device__ __forceinline__ void body_copy_contract(const Step& st, uint32_t tile
 }
 
 // ST_LOCAL_CONTRACT: column sums over the sub-circuit variables, first stage:
-// part[c * R + k] = sum_{y in chunk k} EqR[y] W[y,c] for R = u1 chunks of rows;
-// one thread per (column, chunk), tile t = column block (t % xb) and chunk (t / xb).
-// With fewer columns than threads (n < 8) a chunk's rows are spread over the 2^(8-n)
-// threads of a column, whose sums are added in the workgroup: a thread per column
-// left most of a workgroup idle and needed up to 2^15 chunks (2^18 entries in one
-// column: 512 additions in a row in ST_COPY_TABLES).
+// part[c * R + k] = sum_{y in chunk k} EqR[y] W[y,c] for R = u1 chunks of rows.
+// Tile t = column block (t % xb) of 2^min(n, 6) columns and chunk (t / xb); the rows
+// of a chunk are spread over the threads of a column, whose sums are added in the
+// workgroup. (A thread per column left most of a workgroup idle with few copies,
+// and left the second stage up to 512 additions in a row.)
 // p0 W, p1 EqR, p2 part, u0 n, u1 R, q0 rows.
 __device__ __forceinline__ void body_local_contract(const Step& st, uint32_t tile, uint32_t ntiles) {
   const Fr* __restrict__ W = P<const Fr*>(st, 0);
   const Fr* __restrict__ EqR = P<const Fr*>(st, 1);
   Fr* __restrict__ part = P<Fr*>(st, 2);
   const uint32_t n = st.u[0], R = st.u[1];
-  const uint64_t rows = st.q[0], ncop = 1ull << n;
-  const uint64_t per_chunk = (rows + R - 1) / R;
-  if (n < 8) {
-    __shared__ Fr wave_sums[kBlock];
-    const uint32_t col = threadIdx.x & (uint32_t)(ncop - 1), step = kBlock >> n;
-    for (uint64_t k = tile; k < R; k += ntiles) {
-      const uint64_t y1 = (k + 1) * per_chunk < rows ? (k + 1) * per_chunk : rows;
-      Fr acc = fr_zero();
-      for (uint64_t ya = k * per_chunk + (threadIdx.x >> n); ya < y1; ya += 16ull * step) {
-        FrCols aw = frc_zero();
-        for (uint64_t y = ya; y < y1 && y < ya + 16ull * step; y += step)
-          frc_mac(aw, ldf(EqR, y), ldf(W, (y << n) | col));
-        acc = fr_add(acc, frw_reduce<16>(frc_wide(aw)));
-      }
-      for (uint32_t off = 32; off >= ncop; off >>= 1) acc = fr_add(acc, shfl_xor_fr(acc, off));
-      __syncthreads();  // (the previous chunk's sums are read)
-      wave_sums[threadIdx.x] = acc;
-      __syncthreads();
-      if (threadIdx.x < ncop) {
-        const uint32_t gap = ncop < 64 ? 64 : (uint32_t)ncop;  // the next copy of this column's sums
-        for (uint32_t i = threadIdx.x + gap; i < kBlock; i += gap) acc = fr_add(acc, wave_sums[i]);
-        stf(part, (uint64_t)col * R + k, acc);
-      }
-    }
-    return;
-  }
-  const uint64_t xb = (ncop + kBlock - 1) / kBlock;
+  const uint32_t clog = n < 6 ? n : 6, cols = 1u << clog, step = kBlock >> clog;
+  const uint64_t rows = st.q[0], xb = 1ull << (n - clog), per = (rows + R - 1) / R;
+  __shared__ Fr wave_sums[kBlock / 64][64];
   for (uint64_t t = tile; t < xb * R; t += ntiles) {
-    const uint64_t c = (t % xb) * kBlock + threadIdx.x;
-    const uint64_t k = t / xb;
-    if (c >= ncop) continue;
-    const uint64_t y0 = k * per_chunk, y1 = (y0 + per_chunk < rows) ? y0 + per_chunk : rows;
+    const uint64_t c = (t % xb) * cols + (threadIdx.x & (cols - 1)), k = t / xb;
+    const uint64_t y0 = k * per, y1 = y0 + per < rows ? y0 + per : rows;
     Fr acc = fr_zero();
-    for (uint64_t ya = y0; ya < y1; ya += 16) {
-      const uint64_t yb = ya + 16 < y1 ? ya + 16 : y1;
+    for (uint64_t ya = y0 + (threadIdx.x >> clog); ya < y1; ya += 16ull * step) {
       FrCols aw = frc_zero();
-      for (uint64_t y = ya; y < yb; ++y) frc_mac(aw, ldf(EqR, y), ldf(W, (y << n) | c));
+      for (uint64_t y = ya; y < y1 && y < ya + 16ull * step; y += step) frc_mac(aw, ldf(EqR, y), ldf(W, (y << n) | c));
       acc = fr_add(acc, frw_reduce<16>(frc_wide(aw)));
     }
-    stf(part, c * R + k, acc);
+    for (uint32_t off = 32; off >= cols; off >>= 1) acc = fr_add(acc, shfl_xor_fr(acc, off));
+    __syncthreads();  // (the previous chunk's sums are read)
+    wave_sums[threadIdx.x >> 6][threadIdx.x & 63] = acc;
+    __syncthreads();
+    if (threadIdx.x < cols) {
+#pragma unroll
+      for (int w = 1; w < kBlock / 64; ++w) acc = fr_add(acc, wave_sums[w][threadIdx.x]);
+      stf(part, c * R + k, acc);
+    }
   }
 }
 

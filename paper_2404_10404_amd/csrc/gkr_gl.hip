@@ -163,6 +163,8 @@ __device__ void sha256_words(const uint32_t* in, uint64_t len, int swap, uint32_
 
 #define GTID ((uint64_t)blockIdx.x * blockDim.x + threadIdx.x)
 #define GSTRIDE ((uint64_t)gridDim.x * blockDim.x)
+#define GTILE_ID ((uint64_t)tile * kBlock + threadIdx.x)
+#define GTILE_STRIDE ((uint64_t)ntiles * kBlock)
 
 // ST_GL_FORWARD: V[z*2^n + c] = W[x_z*2^n + c] (+ or *) W[y_z*2^n + c].
 // p0 W, p1 V, p2 gate records (x | type << 31, y), u0 n, q0 count.
@@ -372,13 +374,13 @@ __global__ void __launch_bounds__(kBlock) k_gl_copy_weights(Step st) {
 // ST_GL_P2T: the 2^sigma phase-2 tables for y < q0 from the wiring by y.
 // p0 yrow, p1 yent (z, x | type << 31), p2 aU, p3 bV, p4 EL, p5 S,
 // p6 Fa, p7 Fb, p8 Ka, p9 Kb, p10 Ks.
-__global__ void __launch_bounds__(kBlock) k_gl_p2t(Step st) {
+__device__ __forceinline__ void body_gl_p2t(const Step& st, uint32_t tile, uint32_t ntiles) {
   const uint32_t* __restrict__ yrow = P<const uint32_t*>(st, 0);
   const uint2* __restrict__ yent = P<const uint2*>(st, 1);
   const uint64_t *aU = P<const uint64_t*>(st, 2), *bV = P<const uint64_t*>(st, 3), *EL = P<const uint64_t*>(st, 4);
   const GlState* S = P<const GlState*>(st, 5);
   const uint64_t vx = S->vx, su = S->su, sv = S->sv;
-  for (uint64_t y = GTID; y < st.q[0]; y += GSTRIDE) {
+  for (uint64_t y = GTILE_ID; y < st.q[0]; y += GTILE_STRIDE) {
     uint64_t mu = 0, mv = 0, au = 0, av = 0;
     const uint32_t k1 = yrow[y + 1];
     for (uint32_t k = yrow[y]; k < k1; ++k) {
@@ -401,6 +403,7 @@ __global__ void __launch_bounds__(kBlock) k_gl_p2t(Step st) {
     gst(P<uint64_t*>(st, 10), y, gl_add(gl_mul(su, ka), gl_mul(sv, kb)));
   }
 }
+__global__ void __launch_bounds__(kBlock) k_gl_p2t(Step st) { body_gl_p2t(st, blockIdx.x, gridDim.x); }
 
 // Sum over the wave; valid in every lane.
 __device__ __forceinline__ uint64_t gl_wave_sum(uint64_t v) {
@@ -412,12 +415,12 @@ __device__ __forceinline__ uint64_t gl_wave_sum(uint64_t v) {
 // ST_GL_COPY_CONTRACT: P[y] = sum_c U[c] W[y 2^n + c], Q[y] likewise with V,
 // one wave per row y < q0, two adjacent copies per lane (16-byte loads) from 2^7
 // copies up. p0 W, p1 U, p2 V, p3 P, p4 Q, u0 n.
-__global__ void __launch_bounds__(kBlock) k_gl_copy_contract(Step st) {
+__device__ __forceinline__ void body_gl_copy_contract(const Step& st, uint32_t tile, uint32_t ntiles) {
   const uint64_t *W = P<const uint64_t*>(st, 0), *U = P<const uint64_t*>(st, 1), *V = P<const uint64_t*>(st, 2);
   const uint32_t n = st.u[0];
   const uint64_t ncop = 1ull << n;
   const uint32_t lane = threadIdx.x & 63;
-  const uint64_t wave = GTID >> 6, nwaves = GSTRIDE >> 6;
+  const uint64_t wave = GTILE_ID >> 6, nwaves = GTILE_STRIDE >> 6;
   for (uint64_t y = wave; y < st.q[0]; y += nwaves) {
     uint64_t p = 0, q = 0;
     if (n >= 7) {
@@ -441,10 +444,11 @@ __global__ void __launch_bounds__(kBlock) k_gl_copy_contract(Step st) {
     }
   }
 }
+__global__ void __launch_bounds__(kBlock) k_gl_copy_contract(Step st) { body_gl_copy_contract(st, blockIdx.x, gridDim.x); }
 
 // ST_GL_LOCAL_VALUES (one workgroup): Ka~ = sum_y EqR[y] Ka[y], Kb~ likewise,
 // y < q0, into S->ka_f, S->kb_f. p0 EqR, p1 Ka, p2 Kb, p3 S.
-__global__ void __launch_bounds__(kBlock) k_gl_local_values(Step st) {
+__device__ __forceinline__ void body_gl_local_values(const Step& st, uint32_t, uint32_t) {
   const uint64_t *E = P<const uint64_t*>(st, 0), *Ka = P<const uint64_t*>(st, 1), *Kb = P<const uint64_t*>(st, 2);
   GlState* S = P<GlState*>(st, 3);
   uint64_t acc[2] = {0, 0};
@@ -459,15 +463,16 @@ __global__ void __launch_bounds__(kBlock) k_gl_local_values(Step st) {
     S->kb_f = acc[1];
   }
 }
+__global__ void __launch_bounds__(kBlock) k_gl_local_values(Step st) { body_gl_local_values(st, blockIdx.x, gridDim.x); }
 
 // ST_GL_LOCAL_CONTRACT: part[ch 2^n + c] = sum over the 2^u1 rows y of chunk
 // ch of EqR[y] W[y 2^n + c], for ch 2^n + c < q0. p0 W, p1 EqR, p2 part, u0 n.
-__global__ void __launch_bounds__(kBlock) k_gl_local_contract(Step st) {
+__device__ __forceinline__ void body_gl_local_contract(const Step& st, uint32_t tile, uint32_t ntiles) {
   const uint64_t *W = P<const uint64_t*>(st, 0), *E = P<const uint64_t*>(st, 1);
   uint64_t* part = P<uint64_t*>(st, 2);
   const uint32_t n = st.u[0], lr = st.u[1];
   const uint64_t mask = (1ull << n) - 1;
-  for (uint64_t g = GTID; g < st.q[0]; g += GSTRIDE) {
+  for (uint64_t g = GTILE_ID; g < st.q[0]; g += GTILE_STRIDE) {
     const uint64_t ch = g >> n, c = g & mask;
     const uint64_t y0 = ch << lr, y1 = y0 + (1ull << lr);
     uint64_t acc = 0;
@@ -475,6 +480,7 @@ __global__ void __launch_bounds__(kBlock) k_gl_local_contract(Step st) {
     gst(part, g, acc);
   }
 }
+__global__ void __launch_bounds__(kBlock) k_gl_local_contract(Step st) { body_gl_local_contract(st, blockIdx.x, gridDim.x); }
 
 // ST_GL_COPY_TABLES: for c < q0, Wc[c] = sum of the u0 chunk partials,
 // Fc = U Fa~ + V Fb~, Kc = U Ka~ + V Kb~ (Fa~, Fb~ the first entries of the
@@ -1137,6 +1143,28 @@ static size_t gl_tail_lds(const Step& st, int nt) {
 // 2^13 for three tables).
 static uint32_t gl_tail_log(const Tuning& tun) { return std::min<uint32_t>(tun.tail_log + 3, 12); }
 
+// Two independent steps in one launch (Step::join), as in the BN254 prover.
+__global__ void __launch_bounds__(kBlock) k_gl_p2_pair(Step a, Step b) {
+  if (blockIdx.x < a.ntiles) body_gl_p2t(a, blockIdx.x, a.ntiles);
+  else body_gl_copy_contract(b, blockIdx.x - a.ntiles, b.ntiles);
+}
+__global__ void __launch_bounds__(kBlock) k_gl_local_pair(Step a, Step b) {
+  if (blockIdx.x < a.ntiles) body_gl_local_values(a, blockIdx.x, a.ntiles);
+  else body_gl_local_contract(b, blockIdx.x - a.ntiles, b.ntiles);
+}
+
+bool launch_gl_pair(const Step& st, const Step& next, hipStream_t s) {
+  const bool p2 = st.type == ST_GL_P2T && next.type == ST_GL_COPY_CONTRACT;
+  if (!p2 && !(st.type == ST_GL_LOCAL_VALUES && next.type == ST_GL_LOCAL_CONTRACT)) return false;
+  const int tok = prof_begin(s);
+  const dim3 grid(st.ntiles + next.ntiles), block(kBlock);
+  if (p2) k_gl_p2_pair<<<grid, block, 0, s>>>(st, next);
+  else k_gl_local_pair<<<grid, block, 0, s>>>(st, next);
+  if (tok >= 0)
+    prof_end(tok, s, p2 ? PC_COPY_CONTRACT : PC_LOCAL_CONTRACT, st.bytes + next.bytes, st.mulmods + next.mulmods);
+  return true;
+}
+
 void launch_gl_step(const Step& st, hipStream_t s) {
   const int tok = prof_begin(s);
   const dim3 grid(st.ntiles), block(kBlock);
@@ -1500,6 +1528,7 @@ void gl_emit_proof(std::vector<Step>& steps, const gkr_circuit& c, const GlWs& w
       steps.push_back(st);
     }
     gl_copy_contract(steps, w.layer[i + 1], w.U, w.V, w.P, w.Q, n, rows);
+    steps.back().join = split ? 0 : 1;  // independent of the phase-2 tables
     {
       const uint64_t* src[5] = {w.P, w.Fa, w.Q, w.Fb, w.Ks};
       uint64_t* dst[5] = {w.P, w.Fa, w.Q, w.Fb, w.Ks};
@@ -1526,6 +1555,7 @@ void gl_emit_proof(std::vector<Step>& steps, const gkr_circuit& c, const GlWs& w
       st.p[0] = w.layer[i + 1]; st.p[1] = w.EqR; st.p[2] = w.wpart; st.u[0] = n; st.u[1] = lr;
       st.q[0] = (uint64_t)R * ncop;
       st.bytes = kGE * (double)(rows * ncop + (uint64_t)R * ncop); st.mulmods = (double)(rows * ncop);
+      st.join = 1;  // independent of the local values
       steps.push_back(st);
     }
     {

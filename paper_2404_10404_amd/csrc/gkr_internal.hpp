@@ -179,7 +179,7 @@ enum StepType : uint32_t {
 
 struct Step {
   uint32_t type : 16;
-  uint32_t join : 16;  // 1: independent of the step before it (a lockstep batch runs both together)
+  uint32_t join : 16;  // 1: independent of the step before it (both may run in one launch)
   uint32_t ntiles;     // workgroups
   uint32_t u[6];     // small integers
   uint64_t q[4];     // sizes

@@ -33,6 +33,10 @@ struct RoundPtrs {
 // Launch one step as its own kernel (grid = st.ntiles workgroups).
 void launch_step(const Step& st, hipStream_t s);
 
+// Launch two independent steps as one kernel, if there is one for their types: the
+// workgroups of st come first, then those of next.
+bool launch_pair(const Step& st, const Step& next, hipStream_t s);
+
 // One job of the persistent batch kernel: its step program and counters
 // (ctr[0] current step, ctr[1..nsteps] claimed tiles, ctr[1+nsteps..] done tiles).
 struct BatchJobDev {
