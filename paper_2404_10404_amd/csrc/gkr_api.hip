@@ -210,9 +210,12 @@ void Program::from_mont(const Fr* in, gkr_fr* out, uint64_t n) {
   st.bytes = 2 * kE * n; st.mulmods = (double)n;
   steps.push_back(st);
 }
-void Program::forward(const Fr* W, Fr* V, const uint2* gates, uint32_t n, uint64_t count, uint64_t mul_gates) {
+void Program::forward(const Fr* W, Fr* V, const uint2* gates, uint32_t n, uint32_t sigma, uint32_t sigma_in,
+                      uint64_t mul_gates) {
+  const uint64_t count = 1ull << (sigma + n);
   Step st = mk(ST_FORWARD, tiles_for(count, kSweepTiles));
-  st.p[0] = W; st.p[1] = V; st.p[2] = gates; st.u[0] = n; st.q[0] = count;
+  st.p[0] = W; st.p[1] = V; st.p[2] = gates; st.q[0] = count;
+  st.u[0] = n; st.u[1] = sigma; st.u[2] = forward_block_log(n, sigma_in);
   st.bytes = 3 * kE * count; st.mulmods = (double)mul_gates;
   steps.push_back(st);
 }
@@ -618,7 +621,8 @@ void emit_layer(Program& pg, const gkr_circuit& c, uint32_t i, const Workspace& 
 // Forward evaluation of every layer from Montgomery inputs in layer[d].
 static void emit_forward(Program& pg, const gkr_circuit& c, const Workspace& w) {
   for (int i = (int)c.depth - 1; i >= 0; --i)
-    pg.forward(w.layer[i + 1], w.layer[i], c.wiring[i].gates, c.n, 1ull << c.s(i), (uint64_t)c.mul_gates[i] << c.n);
+    pg.forward(w.layer[i + 1], w.layer[i], c.wiring[i].gates, c.n, c.sigma[i], c.sigma[i + 1],
+               (uint64_t)c.mul_gates[i] << c.n);
 }
 
 // g and the output claim V_0~(g) (into S->scratch[0]); needs layer[0] in Montgomery form.

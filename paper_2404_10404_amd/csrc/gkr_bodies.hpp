@@ -152,19 +152,20 @@ __device__ __forceinline__ void body_from_mont(const Step& st, uint32_t tile, ui
 }
 
 // ST_FORWARD: V_i[z*2^n + c] = W[x_z*2^n + c] (+ or *) W[y_z*2^n + c].
-// p0 W, p1 V, p2 gate records, u0 n, q0 count.
+// p0 W, p1 V, p2 gate records, u0 n, u1 log2 gates, u2 log2 columns of a block, q0 count.
+// Bound by memory; a row is read twice on average (see forward_block_log).
 __device__ __forceinline__ void body_forward(const Step& st, uint32_t tile, uint32_t ntiles) {
   const Fr* __restrict__ W = P<const Fr*>(st, 0);
   Fr* __restrict__ V = P<Fr*>(st, 1);
   const uint2* __restrict__ gates = P<const uint2*>(st, 2);
   const uint32_t n = st.u[0];
-  const uint64_t mask = (1ull << n) - 1;
   for (uint64_t g = GTID; g < st.q[0]; g += GSTRIDE) {
-    const uint64_t z = g >> n, c = g & mask;
-    const uint2 gate = gates[z];
+    const RowCol zc = block_order(g, st.u[1], st.u[2]);
+    const uint64_t c = zc.col;
+    const uint2 gate = gates[zc.row];
     const uint64_t x = gate.x & 0x7fffffffu, y = gate.y;
     const Fr a = ldf(W, (x << n) | c), b = ldf(W, (y << n) | c);
-    stf(V, g, (gate.x >> 31) ? fr_mul(a, b) : fr_add(a, b));
+    stf(V, zc.row << n | c, (gate.x >> 31) ? fr_mul(a, b) : fr_add(a, b));
   }
 }
 

@@ -104,6 +104,14 @@ __device__ __forceinline__ Fr opaque(Fr x) {
   return x;
 }
 
+// Entry i of a 2^rlog-row table taken in blocks of 2^blog columns.
+struct RowCol {
+  uint64_t row, col;
+};
+__device__ __forceinline__ RowCol block_order(uint64_t i, uint32_t rlog, uint32_t blog) {
+  return {(i >> blog) & ((1ull << rlog) - 1), (i >> (rlog + blog)) << blog | (i & ((1ull << blog) - 1))};
+}
+
 template <class T>
 __device__ __forceinline__ T P(const Step& st, int i) {
   return reinterpret_cast<T>(const_cast<void*>(st.p[i]));

@@ -189,6 +189,13 @@ struct Step {
   double mulmods;    // field products (timing reports only)
 };
 
+// Columns (log2) of a block of the forward pass over rows_log + n table entries of
+// 32 bytes: all of a row if the table stays in the 256 MiB last-level cache, else
+// 2^8 columns of every row before the next block, so a row's second read is from
+// that cache (2^14 rows of 2^12 copies: 1,123 -> 960 us a layer; 2^5..2^9 columns
+// alike, 2^10 1,040).
+inline uint32_t forward_block_log(uint32_t n, uint32_t rows_log) { return n <= 8 || rows_log + n + 5 <= 27 ? n : 8; }
+
 // Tunables of the round schedule (autotuned; see gkr_tuning.*).
 struct Tuning {
   uint32_t tail_log;          // single-workgroup tail once a table has <= 2^tail_log entries

@@ -42,7 +42,8 @@ struct Program {
 
   void to_mont(const gkr_fr* in, Fr* out, uint64_t n);
   void from_mont(const Fr* in, gkr_fr* out, uint64_t n);
-  void forward(const Fr* W, Fr* V, const uint2* gates, uint32_t n, uint64_t count, uint64_t mul_gates);
+  void forward(const Fr* W, Fr* V, const uint2* gates, uint32_t n, uint32_t sigma, uint32_t sigma_in,
+               uint64_t mul_gates);
   void digests(const DigestJob* jobs, int count, const Workspace& w);
   void transcript_begin(DevState* S, const Words8& seed_state, const uint32_t* circ, const uint32_t* din,
                         const uint32_t* dout);
