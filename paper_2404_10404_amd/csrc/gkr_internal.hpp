@@ -169,6 +169,7 @@ enum StepType : uint32_t {
   ST_S_P2_RAW,
   ST_S_P2_FINAL,
   ST_S_HANDOFF,
+  ST_S_WIDE_ROUND,
   // Rounds over small tables, one product per thread: launched by
   // launch_wide_step, plain path only.
   ST_W_ROUND_A = 240,

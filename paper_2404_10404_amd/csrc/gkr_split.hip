@@ -208,6 +208,65 @@ __global__ void __launch_bounds__(kBlock, 3) k_s_round(Step st) {
                                 P<uint32_t*>(st, 12));
 }
 
+// ST_S_WIDE_ROUND: ST_S_ROUND for small tables, with a product per thread as in the
+// wide rounds: wave 2 g + t of a big tile folds table t (W, Gm) of its pairs
+// 32 g .. 32 g + 31, the five waves of a small tile fold the five small tables of 32
+// pairs; wave g then evaluates. Pointers and sizes as in ST_S_ROUND. A round with
+// few pairs is one chain of products per thread otherwise (27 us, here 15).
+__global__ void __launch_bounds__(64 * 5) k_s_wide_round(Step st) {
+  const uint32_t nb = st.u[1], wid = threadIdx.x >> 6, lane = threadIdx.x & 63, p = lane & 31;
+  const bool big = blockIdx.x < nb;
+  const Fr r = ldf(P<const Fr*>(st, 13), 0);
+  __shared__ Fr ent[5][64];
+  Fr v = fr_zero();
+  if (big && wid < 4) {
+    const uint64_t half = st.q[0], m = 2 * half;
+    const uint64_t b = (uint64_t)blockIdx.x * 64 + (wid >> 1) * 32 + p, e = lane < 32 ? b : b + half;
+    if (b < half) {
+      if ((wid & 1) == 0) {
+        v = fold_entry(r, ldf(P<const Fr*>(st, 0), e), ldf(P<const Fr*>(st, 0), e + m));
+        stf(P<Fr*>(st, 1), e, v);
+      } else {
+        Fr* G = P<Fr*>(st, 2);
+        const uint32_t k = st.u[2], x = (uint32_t)(e >> st.u[0]);
+        const bool f0 = row_active(P<const uint32_t*>(st, 3), k + 1, x);
+        const bool f1 = row_active(P<const uint32_t*>(st, 3), k + 1, x + (2u << (k - 1)));
+        if (f0 || f1) {
+          v = fold_entry(r, f0 ? ldf(G, e) : fr_zero(), f1 ? ldf(G, e + m) : fr_zero());
+          stf(G, e, v);
+        }
+      }
+    }
+  } else if (!big) {
+    const uint64_t half = st.q[1], m = 2 * half;
+    const uint64_t b = (uint64_t)(blockIdx.x - nb) * 32 + p, e = lane < 32 ? b : b + half;
+    if (b < half) {
+      Fr* t = P<Fr*>(st, 4);
+#pragma unroll
+      for (int k = 1; k < 5; ++k)
+        if (wid == (uint32_t)k) t = P<Fr*>(st, 4 + k);
+      v = fold_entry(r, ldf(t, e), ldf(t, e + m));
+      stf(t, e, v);
+    }
+  }
+  ent[wid][lane] = v;
+  __syncthreads();
+  if (wid < 2) {
+    auto at = [&](uint32_t k) {
+      const Fr lo = opaque(ent[k][p]);
+      return lane < 32 ? lo : opaque(fr_sub(fr_double(opaque(ent[k][32 + p])), lo));
+    };
+    Fr t = fr_mul(at(2 * wid), at(2 * wid + 1));
+    if (wid == 1 && !big) t = fr_add(t, at(4));
+    t = half_wave_sum(t);
+    if (p == 31) put_partial(P<Fr*>(st, 10), (2ull * blockIdx.x + wid) * 2 + (lane >> 5), t);
+    wait_vmem();
+  }
+  if (last_tile(&P<DevState*>(st, 9)->counter, gridDim.x))
+    finish_reduced_round<false>(P<const Fr*>(st, 10), 2 * gridDim.x, P<DevState*>(st, 9), P<Fr*>(st, 11),
+                                P<uint32_t*>(st, 12));
+}
+
 // ST_S_P2_RAW: the phase-2 wiring tables over y < q0, which need eq(rx, .) on
 // the sub-circuit variables only: Ma[y] = sum_{MUL z: y_z = y} aU[z] EL[x_z] (Mb
 // with bV), Aa and Ab over the ADD gates. p0 yrow, p1 yent, p2 aU, p3 bV, p4 EL,
@@ -286,6 +345,7 @@ void launch_split_step(const Step& st, hipStream_t s) {
     case ST_S_SMALL: k_s_small<<<grid, block, 0, s>>>(st); break;
     case ST_S_INIT_ROUND: k_s_init_round<<<grid, block, 0, s>>>(st); cls = PC_PHASE1_INIT; break;
     case ST_S_ROUND: k_s_round<<<grid, block, 0, s>>>(st); cls = PC_ROUND_A; break;
+    case ST_S_WIDE_ROUND: k_s_wide_round<<<grid, dim3(64 * 5), 0, s>>>(st); cls = PC_ROUND_A; break;
     case ST_S_P2_RAW: k_s_p2_raw<<<grid, block, 0, s>>>(st); cls = PC_PHASE2_TABLES; break;
     case ST_S_P2_FINAL: k_s_p2_final<<<grid, block, 0, s>>>(st); cls = PC_PHASE2_TABLES; break;
     case ST_S_HANDOFF: k_s_handoff<<<grid, block, 0, s>>>(st); break;
@@ -300,6 +360,9 @@ namespace {
 
 constexpr double kE = 32.0;
 constexpr uint32_t kSplitMinLogCopies = 8, kSplitMinLogRows = 10, kSplitMinLogWidth = 21;
+// Most pairs (log2) of a wide round: a layer of 2^22 gates took 2,000 us without,
+// 1,953 up to 2^12 pairs, 1,927 up to 2^14, 1,925 up to 2^15, 1,927 up to 2^16.
+constexpr uint32_t kSplitWideMaxLogHalf = 15;
 constexpr uint32_t kSplitBlocks = 768;  // workgroups of a round over (x, c): three per CU
 
 Step smk(uint32_t type, uint64_t items, uint64_t cap = 1u << 20) {
@@ -339,6 +402,11 @@ void emit_phase1_split(Program& pg, const Workspace& w, const LayerWiring& lw, c
     Step st = smk(j == 0 ? ST_S_INIT_ROUND : ST_S_ROUND, half, j == 0 ? 2 * kSplitBlocks : kSplitBlocks);
     st.u[0] = n; st.u[1] = st.ntiles; st.u[2] = sigma - j;
     st.ntiles += ns;
+    if (j > 0 && half <= 1ull << kSplitWideMaxLogHalf) {
+      st.type = ST_S_WIDE_ROUND;
+      st.u[1] = (uint32_t)((half + 63) / 64);
+      st.ntiles = st.u[1] + (uint32_t)((shalf + 31) / 32);
+    }
     st.q[0] = half; st.q[1] = shalf;
     st.p[9] = S; st.p[10] = w.partials; st.p[11] = rx + j; st.p[12] = proof + 24 * j;
     if (j == 0) {
