@@ -103,13 +103,15 @@ CLASS_KERNEL = {"round": "k_round_a", "round_sub": "k_round_b", "tail": "k_tail_
                 "local_contract": "k_local_contract", "digest": "k_digest", "g_gather": "k_g_gather",
                 "g_forward": "k_g_forward", "g_claim_tables": "k_g_ttable", "g_phase1_init": "k_g_p1",
                 "g_phase2_tables": "k_g_p2"}
-KERNEL_SOURCES = ["fr.hpp", "sha256.hpp", "gkr_device.hpp", "gkr_kernels.hpp", "gkr_bodies.hpp", "gkr_kernels.hip"]
+KERNEL_SOURCES = ["fr.hpp", "fr_row.hpp", "sha256.hpp", "sha256_wave.hpp", "gkr_device.hpp", "gkr_kernels.hpp",
+                  "gkr_bodies.hpp", "gkr_kernels.hip"]
 # The Goldilocks prover's classes and the sources its kernels are built from.
 GL_CLASS_KERNEL = {"round": "k_gl_round<3>", "round_sub": "k_gl_round<5>", "tail": "k_gl_tail<3>",
                    "tail_sub": "k_gl_tail<5>", "phase1_init": "k_gl_p1", "phase2_tables": "k_gl_p2t",
                    "forward": "k_gl_forward", "digest": "k_gl_digest", "copy_contract": "k_gl_copy_contract",
                    "local_contract": "k_gl_local_contract"}
-GL_KERNEL_SOURCES = ["fr.hpp", "sha256.hpp", "gkr_device.hpp", "gkr_kernels.hpp", "gkr_bodies.hpp", "gl.hpp", "gkr_gl.hip"]
+GL_KERNEL_SOURCES = ["fr.hpp", "fr_row.hpp", "sha256.hpp", "sha256_wave.hpp", "gkr_device.hpp", "gkr_kernels.hpp",
+                     "gkr_bodies.hpp", "gl.hpp", "gkr_gl.hip"]
 
 
 def kernel_sources_digest(sources=None):
@@ -441,8 +443,8 @@ def goldilocks_leg(gkr, steps, warmup, profile_steps, mac_peak_tops, bn254_ms=No
 
 
 VPD_CLASS_KERNEL = {"vpd_ntt": "k_vpd_ntt", "vpd_fri": "k_vpd_fold", "vpd_merkle": "k_vpd_leaves"}
-VPD_KERNEL_SOURCES = ["fr.hpp", "sha256.hpp", "gkr_device.hpp", "gkr_kernels.hpp", "gkr_bodies.hpp", "gkr_vpd.hpp",
-                      "gkr_vpd.hip"]
+VPD_KERNEL_SOURCES = ["fr.hpp", "fr_row.hpp", "sha256.hpp", "sha256_wave.hpp", "gkr_device.hpp", "gkr_kernels.hpp",
+                      "gkr_bodies.hpp", "gkr_vpd.hpp", "gkr_vpd.hip"]
 
 
 def committed_leg(gkr, steps, warmup, profile_steps, mac_peak_tops, plain_ms=None):

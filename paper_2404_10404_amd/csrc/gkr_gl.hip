@@ -10,9 +10,10 @@
 //   values         vx, vy absorbed with "GKRV" as 8 bytes
 // Elements are 8 bytes, so a wave's load of 64 consecutive entries is 512
 // bytes; a product is four 32 x 32 multiplies and the reduction of gl.hpp.
-// The kernels are written plainly (one kernel per step type, serial round
-// finishers, phase-2 tables materialised over the whole layer): the BN254
-// prover's factored phase 2 and two-chain finishers are not repeated here.
+// One kernel per step type. Phase 2 contracts the copy factors and big layers take
+// phase 1 with the addition gates contracted over the copies, as the BN254 prover
+// does; products are cheap here, so a round's finisher is one chain (the hash, spread
+// over a wave's lanes) and the small rounds of a phase run in one workgroup.
 #include <string.h>
 
 #include <algorithm>
@@ -422,22 +423,23 @@ __device__ __forceinline__ void body_gl_copy_contract(const Step& st, uint32_t t
   const uint32_t lane = threadIdx.x & 63;
   const uint64_t wave = GTILE_ID >> 6, nwaves = GTILE_STRIDE >> 6;
   for (uint64_t y = wave; y < st.q[0]; y += nwaves) {
-    uint64_t p = 0, q = 0;
+    GlAcc ps, qs;
     if (n >= 7) {
       for (uint64_t c = 2 * lane; c < ncop; c += 128) {
         const U64x2 w = gld2(W, (y << n) | c), u = gld2(U, c), v = gld2(V, c);
-        p = gl_add(p, gl_add(gl_mul(u.x, w.x), gl_mul(u.y, w.y)));
-        q = gl_add(q, gl_add(gl_mul(v.x, w.x), gl_mul(v.y, w.y)));
+        gl_mac(ps, u.x, w.x);
+        gl_mac(qs, v.x, w.x);
+        gl_mac(ps, u.y, w.y);
+        gl_mac(qs, v.y, w.y);
       }
     } else {
       for (uint64_t c = lane; c < ncop; c += 64) {
         const uint64_t w = gld(W, (y << n) | c);
-        p = gl_add(p, gl_mul(gld(U, c), w));
-        q = gl_add(q, gl_mul(gld(V, c), w));
+        gl_mac(ps, gld(U, c), w);
+        gl_mac(qs, gld(V, c), w);
       }
     }
-    p = gl_wave_sum(p);
-    q = gl_wave_sum(q);
+    const uint64_t p = gl_wave_sum(gl_acc_value(ps)), q = gl_wave_sum(gl_acc_value(qs));
     if (lane == 0) {
       gst(P<uint64_t*>(st, 3), y, p);
       gst(P<uint64_t*>(st, 4), y, q);
@@ -467,17 +469,32 @@ __global__ void __launch_bounds__(kBlock) k_gl_local_values(Step st) { body_gl_l
 
 // ST_GL_LOCAL_CONTRACT: part[ch 2^n + c] = sum over the 2^u1 rows y of chunk
 // ch of EqR[y] W[y 2^n + c], for ch 2^n + c < q0. p0 W, p1 EqR, p2 part, u0 n.
+// Two adjacent columns per thread (n >= 1). Bound by memory; with reduced
+// products and 8-byte loads 2^26 entries took 174 us.
 __device__ __forceinline__ void body_gl_local_contract(const Step& st, uint32_t tile, uint32_t ntiles) {
   const uint64_t *W = P<const uint64_t*>(st, 0), *E = P<const uint64_t*>(st, 1);
   uint64_t* part = P<uint64_t*>(st, 2);
   const uint32_t n = st.u[0], lr = st.u[1];
   const uint64_t mask = (1ull << n) - 1;
-  for (uint64_t g = GTILE_ID; g < st.q[0]; g += GTILE_STRIDE) {
+  if (n == 0) {
+    for (uint64_t g = GTILE_ID; g < st.q[0]; g += GTILE_STRIDE) {
+      GlAcc acc;
+      for (uint64_t y = g << lr; y < (g + 1) << lr; ++y) gl_mac(acc, gld(E, y), gld(W, y));
+      gst(part, g, gl_acc_value(acc));
+    }
+    return;
+  }
+  for (uint64_t g = 2 * GTILE_ID; g < st.q[0]; g += 2 * GTILE_STRIDE) {
     const uint64_t ch = g >> n, c = g & mask;
     const uint64_t y0 = ch << lr, y1 = y0 + (1ull << lr);
-    uint64_t acc = 0;
-    for (uint64_t y = y0; y < y1; ++y) acc = gl_add(acc, gl_mul(gld(E, y), gld(W, (y << n) | c)));
-    gst(part, g, acc);
+    GlAcc a, b;
+    for (uint64_t y = y0; y < y1; ++y) {
+      const U64x2 w = gld2(W, (y << n) | c);
+      const uint64_t e = gld(E, y);
+      gl_mac(a, e, w.x);
+      gl_mac(b, e, w.y);
+    }
+    gst2(part, g, U64x2{gl_acc_value(a), gl_acc_value(b)});
   }
 }
 __global__ void __launch_bounds__(kBlock) k_gl_local_contract(Step st) { body_gl_local_contract(st, blockIdx.x, gridDim.x); }
@@ -898,17 +915,17 @@ __global__ void __launch_bounds__(kBlock) k_gl_s_local2(Step st) {
   for (uint64_t g = 2 * GTID; g < st.q[0]; g += 2 * GSTRIDE) {
     const uint64_t ch = g >> n, c = g & mask;
     const uint64_t y0 = ch << lr, y1 = y0 + (1ull << lr);
-    U64x2 a = {0, 0}, b = {0, 0};
+    GlAcc ax, ay, bx, by;
     for (uint64_t y = y0; y < y1; ++y) {
       const U64x2 w = gld2(W, (y << n) | c);
       const uint64_t ea = gld(A, y), eb = gld(B, y);
-      a.x = gl_add(a.x, gl_mul(ea, w.x));
-      a.y = gl_add(a.y, gl_mul(ea, w.y));
-      b.x = gl_add(b.x, gl_mul(eb, w.x));
-      b.y = gl_add(b.y, gl_mul(eb, w.y));
+      gl_mac(ax, ea, w.x);
+      gl_mac(ay, ea, w.y);
+      gl_mac(bx, eb, w.x);
+      gl_mac(by, eb, w.y);
     }
-    gst2(P<uint64_t*>(st, 2), g, a);
-    gst2(P<uint64_t*>(st, 4), g, b);
+    gst2(P<uint64_t*>(st, 2), g, U64x2{gl_acc_value(ax), gl_acc_value(ay)});
+    gst2(P<uint64_t*>(st, 4), g, U64x2{gl_acc_value(bx), gl_acc_value(by)});
   }
 }
 
@@ -1551,7 +1568,7 @@ void gl_emit_proof(std::vector<Step>& steps, const gkr_circuit& c, const GlWs& w
     {
       uint32_t lr = 0;
       while ((1ull << (lr + 1)) * R <= rows) ++lr;  // rows per chunk = rows / R
-      Step st = gl_mk(ST_GL_LOCAL_CONTRACT, gl_tiles((uint64_t)R * ncop, kGlSweepTiles));
+      Step st = gl_mk(ST_GL_LOCAL_CONTRACT, gl_tiles(n ? (uint64_t)R * ncop / 2 : R, kGlSweepTiles));
       st.p[0] = w.layer[i + 1]; st.p[1] = w.EqR; st.p[2] = w.wpart; st.u[0] = n; st.u[1] = lr;
       st.q[0] = (uint64_t)R * ncop;
       st.bytes = kGE * (double)(rows * ncop + (uint64_t)R * ncop); st.mulmods = (double)(rows * ncop);

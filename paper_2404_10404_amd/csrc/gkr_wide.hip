@@ -8,9 +8,8 @@
 // product deep; the folded entries meet in shared memory, and one wave (two
 // for five tables) evaluates, lanes 0..31 at t = 0 and 32..63 at t = 2, one product
 // each. A round of 2^9..2^13 pairs takes 12 us instead of 20 (three tables).
-// Above 2^13 pairs (c2, sweep of the limit: 14.20 ms at 2^15, 14.06 at 2^14, 14.02
-// at 2^13, 14.06 at 2^12) the chip fills either way and more than 256 workgroups
-// queue on the round's counter.
+// Above 2^13 pairs the chip fills either way (a proof of 2^20 gates x 16 layers
+// with the limit at 2^12: 11.89 ms, 2^13: 11.81, 2^14: 11.80).
 #include "gkr_bodies.hpp"
 #include "gkr_profile.hpp"
 #include "gkr_wide_bodies.hpp"

@@ -7,6 +7,8 @@
 // hi = hh * 2^32 + hl, x = lo - hh + hl (2^32 - 1) (mod p).
 #pragma once
 
+#include "fr.hpp"
+
 #include <stdint.h>
 
 #if defined(__HIPCC__)
@@ -58,6 +60,29 @@ GL_HD uint64_t gl_mul(uint64_t a, uint64_t b) {
   const unsigned __int128 x = (unsigned __int128)a * b;
   return gl_reduce128((uint64_t)x, (uint64_t)(x >> 64));
 #endif
+}
+
+// A sum of products, unreduced: columns of weight 2^0, 2^32 and 2^64, each a 64-bit sum
+// with an overflow word. A product costs its four multiply-adds with carries
+// instead of a multiplication, a reduction and an addition (below 2^32 products).
+struct GlAcc {
+  uint64_t c[3] = {0, 0, 0};
+  uint32_t o[3] = {0, 0, 0};
+};
+GL_HD void gl_mac(GlAcc& s, uint64_t a, uint64_t b) {
+  const uint32_t a0 = (uint32_t)a, a1 = (uint32_t)(a >> 32), b0 = (uint32_t)b, b1 = (uint32_t)(b >> 32);
+  fr_mac_vv(s.c[0], s.o[0], a0, b0);
+  fr_mac_vv(s.c[1], s.o[1], a0, b1);
+  fr_mac_vv(s.c[1], s.o[1], a1, b0);
+  fr_mac_vv(s.c[2], s.o[2], a1, b1);
+}
+// The sum mod p: 2^64 = 2^32 - 1, 2^96 = -1, 2^128 = -2^32.
+GL_HD uint64_t gl_acc_value(const GlAcc& s) {
+  uint64_t r = gl_reduce128(s.c[0], s.o[0]);
+  r = gl_add(r, gl_reduce128(s.c[1] << 32, s.c[1] >> 32));
+  r = gl_sub(r, s.o[1]);
+  r = gl_add(r, gl_reduce128(0, s.c[2]));
+  return gl_sub(r, gl_reduce128((uint64_t)s.o[2] << 32, 0));
 }
 
 GL_HD uint64_t gl_one_minus(uint64_t a) { return gl_sub(1, a); }

@@ -2,6 +2,7 @@
 // case is run by one wave or one workgroup on data the test supplies.
 #include <hip/hip_runtime.h>
 
+#include "../../paper_2404_10404_amd/csrc/fr_row.hpp"
 #include "../../paper_2404_10404_amd/csrc/sha256_wave.hpp"
 
 using namespace gkr;
@@ -42,7 +43,25 @@ __global__ void __launch_bounds__(64) k_sha_message(const uint32_t* msg, uint32_
   sha_lanes_store(out + 8ull * blockIdx.x, s);
 }
 
+// Four cases per wave, a row of 16 lanes each: the quadratic (v0, v1, c2) at r, from
+// 32 words per case (r, v0, v1, c2).
+__global__ void __launch_bounds__(64) k_row_quadratic(const uint32_t* in, uint32_t* out) {
+  const uint32_t i = threadIdx.x & 15;
+  const uint64_t k = 4ull * blockIdx.x + (threadIdx.x >> 4);
+  const uint32_t* c = in + 32 * k;
+  uint32_t r[8];
+  for (int j = 0; j < 8; ++j) r[j] = c[j];
+  const uint32_t e = row_quadratic(r, i < 8 ? c[8 + i] : 0, i < 8 ? c[16 + i] : 0, i < 8 ? c[24 + i] : 0);
+  if (i < 8) out[8 * k + i] = e;
+}
+
 }  // namespace
+
+extern "C" int wavecheck_row_quadratic(const void* d_in, void* d_out, uint32_t waves) {
+  if (!d_in || !d_out || waves < 1 || waves > 4096) return -1;
+  k_row_quadratic<<<waves, 64>>>(static_cast<const uint32_t*>(d_in), static_cast<uint32_t*>(d_out));
+  return hipGetLastError() != hipSuccess || hipDeviceSynchronize() != hipSuccess ? -3 : 0;
+}
 
 // Synchronous; 0, -1 for bad arguments, -3 when the launch fails.
 extern "C" int wavecheck_sha_chain(const void* d_st, const void* d_blocks, void* d_out, uint32_t cases, uint32_t rounds,
