@@ -558,7 +558,7 @@ void emit_layer(Program& pg, const gkr_circuit& c, uint32_t i, const Workspace& 
   Fr* ta_dst[3] = {w.Wf, w.G, w.H};
   const uint32_t off_vx = 24 * s1, off_p2 = off_vx + 8, off_vy = off_p2 + 24 * s1;
   // (the contracted form uses kernels that only the plain launcher has)
-  const bool split = pg.plain() && tun.matrix_cores && split_applies(n, sg1);
+  const bool split = pg.plain() && tun.matrix_cores && split_applies(n, sg1, c.mul_gates[i]);
   if (split) {
     emit_phase1_split(pg, w, c.wiring[i], W, n, sg1, 1ull << sg, c.mul_gates[i], rx, proof, tun);
   } else if (pg.wide() && s1 > 1 && s1 - 1 <= (pg.plain() ? kWideMaxLogHalf : kLockP1MaxLogHalf) &&

@@ -1348,8 +1348,10 @@ void gl_copy_contract(std::vector<Step>& steps, const uint64_t* W, const uint64_
   steps.push_back(st);
 }
 
-// Layers whose phase 1 takes the contracted form.
-constexpr uint32_t kGlSplitMinLogCopies = 8, kGlSplitMinLogRows = 8, kGlSplitMinLogWidth = 22;
+// Layers whose phase 1 takes the contracted form. Four layers with it and without
+// (half of the gates MUL), us: 2^22 entries 2,605 / 2,456, 2^23 2,979 / 3,084 (with
+// 2^8 copies 3,478 / 3,406), 2^24 3,893 / 4,478; all gates MUL 2^23 3,047 / 3,081.
+constexpr uint32_t kGlSplitMinLogCopies = 9, kGlSplitMinLogRows = 8, kGlSplitMinLogWidth = 23;
 
 bool gl_split_applies(uint32_t n, uint32_t sigma) {
   return n >= kGlSplitMinLogCopies && sigma >= kGlSplitMinLogRows && n + sigma >= kGlSplitMinLogWidth;

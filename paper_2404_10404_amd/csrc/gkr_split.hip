@@ -359,7 +359,7 @@ void launch_split_step(const Step& st, hipStream_t s) {
 namespace {
 
 constexpr double kE = 32.0;
-constexpr uint32_t kSplitMinLogCopies = 8, kSplitMinLogRows = 10, kSplitMinLogWidth = 21;
+constexpr uint32_t kSplitMinLogCopies = 9, kSplitMinLogRows = 10, kSplitMinLogWidth = 23;
 // Most pairs (log2) of a wide round: a layer of 2^22 gates took 2,000 us without,
 // 1,953 up to 2^12 pairs, 1,927 up to 2^14, 1,925 up to 2^15, 1,927 up to 2^16.
 constexpr uint32_t kSplitWideMaxLogHalf = 15;
@@ -375,8 +375,16 @@ Step smk(uint32_t type, uint64_t items, uint64_t cap = 1u << 20) {
 
 }  // namespace
 
-bool split_applies(uint32_t n, uint32_t sigma) {
-  return n >= kSplitMinLogCopies && sigma >= kSplitMinLogRows && n + sigma >= kSplitMinLogWidth &&
+// The form trades three passes over three tables for two contractions more, and
+// gains what Gm's empty rows leave out. Four layers, this form and the other, us:
+//   entries (copies)   MUL 1/10        1/2             all
+//   2^22 (2^9)         5,640 / 5,656   6,020 / 5,630   6,236 / 5,628
+//   2^23 (2^10)        7,506 / 8,428   8,296 / 8,408   8,965 / 8,435
+//   2^24 (2^11)       10,900 / 13,500 12,515 / 13,489 13,711 / 13,575 (3/4: 13,266 / 13,662)
+//   2^23 (2^8)         7,750 / 8,163   8,544 / 8,191   9,097 / 8,158 (no matrix cores)
+bool split_applies(uint32_t n, uint32_t sigma, uint64_t mul_gates) {
+  const bool sparse = n + sigma > kSplitMinLogWidth ? 4 * mul_gates <= 3ull << sigma : 2 * mul_gates <= 1ull << sigma;
+  return sparse && n >= kSplitMinLogCopies && sigma >= kSplitMinLogRows && n + sigma >= kSplitMinLogWidth &&
          cc_scratch_bytes(sigma, n) <= sizeof(Fr) << (n + sigma);
 }
 

@@ -7,8 +7,9 @@
 
 namespace gkr {
 
-// Whether a layer whose next layer has 2^sigma wires in 2^n copies takes this form.
-bool split_applies(uint32_t n, uint32_t sigma);
+// Whether a layer with mul_gates MUL gates whose next layer has 2^sigma wires in 2^n
+// copies takes this form.
+bool split_applies(uint32_t n, uint32_t sigma, uint64_t mul_gates);
 
 // Phase 1 of a layer (tables, rounds, vx): W = V_{i+1}, rx the challenges,
 // proof the layer's messages. Leaves EL (eq at the local part of rx) in w.EL and

@@ -1,10 +1,10 @@
 """Phase 1 with the addition gates contracted over the copies (csrc/gkr_split.hip,
 wide layers of many copies) against the three-table form of the same library,
 which the parity tests hold to the oracle: proofs and outputs byte for byte,
-and the library's verifier accepts. Shapes at the edges of the rule (2^21
-entries: fewest copies, fewest wires), layers of other widths beside such a
-layer (so both forms meet in one proof), and only MUL or only ADD gates (every
-row of the MUL table nonzero, or none)."""
+and the library's verifier accepts. Shapes at the edges of the rule (2^23
+entries: fewest copies, fewest wires, as many MUL gates as it takes), layers of
+other widths beside such a layer (so both forms meet in one proof), and only MUL
+or only ADD gates (no addition term, or a MUL table without a nonzero row)."""
 import numpy as np
 import pytest
 
@@ -14,8 +14,8 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("copies,widths,mu", [
-    (8, (13, 13), (1, 2)), (11, (10, 10, 10), (3, 10)), (9, (11, 12, 12), (1, 10)), (8, (13, 13), (1, 1)),
-    (10, (9, 11), (0, 1)), (8, (6, 13, 9, 13), (1, 4)),
+    (9, (14, 14), (49, 100)), (13, (10, 10, 10), (3, 10)), (10, (12, 13, 13), (1, 10)), (9, (13, 14), (1, 1)),
+    (10, (11, 13), (0, 1)), (9, (7, 14, 9, 14), (1, 4)), (9, (15, 15), (7, 10)),
 ])
 def test_equals_the_three_table_form(copies, widths, mu):
     import torch
@@ -45,12 +45,13 @@ def test_equals_the_three_table_form(copies, widths, mu):
 
 
 @pytest.mark.parametrize("copies,widths,mu", [
-    (8, (14, 14), (1, 2)), (12, (10, 10), (3, 10)), (9, (12, 13), (0, 1)), (8, (13, 14), (1, 1)), (13, (9, 5, 9), (1, 4)),
+    (9, (14, 14), (1, 2)), (13, (10, 10), (3, 10)), (10, (12, 13), (0, 1)), (9, (13, 14), (1, 1)),
+    (15, (8, 5, 8), (1, 4)),
 ])
 def test_goldilocks_proofs_are_accepted(copies, widths, mu):
     """The same form over the Goldilocks field: the verifier, which evaluates the
     wiring predicates and the inputs itself, accepts (a wrong round sum is
-    rejected but for a chance below 2^-50). 2^22 entries and more."""
+    rejected but for a chance below 2^-50). 2^23 entries and more."""
     import torch
 
     from paper_2404_10404_amd import gkr
