@@ -220,7 +220,7 @@ void Program::forward(const Fr* W, Fr* V, const uint2* gates, uint32_t n, uint32
   steps.push_back(st);
 }
 void emit_digests(std::vector<Step>& steps, uint32_t thread_type, const DigestJob* jobs, int count, uint32_t* dig_a,
-                  uint32_t* dig_b, uint32_t* small) {
+                  uint32_t* dig_b, uint32_t* small, uint64_t small_digests) {
   // the state of each tree: its current level
   struct Cur {
     const uint32_t* in;
@@ -240,6 +240,37 @@ void emit_digests(std::vector<Step>& steps, uint32_t thread_type, const DigestJo
     cur[v].area ^= 1;
     return small + (2 * v + cur[v].area) * (kDigestWaveChunks * 8);
   };
+  if (count == 2) {
+    uint64_t words[2] = {jobs[0].words, jobs[1].words};
+    const uint64_t room = small_digests / 2;
+    if (chunks_of(8 * chunks_of(words[0])) <= room && chunks_of(8 * chunks_of(words[1])) <= room) {
+      const uint32_t* in[2] = {jobs[0].in, jobs[1].in};
+      uint32_t* const sets[2][2] = {{dig_a, dig_b}, {small, small + 8 * room}};
+      bool done[2] = {false, false};
+      for (int level = 0; !done[0] || !done[1]; ++level) {
+        Step st = mk(ST_DIGEST_WAVE, 1);
+        uint64_t tiles = 0, most = 0;
+        for (int v = 0, k = 0; v < 2; ++v) {
+          if (done[v]) continue;
+          const uint64_t n = chunks_of(words[v]);
+          uint32_t* out = n == 1 ? jobs[v].out : sets[level & 1][v];
+          st.p[2 * k] = in[v]; st.p[2 * k + 1] = out; st.u[k] = level == 0 ? 1 : 0;
+          st.q[2 * k] = words[v]; st.q[2 * k + 1] = n;
+          st.bytes += 4.0 * words[v] + 32.0 * n;
+          tiles += n;
+          most = std::max(most, n);
+          in[v] = out;
+          words[v] = 8 * n;
+          done[v] = n == 1;
+          ++k;
+        }
+        if (most > kDigestWaveChunks) st.type = thread_type;
+        st.ntiles = most > kDigestWaveChunks ? tiles_for(tiles, kSweepTiles) : (uint32_t)tiles;
+        steps.push_back(st);
+      }
+      return;
+    }
+  }
   auto wave_level = [&](int a, int b) {  // b < 0: one tree
     Step st = mk(ST_DIGEST_WAVE, 1);
     const int vs[2] = {a, b};
@@ -281,7 +312,8 @@ void emit_digests(std::vector<Step>& steps, uint32_t thread_type, const DigestJo
   }
 }
 void Program::digests(const DigestJob* jobs, int count, const Workspace& w) {
-  emit_digests(steps, ST_DIGEST, jobs, count, w.dig_a, w.dig_b, reinterpret_cast<uint32_t*>(w.partials));
+  emit_digests(steps, ST_DIGEST, jobs, count, w.dig_a, w.dig_b, reinterpret_cast<uint32_t*>(w.partials),
+               (uint64_t)kMaxRoundBlocks * kMaxPartialValues);
 }
 void Program::transcript_begin(DevState* S, const Words8& seed_state, const uint32_t* circ,
                                const uint32_t* din, const uint32_t* dout) {

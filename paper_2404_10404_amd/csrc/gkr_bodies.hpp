@@ -171,13 +171,15 @@ __device__ __forceinline__ void body_forward(const Step& st, uint32_t tile, uint
 
 // ST_DIGEST: one level of a tree digest; chunk t of q0 words (256 words, 1 KiB,
 // per chunk) is hashed by thread t; element words are byte-swapped (limbs are
-// little-endian). p0 in, p1 out, q0 nwords, q1 nchunks, u0 swap.
+// little-endian). p0 in, p1 out, q0 nwords, q1 nchunks, u0 swap; p2, p3, q2, q3, u1 the
+// same of a second vector (q3 = 0: none), whose chunks come after.
 __device__ __forceinline__ void body_digest(const Step& st, uint32_t tile, uint32_t ntiles) {
-  const uint32_t* __restrict__ in = P<const uint32_t*>(st, 0);
-  uint32_t* __restrict__ out = P<uint32_t*>(st, 1);
-  const uint64_t nwords = st.q[0];
-  const int swap = st.u[0];
-  for (uint64_t t = GTID; t < st.q[1]; t += GSTRIDE) {
+  for (uint64_t g = GTID; g < st.q[1] + st.q[3]; g += GSTRIDE) {
+    const bool second = g >= st.q[1];
+    const uint32_t* in = second ? P<const uint32_t*>(st, 2) : P<const uint32_t*>(st, 0);
+    uint32_t* out = second ? P<uint32_t*>(st, 3) : P<uint32_t*>(st, 1);
+    const uint64_t nwords = second ? st.q[2] : st.q[0], t = second ? g - st.q[1] : g;
+    const uint32_t swap = second ? st.u[1] : st.u[0];
     const uint64_t begin = t * kChunkWords;
     const uint64_t end = (begin + kChunkWords < nwords) ? begin + kChunkWords : nwords;
     const uint64_t len = end - begin;  // a multiple of 8 words

@@ -184,15 +184,16 @@ __global__ void __launch_bounds__(kBlock) k_gl_forward(Step st) {
 }
 
 // ST_GL_DIGEST: one level of a tree digest; chunk t (256 words) hashed by thread t.
-// p0 in, p1 out, q0 nwords, q1 nchunks, u0 swap.
+// p0 in, p1 out, q0 nwords, q1 nchunks, u0 swap; a second vector as in ST_DIGEST.
 __global__ void __launch_bounds__(kBlock) k_gl_digest(Step st) {
-  const uint32_t* in = P<const uint32_t*>(st, 0);
-  uint32_t* out = P<uint32_t*>(st, 1);
-  const uint64_t nwords = st.q[0];
-  for (uint64_t t = GTID; t < st.q[1]; t += GSTRIDE) {
+  for (uint64_t g = GTID; g < st.q[1] + st.q[3]; g += GSTRIDE) {
+    const bool second = g >= st.q[1];
+    const uint32_t* in = second ? P<const uint32_t*>(st, 2) : P<const uint32_t*>(st, 0);
+    uint32_t* out = second ? P<uint32_t*>(st, 3) : P<uint32_t*>(st, 1);
+    const uint64_t nwords = second ? st.q[2] : st.q[0], t = second ? g - st.q[1] : g;
     const uint64_t begin = t * kChunkWords;
     const uint64_t end = (begin + kChunkWords < nwords) ? begin + kChunkWords : nwords;
-    sha256_words(in + begin, end - begin, st.u[0], out + 8 * t);
+    sha256_words(in + begin, end - begin, second ? st.u[1] : st.u[0], out + 8 * t);
   }
 }
 
@@ -1452,7 +1453,8 @@ void gl_emit_proof(std::vector<Step>& steps, const gkr_circuit& c, const GlWs& w
   // statement
   const DigestJob jobs[2] = {{reinterpret_cast<const uint32_t*>(w.layer[d]), 2ull << c.s(d), w.dig_in},
                              {reinterpret_cast<const uint32_t*>(w.layer[0]), 2ull << c.s(0), w.dig_out}};
-  emit_digests(steps, ST_GL_DIGEST, jobs, 2, w.dig_a, w.dig_b, reinterpret_cast<uint32_t*>(w.partials));
+  emit_digests(steps, ST_GL_DIGEST, jobs, 2, w.dig_a, w.dig_b, reinterpret_cast<uint32_t*>(w.partials),
+               kGE * 2 * kMaxRoundBlocks / 32);
   {
     Step st = gl_mk(ST_GL_BEGIN, 1);
     st.p[0] = w.S; st.p[1] = w.dig_in; st.p[2] = w.dig_out;

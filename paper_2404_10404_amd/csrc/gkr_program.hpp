@@ -19,15 +19,17 @@ struct DigestJob {
 };
 
 // Levels of more than kDigestWaveChunks chunks take a thread per chunk (the chip
-// is full, or nearly), smaller ones a workgroup per chunk, both trees' levels
-// in one launch.
+// is full, or nearly), smaller ones a workgroup per chunk.
 constexpr uint64_t kDigestWaveChunks = 512;
 
-// The levels of one or two tree digests. dig_a, dig_b hold the large levels,
-// small (four areas of kDigestWaveChunks digests) the others; thread_type is the
-// step type of a thread-per-chunk level.
+// The levels of one or two tree digests, both trees' levels in one launch if
+// their second levels fit in `small` (a level of 2^10..2^17 chunks takes about 55
+// us, whatever its size: one chain of 17 compressions), else the large levels one
+// tree after the other. dig_a, dig_b (a first level each) and small (small_digests
+// digests, at least four times kDigestWaveChunks) hold the levels; thread_type is
+// the step type of a thread-per-chunk level.
 void emit_digests(std::vector<Step>& steps, uint32_t thread_type, const DigestJob* jobs, int count, uint32_t* dig_a,
-                  uint32_t* dig_b, uint32_t* small);
+                  uint32_t* dig_b, uint32_t* small, uint64_t small_digests);
 
 struct Program {
   std::vector<Step> steps;
