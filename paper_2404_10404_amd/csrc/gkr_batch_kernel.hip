@@ -85,7 +85,7 @@ __global__ void __launch_bounds__(kBlock, 2) k_batch(BatchArgs a) {
     }
     const uint32_t j = sh_job, s = sh_step, tile = sh_tile;
     const BatchJobDev& jb = a.jobs[j];
-    // copy the step record to LDS (256-byte record, 4-byte words)
+    // copy the step record to LDS (4-byte words)
     {
       const uint32_t* src = reinterpret_cast<const uint32_t*>(&jb.steps[s]);
       uint32_t* dst = reinterpret_cast<uint32_t*>(&sh_st);

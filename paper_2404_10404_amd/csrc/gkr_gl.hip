@@ -25,6 +25,7 @@
 #include "gkr_gl.hpp"
 #include "gkr_profile.hpp"
 #include "gkr_program.hpp"
+#include "gkr_split.hpp"
 #include "gkr_tuning.hpp"
 #include "gl.hpp"
 
@@ -1389,12 +1390,16 @@ void gl_emit_phase1_split(std::vector<Step>& steps, const gkr_circuit& c, uint32
       st.p[0] = W; st.p[1] = w.G; st.p[2] = lw.xrow; st.p[3] = lw.xmid; st.p[4] = lw.xent; st.p[5] = w.aU;
       st.p[6] = w.bV; st.p[7] = w.Cu; st.p[8] = w.Cv; st.p[13] = small[0];
       for (int k = 0; k < 5; ++k) st.w[k] = (uint32_t)(small[k] - small[0]);
-      st.bytes = kGE * (2.0 * muls * ncop + full); st.mulmods = 3.0 * muls * ncop + 2.0 * half;
+      const double a0 = split_active_share(muls, rows, 0), a1 = split_active_share(muls, rows, 1);
+      st.bytes = kGE * (muls * ncop + a0 * full + a1 * full);
+      st.mulmods = 3.0 * muls * ncop + (a0 + a1) * half;
     } else {
       st.p[0] = Ws; st.p[1] = w.Wf; st.p[2] = w.G; st.p[3] = lw.act; st.p[13] = rx + j - 1;
       for (int k = 0; k < 5; ++k) st.p[4 + k] = small[k];
       Ws = w.Wf;
-      st.bytes = kGE * 12.0 * half; st.mulmods = 6.0 * half;
+      const double a0 = split_active_share(muls, rows, j - 1), a1 = split_active_share(muls, rows, j);
+      const double a2 = split_active_share(muls, rows, j + 1);
+      st.bytes = kGE * half * (6.0 + 4.0 * a0 + 2.0 * a1); st.mulmods = half * (2.0 + 3.0 * a1 + a2);
     }
     steps.push_back(st);
   }

@@ -422,13 +422,17 @@ void emit_phase1_split(Program& pg, const Workspace& w, const LayerWiring& lw, c
       st.p[6] = w.bV; st.p[7] = w.Cu; st.p[8] = w.Cv;
       for (int k = 0; k < 5; ++k) st.w[k] = (uint32_t)(small[k] - small[0]);
       st.p[13] = small[0];
-      st.bytes = kE * (2.0 * mul_gates * ncop + full); st.mulmods = 2.5 * mul_gates * ncop + 2.0 * half;
+      const double a0 = split_active_share(mul_gates, rows, 0), a1 = split_active_share(mul_gates, rows, 1);
+      st.bytes = kE * (mul_gates * ncop + a0 * full + a1 * full);  // gathers, Gm, W beside active rows
+      st.mulmods = 2.5 * mul_gates * ncop + (a0 + a1) * half;
     } else {
       st.p[0] = Ws; st.p[1] = w.Wf; st.p[2] = w.G; st.p[3] = lw.act;
       for (int k = 0; k < 5; ++k) st.p[4 + k] = small[k];
       st.p[13] = rx + j - 1;
       Ws = w.Wf;
-      st.bytes = kE * 12.0 * half; st.mulmods = 6.0 * half;
+      const double a0 = split_active_share(mul_gates, rows, j - 1), a1 = split_active_share(mul_gates, rows, j);
+      const double a2 = split_active_share(mul_gates, rows, j + 1);
+      st.bytes = kE * half * (6.0 + 4.0 * a0 + 2.0 * a1); st.mulmods = half * (2.0 + 3.0 * a1 + a2);
     }
     pg.steps.push_back(st);
   }

@@ -2,6 +2,8 @@
 // used by the plain path for wide layers of many copies.
 #pragma once
 
+#include <cmath>
+
 #include "gkr_internal.hpp"
 #include "gkr_program.hpp"
 
@@ -21,5 +23,11 @@ void emit_phase1_split(Program& pg, const Workspace& w, const LayerWiring& lw, c
 void emit_p2_final(Program& pg, const Workspace& w, uint64_t rows);
 
 void launch_split_step(const Step& st, hipStream_t s);
+
+// Expected share of the MUL table's rows that are not zero after j folds, for mul_gates
+// gates with random left inputs over rows (for the work records only).
+inline double split_active_share(uint64_t mul_gates, uint64_t rows, uint32_t j) {
+  return 1.0 - std::exp(-(double)(1ull << j) * (double)mul_gates / (double)rows);
+}
 
 }  // namespace gkr
