@@ -378,7 +378,9 @@ int32_t gkr_verify(const gkr_circuit* circuit, const gkr_fr* inputs, const gkr_f
  * Round-schedule tuning (process-wide; used by the autotuner; this library's
  * own, no passage). Proof bytes
  * never depend on it. tail_log: tables of at most 2^tail_log entries finish
- * their phase in one workgroup (1..20); max_round_blocks: cap on the
+ * their phase in one workgroup (1..20; plain BN254 proofs and lockstep batches
+ * use it up to 2^7 and 2^2 entries, Goldilocks proofs three more, up to 2^12);
+ * max_round_blocks: cap on the
  * workgroups of one grid-wide round (1..4096); pairs_per_thread: a grid-wide
  * round gets ceil(pairs / (256 * pairs_per_thread)) workgroups, capped
  * (1..1024). Proofs read the tuning when they are queued. Errors: GKR_EINVAL
