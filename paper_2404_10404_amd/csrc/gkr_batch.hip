@@ -197,9 +197,9 @@ int32_t gkr_run_batch(gkr_plan* const* plans, uint32_t n, uint32_t* d_ctl, uint3
       cus = 256;
     }
     workgroups = (uint32_t)cus * batch_kernel_max_workgroups_per_cu();
-    // plans begun before: three workgroups per four CUs do best (64 uneven proofs 165
-    // ms, against 212 ms with two per CU, which contend for the step counters)
-    if (lockstep) workgroups = std::max(1u, (uint32_t)cus * 3 / 4);
+    // plans begun before: a workgroup per CU does best (64 uneven proofs 81.0 ms, against
+    // 84.6 with two per CU, which contend for the step counters, and 88.7 with 5 per 8 CUs)
+    if (lockstep) workgroups = (uint32_t)cus;
   }
   hipStream_t s = static_cast<hipStream_t>(stream);
   launch_fill_u32(d_ctl, 4, 0u, s);
