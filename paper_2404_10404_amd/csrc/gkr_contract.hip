@@ -19,11 +19,12 @@
 // sums of U and V. Each workgroup takes 128 rows and one chunk of K
 // (at most 2^15 bytes: |sum a_s b_s| < 2^29 fits the 32-bit accumulators) and
 // stores its partial columns; the epilogue adds the chunks, applies the
-// offsets, assembles the 520-bit integer per row and reduces it.
+// offsets, assembles the integer per row and reduces it (cc_sum.hpp).
 #include <string.h>
 
 #include <algorithm>
 
+#include "cc_sum.hpp"
 #include "gkr_bodies.hpp"
 #include "gkr_contract.hpp"
 #include "gkr_profile.hpp"
@@ -197,9 +198,8 @@ __global__ void __launch_bounds__(kCcThreads) k_cc_gemm(Step st) {
 // otherwise. All threads first add the chunks'
 // partial columns, two rows of 128 consecutive columns at a time, into shared
 // memory; then one thread per (row, vector) takes the 63 band columns of its
-// vector and the ones column, the offsets, the integer sum_k 2^(8k) E_k (below
-// 2^520), its top bits folded by 2^508 mod p (w[0..7], plain form), and makes one
-// Montgomery reduction. (With the two threads of a row also adding the chunks,
+// vector and the ones column, the offsets, the integer sum_k 2^(8k) E_k and its
+// Montgomery reduction (cc_sum.hpp; w[0..7] 2^508 mod p). (With the two threads of a row also adding the chunks,
 // 63 loads per chunk at a stride of a row, 2^14 rows took 57 us.)
 // p0 part, p1 BS, p2 P out, p3 Q out; u0 chunks, u1 rows per workgroup; q0 rows.
 constexpr uint32_t kCcEpiRows = 8;
@@ -235,38 +235,14 @@ __global__ void __launch_bounds__(kBlock) k_cc_epilogue(Step st) {
   const uint32_t row = threadIdx.x >> 1, v = threadIdx.x & 1;
   if (threadIdx.x >= 2 * per || y0 + row >= rows) return;
   const int64_t rs = sums[row][kCcOnes];
-  uint64_t acc[18];
+  CcSum sum = cc_sum_zero();
 #pragma unroll
-  for (int i = 0; i < 18; ++i) acc[i] = 0;
-#pragma unroll
-  for (int k = 0; k < 63; ++k) {
+  for (int k = 0; k < kCcBands; ++k) {
     // sum_K b_u of band k covers bytes max(0, k - 31) .. min(k, 31)
     const uint64_t cs = ps[v][k < 31 ? k + 1 : 32] - ps[v][k > 31 ? k - 31 : 0];
-    const uint64_t e = (uint64_t)(sums[row][64 * v + k] + 128 * rs + 128 * (int64_t)cs);  // E_k, below 2^35
-    const uint64_t sh = e << (8 * (k & 3));                                              // below 2^59
-    acc[k >> 2] += sh & 0xffffffffu;
-    acc[(k >> 2) + 1] += sh >> 32;
+    cc_sum_band(sum, k, (uint64_t)(sums[row][64 * v + k] + 128 * rs + 128 * (int64_t)cs));
   }
-  uint32_t lim[17];
-  uint64_t carry = 0;
-#pragma unroll
-  for (int i = 0; i < 17; ++i) {
-    const uint64_t s = acc[i] + carry;
-    lim[i] = (uint32_t)s;
-    carry = s >> 32;
-  }
-  // fold: S = H 2^508 + L  ==  L + H (2^508 mod p)
-  const uint32_t H = (lim[15] >> 28) | (lim[16] << 4);
-  lim[15] &= 0x0fffffffu;
-  FrWide T;
-  uint64_t c2 = 0;
-#pragma unroll
-  for (int i = 0; i < 16; ++i) {
-    const uint64_t s = (uint64_t)lim[i] + (i < 8 ? (uint64_t)H * st.w[i] : 0) + c2;
-    T.w[i] = (uint32_t)s;
-    c2 = s >> 32;
-  }
-  const Fr out = frw_reduce<4>(T);
+  const Fr out = cc_sum_reduce(sum, st.w);
   Fr *ou = P<Fr*>(st, 2), *ov = P<Fr*>(st, 3);
   stf(v ? ov : ou, y0 + row, out);
 }
