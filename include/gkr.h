@@ -393,8 +393,9 @@ int32_t gkr_get_tuning(uint32_t* tail_log, uint32_t* max_round_blocks, uint32_t*
 /*
  * How plain proofs contract the copy factors (process-wide; this library's
  * own, no passage; proof bytes never depend on it): 1 (the default) runs phase
- * 2's contraction on the int8 matrix cores for layers with at least 2^9 copies
- * and 2^8 sub-circuit wires, and phase 1 with its addition gates contracted
+ * 2's contraction on the int8 matrix cores for layers with at least 2^8
+ * sub-circuit wires and 2^10 copies (or 2^9 where phase 1's tables can hold its
+ * scratch), and phase 1 with its addition gates contracted
  * over the copies for layers with at least 2^9 copies, 2^10 wires and 2^23
  * entries of which few have a MUL gate; 0 always runs the scalar lazy-product pass and the three-table
  * phase 1. Proofs read it when they are queued. Errors: GKR_EINVAL

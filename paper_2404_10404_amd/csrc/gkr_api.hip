@@ -125,7 +125,8 @@ size_t plan_workspace(const gkr_circuit& c, Plan& p) {
   p.off_chal = take(E * ((size_t)c.s(0) + 2ull * d * sp_max + 2ull * s_max + 8));
   p.off_state = take(sizeof(DevState));
   p.cc_bytes = 0;
-  for (uint32_t i = 0; i < d; ++i) p.cc_bytes = std::max(p.cc_bytes, cc_scratch_bytes(n, c.sigma[i + 1]));
+  for (uint32_t i = 0; i < d && n >= kCcOwnLogCopies; ++i)
+    p.cc_bytes = std::max(p.cc_bytes, cc_scratch_bytes(n, c.sigma[i + 1]));
   p.off_cc = take(p.cc_bytes);
   p.total = off;
   return off;
@@ -619,8 +620,10 @@ void emit_layer(Program& pg, const gkr_circuit& c, uint32_t i, const Workspace& 
   pg.copy_weights(w.Cu, w.Cv, w.EC, w.U, w.V, 1ull << n, S);
   if (split) emit_p2_final(pg, w, 1ull << sg1);
   else pg.p2_tables(c.wiring[i], w.aU, w.bV, w.EL, S, w.Fa, w.Fb, w.Ka, w.Kb, w.Ks, 1ull << sg1, 1ull << sg);
-  if (pg.plain() && tun.matrix_cores && w.cc && cc_applies(n, sg1)) emit_contract_mfma(pg, W, w.U, w.V, w.P, w.Q, n, sg1, false, w.cc);
-  else {
+  void* cc = pg.plain() && tun.matrix_cores ? cc_scratch(w, n, sg1) : nullptr;
+  if (cc) {
+    emit_contract_mfma(pg, W, w.U, w.V, w.P, w.Q, n, sg1, false, cc);
+  } else {
     pg.copy_contract(W, w.U, w.V, w.P, w.Q, n, 1ull << sg1);
     pg.steps.back().join = 1;  // independent of the phase-2 tables
   }

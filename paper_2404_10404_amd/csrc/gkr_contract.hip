@@ -287,6 +287,13 @@ size_t cc_scratch_bytes(uint32_t n, uint32_t sigma) {
   return cp.bt_bytes + cp.part_bytes + 256;
 }
 
+void* cc_scratch(const Workspace& w, uint32_t n, uint32_t sigma) {
+  if (!cc_applies(n, sigma)) return nullptr;
+  if (n >= kCcOwnLogCopies) return w.cc;
+  const size_t room = 2 * sizeof(Fr) * (size_t)(w.H - w.G);  // H follows G and is as large
+  return cc_scratch_bytes(n, sigma) <= room ? w.G : nullptr;
+}
+
 // 2^508 mod p in plain form: (2^508 R) R^-1 from Montgomery powers of 2.
 static void two_pow_508(uint32_t out[8]) {
   const Fr two = fr_to_mont(fr_make(2, 0, 0, 0, 0, 0, 0, 0));

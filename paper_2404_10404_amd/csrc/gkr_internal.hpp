@@ -213,7 +213,7 @@ struct Workspace {
   Fr *P, *Q, *Fa, *Fb, *Ks, *Ka, *Kb;
   Fr *Wc, *Fc, *Kc, *wpart;
   Fr* partials;
-  void* cc;                 // matrix-core contraction scratch (null if no layer uses it)
+  void* cc;                 // matrix-core contraction scratch (null if no layer has its own)
   uint32_t *dig_a, *dig_b;  // tree-digest levels (8 words per digest)
   uint32_t* dig_in;         // final digests (8 words each)
   uint32_t* dig_out;

@@ -393,7 +393,7 @@ void emit_phase1_split(Program& pg, const Workspace& w, const LayerWiring& lw, c
   DevState* S = w.state;
   const uint64_t rows = 1ull << sigma, ncop = 1ull << n, full = rows << n;
   // Pu, Pv where phase 2 will have P, Q; sa, sb, h where it will have Fa, Fb, Ks
-  if (cc_applies(n, sigma) && w.cc) emit_contract_mfma(pg, W, w.Cu, w.Cv, w.P, w.Q, n, sigma, false, w.cc);
+  if (void* cc = cc_scratch(w, n, sigma)) emit_contract_mfma(pg, W, w.Cu, w.Cv, w.P, w.Q, n, sigma, false, cc);
   else pg.copy_contract(W, w.Cu, w.Cv, w.P, w.Q, n, rows);
   Fr* small[5] = {w.P, w.Fa, w.Q, w.Fb, w.Ks};
   {
