@@ -317,12 +317,15 @@ int32_t gkr_prove_layer(const gkr_circuit* circuit, uint32_t layer, const gkr_fr
  * (the buffers gkr_prove_circuit takes). gkr_plan_create records the job's
  * proof as a step program in device memory (allocates and copies: call it
  * outside any timed or captured region). gkr_run_batch then runs 1..64 plans
- * together: on the whole device without a limit in lockstep, a launch per step of
- * all plans; otherwise in one persistent launch, whose resident workgroups take
- * tiles of whichever plan has work. Either way the serial Fiat-Shamir steps of
- * one proof overlap the table sweeps of the others. A run allocates nothing and copies nothing between host and device
- * (graph-capturable). Each plan's proof bytes are identical to its
- * gkr_prove_circuit bytes. Buffers of different jobs must not overlap.
+ * together: on the whole device without a limit, and where their sizes make it the
+ * faster form, in lockstep, a launch per step of all plans (as many launches as
+ * the longest plan has steps: about 40 per layer, 1,350 for depth 32 and 2^18
+ * gates); otherwise in one persistent launch, whose resident workgroups take tiles
+ * of whichever plan has work. Either way the serial Fiat-Shamir steps of one proof
+ * overlap the table sweeps of the others. A run allocates nothing and copies
+ * nothing between host and device (graph-capturable). Each plan's proof bytes are
+ * identical to its gkr_prove_circuit bytes. Buffers of different jobs must not
+ * overlap.
  */
 typedef struct {
   const gkr_circuit* circuit;
@@ -349,9 +352,10 @@ int32_t gkr_plan_reset(gkr_plan* plan, void* stream);
  * persistent launch (0 = the whole device). step_budget > 0 stops the run
  * after about that many completed steps; stop_on_finish stops it when any plan
  * finishes. A stopped run leaves every plan resumable: run it again to
- * continue. Plans already finished are skipped. With workgroups,
- * step_budget and stop_on_finish all 0, plans that have not begun run in
- * lockstep launches; plans begun before go on in the persistent launch after them.
+ * continue. Plans already finished are skipped. With workgroups, step_budget and
+ * stop_on_finish all 0, plans that have not begun may run in lockstep launches (plans
+ * with the same steps and single ones always, uneven ones by their sizes); the
+ * others go on in the persistent launch after them.
  */
 int32_t gkr_run_batch(gkr_plan* const* plans, uint32_t n, uint32_t* d_ctl, uint32_t workgroups,
                       uint32_t step_budget, uint32_t stop_on_finish, void* stream);

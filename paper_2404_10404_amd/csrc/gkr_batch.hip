@@ -30,6 +30,8 @@ struct gkr_plan {
   // run together) the first step; per step the workgroups.
   gkr::Step* lock_steps = nullptr;
   std::vector<uint32_t> stage_first, lock_tiles;
+  uint64_t gates = 0;  // gates of all layers and inputs
+  uint64_t form = 0;   // hash of the lockstep program's step types
   uint32_t* flag() const { return ctr + ctr_words - 1; }
 };
 
@@ -38,6 +40,41 @@ static bool aligned16b(const void* p) { return (reinterpret_cast<uintptr_t>(p) &
 }  // namespace gkr
 
 using namespace gkr;
+
+// Whether a run to the end goes in lockstep: the smaller of two estimates, in ns.
+// Lockstep: launches of the longest plan, waiting for the next longest one (each
+// stage takes as long as its longest step, and uneven plans are at different
+// points), a little per further plan's stage, and the gates of all. Persistent: the
+// chain of the longest plan, a publication and a scan of the counters per step, and
+// the gates, which pass through tiles. Fitted to 54 runs of 1..64 plans (2^10..2^20
+// gates per layer, depth 2..32), 7 % off on average; the choice was never above the
+// better form by more than 4 %. Lockstep / persistent, ms, with the persistent
+// kernel that released its L2 for every tile in brackets:
+//   16 plans of 2^10..2^13 gates, depth 2..12     9.1 /  6.6  [6.8]
+//   uneven ones (2^10..2^18, depth 8..32):  4    17.1 / 14.6 [16.2]
+//     8                                          24.0 / 19.8 [21.3]
+//    16                                          28.8 / 25.5 [36.9]
+//    32                                          36.1 / 34.2 [55.4]
+//    48                                          46.0 / 56.0 [113.7]
+//    64                                          58.9 / 82.1 [153.9]
+//   6 of 2^12..2^20, depth 8..16                 21.5 / 33.1 [45.3]
+// Plans with the same steps do not wait: one of 28 x 2^12 11.1 / 12.4 [13.3], one of
+// 16 x 2^20 15.2 / 25.2 [30.3], two of 4 x 2^10 1.72 / 1.92 [2.59].
+static bool lockstep_pays(gkr_plan* const* plans, uint32_t n) {
+  double gates = 0, stages = 0, first = 0, second = 0, chain = 0;
+  bool alike = true;
+  for (uint32_t i = 0; i < n; ++i) {
+    const double k = (double)(plans[i]->stage_first.size() - 1), g = (double)plans[i]->gates;
+    gates += g;
+    stages += k;
+    second = std::max(second, std::min(first, k));
+    first = std::max(first, k);
+    chain = std::max(chain, 14000 * k + 0.30 * g);
+    alike = alike && plans[i]->form == plans[0]->form;
+  }
+  const double lockstep = 12400 * first + 5500 * second + 400 * (stages - first) + 0.34 * gates;
+  return alike || lockstep < chain + 0.78 * gates;
+}
 
 // The lockstep run of the plans in a that have not begun: a launch decides which
 // they are, then one launch per stage, then one that marks them finished.
@@ -107,7 +144,10 @@ int32_t gkr_plan_create(const gkr_job* job, gkr_plan** out) {
     for (size_t k = 0; k < lk.steps.size(); ++k) {
       if (!lk.steps[k].join) p->stage_first.push_back((uint32_t)k);
       p->lock_tiles.push_back(lk.steps[k].ntiles);
+      p->form = (p->form ^ (2 * lk.steps[k].type + lk.steps[k].join + 1)) * 0x9e3779b97f4a7c15ull;
+      p->form ^= p->form >> 29;
     }
+    for (uint32_t i = 0; i <= c->depth; ++i) p->gates += 1ull << c->s(i);
     p->stage_first.push_back((uint32_t)lk.steps.size());
     const size_t lock_bytes = sizeof(Step) * lk.steps.size();
     const size_t step_bytes = sizeof(Step) * pg.steps.size();
@@ -184,11 +224,12 @@ int32_t gkr_run_batch(gkr_plan* const* plans, uint32_t n, uint32_t* d_ctl, uint3
   a.stop_on_finish = stop_on_finish ? 1 : 0;
   a.ctl = d_ctl;
   // A run to the end on the whole device takes the plans that have not begun in
-  // lockstep: stage k of every one of them in launch k. The persistent kernel then
-  // finds those finished, and carries on those that an earlier run with a limit
-  // began. A count of workgroups is a limit on the share of the device, which the
-  // lockstep launches do not keep: with one the persistent kernel runs alone.
-  const bool lockstep = workgroups == 0 && step_budget == 0 && !stop_on_finish;
+  // lockstep where that pays: stage k of every one of them in launch k. The persistent
+  // kernel then finds those finished, and carries on those that an earlier run with a
+  // limit began. A count of workgroups is a limit on the share of the device, which
+  // the lockstep launches do not keep: with one the persistent kernel runs alone.
+  const bool whole = workgroups == 0 && step_budget == 0 && !stop_on_finish;
+  const bool lockstep = whole && lockstep_pays(plans, n);
   if (workgroups == 0) {
     int dev = 0, cus = 0;
     hipGetDevice(&dev);
@@ -197,9 +238,9 @@ int32_t gkr_run_batch(gkr_plan* const* plans, uint32_t n, uint32_t* d_ctl, uint3
       cus = 256;
     }
     workgroups = (uint32_t)cus * batch_kernel_max_workgroups_per_cu();
-    // plans begun before: a workgroup per CU does best (64 uneven proofs 81.0 ms, against
-    // 84.6 with two per CU, which contend for the step counters, and 88.7 with 5 per 8 CUs)
-    if (lockstep) workgroups = (uint32_t)cus;
+    // to the end a workgroup per CU does best (64 uneven proofs 81.0 ms, against 84.6
+    // with two per CU, which contend for the step counters, and 88.7 with 5 per 8 CUs)
+    if (whole) workgroups = (uint32_t)cus;
   }
   hipStream_t s = static_cast<hipStream_t>(stream);
   launch_fill_u32(d_ctl, 4, 0u, s);
