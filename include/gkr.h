@@ -353,9 +353,9 @@ int32_t gkr_plan_reset(gkr_plan* plan, void* stream);
  * after about that many completed steps; stop_on_finish stops it when any plan
  * finishes. A stopped run leaves every plan resumable: run it again to
  * continue. Plans already finished are skipped. With workgroups, step_budget and
- * stop_on_finish all 0, plans that have not begun may run in lockstep launches (plans
- * with the same steps and single ones always, uneven ones by their sizes); the
- * others go on in the persistent launch after them.
+ * stop_on_finish all 0, plans that no run has taken since they were made or reset
+ * may run in lockstep launches (plans with the same steps and single ones always,
+ * uneven ones by their sizes); the others go on in the persistent launch after them.
  */
 int32_t gkr_run_batch(gkr_plan* const* plans, uint32_t n, uint32_t* d_ctl, uint32_t workgroups,
                       uint32_t step_budget, uint32_t stop_on_finish, void* stream);

@@ -10,6 +10,7 @@
 #include <string.h>
 
 #include <algorithm>
+#include <atomic>
 #include <memory>
 #include <new>
 #include <string>
@@ -32,6 +33,9 @@ struct gkr_plan {
   std::vector<uint32_t> stage_first, lock_tiles;
   uint64_t gates = 0;  // gates of all layers and inputs
   uint64_t form = 0;   // hash of the lockstep program's step types
+  // Queued in a run since the last reset. Only a hint for which launches to queue: the
+  // device's counters say what is left to do (a reset may be replayed from a graph).
+  std::atomic<bool> queued{false};
   uint32_t* flag() const { return ctr + ctr_words - 1; }
 };
 
@@ -40,6 +44,15 @@ static bool aligned16b(const void* p) { return (reinterpret_cast<uintptr_t>(p) &
 }  // namespace gkr
 
 using namespace gkr;
+
+static BatchJobDev job_dev(const gkr_plan& p) {
+  BatchJobDev j;
+  memset(&j, 0, sizeof(j));
+  j.steps = p.steps;
+  j.ctr = p.ctr;
+  j.nsteps = p.nsteps;
+  return j;
+}
 
 // Whether a run to the end goes in lockstep: the smaller of two estimates, in ns.
 // Lockstep: launches of the longest plan, waiting for the next longest one (each
@@ -76,12 +89,17 @@ static bool lockstep_pays(gkr_plan* const* plans, uint32_t n) {
   return alike || lockstep < chain + 0.78 * gates;
 }
 
-// The lockstep run of the plans in a that have not begun: a launch decides which
-// they are, then one launch per stage, then one that marks them finished.
-static void run_lockstep(gkr_plan* const* plans, uint32_t n, const BatchArgs& a, hipStream_t s) {
+// The lockstep run of those of the n plans that have not begun: a launch decides
+// which they are, then one launch per stage, then one that marks them finished.
+static void run_lockstep(gkr_plan* const* plans, uint32_t n, uint32_t* d_ctl, hipStream_t s) {
   uint32_t* flags[kMaxBatchJobs];
   size_t stages = 0;
+  BatchArgs a;
+  memset(&a, 0, sizeof(a));
+  a.njobs = n;
+  a.ctl = d_ctl;
   for (uint32_t i = 0; i < n; ++i) {
+    a.jobs[i] = job_dev(*plans[i]);
     flags[i] = plans[i]->flag();
     stages = std::max(stages, plans[i]->stage_first.size() - 1);
   }
@@ -189,6 +207,7 @@ int32_t gkr_plan_reset(gkr_plan* p, void* stream) {
     return GKR_EINVAL;
   }
   launch_fill_u32(p->ctr, p->ctr_words, 0u, static_cast<hipStream_t>(stream));
+  p->queued.store(false, std::memory_order_relaxed);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) {
     set_error(std::string("kernel launch failed: ") + hipGetErrorString(e));
@@ -215,9 +234,7 @@ int32_t gkr_run_batch(gkr_plan* const* plans, uint32_t n, uint32_t* d_ctl, uint3
         set_error("a plan appears twice in one run");
         return GKR_EINVAL;
       }
-    a.jobs[i].steps = plans[i]->steps;
-    a.jobs[i].ctr = plans[i]->ctr;
-    a.jobs[i].nsteps = plans[i]->nsteps;
+    a.jobs[i] = job_dev(*plans[i]);
   }
   a.njobs = n;
   a.step_budget = step_budget;
@@ -228,8 +245,14 @@ int32_t gkr_run_batch(gkr_plan* const* plans, uint32_t n, uint32_t* d_ctl, uint3
   // kernel then finds those finished, and carries on those that an earlier run with a
   // limit began. A count of workgroups is a limit on the share of the device, which
   // the lockstep launches do not keep: with one the persistent kernel runs alone.
+  // Plans that an earlier run has taken are left out: the launches of their stages
+  // would find nothing to do (4 ms for a finished plan of depth 28).
   const bool whole = workgroups == 0 && step_budget == 0 && !stop_on_finish;
-  const bool lockstep = whole && lockstep_pays(plans, n);
+  gkr_plan* fresh[kMaxBatchJobs];
+  uint32_t nfresh = 0;
+  for (uint32_t i = 0; i < n; ++i)
+    if (!plans[i]->queued.exchange(true, std::memory_order_relaxed)) fresh[nfresh++] = plans[i];
+  const bool lockstep = whole && nfresh > 0 && lockstep_pays(fresh, nfresh);
   if (workgroups == 0) {
     int dev = 0, cus = 0;
     hipGetDevice(&dev);
@@ -244,7 +267,7 @@ int32_t gkr_run_batch(gkr_plan* const* plans, uint32_t n, uint32_t* d_ctl, uint3
   }
   hipStream_t s = static_cast<hipStream_t>(stream);
   launch_fill_u32(d_ctl, 4, 0u, s);
-  if (lockstep) run_lockstep(plans, n, a, s);
+  if (lockstep) run_lockstep(fresh, nfresh, d_ctl, s);
   launch_batch(a, workgroups, s);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) {

@@ -113,3 +113,31 @@ def test_captured_lockstep_run_of_the_mix_replays(gkr):  # noqa: F811
         gkr.prove_circuit(jobs[0].c, jobs[0].d_in, jobs[0].spec.seed, jobs[0].out, jobs[0].proof, jobs[0].ws)
         torch.cuda.synchronize()
         assert jobs[0].proof_bytes() == want[0], rep
+
+
+@pytest.mark.parametrize("specs", [[LARGE], [LARGE, _spec(5, 7, 10, 12)]], ids=["one", "two"])
+def test_begun_and_finished_plans_take_one_launch(gkr, specs):  # noqa: F811
+    """Plans taken by a run since their last reset: only those that have not begun are worth
+    the launches of a lockstep run."""
+    import torch
+    jobs = [_Job(gkr, s) for s in specs]
+    plans = [gkr.Plan(j.job) for j in jobs]
+    ctl = torch.zeros(4, dtype=torch.int32, device="cuda")
+    for j in jobs:
+        gkr.prove_circuit(j.c, j.d_in, j.spec.seed, j.out, j.proof, j.ws)
+    torch.cuda.synchronize()
+    want = [j.proof_bytes() for j in jobs]
+    for begun in (plans, plans[:1]):
+        for j, p in zip(jobs, plans):
+            j.proof.zero_()
+            p.reset()
+        gkr.run_batch(begun, ctl, step_budget=5)
+        launches = _batch_launches(gkr, lambda: gkr.run_batch(plans, ctl))
+        assert launches == 1 if len(begun) == len(plans) else launches > 50, launches
+        assert int(ctl[0]) == len(plans)
+        assert [j.proof_bytes() for j in jobs] == want
+        assert _batch_launches(gkr, lambda: gkr.run_batch(plans, ctl)) == 1
+        assert int(ctl[0]) == 0
+    plans[-1].reset()
+    assert _batch_launches(gkr, lambda: gkr.run_batch(plans, ctl)) > 50
+    assert int(ctl[0]) == 1 and [j.proof_bytes() for j in jobs] == want
