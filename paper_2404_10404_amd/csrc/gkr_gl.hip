@@ -424,22 +424,33 @@ __device__ __forceinline__ void body_gl_copy_contract(const Step& st, uint32_t t
   const uint64_t ncop = 1ull << n;
   const uint32_t lane = threadIdx.x & 63;
   const uint64_t wave = GTILE_ID >> 6, nwaves = GTILE_STRIDE >> 6;
+  if (n < 7) {
+    // one product per lane at most: an unreduced sum's own reduction would cost more
+    // (2^22 rows of one entry: 2.6 ms a layer instead of 1.6)
+    for (uint64_t y = wave; y < st.q[0]; y += nwaves) {
+      uint64_t p = 0, q = 0;
+      if (lane < ncop) {
+        const uint64_t w = gld(W, (y << n) | lane);
+        p = gl_mul(gld(U, lane), w);
+        q = gl_mul(gld(V, lane), w);
+      }
+      p = gl_wave_sum(p);
+      q = gl_wave_sum(q);
+      if (lane == 0) {
+        gst(P<uint64_t*>(st, 3), y, p);
+        gst(P<uint64_t*>(st, 4), y, q);
+      }
+    }
+    return;
+  }
   for (uint64_t y = wave; y < st.q[0]; y += nwaves) {
     GlAcc ps, qs;
-    if (n >= 7) {
-      for (uint64_t c = 2 * lane; c < ncop; c += 128) {
-        const U64x2 w = gld2(W, (y << n) | c), u = gld2(U, c), v = gld2(V, c);
-        gl_mac(ps, u.x, w.x);
-        gl_mac(qs, v.x, w.x);
-        gl_mac(ps, u.y, w.y);
-        gl_mac(qs, v.y, w.y);
-      }
-    } else {
-      for (uint64_t c = lane; c < ncop; c += 64) {
-        const uint64_t w = gld(W, (y << n) | c);
-        gl_mac(ps, gld(U, c), w);
-        gl_mac(qs, gld(V, c), w);
-      }
+    for (uint64_t c = 2 * lane; c < ncop; c += 128) {
+      const U64x2 w = gld2(W, (y << n) | c), u = gld2(U, c), v = gld2(V, c);
+      gl_mac(ps, u.x, w.x);
+      gl_mac(qs, v.x, w.x);
+      gl_mac(ps, u.y, w.y);
+      gl_mac(qs, v.y, w.y);
     }
     const uint64_t p = gl_wave_sum(gl_acc_value(ps)), q = gl_wave_sum(gl_acc_value(qs));
     if (lane == 0) {
@@ -450,18 +461,35 @@ __device__ __forceinline__ void body_gl_copy_contract(const Step& st, uint32_t t
 }
 __global__ void __launch_bounds__(kBlock) k_gl_copy_contract(Step st) { body_gl_copy_contract(st, blockIdx.x, gridDim.x); }
 
-// ST_GL_LOCAL_VALUES (one workgroup): Ka~ = sum_y EqR[y] Ka[y], Kb~ likewise,
-// y < q0, into S->ka_f, S->kb_f. p0 EqR, p1 Ka, p2 Kb, p3 S.
-__device__ __forceinline__ void body_gl_local_values(const Step& st, uint32_t, uint32_t) {
+// ST_GL_LOCAL_VALUES: Ka~ = sum_y EqR[y] Ka[y], Kb~ likewise, y < q0, into S->ka_f,
+// S->kb_f, a workgroup per 2^14 rows: a row is a chain of loads and a product, so
+// one workgroup over 2^22 rows took 10 ms. p0 EqR, p1 Ka, p2 Kb, p3 S, p4 partials.
+constexpr uint64_t kGlLocalValueRows = 1u << 14;
+
+__device__ __forceinline__ void body_gl_local_values(const Step& st, uint32_t tile, uint32_t ntiles) {
   const uint64_t *E = P<const uint64_t*>(st, 0), *Ka = P<const uint64_t*>(st, 1), *Kb = P<const uint64_t*>(st, 2);
   GlState* S = P<GlState*>(st, 3);
   uint64_t acc[2] = {0, 0};
-  for (uint64_t y = threadIdx.x; y < st.q[0]; y += blockDim.x) {
+  for (uint64_t y = GTILE_ID; y < st.q[0]; y += GTILE_STRIDE) {
     const uint64_t e = gld(E, y);
     acc[0] = gl_add(acc[0], gl_mul(e, gld(Ka, y)));
     acc[1] = gl_add(acc[1], gl_mul(e, gld(Kb, y)));
   }
   gl_block_sum<2>(acc);
+  if (ntiles > 1) {
+    uint64_t* partials = P<uint64_t*>(st, 4);
+    if (threadIdx.x == 0) {
+      put_word(partials + 2 * tile, acc[0]);
+      put_word(partials + 2 * tile + 1, acc[1]);
+    }
+    if (!last_tile(&S->counter, ntiles)) return;
+    acc[0] = acc[1] = 0;
+    for (uint32_t b = threadIdx.x; b < ntiles; b += kBlock) {
+      acc[0] = gl_add(acc[0], get_word(partials + 2 * b));
+      acc[1] = gl_add(acc[1], get_word(partials + 2 * b + 1));
+    }
+    gl_block_sum<2>(acc);
+  }
   if (threadIdx.x == 0) {
     S->ka_f = acc[0];
     S->kb_f = acc[1];
@@ -1568,8 +1596,8 @@ void gl_emit_proof(std::vector<Step>& steps, const gkr_circuit& c, const GlWs& w
       gl_eq(steps, 1, bits, pts, scl, outs);
     }
     {
-      Step st = gl_mk(ST_GL_LOCAL_VALUES, 1);
-      st.p[0] = w.EqR; st.p[1] = w.Ka; st.p[2] = w.Kb; st.p[3] = w.S; st.q[0] = rows;
+      Step st = gl_mk(ST_GL_LOCAL_VALUES, (uint32_t)std::min<uint64_t>(std::max<uint64_t>(1, rows / kGlLocalValueRows), 256));
+      st.p[0] = w.EqR; st.p[1] = w.Ka; st.p[2] = w.Kb; st.p[3] = w.S; st.p[4] = w.partials; st.q[0] = rows;
       st.bytes = kGE * 3.0 * rows; st.mulmods = 2.0 * rows;
       steps.push_back(st);
     }
