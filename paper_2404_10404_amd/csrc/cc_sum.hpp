@@ -13,6 +13,10 @@ namespace gkr {
 
 constexpr int kCcBands = 63;
 
+// 2^508 mod p (plain form).
+constexpr uint32_t kCcPow508[8] = {0x91e216dbu, 0xe7eaa887u, 0xe2ae14efu, 0xbbdd1653u,
+                                   0x7e1479bcu, 0xd071bf6au, 0xb6a0ce61u, 0x1b59d92bu};
+
 // acc[i] collects 32-bit words of weight 2^(32 i).
 struct CcSum {
   uint64_t acc[18];

@@ -294,15 +294,6 @@ void* cc_scratch(const Workspace& w, uint32_t n, uint32_t sigma) {
   return cc_scratch_bytes(n, sigma) <= room ? w.G : nullptr;
 }
 
-// 2^508 mod p in plain form: (2^508 R) R^-1 from Montgomery powers of 2.
-static void two_pow_508(uint32_t out[8]) {
-  const Fr two = fr_to_mont(fr_make(2, 0, 0, 0, 0, 0, 0, 0));
-  Fr acc = fr_to_mont(fr_make(1, 0, 0, 0, 0, 0, 0, 0));
-  for (int i = 0; i < 508; ++i) acc = fr_mul(acc, two);
-  const Fr plain = fr_from_mont(acc);
-  for (int k = 0; k < 8; ++k) out[k] = plain.v[k];
-}
-
 void emit_contract_mfma(Program& pg, const Fr* W, const Fr* U, const Fr* V, Fr* out_u, Fr* out_v, uint32_t log_terms,
                         uint32_t log_rows, bool transposed, void* scratch) {
   const uint32_t n = log_terms;
@@ -345,7 +336,7 @@ void emit_contract_mfma(Program& pg, const Fr* W, const Fr* U, const Fr* V, Fr* 
     Step st = mk(ST_CC_EPILOGUE, (uint32_t)((rows + per - 1) / per));
     st.u[1] = per;
     st.p[0] = part; st.p[1] = BS; st.p[2] = out_u; st.p[3] = out_v; st.u[0] = cp.chunks; st.q[0] = rows;
-    two_pow_508(st.w);
+    memcpy(st.w, kCcPow508, sizeof(kCcPow508));
     st.bytes = (double)cp.part_bytes + 64.0 * rows;
     st.mulmods = (double)rows;  // one reduction per row and vector
     pg.steps.push_back(st);

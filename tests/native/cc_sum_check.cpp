@@ -1,6 +1,6 @@
 // Host check of the arithmetic that ends a matrix-core contraction: reads 2^508 mod
 // p (8 limbs), then lines of 63 band sums, and prints the reduced value of each line
-// as 64 hex digits.
+// as 64 hex digits. With an argument: prints the limbs of kCcPow508.
 #include <cinttypes>
 #include <cstdio>
 
@@ -8,7 +8,11 @@
 
 using namespace gkr;
 
-int main() {
+int main(int argc, char**) {
+  if (argc > 1) {
+    for (uint32_t x : kCcPow508) printf("%" PRIu32 "\n", x);
+    return 0;
+  }
   uint32_t w[8];
   for (int i = 0; i < 8; ++i)
     if (scanf("%" SCNu32, &w[i]) != 1) return 1;

@@ -40,3 +40,8 @@ def test_band_sums_up_to_their_bound(checker, log_terms):
     lines += [" ".join(map(str, r)) for r in rows]
     out = subprocess.run([checker], input="\n".join(lines) + "\n", capture_output=True, text=True, check=True).stdout
     assert [int(x, 16) for x in out.split()] == [sum(e << (8 * k) for k, e in enumerate(r)) * RINV % P for r in rows]
+
+
+def test_power_of_two_that_folds_the_top_bits(checker):
+    out = subprocess.run([checker, "constant"], capture_output=True, text=True, check=True).stdout
+    assert sum(int(x) << (32 * i) for i, x in enumerate(out.split())) == pow(2, 508, P)
