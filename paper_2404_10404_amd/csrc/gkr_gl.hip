@@ -848,7 +848,7 @@ __global__ void __launch_bounds__(kBlock) k_gl_s_round(Step st) {
   const uint64_t r = *P<const uint64_t*>(st, 13);
   uint64_t acc[2] = {0, 0};
   if (blockIdx.x < nb) {
-    const uint64_t* __restrict__ Ws = P<const uint64_t*>(st, 0);
+    const uint64_t* Ws = P<const uint64_t*>(st, 0);  // from the third round on the same table as Wd
     uint64_t *Wd = P<uint64_t*>(st, 1), *G = P<uint64_t*>(st, 2);
     const uint32_t* __restrict__ act = P<const uint32_t*>(st, 3);
     const uint32_t n = st.u[0], k = st.u[2], rh = 1u << (k - 1);

@@ -156,7 +156,7 @@ __global__ void __launch_bounds__(kBlock, 3) k_s_round(Step st) {
   const Fr r = ldf(P<const Fr*>(st, 13), 0);
   Fr acc[2] = {fr_zero(), fr_zero()};
   if (blockIdx.x < nb) {
-    const Fr* __restrict__ Ws = P<const Fr*>(st, 0);
+    const Fr* Ws = P<const Fr*>(st, 0);  // from the third round on the same table as Wd
     Fr* Wd = P<Fr*>(st, 1);
     Fr* G = P<Fr*>(st, 2);
     const uint32_t* __restrict__ act = P<const uint32_t*>(st, 3);
