@@ -401,7 +401,8 @@ int32_t gkr_get_tuning(uint32_t* tail_log, uint32_t* max_round_blocks, uint32_t*
  * sub-circuit wires and 2^10 copies (or 2^9 where phase 1's tables can hold its
  * scratch), and phase 1 with its addition gates contracted
  * over the copies for layers with at least 2^9 copies, 2^10 wires and 2^23
- * entries of which few have a MUL gate; 0 always runs the scalar lazy-product pass and the three-table
+ * entries of which few have a MUL gate (Goldilocks proofs for 2^9 copies, 2^8 wires
+ * and 2^23 entries); 0 always runs the scalar lazy-product pass and the three-table
  * phase 1. Proofs read it when they are queued. Errors: GKR_EINVAL
  * for a mode above 1 (nothing is changed). gkr_get_contraction writes the
  * current mode to a non-null pointer.

@@ -778,7 +778,6 @@ __device__ __forceinline__ U64x2 gl_split_entry(const uint64_t* __restrict__ W, 
   return g;
 }
 
-__device__ __forceinline__ U64x2 gl_sub2(U64x2 a, U64x2 b) { return U64x2{gl_sub(a.x, b.x), gl_sub(a.y, b.y)}; }
 __device__ __forceinline__ U64x2 gl_fold2(uint64_t r, U64x2 a0, U64x2 a1) {
   return U64x2{gl_add(a0.x, gl_mul(r, gl_sub(a1.x, a0.x))), gl_add(a0.y, gl_mul(r, gl_sub(a1.y, a0.y)))};
 }
@@ -1538,7 +1537,7 @@ void gl_emit_proof(std::vector<Step>& steps, const gkr_circuit& c, const GlWs& w
     }
     const LayerWiring& lw = c.wiring[i];
     const uint64_t ncop = 1ull << n, rows = 1ull << sg1;
-    const bool split = gl_split_applies(n, sg1);
+    const bool split = tun.matrix_cores && gl_split_applies(n, sg1);
     if (split) gl_emit_phase1_split(steps, c, i, w, rx, pr, tun);
     if (!split) {
       Step st = gl_mk(ST_GL_P1, gl_tiles(1ull << s1, kGlSweepTiles));
