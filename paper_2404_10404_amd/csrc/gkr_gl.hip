@@ -1235,8 +1235,8 @@ void launch_gl_step(const Step& st, hipStream_t s) {
     case ST_GL_LOCAL_CONTRACT: k_gl_local_contract<<<grid, block, 0, s>>>(st); cls = PC_LOCAL_CONTRACT; break;
     case ST_GL_COPY_TABLES: k_gl_copy_tables<<<grid, block, 0, s>>>(st); cls = PC_SMALL; break;
     case ST_GL_S_SMALL: k_gl_s_small<<<grid, block, 0, s>>>(st); break;
-    case ST_GL_S_INIT_ROUND: k_gl_s_init_round<<<grid, block, 0, s>>>(st); cls = PC_PHASE1_INIT; break;
-    case ST_GL_S_ROUND: k_gl_s_round<<<grid, block, 0, s>>>(st); cls = PC_ROUND_A; break;
+    case ST_GL_S_INIT_ROUND: k_gl_s_init_round<<<grid, block, 0, s>>>(st); cls = PC_PHASE1_SPLIT; break;
+    case ST_GL_S_ROUND: k_gl_s_round<<<grid, block, 0, s>>>(st); cls = PC_ROUND_SPLIT; break;
     case ST_GL_S_P2_RAW: k_gl_s_p2_raw<<<grid, block, 0, s>>>(st); cls = PC_PHASE2_TABLES; break;
     case ST_GL_S_P2_FINAL: k_gl_s_p2_final<<<grid, block, 0, s>>>(st); cls = PC_PHASE2_TABLES; break;
     case ST_GL_S_LOCAL2: k_gl_s_local2<<<grid, block, 0, s>>>(st); cls = PC_LOCAL_CONTRACT; break;

@@ -37,7 +37,8 @@ const char* kNames[PC_COUNT] = {"forward",        "digest",         "transcript"
                                 "local_contract", "small",          "convert",       "batch",
                                 "g_gather",       "g_forward",      "g_claim_tables", "g_phase1_init",
                                 "g_phase2_tables", "vpd_ntt",        "vpd_merkle",    "vpd_fri",
-                                "vpd_other"};
+                                "vpd_other",       "phase1_wide",    "phase1_contracted", "round_wide",
+                                "round_contracted"};
 
 hipEvent_t get_event() {
   if (!g_pool.empty()) {

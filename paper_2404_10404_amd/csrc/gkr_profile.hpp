@@ -31,6 +31,10 @@ enum ProfClass {
   PC_VPD_MERKLE,
   PC_VPD_FRI,
   PC_VPD_OTHER,
+  PC_PHASE1_WIDE,   // small phase-1 tables: the gates' chains, their sums and round 1
+  PC_PHASE1_SPLIT,  // the contracted phase 1: Gm and round 1
+  PC_ROUND_WIDE,    // rounds with a product per thread (any form)
+  PC_ROUND_SPLIT,   // rounds of the contracted phase 1 over big tables
   PC_COUNT
 };
 

@@ -343,9 +343,9 @@ void launch_split_step(const Step& st, hipStream_t s) {
   ProfClass cls = PC_SMALL;
   switch (st.type) {
     case ST_S_SMALL: k_s_small<<<grid, block, 0, s>>>(st); break;
-    case ST_S_INIT_ROUND: k_s_init_round<<<grid, block, 0, s>>>(st); cls = PC_PHASE1_INIT; break;
-    case ST_S_ROUND: k_s_round<<<grid, block, 0, s>>>(st); cls = PC_ROUND_A; break;
-    case ST_S_WIDE_ROUND: k_s_wide_round<<<grid, dim3(64 * 5), 0, s>>>(st); cls = PC_ROUND_A; break;
+    case ST_S_INIT_ROUND: k_s_init_round<<<grid, block, 0, s>>>(st); cls = PC_PHASE1_SPLIT; break;
+    case ST_S_ROUND: k_s_round<<<grid, block, 0, s>>>(st); cls = PC_ROUND_SPLIT; break;
+    case ST_S_WIDE_ROUND: k_s_wide_round<<<grid, dim3(64 * 5), 0, s>>>(st); cls = PC_ROUND_WIDE; break;
     case ST_S_P2_RAW: k_s_p2_raw<<<grid, block, 0, s>>>(st); cls = PC_PHASE2_TABLES; break;
     case ST_S_P2_FINAL: k_s_p2_final<<<grid, block, 0, s>>>(st); cls = PC_PHASE2_TABLES; break;
     case ST_S_HANDOFF: k_s_handoff<<<grid, block, 0, s>>>(st); break;

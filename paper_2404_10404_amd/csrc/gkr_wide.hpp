@@ -1,5 +1,5 @@
 // Rounds over tables too small to fill the chip, one product per thread
-// (gkr_wide.hip; plain path only).
+// (gkr_wide.hip; the lockstep kernel of a batch runs the same bodies).
 #pragma once
 
 #include "gkr_internal.hpp"

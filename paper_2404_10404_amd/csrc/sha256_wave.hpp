@@ -318,7 +318,7 @@ __device__ __forceinline__ void sha_rehash_wave(ShaLanes& st, ShaBuf* buf) {
   st = sha_message_wave<9>(buf);
 }
 
-// The state rehashed until it is a challenge (see accept).
+// The state rehashed until it is a challenge (the candidate rule in gkr_bodies.hpp).
 __device__ __forceinline__ void sha_accept_wave(ShaLanes& st, ShaBuf* buf) {
   for (int attempt = 0; attempt < 4096 && !sha_candidate_canonical(st); ++attempt) sha_rehash_wave(st, buf);
 }
