@@ -149,39 +149,42 @@ int32_t gkr_plan_create(const gkr_job* job, gkr_plan** out) {
   if (rc) return rc;
   try {
     Workspace w = bind_workspace(*c, job->d_ws);
+    // the persistent program, then the lockstep program, then the counters (zero), in one
+    // vector and one upload: a plan holds one statement, so a program makes many
     Program pg;
+    pg.steps.reserve(96ull * c->depth + 64);
     pg.mode = Program::kPersistent;
     emit_prove_circuit(pg, *c, w, job->d_inputs, job->seed, job->d_outputs, job->d_proof, current_tuning());
     std::unique_ptr<gkr_plan> p(new gkr_plan());
     p->job = *job;
     p->nsteps = (uint32_t)pg.steps.size();
     p->ctr_words = 2 + 2ull * p->nsteps;
-    Program lk;
-    lk.mode = Program::kLockstep;
-    emit_prove_circuit(lk, *c, w, job->d_inputs, job->seed, job->d_outputs, job->d_proof, current_tuning());
-    for (size_t k = 0; k < lk.steps.size(); ++k) {
-      if (!lk.steps[k].join) p->stage_first.push_back((uint32_t)k);
-      p->lock_tiles.push_back(lk.steps[k].ntiles);
-      p->form = (p->form ^ (2 * lk.steps[k].type + lk.steps[k].join + 1)) * 0x9e3779b97f4a7c15ull;
+    pg.mode = Program::kLockstep;
+    emit_prove_circuit(pg, *c, w, job->d_inputs, job->seed, job->d_outputs, job->d_proof, current_tuning());
+    const size_t lock_steps = pg.steps.size() - p->nsteps;
+    p->stage_first.reserve(lock_steps + 1);
+    p->lock_tiles.reserve(lock_steps);
+    for (size_t k = 0; k < lock_steps; ++k) {
+      const Step& st = pg.steps[p->nsteps + k];
+      if (!st.join) p->stage_first.push_back((uint32_t)k);
+      p->lock_tiles.push_back(st.ntiles);
+      p->form = (p->form ^ (2 * st.type + st.join + 1)) * 0x9e3779b97f4a7c15ull;
       p->form ^= p->form >> 29;
     }
+    p->stage_first.push_back((uint32_t)lock_steps);
     for (uint32_t i = 0; i <= c->depth; ++i) p->gates += 1ull << c->s(i);
-    p->stage_first.push_back((uint32_t)lk.steps.size());
-    const size_t lock_bytes = sizeof(Step) * lk.steps.size();
     const size_t step_bytes = sizeof(Step) * pg.steps.size();
-    const size_t total = step_bytes + lock_bytes + 4 * p->ctr_words;
+    pg.steps.resize(pg.steps.size() + (4 * p->ctr_words + sizeof(Step) - 1) / sizeof(Step));
+    const size_t total = sizeof(Step) * pg.steps.size();
     if (hipMalloc(&p->dev, total) != hipSuccess) {
       (void)hipGetLastError();
       set_error("device allocation of the plan failed");
       return GKR_ENOMEM;
     }
     p->steps = static_cast<Step*>(p->dev);
-    p->lock_steps = reinterpret_cast<Step*>(static_cast<char*>(p->dev) + step_bytes);
-    p->ctr = reinterpret_cast<uint32_t*>(static_cast<char*>(p->dev) + step_bytes + lock_bytes);
-    std::vector<uint32_t> zeros(p->ctr_words, 0);
-    pg.steps.insert(pg.steps.end(), lk.steps.begin(), lk.steps.end());
-    if (hipMemcpy(p->steps, pg.steps.data(), step_bytes + lock_bytes, hipMemcpyHostToDevice) != hipSuccess ||
-        hipMemcpy(p->ctr, zeros.data(), 4 * p->ctr_words, hipMemcpyHostToDevice) != hipSuccess) {
+    p->lock_steps = p->steps + p->nsteps;
+    p->ctr = reinterpret_cast<uint32_t*>(static_cast<char*>(p->dev) + step_bytes);
+    if (hipMemcpy(p->dev, pg.steps.data(), total, hipMemcpyHostToDevice) != hipSuccess) {
       (void)hipGetLastError();
       hipFree(p->dev);
       set_error("upload of the plan failed");
