@@ -195,12 +195,12 @@ __global__ void __launch_bounds__(kCcThreads) k_cc_gemm(Step st) {
 
 // ST_CC_EPILOGUE: a workgroup takes u1 rows, two for tables of few rows (which
 // have many chunks: 2^9 rows, 128 chunks took 142 us with eight) and eight
-// otherwise. All threads first add the chunks'
-// partial columns, two rows of 128 consecutive columns at a time, into shared
-// memory; then one thread per (row, vector) takes the 63 band columns of its
-// vector and the ones column, the offsets, the integer sum_k 2^(8k) E_k and its
-// Montgomery reduction (cc_sum.hpp; w[0..7] 2^508 mod p). (With the two threads of a row also adding the chunks,
-// 63 loads per chunk at a stride of a row, 2^14 rows took 57 us.)
+// otherwise. All threads first add the chunks' partial columns, two rows of 128
+// consecutive columns at a time, into shared memory; then one thread per (row,
+// vector) takes the 63 band columns of its vector and the ones column, the offsets,
+// the integer sum_k 2^(8k) E_k and its Montgomery reduction (cc_sum.hpp; w[0..7]
+// 2^508 mod p). 2^14 rows take 18 us (57 with the two threads of a row also adding
+// the chunks, 63 loads per chunk at a stride of a row).
 // p0 part, p1 BS, p2 P out, p3 Q out; u0 chunks, u1 rows per workgroup; q0 rows.
 constexpr uint32_t kCcEpiRows = 8;
 

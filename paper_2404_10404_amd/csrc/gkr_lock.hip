@@ -5,12 +5,14 @@
 // workgroups; between two steps of a proof lie a tile's publication (an L2
 // write-back), a counter and another workgroup's scan and L2 invalidation, so
 // 64 uneven proofs (depth 8..32, 2^10..2^18 gates per layer) take 81 ms (155 when
-// every tile of a reduction wrote its L2 back) although their products take 4. Here a proof's next step begins with the next launch: no
-// tile protocol, and a step of the whole batch costs one launch and its longest
-// member: 58.7 ms, 1,350 launches of 43 us, of which about 16 are a launch and the
-// shortest steps (a round's serial transcript), 20 the products and tiles of
-// all proofs, the rest the wait for the longest step. Holding long steps back
-// until every proof has one lowers a launch to 23 us but takes 5,700 of them.
+// every tile of a reduction wrote its L2 back) although their products take 4. Here
+// a proof's next step begins with the next launch: no tile protocol, and a step of
+// the whole batch costs one launch and its longest member: 58.7 ms, 1,350 launches
+// of 43 us, of which about 16 are a launch and the shortest steps (a round's serial
+// transcript), 20 the products and tiles of all proofs, the rest the wait for the
+// longest step, which a few uneven proofs pay most (gkr_run_batch weighs it). Holding
+// long steps back until every proof has one lowers a launch to 23 us but takes
+// 5,700 of them.
 #include "gkr_bodies.hpp"
 #include "gkr_profile.hpp"
 #include "gkr_wide_bodies.hpp"
